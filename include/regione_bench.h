@@ -12,10 +12,9 @@
 extern "C" {
 #endif
 
-/* Tuning knob for experiments: forces the GEMM wave tile (1 or 2 blocks of 32 columns; 3 or 4 =
- * the same two widths with the kernel that stages both operands through LDS, 5 or 6 = that
- * kernel with 256-row workgroup tiles) and the number of K splits of every later GEMM of this
- * context; 0 restores the automatic choice. */
+/* Tuning knob for experiments: forces the tile (1..6: six tiles from 64 x 64 to 256 x 256; larger numbers are the tile
+ * codes of csrc/gemm_tiles.h) and the number of K splits of every later GEMM of this context; 0 restores the automatic
+ * choice. */
 int regione_tune_gemm(regione_ctx* ctx, int32_t wave_tile_blocks, int32_t k_splits);
 
 /* Tuning knob for experiments: forces the number of key-range splits (1..8) of every later

@@ -14,8 +14,11 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libregione.so")
-SOURCES = ["api.hip", "partition.hip", "rows.hip", "gemm.hip", "attention.hip", "block_extras.hip", "fp8.hip", "peaks.hip",
-           "fp32.hip", "host_logic.cpp"]
+SOURCES = ["api.hip", "partition.hip", "rows.hip", "gemm.hip", "gemm_tiles_wide.hip", "gemm_tiles_128.hip", "gemm_tiles_96.hip", "gemm_tiles_fp8.hip",
+           "attention.hip", "block_extras.hip", "fp8.hip", "peaks.hip", "fp32.hip", "host_logic.cpp"]
+
+# sources whose machine code is checked (isa_check.py)
+CHECKED = ("gemm.hip", "gemm_tiles_wide.hip", "gemm_tiles_128.hip", "gemm_tiles_96.hip", "gemm_tiles_fp8.hip")
 
 
 def flags() -> list[str]:
@@ -43,28 +46,30 @@ def build(verbose: bool = False, only=None) -> str:
     os.makedirs(OBJ, exist_ok=True)
     sources = [s for s in SOURCES if only is None or s in only]
     if only is not None:   # a partial build is only sound while no header is newer than the objects that are kept
-        headers = [os.path.join(CSRC, "common.h")] + [os.path.join(ROOT, "include", h) for h in os.listdir(os.path.join(ROOT, "include"))]
+        headers = [os.path.join(CSRC, h) for h in os.listdir(CSRC) if h.endswith(".h")] + [os.path.join(ROOT, "include", h) for h in os.listdir(os.path.join(ROOT, "include"))]
         newest = max(os.path.getmtime(h) for h in headers)
         kept = [os.path.join(OBJ, os.path.splitext(s)[0] + ".o") for s in SOURCES if s not in sources]
         if any(not os.path.exists(o) or os.path.getmtime(o) < newest for o in kept):
             sources = list(SOURCES)
 
     def compile_one(src):
-        obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-        _run([hipcc, *fl, "-fPIC", "-c", os.path.join(CSRC, src), "-o", obj], verbose)
+        stem = os.path.splitext(src)[0]
+        obj = os.path.join(OBJ, stem + ".o")
+        checked = src in CHECKED
+        _run([hipcc, *fl, "-fPIC", "-c", os.path.join(CSRC, src), "-o", obj, *(["-save-temps=obj"] if checked else [])], verbose)
+        if checked:
+            # hand-counted copies are only correct if the compiler left them alone: proved on the machine code just made
+            from . import isa_check
+            asm = os.path.join(OBJ, stem + "-hip-amdgcn-amd-amdhsa-gfx950.s")
+            isa_check.check_asm(open(asm).read())
+            for f in os.listdir(OBJ):
+                if f.startswith((stem + "-hip", stem + "-host", stem + ".hip", stem + ".bc")) or f in (stem + ".s", stem + ".cui"):
+                    os.remove(os.path.join(OBJ, f))
         return obj
-
-    def check_isa(_):
-        # The GEMM's hand-pipelined loads are only correct if the compiler left their registers alone: prove it on the
-        # machine code before anything is linked, with the very flags of the build.
-        from . import isa_check
-        isa_check.check_gemm(hipcc, fl, os.path.join(CSRC, "gemm.hip"))
 
     jobs = int(os.environ.get("MAX_JOBS", "8"))
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, 16))) as pool:
         futs = [pool.submit(compile_one, s) for s in sources]
-        if only is None or "gemm.hip" in only:
-            futs.append(pool.submit(check_isa, None))
         for f in futs:
             f.result()
     objs = [os.path.join(OBJ, os.path.splitext(s)[0] + ".o") for s in SOURCES]

@@ -18,7 +18,7 @@ int dev_alloc(T** p, size_t count) {
     return REGIONE_OK;
 }
 void free_all(regione_ctx* c) {
-    void* ptrs[] = {c->part_counts, c->u, c->q, c->kf, c->vf, c->a, c->h1, c->m, c->slot_all, c->mod_ws, c->attn_part, c->gemm_part, c->q8, c->q8_scale};
+    void* ptrs[] = {c->part_counts, c->u, c->q, c->kf, c->vf, c->a, c->h1, c->m, c->slot_all, c->mod_ws, c->attn_part, c->gemm_part, c->gemm_arrived, c->q8, c->q8_scale};
     for (void* p : ptrs) if (p) (void)hipFree(p);
     if (c->n_edited_pinned) (void)hipHostFree(c->n_edited_pinned);
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
@@ -69,6 +69,11 @@ extern "C" int regione_create(regione_ctx** out, const regione_dims* dims, void*
     if (rc == REGIONE_OK) rc = dev_alloc(reinterpret_cast<char**>(&c->attn_part), c->attn_part_bytes);
     c->gemm_part_bytes = n > 0 ? static_cast<size_t>(128) << 20 : 0;
     if (rc == REGIONE_OK) rc = dev_alloc(reinterpret_cast<char**>(&c->gemm_part), c->gemm_part_bytes);
+    if (rc == REGIONE_OK) rc = dev_alloc(&c->gemm_arrived, 2 * kMaxSplitTiles);
+    if (rc == REGIONE_OK && (hipMemset(c->gemm_arrived, 0, 2 * kMaxSplitTiles * sizeof(int)) != hipSuccess || hipDeviceSynchronize() != hipSuccess)) {
+        regione_set_error("create: cannot clear the arrival counters");
+        rc = REGIONE_ERR_HIP;
+    }
     if (rc == REGIONE_OK) {   // pinned, device-visible host word for the edited-token count (saves the device-to-host copy)
         void* host = nullptr; void* dev = nullptr;
         if (hipHostMalloc(&host, 64, hipHostMallocMapped) != hipSuccess || hipHostGetDevicePointer(&dev, host, 0) != hipSuccess) {
@@ -135,7 +140,7 @@ extern "C" int regione_layernorm(regione_ctx* ctx, const void* h, int32_t h_dtyp
 
 // Velocity head of the step, fused with what follows it in a fresh region step: v = h W^T + b in the storage type, the
 // velocity cache takes v (Eq.9, fresh branch), x_e <- x_e - dt v (Eq.4), and the updated rows are written to their
-// positions in the full latent (the merge).  One GEMM launch and one merge launch in bf16 contexts.
+// positions in the full latent (the merge).  One launch in bf16 contexts.
 extern "C" int regione_velocity_head(regione_ctx* ctx, const void* h_rows, const void* w_head_packed, const float* b_head_opt,
                                      int32_t n, int32_t c, int32_t hidden, float dt, void* v_out_opt, void* c_a, void* x_e,
                                      void* x_full_opt, const int32_t* index_opt, int32_t dtype) {
@@ -221,15 +226,16 @@ int lane_join(regione_ctx* ctx) {
 // While alive, launches through the context go to the side lane: its stream and the upper half of the K-split workspace
 // (the main lane is left the lower half for the same time by LaneHalf).
 struct LaneSwap {
-    regione_ctx* c; hipStream_t stream; float* part; size_t bytes; bool on;
-    LaneSwap(regione_ctx* ctx, bool side) : c(ctx), stream(ctx->stream), part(ctx->gemm_part), bytes(ctx->gemm_part_bytes), on(side) {
+    regione_ctx* c; hipStream_t stream; float* part; size_t bytes; int* arrived; bool on;
+    LaneSwap(regione_ctx* ctx, bool side) : c(ctx), stream(ctx->stream), part(ctx->gemm_part), bytes(ctx->gemm_part_bytes), arrived(ctx->gemm_arrived), on(side) {
         if (!on) return;
         const size_t half = (bytes / 2) & ~static_cast<size_t>(255);
         c->stream = c->side_stream;
         c->gemm_part = reinterpret_cast<float*>(reinterpret_cast<char*>(part) + half);
         c->gemm_part_bytes = half;
+        c->gemm_arrived = arrived + kMaxSplitTiles;
     }
-    ~LaneSwap() { if (on) { c->stream = stream; c->gemm_part = part; c->gemm_part_bytes = bytes; } }
+    ~LaneSwap() { if (on) { c->stream = stream; c->gemm_part = part; c->gemm_part_bytes = bytes; c->gemm_arrived = arrived; } }
 };
 struct LaneHalf {
     regione_ctx* c; size_t bytes; bool on;

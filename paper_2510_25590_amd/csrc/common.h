@@ -9,6 +9,11 @@
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits in memory
 
+constexpr int kMaxSplitTiles = 1024;   // tiles of one K-split GEMM launch
+
+constexpr int kGemmPlanSlots = 64;
+struct GemmPlanSlot { int m, n, k, fp8, tile, splits; size_t part_bytes; };   // a remembered choice of GEMM tile and K splits
+
 struct regione_ctx {
     hipStream_t stream;
     regione_dims dims;
@@ -36,11 +41,13 @@ struct regione_ctx {
     uint8_t* q8; size_t q8_bytes; float* q8_scale;
     float* gemm_part;  // split-K partial sums
     size_t gemm_part_bytes;
+    int* gemm_arrived;     // [2][kMaxSplitTiles] arrival counters of K-split GEMMs' tiles, one set per lane; zero between launches
     // second lane for independent work inside one call (text and image rows of a double-stream block use different
     // weights, so their projections do not depend on each other): a stream of the default priority and two events,
     // created on first use; while a lane swap is active, `stream` and `gemm_part` name the lane's own stream and half
     hipStream_t side_stream;
     hipEvent_t ev_fork, ev_join;
+    GemmPlanSlot gemm_plans[kGemmPlanSlots];
     int gemm_force_tn, gemm_force_splits;  // 0 = chosen per call
     int attn_force_splits;  // 0 = chosen per call
     // kernels that need more than 64 KiB of LDS have to be granted it once per device: one bit per kernel family and
@@ -83,7 +90,7 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
 }
 
 // ---- internal launchers (each enqueues on ctx->stream and returns an error code)
-enum { EPI_PLAIN = 0, EPI_QKV = 1, EPI_RESID = 2, EPI_VELOCITY = 3 };   // EPI_VELOCITY exists only as the merge step of a K-split GEMM
+enum { EPI_PLAIN = 0, EPI_QKV = 1, EPI_RESID = 2, EPI_VELOCITY = 3 };
 
 struct GemmEpilogue {
     int kind;            // EPI_*
@@ -100,15 +107,14 @@ struct GemmEpilogue {
     const void* resid; int ldr; int resid_f32; const float* gate;
     // 8-bit GEMM only: the float32 sums are multiplied by row_scale[row] * col_scale[col] before anything else
     const float* row_scale; const float* col_scale;
-    // merge_kind == EPI_VELOCITY (a plain K-split GEMM whose merge kernel finishes the step, Eq.9 fresh branch + Eq.4 + merge):
+    // EPI_VELOCITY (the head's product finishes the step: Eq.9 fresh branch, Eq.4, merge):
     //   v = storage-rounded(acc + bias); y (if non-null) = v; vel_ca = v; vel_xe -= vel_dt * v; vel_xfull[vel_index[row]] = vel_xe
-    int merge_kind;
     void* vel_ca; void* vel_xe; void* vel_xfull; const int32_t* vel_index; float vel_dt;
 };
 
 // a, w_packed (and the epilogue's q, k, v, y, resid where they are activations) are bf16, or float32 in a float32 context
 int rg_gemm(regione_ctx* ctx, const void* a, int lda, const void* w_packed, int m, int n, int k, const GemmEpilogue& ep);
-// y = x W^T + b as a K-split GEMM whose merge kernel applies the velocity step described at GemmEpilogue::merge_kind (bf16 contexts)
+// y = x W^T + b with the velocity step (EPI_VELOCITY) as its epilogue (bf16 contexts)
 int rg_gemm_velocity(regione_ctx* ctx, const void* a, int lda, const void* w_packed, int m, int n, int k, const GemmEpilogue& ep);
 int rg_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m, int n, int k, const GemmEpilogue& ep);
 // E4M3 operands (k counts 8-bit elements, a multiple of 128; lda in bytes, a multiple of 16); ep.row_scale / col_scale set

@@ -1,0 +1,42 @@
+// Launch of one instantiation of the two-group GEMM kernels.
+#pragma once
+#include "gemm_pp.h"
+#include "gemm_tiles.h"
+#include <atomic>
+
+namespace {
+
+template <typename T, typename Kernel>
+int launch_tile(regione_ctx* ctx, Kernel kernel, std::atomic<uint64_t>& granted, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
+    const int m_tiles = (m + T::ROWS - 1) / T::ROWS, n_tiles = (n + T::COLS - 1) / T::COLS;
+    const int tiles = m_tiles * n_tiles;
+    const int steps = k / 64, per = (steps + splits - 1) / splits;
+    const int used_splits = (steps + per - 1) / per;
+    if (used_splits > 1 && (static_cast<size_t>(used_splits) * tiles * T::PART_FLOATS * sizeof(float) > ctx->gemm_part_bytes || tiles > kMaxSplitTiles))
+        RG_FAIL(REGIONE_ERR_WORKSPACE, "gemm: %d K-splits of a %d x %d result exceed the workspace", used_splits, m, n);
+    // many row tiles: groups of four (the workgroups that run at a time on an XCD then share weight and activation lines in
+    // its L2: 2-7 % on the 8704-row GEMMs against all row tiles of a column tile in a row); few row tiles: one group
+    const int group_rows = m_tiles > 8 ? 4 : m_tiles;
+    const uint64_t bit = uint64_t{1} << (ctx->device & 63);   // more than 64 KiB of LDS has to be granted explicitly, once per device
+    if (!(granted.load(std::memory_order_relaxed) & bit)) {
+        RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(T::LDS_BYTES)));
+        granted.fetch_or(bit, std::memory_order_relaxed);
+    }
+    const int units_per_xcd = (tiles * used_splits + 7) / 8;
+    hipLaunchKernelGGL(kernel, dim3(units_per_xcd * 8), dim3(T::THREADS), T::LDS_BYTES, ctx->stream,
+                       a, lda, wp, m, n, k, m_tiles, n_tiles, units_per_xcd, group_rows, used_splits, per, ctx->gemm_part, ctx->gemm_arrived, ep);
+    RG_LAUNCH_CHECK();
+    return REGIONE_OK;
+}
+template <int RF, int CF, int KIND, bool FP8>
+int launch_pp(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
+    static std::atomic<uint64_t> granted{0};
+    return launch_tile<PpTile<RF, CF>>(ctx, gemm_pp_kernel<RF, CF, KIND, FP8>, granted, a, lda, wp, m, n, k, splits, ep);
+}
+template <int RF, int CF, int WM, int KIND>
+int launch_kg(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
+    static std::atomic<uint64_t> granted{0};
+    return launch_tile<KgTile<RF, CF, WM>>(ctx, gemm_kg_kernel<RF, CF, WM, KIND>, granted, a, lda, wp, m, n, k, splits, ep);
+}
+
+}  // namespace

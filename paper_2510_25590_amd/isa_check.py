@@ -1,14 +1,12 @@
-"""Static check of the hand-pipelined global loads in the GEMM kernels' machine code.
+"""Static checks of the GEMM kernels' machine code, run by every build.
 
-csrc/gemm.hip issues its pipeline loads as inline assembly and waits for them by hand with `s_waitcnt vmcnt(N)`.
-The compiler does not know that such a load writes its destination registers later than the point where the
-instruction stands.  That is only correct while the generated code leaves those registers alone between the load and
-the wait that covers it: no copy (a spill to an accumulation register or a move would copy stale data), no other
-read, no other write.  Register pressure can make the compiler break that rule without any warning, and the result is
-a kernel that reads or writes through corrupted registers.  This module compiles the file to assembly and proves the
-rule on the control-flow graph of every `gemm_bf16_kernel` instantiation; the build fails otherwise.
+The kernels issue global-to-LDS copies as inline assembly and wait for them by hand with `s_waitcnt vmcnt(N)`: the compiler
+neither knows what the counts stand for nor waits itself.  `check_asm` proves on the generated code that (1) the K loops hold
+no vector-memory instruction besides the counted copies and no kernel with such copies spills to scratch memory (spills share
+the counter); (2) no wide store's data registers are overwritten by the next instruction; (3) registers that are the
+destination of an assembly load are left alone until a wait covers them (`check_function`).
 
-Model: loads complete in issue order.  Every destination register of an asm load is "pending" with an age = number
+Model of (3): loads complete in issue order.  Every destination register of an asm load is "pending" with an age = number
 of vector-memory loads issued after it.  `s_waitcnt vmcnt(N)` lands every register whose age is at least N.  At a
 join the state is the union of the predecessors' pending sets with the smaller age.  Any instruction that names a
 pending register is a violation (the load's own address operand excepted).
@@ -195,26 +193,75 @@ def check_function(name: str, lines, unroll: int = 0) -> list[str]:
     return errors
 
 
+_COPY = "global_load_lds_dwordx4"
+_WIDE_STORE = re.compile(r"^(buffer|global)_store_dwordx[34]\b")
+
+
+def check_copies(name: str, lines) -> list[str]:
+    """The two-group kernels count their global-to-LDS copies by hand: inside a K loop (every basic block that runs MFMAs or
+    such copies and is reached again from itself) no other vector-memory instruction may stand, or the counts are off."""
+    blocks = _blocks(lines)
+    short = name[:70]
+    errors = []
+    reach: list[set[int]] = []
+    for k in range(len(blocks)):
+        seen, work = set(), list(blocks[k][2])
+        while work:
+            b = work.pop()
+            if b not in seen:
+                seen.add(b)
+                work += blocks[b][2]
+        reach.append(seen)
+    for k, b in enumerate(blocks):
+        if k not in reach[k] or not any(i.startswith(_COPY) or i.startswith("v_mfma") for i, _ in b[1]):
+            continue
+        for instr, in_asm in b[1]:
+            op = instr.split()[0]
+            if re.match(r"^(global|buffer|flat|scratch)_(load|store|atomic)", op) and not (in_asm and op == _COPY):
+                errors.append(f"{short} block {b[0] or k}: '{instr}' among the counted copies")
+    return errors
+
+
+def check_wide_stores(name: str, lines) -> list[str]:
+    """A vector-memory store of more than eight bytes reads its data registers one wait state late; with a scalar offset
+    register the compiler does not keep that distance.  No such store may be followed by a write of its data."""
+    instrs = [i for b in _blocks(lines) for i, _ in b[1]]
+    errors = []
+    for cur, nxt in zip(instrs, instrs[1:]):
+        if not _WIDE_STORE.match(cur) or not nxt.startswith("v_"):
+            continue
+        operands = cur.split(None, 1)[1].split(",")
+        data = _regs(operands[0] if cur.startswith("buffer") else operands[1])
+        if data & _regs(nxt.split(None, 1)[1].split(",")[0]):
+            errors.append(f"{name[:70]}: '{nxt}' overwrites the data of '{cur}'")
+    return errors
+
+
+def check_asm(asm: str) -> None:
+    """Checks every GEMM kernel of one translation unit's assembly; raises RuntimeError on a violation."""
+    n = 0
+    problems: list[str] = []
+    for name, lines in _kernel_bodies(asm, "gemm_"):
+        n += 1
+        text = "\n".join(lines)
+        if _COPY in text:
+            m = re.search(r"; ScratchSize: (\d+)", asm[asm.index(name + ":"):])
+            if m and int(m.group(1)) != 0:
+                problems.append(f"{name[:70]}: uses {m.group(1)} bytes of scratch memory (its accesses share the copies' counter)")
+            problems += check_copies(name, lines)
+        problems += check_wide_stores(name, lines)
+        problems += check_function(name, lines)
+    if n == 0:
+        problems.append("no GEMM kernel found in the assembly")
+    if problems:
+        raise RuntimeError("GEMM machine-code check failed:\n  " + "\n  ".join(problems[:20]))
+
+
 def check_gemm(hipcc: str, flags: list[str], source: str) -> None:
-    """Compiles `source` to gfx950 assembly and checks every gemm_bf16_kernel; raises RuntimeError on a violation."""
+    """Compiles `source` to gfx950 assembly and checks its GEMM kernels."""
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "gemm.s")
         proc = subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", source, "-o", out], capture_output=True, text=True)
         if proc.returncode != 0:
-            raise RuntimeError("hipcc failed emitting assembly for the load check:\n" + proc.stderr)
-        asm = open(out).read()
-    n = 0
-    problems: list[str] = []
-    for name, lines in _kernel_bodies(asm, "gemm_bf16_kernel"):
-        n += 1
-        text = "\n".join(lines)
-        m = re.search(r"; ScratchSize: (\d+)", asm[asm.index(name + ":"):])
-        if m and int(m.group(1)) != 0:
-            problems.append(f"{name[:60]}: uses {m.group(1)} bytes of scratch memory (its accesses share the load counter)")
-        if "global_load_dwordx4" not in text:
-            problems.append(f"{name[:60]}: no pipeline loads found")
-        problems += check_function(name, lines)
-    if n == 0:
-        problems.append("no gemm_bf16_kernel instantiation found in the assembly")
-    if problems:
-        raise RuntimeError("GEMM pipeline-load check failed:\n  " + "\n  ".join(problems[:20]))
+            raise RuntimeError("hipcc failed emitting assembly for the check:\n" + proc.stderr)
+        check_asm(open(out).read())
