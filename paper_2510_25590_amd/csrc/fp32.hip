@@ -1,18 +1,22 @@
-// The float32 context: dense projections on v_mfma_f32_32x32x2_f32 and attention with the Region-Instruction KV
+// The float32 context: dense projections on v_mfma_f32_16x16x4_f32 and attention with the Region-Instruction KV
 // cache (Eq.6) with float32 operands, float32 sums and a float32 softmax.  This is the arithmetic of the small
 // float32 configuration on which the method's path is first checked against the CPU definition at a tight
-// tolerance; one simple tile shape each, written for correctness, not speed (the bf16 kernels are the fast path).
+// tolerance.  Its launches are a few dozen rows wide, so every kernel here is a chain of memory latencies rather than
+// arithmetic: the k elements of a product (the keys of an attention) are dealt to the waves of a workgroup, each wave
+// reads its operands from global memory straight into fragments, several loads in flight, and the waves' float32
+// partial results meet once in LDS, in wave order.
 #include <cmath>
+#include <type_traits>
 #include "common.h"
 
 namespace {
 
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int kThreads = 256;
-constexpr int FB = 64;   // rows and columns of a workgroup tile: four waves, one 32 x 32 block each
-constexpr int FK = 16;   // k elements per step
+constexpr int FB = 64;   // rows and columns of a tile of the wide form: four waves, one 32 x 32 block each
+constexpr int FK = 16;   // k elements per step of the wide form, and per chunk of the other: one 16-byte load per lane and fragment, four MFMAs
 
 __device__ __forceinline__ float gelu_tanh_exact(float x) {
     return 0.5f * x * (1.0f + tanhf(0.7978845608028654f * (x + 0.044715f * x * x * x)));
@@ -52,9 +56,89 @@ __device__ __forceinline__ void store_f32(const GemmEpilogue& ep, int row, int c
 
 // C[m, n] = sum_k A[m, k] W[n, k]; A row-major float32 (lda a multiple of 4), W row-major [n, k], K a multiple of 16.
 // Rows past M and columns past N are computed on a repeated valid row and never stored.
+// A workgroup of NW waves owns a tile of RB*16 x CB*16; the waves split K into NW contiguous ranges of 16-wide chunks.
+// Which k of the instruction an element becomes is irrelevant as long as both operands agree: lane l holds row
+// (column) l % 16 of the block and, in MFMA e of a chunk, k = 4 * (l / 16) + e, so a chunk of a fragment is one 16-byte
+// load per lane, 64 contiguous bytes per row.  PF chunks are requested before the first of them is used.
+// 36 rows, float32 (same box, in a loop): 768 columns of K 256 11.1 -> 5.0 us, 256 of K 1024 30.0 -> 5.5, most of it the
+// launch; 640 x 256 x 1024 30.6 -> 12.9.
+// LDS row stride TN + 4: the four row groups that a store of the accumulator touches fall into different banks.
+template <int KIND, int RB, int CB, int NW, int PF>
+__global__ void __launch_bounds__(NW * 64)
+gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int M, int N, int K, GemmEpilogue ep) {
+    constexpr int TM = RB * 16, TN = CB * 16, LD = TN + 4;
+    __shared__ float part[NW][TM][LD];
+    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l16 = lane & 15, lq = lane >> 4;
+    const float* ap[RB];
+    const float* wp[CB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        int r = m0 + 16 * i + l16; r = r < M ? r : M - 1;
+        ap[i] = A + static_cast<int64_t>(r) * lda + 4 * lq;
+    }
+#pragma unroll
+    for (int j = 0; j < CB; ++j) {
+        int r = n0 + 16 * j + l16; r = r < N ? r : N - 1;
+        wp[j] = W + static_cast<int64_t>(r) * K + 4 * lq;
+    }
+    f32x4 acc[RB][CB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto chunks = [&](int c, auto count) __attribute__((always_inline)) {
+        constexpr int P = decltype(count)::value;
+        f32x4 av[P][RB], wv[P][CB];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+#pragma unroll
+            for (int i = 0; i < RB; ++i) av[p][i] = *reinterpret_cast<const f32x4*>(ap[i] + (c + p) * FK);
+#pragma unroll
+            for (int j = 0; j < CB; ++j) wv[p][j] = *reinterpret_cast<const f32x4*>(wp[j] + (c + p) * FK);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // every load of the group is on its way before the first product
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+#pragma unroll
+                    for (int j = 0; j < CB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[p][i][e], wv[p][j][e], acc[i][j], 0, 0, 0);
+    };
+    const int64_t n_chunks = K / FK;
+    int c = __builtin_amdgcn_readfirstlane(static_cast<int>(n_chunks * wave / NW));
+    const int c_end = __builtin_amdgcn_readfirstlane(static_cast<int>(n_chunks * (wave + 1) / NW));
+    for (; c + PF <= c_end; c += PF) chunks(c, std::integral_constant<int, PF>{});
+    for (; c + 2 <= c_end; c += 2) chunks(c, std::integral_constant<int, 2>{});
+    if (c < c_end) chunks(c, std::integral_constant<int, 1>{});
+    // accumulator r of a lane: row 4*(lane/16) + r, column lane%16 of a 16 x 16 block
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[wave][16 * i + 4 * lq + r][16 * j + l16] = acc[i][j][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < TM * TN; e += NW * 64) {
+        const int r = e / TN, cc = e % TN;
+        if (m0 + r >= M || n0 + cc >= N) continue;
+        float sum = part[0][r][cc];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += part[w][r][cc];
+        store_f32<KIND>(ep, m0 + r, n0 + cc, sum);
+    }
+}
+
+// C[m, n] = sum_k A[m, k] W[n, k]; A row-major float32 (lda a multiple of 4), W row-major [n, k], K a multiple of 16.
+// Rows past M and columns past N are computed on a repeated valid row and never stored.
+// The form for many tiles: 64 x 64 per workgroup, operands shared through LDS, so that the rows are fetched half as
+// often as with 32 x 32 tiles (2000 x 1024 x 256: 16.3 us against 22.2).
 template <int KIND>
 __global__ void __launch_bounds__(kThreads)
-gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int M, int N, int K, GemmEpilogue ep) {
+gemm_f32_wide_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int M, int N, int K, GemmEpilogue ep) {
     __shared__ float a_lds[FB][FK + 1];   // odd row stride: the 32 rows a fragment read touches fall into 32 banks
     __shared__ float w_lds[FB][FK + 1];
     const int m0 = blockIdx.y * FB, n0 = blockIdx.x * FB;
@@ -109,79 +193,163 @@ struct AttnF32Args {
     float scale; float* out; int ldo;
 };
 
-// Eq.6 for one (query row, head) per wave: the key list is the fresh rows followed by the cache rows in use.  Lane j of
-// the wave scores key j of a group of 64, the softmax runs online over the groups (running maximum and sum are the
-// same in every lane), and lane l accumulates output elements l and l + 64.
-template <int D>
-__global__ void __launch_bounds__(64)
+// Eq.6 for 16 query rows of one head per workgroup: the key list is the fresh rows followed by the cache rows in use,
+// in groups of 16 that are dealt to the NW waves in contiguous ranges.  A wave forms the transposed scores
+// S^T = K Q^T of a group with v_mfma_f32_16x16x4_f32: a lane then holds, for ONE query (l % 16), the scores of keys
+// 4 * (l / 16) + r, which is already the "B" operand of O^T = V^T P^T (MFMA r multiplies the keys 4 * (l / 16) + r).
+// Row i of V^T block (j, e) is output element d = 64 j + 4 i + e, so a lane reads V in 16-byte pieces, 256 contiguous
+// bytes per key, and holds 4 consecutive output elements per accumulator index.  K and V of the next group are
+// requested before the present group is used.  The waves' partial results (maximum, sum, O) meet in LDS, in wave order.
+// One wave per (query, head) with a serial walk over the values, the form before this one, took 96.5 us for 36 queries
+// on 544 keys (4 heads of 64) and 290 for 640 on 1216; now 13.3 and 24.4: the matrix instructions of one CU per 16
+// queries and head, and the launch.
+template <int D, int NW>
+__global__ void __launch_bounds__(NW * 64)
 attn_f32_kernel(AttnF32Args a) {
-    __shared__ float q_lds[D];
-    __shared__ float p_lds[64];
-    const int lane = threadIdx.x;
-    const int qrow = blockIdx.x, head = blockIdx.y;
+    constexpr int KC = D / 16, VJ = D / 64;
+    __shared__ float m_lds[NW][16], l_lds[NW][16];
+    __shared__ f32x4 o_lds[NW][16][D / 4 + 1];      // odd row stride in 16-byte pieces
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int q0 = blockIdx.x * 16, head = blockIdx.y;
     const int n_keys = a.n0 + a.n1;
-    const float* qp = a.q + static_cast<int64_t>(qrow) * a.ldq + head * D;
-    for (int d = lane; d < D; d += 64) q_lds[d] = qp[d];
-    __syncthreads();
-    auto key_row = [&](int key, const float*& kp, const float*& vp) {
-        if (key < a.n0) {
-            const int64_t off = static_cast<int64_t>(key) * a.ldkv0 + head * D;
-            kp = a.k0 + off; vp = a.v0 + off;
-        } else {
-            int64_t r = key - a.n0;
-            if (a.idx1) r = a.idx1[r];
-            const int64_t off = r * a.ldkv1 + head * D;
-            kp = a.k1 + off; vp = a.v1 + off;
+    const int64_t n_groups = (static_cast<int64_t>(n_keys) + 15) / 16;
+    const int g0 = __builtin_amdgcn_readfirstlane(static_cast<int>(n_groups * wave / NW));
+    const int g1 = __builtin_amdgcn_readfirstlane(static_cast<int>(n_groups * (wave + 1) / NW));
+    f32x4 q[KC];
+    {
+        int r = q0 + l16; r = r < a.n_q ? r : a.n_q - 1;
+        const float* qp = a.q + static_cast<int64_t>(r) * a.ldq + head * D + 4 * lq;
+        // rows of q carry no alignment promise beyond their elements'
+#pragma unroll
+        for (int c = 0; c < KC; ++c) q[c] = f32x4{qp[16 * c], qp[16 * c + 1], qp[16 * c + 2], qp[16 * c + 3]};
+    }
+    auto row_of = [&](int key, const float* base0, const float* base1) -> const float* {
+        key = key < n_keys ? key : n_keys - 1;      // keys past the end repeat a valid one; their weight is zero
+        if (key < a.n0) return base0 + static_cast<int64_t>(key) * a.ldkv0 + head * D;
+        int64_t r = key - a.n0;
+        if (a.idx1) r = a.idx1[r];
+        return base1 + r * a.ldkv1 + head * D;
+    };
+    auto load = [&](int g, f32x4 (&k)[KC], f32x4 (&v)[4][VJ]) __attribute__((always_inline)) {
+        const float* kp = row_of(16 * g + l16, a.k0, a.k1) + 4 * lq;
+        const float* vp[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) vp[r] = row_of(16 * g + 4 * lq + r, a.v0, a.v1) + 4 * l16;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) k[c] = *reinterpret_cast<const f32x4*>(kp + 16 * c);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < VJ; ++j) v[r][j] = *reinterpret_cast<const f32x4*>(vp[r] + 64 * j);
+    };
+    f32x4 o[VJ][4];
+#pragma unroll
+    for (int j = 0; j < VJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[j][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;           // l_run: this lane's keys only, until the end
+    auto group = [&](int g, const f32x4 (&k)[KC], const f32x4 (&v)[4][VJ]) __attribute__((always_inline)) {
+        // two chains of products: even and odd chunks
+        f32x4 s = {0.f, 0.f, 0.f, 0.f}, s2 = s;
+#pragma unroll
+        for (int c = 0; c < KC; c += 2)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[c][e], q[c][e], s, 0, 0, 0);
+                s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(k[c + 1][e], q[c + 1][e], s2, 0, 0, 0);
+            }
+        const int live = n_keys - (16 * g + 4 * lq);   // of this lane's four keys, those below `live` exist
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s[r] = r < live ? (s[r] + s2[r]) * a.scale : -INFINITY;
+            mx = fmaxf(mx, s[r]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m_run, mx);
+        const float ref = m_new == -INFINITY ? 0.f : m_new;   // only -inf so far: weights 0, not NaN
+        const float alpha = expf(m_run - ref);                // 0 for the first group
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int j = 0; j < VJ; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[j][e] *= alpha;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float p = r < live ? expf(s[r] - ref) : 0.f;
+            l_run += p;
+#pragma unroll
+            for (int j = 0; j < VJ; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)   // a repeated row contributes 0 * 0 even where it holds an infinity
+                    o[j][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(r < live ? v[r][j][e] : 0.f, p, o[j][e], 0, 0, 0);
         }
     };
-    float m_run = -INFINITY, l_run = 0.f;
-    float o[D / 64];
-#pragma unroll
-    for (int i = 0; i < D / 64; ++i) o[i] = 0.f;
-    for (int key0 = 0; key0 < n_keys; key0 += 64) {
-        const int key = key0 + lane;
-        float s = -INFINITY;
-        if (key < n_keys) {
-            const float* kp; const float* vp;
-            key_row(key, kp, vp);
-            float dot = 0.f;
-#pragma unroll 8
-            for (int d = 0; d < D; d += 4) {
-                const f32x4 kv = *reinterpret_cast<const f32x4*>(kp + d);
-                dot = fmaf(q_lds[d], kv[0], dot); dot = fmaf(q_lds[d + 1], kv[1], dot);
-                dot = fmaf(q_lds[d + 2], kv[2], dot); dot = fmaf(q_lds[d + 3], kv[3], dot);
-            }
-            s = dot * a.scale;
+    f32x4 ka[KC], va[4][VJ], kb[KC], vb[4][VJ];
+    if (g0 < g1) load(g0, ka, va);
+    for (int g = g0; g < g1; g += 2) {
+        if (g + 1 < g1) load(g + 1, kb, vb);
+        __builtin_amdgcn_sched_barrier(0);
+        group(g, ka, va);
+        if (g + 1 < g1) {
+            if (g + 2 < g1) load(g + 2, ka, va);
+            __builtin_amdgcn_sched_barrier(0);
+            group(g + 1, kb, vb);
         }
-        float mx = s;
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-        const float m_new = fmaxf(m_run, mx);            // finite: every group holds at least one key
-        const float alpha = expf(m_run - m_new);         // 0 for the first group
-        const float p = key < n_keys ? expf(s - m_new) : 0.f;
-        float psum = p;
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) psum += __shfl_xor(psum, m, 64);
-        l_run = l_run * alpha + psum;
-        m_run = m_new;
-#pragma unroll
-        for (int i = 0; i < D / 64; ++i) o[i] *= alpha;
-        p_lds[lane] = p;
-        __syncthreads();
-        const int live = n_keys - key0 < 64 ? n_keys - key0 : 64;
-        for (int j = 0; j < live; ++j) {
-            const float* kp; const float* vp;
-            key_row(key0 + j, kp, vp);
-            const float pj = p_lds[j];
-#pragma unroll
-            for (int i = 0; i < D / 64; ++i) o[i] = fmaf(pj, vp[lane + 64 * i], o[i]);
-        }
-        __syncthreads();   // p_lds is rewritten by the next group
     }
-    float* op = a.out + static_cast<int64_t>(qrow) * a.ldo + head * D;
-    const float inv = 1.0f / l_run;
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+    if (lq == 0) { m_lds[wave][l16] = m_run; l_lds[wave][l16] = l_run; }
+    // accumulator r of block (j, e): query l16, d = 64 j + 4 (4 lq + r) + e
 #pragma unroll
-    for (int i = 0; i < D / 64; ++i) op[lane + 64 * i] = o[i] * inv;
+    for (int j = 0; j < VJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o_lds[wave][l16][16 * j + 4 * lq + r] = f32x4{o[j][0][r], o[j][1][r], o[j][2][r], o[j][3][r]};
+    __syncthreads();
+    for (int t = threadIdx.x; t < 16 * (D / 4); t += NW * 64) {
+        const int row = t / (D / 4), piece = t % (D / 4);
+        if (q0 + row >= a.n_q) continue;
+        float m = m_lds[0][row];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = fmaxf(m, m_lds[w][row]);
+        const float ref = m == -INFINITY ? 0.f : m;
+        float l = 0.f;
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            if (n_groups * w / NW == n_groups * (w + 1) / NW) continue;   // a wave without keys
+            const float f = expf(m_lds[w][row] - ref);
+            l = fmaf(f, l_lds[w][row], l);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] = fmaf(f, o_lds[w][row][piece][e], sum[e]);
+        }
+        const float inv = 1.0f / l;
+        float* op = a.out + static_cast<int64_t>(q0 + row) * a.ldo + head * D + 4 * piece;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) op[e] = sum[e] * inv;
+    }
+}
+
+void launch_gemm_f32_wide(regione_ctx* ctx, const float* a, int lda, const float* w, int m, int n, int k, const GemmEpilogue& ep) {
+    const dim3 grid((n + FB - 1) / FB, (m + FB - 1) / FB);
+    switch (ep.kind) {
+        case EPI_PLAIN: hipLaunchKernelGGL((gemm_f32_wide_kernel<EPI_PLAIN>), grid, dim3(kThreads), 0, ctx->stream, a, lda, w, m, n, k, ep); break;
+        case EPI_QKV: hipLaunchKernelGGL((gemm_f32_wide_kernel<EPI_QKV>), grid, dim3(kThreads), 0, ctx->stream, a, lda, w, m, n, k, ep); break;
+        default: hipLaunchKernelGGL((gemm_f32_wide_kernel<EPI_RESID>), grid, dim3(kThreads), 0, ctx->stream, a, lda, w, m, n, k, ep); break;
+    }
+}
+
+template <int RB, int CB, int NW, int PF>
+void launch_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m, int n, int k, const GemmEpilogue& ep) {
+    const dim3 grid((n + CB * 16 - 1) / (CB * 16), (m + RB * 16 - 1) / (RB * 16)), block(NW * 64);
+    switch (ep.kind) {
+        case EPI_PLAIN: hipLaunchKernelGGL((gemm_f32_kernel<EPI_PLAIN, RB, CB, NW, PF>), grid, block, 0, ctx->stream, a, lda, w, m, n, k, ep); break;
+        case EPI_QKV: hipLaunchKernelGGL((gemm_f32_kernel<EPI_QKV, RB, CB, NW, PF>), grid, block, 0, ctx->stream, a, lda, w, m, n, k, ep); break;
+        default: hipLaunchKernelGGL((gemm_f32_kernel<EPI_RESID, RB, CB, NW, PF>), grid, block, 0, ctx->stream, a, lda, w, m, n, k, ep); break;
+    }
 }
 
 }  // namespace
@@ -200,14 +368,16 @@ int rg_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m
     if (k <= 0 || (k % FK) || (lda & 3)) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "gemm (float32): k=%d must be a positive multiple of 16 and lda=%d of 4", k, lda);
     if (!rg_aligned16(a) || !rg_aligned16(w)) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm (float32): operands must be 16-byte aligned");
     ProfScope prof(ctx, REGIONE_PROF_GEMM);
-    const dim3 grid((n + FB - 1) / FB, (m + FB - 1) / FB);
-    if (grid.y > 65535) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "gemm (float32): %d rows exceed this simple kernel's grid", m);
-    switch (ep.kind) {
-        case EPI_PLAIN: hipLaunchKernelGGL((gemm_f32_kernel<EPI_PLAIN>), grid, dim3(kThreads), 0, ctx->stream, a, lda, w, m, n, k, ep); break;
-        case EPI_QKV: hipLaunchKernelGGL((gemm_f32_kernel<EPI_QKV>), grid, dim3(kThreads), 0, ctx->stream, a, lda, w, m, n, k, ep); break;
-        case EPI_RESID: hipLaunchKernelGGL((gemm_f32_kernel<EPI_RESID>), grid, dim3(kThreads), 0, ctx->stream, a, lda, w, m, n, k, ep); break;
-        default: RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm (float32): bad epilogue kind %d", ep.kind);
-    }
+    if ((static_cast<int64_t>(m) + 63) / 64 > 65535) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "gemm (float32): %d rows exceed this simple kernel's grid", m);
+    if (ep.kind != EPI_PLAIN && ep.kind != EPI_QKV && ep.kind != EPI_RESID) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm (float32): bad epilogue kind %d", ep.kind);
+    // The smaller the tile, the more workgroups share the latency of a short product; the larger, the fewer bytes per
+    // product.  Measured (us, tiles of 16 / 32 / 64): 36 x 768 x 256 3.8 / 4.3 / 11, 205 x 256 x 1024 5.6 / 10.3 / 30,
+    // 205 x 768 x 256 (624 tiles of 16) 5.0 / 4.5 / 11, 640 x 256 x 1024 (640) 12.6 / 10.4 / 31,
+    // 1216 x 768 x 256 (228 tiles of 64) 17 / 11.6 / 11.7, 2000 x 1024 x 256 (512) 34 / 22 / 16.
+    auto tiles = [&](int64_t b) { return ((m + b - 1) / b) * ((n + b - 1) / b); };
+    if (tiles(64) >= 256) launch_gemm_f32_wide(ctx, a, lda, w, m, n, k, ep);
+    else if (tiles(16) > 512) launch_gemm_f32<2, 2, 8, 4>(ctx, a, lda, w, m, n, k, ep);
+    else launch_gemm_f32<1, 1, 8, 8>(ctx, a, lda, w, m, n, k, ep);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }
@@ -223,9 +393,9 @@ int rg_attention_f32(regione_ctx* ctx, const float* q, int ldq, int n_q,
     if (heads > 65535) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "attention (float32): %d heads", heads);
     ProfScope prof(ctx, REGIONE_PROF_ATTENTION);
     AttnF32Args a = {q, ldq, n_q, k0, v0, ldkv0, n0, k1, v1, ldkv1, n1, idx1, scale > 0.f ? scale : 1.0f / sqrtf(static_cast<float>(d)), out, ldo};
-    const dim3 grid(static_cast<unsigned>(n_q), static_cast<unsigned>(heads));
-    if (d == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64), 0, ctx->stream, a);
-    else hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64), 0, ctx->stream, a);
+    const dim3 grid(static_cast<unsigned>((n_q + 15) / 16), static_cast<unsigned>(heads));
+    if (d == 64) hipLaunchKernelGGL((attn_f32_kernel<64, 12>), grid, dim3(768), 0, ctx->stream, a);
+    else hipLaunchKernelGGL((attn_f32_kernel<128, 4>), grid, dim3(256), 0, ctx->stream, a);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }

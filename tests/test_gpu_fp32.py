@@ -65,6 +65,42 @@ def test_attention_float32_three_key_sources(d):
     ctx.close()
 
 
+# every tile of the product (16 x 16, 32 x 32 and 64 x 64 by the number of tiles) at ragged rows and columns, K of fewer
+# chunks than waves and of more than a load group
+@pytest.mark.parametrize("m,n,k", [(17, 33, 64), (15, 70, 192), (511, 1025, 64), (1100, 1000, 192), (2049, 500, 320)])
+def test_linear_float32_tile_edges(m, n, k):
+    rng = np.random.default_rng(300 + m)
+    x, w = rng.standard_normal((m, k)).astype(np.float32), rng.standard_normal((n, k)).astype(np.float32)
+    b = rng.standard_normal(n).astype(np.float32)
+    ctx = _ctx()
+    y = torch.full((m + 1, n), 7.0, dtype=torch.float32, device="cuda")
+    rg.regione_linear(ctx, f32(x), rg.pack_weight(ctx, f32(w)), f32(b), m, n, k, rg.ACT_NONE, rg.FP32, y)
+    got = host(y)
+    x, w = x.astype(np.float64), w.astype(np.float64)
+    # k + 1 float32 roundings of partial sums, each at most 2^-24 of the sum of magnitudes
+    assert np.all(np.abs(got[:m] - (x @ w.T + b)) <= (np.abs(x) @ np.abs(w).T + np.abs(b)) * (k + 1) * 2.0 ** -24)
+    assert np.all(got[m] == 7.0)
+    ctx.close()
+
+
+# queries around a workgroup's 16; keys from fewer groups of 16 than waves to a last group of one key; an infinite last value
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_q,n_fresh,n_c", [(1, 0, 1), (15, 3, 14), (16, 16, 1), (17, 0, 128), (33, 5, 300)])
+def test_attention_float32_edges(d, n_q, n_fresh, n_c):
+    rng = np.random.default_rng(400 + n_q + d)
+    q, kf, vf, kc, vc = (rng.standard_normal((n, 2, d)).astype(np.float32) for n in (n_q, n_fresh, n_fresh, n_c, n_c))
+    ctx = _ctx(hidden=2 * d, heads=2, d=d, mlp=64)
+    out = torch.full((n_q + 1, 2, d), 7.0, dtype=torch.float32, device="cuda")
+    fresh = (f32(kf), f32(vf)) if n_fresh else (None, None)
+    rg.regione_attn_kvcache(ctx, f32(q), n_q, *fresh, n_fresh, f32(kc), f32(vc), n_c, None, 0, 2, d, 0.0, out)
+    assert_close(host(out)[:n_q], orc.attention_kvcache(q, kf, vf, kc, vc), "float32 attention edges", **TOL)
+    vc[-1, 0, 0] = np.inf
+    rg.regione_attn_kvcache(ctx, f32(q), n_q, *fresh, n_fresh, f32(kc), f32(vc), n_c, None, 0, 2, d, 0.0, out)
+    got = host(out)
+    assert np.all(np.isposinf(got[:n_q, 0, 0])) and np.all(np.isfinite(got[:n_q, 1])) and np.all(got[n_q] == 7.0)
+    ctx.close()
+
+
 def _block_to_device_f32(streams, kind, ctx):
     keep, bw = [], rg.BlockWeights()
     for name, w in zip(("txt", "img") if kind == "double" else ("img",), streams):
