@@ -40,6 +40,11 @@ struct AttnArgs {
     int splits; int tiles_per_split; float* part;  // [splits][heads][n_q_pad][D + 4] when splits > 1: O, maximum, sum, two unused (rows stay 16-byte aligned)
     int n_q_pad;
     int q_tiles;
+    // Even ranges (see launch_attention): after `full_blocks` workgroups, each with one key range of one of the first
+    // q_full query tiles of a head, range_wgs workgroups take `range` consecutive key tiles each of the list (head, query tile >= q_full,
+    // key tile).  A range that covers a query tile's keys only in part leaves its partial result in slot 2 w (the range's
+    // first query tile) or 2 w + 1 (its last), rows of the query tile, D + 4 floats each as above.
+    int full_blocks, q_full, range, range_wgs;
 };
 
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
@@ -266,7 +271,8 @@ __device__ __forceinline__ void attn_tile(const bf16_t* smem, int t, int n_keys,
 }
 
 // NW waves per workgroup, QB blocks of 32 queries per wave, NSTAGE LDS stages.
-template <int D, int NW, int QB, int NSTAGE, int WPE, int MODE>
+// RANGED: the grid holds even ranges (AttnArgs); a form of its own because the loop over query tiles costs registers.
+template <int D, int NW, int QB, int NSTAGE, int WPE, int MODE, bool RANGED>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 attn_kvcache_kernel(AttnArgs a) {
     constexpr int DB = D / 32;   // 32-wide d blocks of the output
@@ -281,30 +287,40 @@ attn_kvcache_kernel(AttnArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     // XCD-aware numbering (workgroup i runs on XCD i % 8): all query tiles of one (head, key split) get consecutive
-    // slots on ONE XCD, so that the K/V range they share is filled into a single L2 once instead of once per query tile.
-    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-    const int group = (local / a.q_tiles) * 8 + xcd;            // (head, split) pair
-    if (group >= a.heads * a.splits) return;
-    const int q_tile = local % a.q_tiles;
-    const int head = group % a.heads;
-    const int split = group / a.heads;
-    const int q_base = q_tile * QW + wave * (QB * 32);
+    // slots on ONE XCD, so that the K/V range they share is filled into a single L2 once instead of once per query tile;
+    // for the same reason an XCD's even ranges are consecutive ones.
+    const int xcd = blockIdx.x & 7;
     const int n_keys = a.n0 + a.n1;
     const int n_tiles = (n_keys + KT - 1) / KT;
-    const int tile_begin = split * a.tiles_per_split;
-    int tile_end = tile_begin + a.tiles_per_split;
-    tile_end = tile_end < n_tiles ? tile_end : n_tiles;
-
-    // Q fragments ("B" operand): lane holds query l32 of the block, d = kk*16 + 8*lh + 0..7
-    bf16x8 qf[QB][KK];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        int qrow = q_base + qb * 32 + l32;
-        qrow = qrow < a.n_q ? qrow : a.n_q - 1;
-        const bf16_t* qp = a.q + static_cast<int64_t>(qrow) * a.ldq + head * D + 8 * lh;
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) qf[qb][kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16);
+    const bool ranged = RANGED && static_cast<int>(blockIdx.x) >= a.full_blocks;
+    int head, q_tile, tile_begin, tile_end, left = 0, slot = 0;
+    if (!ranged) {
+        const int local = blockIdx.x >> 3;
+        const int group = (local / a.q_full) * 8 + xcd;            // (head, split) pair
+        if (group >= a.heads * a.splits) return;
+        q_tile = local % a.q_full;
+        head = group % a.heads;
+        slot = group / a.heads;
+        tile_begin = slot * a.tiles_per_split;
+        tile_end = tile_begin + a.tiles_per_split;
+        tile_end = tile_end < n_tiles ? tile_end : n_tiles;
+    } else {
+        const int per_xcd = (a.range_wgs + 7) / 8;
+        const int w = xcd * per_xcd + ((static_cast<int>(blockIdx.x) - a.full_blocks) >> 3);
+        const int q_rest = a.q_tiles - a.q_full;
+        const int first = w * a.range;
+        const int total = a.heads * q_rest * n_tiles;              // the launcher keeps it below 2^30
+        if (w >= a.range_wgs || first >= total) return;
+        left = total - first < a.range ? total - first : a.range;
+        const int seg = first / n_tiles;
+        head = seg / q_rest;
+        q_tile = a.q_full + seg % q_rest;
+        tile_begin = first - seg * n_tiles;
+        tile_end = tile_begin + left < n_tiles ? tile_begin + left : n_tiles;
+        slot = 2 * w;
     }
+    head = __builtin_amdgcn_readfirstlane(head); q_tile = __builtin_amdgcn_readfirstlane(q_tile); slot = __builtin_amdgcn_readfirstlane(slot);
+    tile_begin = __builtin_amdgcn_readfirstlane(tile_begin); tile_end = __builtin_amdgcn_readfirstlane(tile_end); left = __builtin_amdgcn_readfirstlane(left);
 
     // per-lane LDS offsets (elements) of the fragment reads
     int koff[KK], voff[DB];
@@ -319,17 +335,6 @@ attn_kvcache_kernel(AttnArgs a) {
         }
     }
 
-    f32x16 o[QB][DB];
-    float m_run[QB], l_run[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        m_run[qb] = -INFINITY;
-        l_run[qb] = 0.f;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[qb][db][r] = 0.f;
-    }
     const float c = a.scale_log2e;
 
     // Two LDS stages, copies one tile ahead.  Per tile: wait until this tile's copies have landed, barrier (publishes
@@ -347,7 +352,7 @@ attn_kvcache_kernel(AttnArgs a) {
         for (int i = 0; i < LD_N; ++i) {
             const int pos = (wave * LD_N + i) * 64 + lane;
             const int row = pos / CPR, phys = pos % CPR;
-            const unsigned row_off = static_cast<unsigned>(row) * static_cast<unsigned>(src_ld) + static_cast<unsigned>(head * D);
+            const unsigned row_off = static_cast<unsigned>(row) * static_cast<unsigned>(src_ld);
             off_k[i] = (row_off + static_cast<unsigned>(k_swz<D>(row, phys) << 3)) * 2u;
             off_v[i] = (row_off + static_cast<unsigned>(v_swz<D>(row, phys) << 3)) * 2u;
         }
@@ -356,8 +361,8 @@ attn_kvcache_kernel(AttnArgs a) {
     auto issue_tile = [&](int t, unsigned stage_bytes) __attribute__((always_inline)) {
         const int tc = t < tile_end ? t : tile_end - 1;
         if (MODE == SRC_CONTIG && (tc + 1) * KT <= n_keys) {     // a full tile of one array: scalar base + fixed lane offsets
-            const bf16_t* kb = src_k + static_cast<int64_t>(tc) * KT * src_ld;
-            const bf16_t* vb = src_v + static_cast<int64_t>(tc) * KT * src_ld;
+            const bf16_t* kb = src_k + static_cast<int64_t>(tc) * KT * src_ld + head * D;
+            const bf16_t* vb = src_v + static_cast<int64_t>(tc) * KT * src_ld + head * D;
 #pragma unroll
             for (int i = 0; i < LD_N; ++i) {
                 const unsigned lds_blk = stage_bytes + wave_lds + static_cast<unsigned>(i) * 1024u;
@@ -368,66 +373,101 @@ attn_kvcache_kernel(AttnArgs a) {
             kv_tile_issue<D, NW, MODE == SRC_CONTIG ? SRC_TWO : MODE>(a, head, tc * KT, n_keys, stage_bytes);
         }
     };
-    if (tile_begin < tile_end) issue_tile(tile_begin, smem_bytes0);
-#define RG_ATTN_TILE(T, STAGE, MASK)                                                                      \
-    {                                                                                                     \
-        const int t_ = (T);                                                                               \
-        wait_async_copies<0>();                                                                           \
-        __syncthreads();                                                                                  \
-        issue_tile(t_ + 1, smem_bytes0 + ((STAGE) ^ 1) * STAGE_BYTES);                                    \
-        attn_tile<D, STAGE, QB, MASK>(smem, t_, n_keys, c, lh, koff, voff, qf, o, m_run, l_run);          \
-    }
-    // only the very last tile of the key list can be partial; it runs outside the main loop with the masking code
-    const bool last_partial = tile_end * KT > n_keys;
-    const int full_end = last_partial ? tile_end - 1 : tile_end;
-    for (int t = tile_begin; t < full_end; t += 2) {
-        RG_ATTN_TILE(t, 0, false)
-        if (t + 1 < full_end) RG_ATTN_TILE(t + 1, 1, false)
-    }
-    if (full_end < tile_end && tile_begin < tile_end) {   // its stage follows from the number of full tiles before it
-        if (((full_end - tile_begin) & 1) == 0) RG_ATTN_TILE(full_end, 0, true) else RG_ATTN_TILE(full_end, 1, true)
-    }
-#undef RG_ATTN_TILE
-    wait_async_copies<0>();   // nothing may still be writing LDS when the workgroup ends
-
-    // ---- finish: O^T accumulator r of d-block db: d = db*32 + 8*(r/4) + 4*lh + r%4, query = l32
+    for (;;) {   // one query tile and key range; an even range may run on into further query tiles
+        if (tile_begin < tile_end) issue_tile(tile_begin, smem_bytes0);
+        const int q_base = q_tile * QW + wave * (QB * 32);
+        // Q fragments ("B" operand): lane holds query l32 of the block, d = kk*16 + 8*lh + 0..7
+        bf16x8 qf[QB][KK];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int qrow = q_base + qb * 32 + l32;
-        const float l_tot = sum_across_halves(l_run[qb]);
-        if (qrow >= a.n_q) continue;
-        if (a.splits == 1) {
-            const float inv = 1.0f / l_tot;
-            bf16_t* op = a.out + static_cast<int64_t>(qrow) * a.ldo + head * D;
+        for (int qb = 0; qb < QB; ++qb) {
+            int qrow = q_base + qb * 32 + l32;
+            qrow = qrow < a.n_q ? qrow : a.n_q - 1;
+            const bf16_t* qp = a.q + static_cast<int64_t>(qrow) * a.ldq + head * D + 8 * lh;
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int d = db * 32 + 8 * g + 4 * lh;
-                    bf16x4 pk;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) pk[e] = static_cast<__bf16>(o[qb][db][4 * g + e] * inv);
-                    *reinterpret_cast<bf16x4*>(op + d) = pk;
-                }
-        } else {
-            // partial result: unnormalised O, running max (log2 domain) and sum
-            float* pp = a.part + ((static_cast<int64_t>(split) * a.heads + head) * a.n_q_pad + qrow) * (D + 4);
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int d = db * 32 + 8 * g + 4 * lh;
-                    *reinterpret_cast<f32x4*>(pp + d) = f32x4{o[qb][db][4 * g], o[qb][db][4 * g + 1], o[qb][db][4 * g + 2], o[qb][db][4 * g + 3]};
-                }
-            if (lh == 0) { pp[D] = m_run[qb] * c; pp[D + 1] = l_tot; }   // maximum in the log2 domain, as the merge kernel expects
+            for (int kk = 0; kk < KK; ++kk) qf[qb][kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16);
         }
+        f32x16 o[QB][DB];
+        float m_run[QB], l_run[QB];
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            m_run[qb] = -INFINITY;
+            l_run[qb] = 0.f;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[qb][db][r] = 0.f;
+        }
+#define RG_ATTN_TILE(T, STAGE, MASK)                                                                      \
+        {                                                                                                     \
+            const int t_ = (T);                                                                               \
+            wait_async_copies<0>();                                                                           \
+            __syncthreads();                                                                                  \
+            issue_tile(t_ + 1, smem_bytes0 + ((STAGE) ^ 1) * STAGE_BYTES);                                    \
+            attn_tile<D, STAGE, QB, MASK>(smem, t_, n_keys, c, lh, koff, voff, qf, o, m_run, l_run);          \
+        }
+        // only the very last tile of the key list can be partial; it runs outside the main loop with the masking code
+        const bool last_partial = tile_end * KT > n_keys;
+        const int full_end = last_partial ? tile_end - 1 : tile_end;
+        for (int t = tile_begin; t < full_end; t += 2) {
+            RG_ATTN_TILE(t, 0, false)
+            if (t + 1 < full_end) RG_ATTN_TILE(t + 1, 1, false)
+        }
+        if (full_end < tile_end && tile_begin < tile_end) {   // its stage follows from the number of full tiles before it
+            if (((full_end - tile_begin) & 1) == 0) RG_ATTN_TILE(full_end, 0, true) else RG_ATTN_TILE(full_end, 1, true)
+        }
+#undef RG_ATTN_TILE
+        wait_async_copies<0>();   // nothing may still be writing LDS when the workgroup ends
+
+        const bool whole = ranged ? tile_begin == 0 && tile_end == n_tiles : a.splits == 1;
+        // ---- finish: O^T accumulator r of d-block db: d = db*32 + 8*(r/4) + 4*lh + r%4, query = l32
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const int qrow = q_base + qb * 32 + l32;
+            const float l_tot = sum_across_halves(l_run[qb]);
+            if (qrow >= a.n_q) continue;
+            if (whole) {
+                const float inv = 1.0f / l_tot;
+                bf16_t* op = a.out + static_cast<int64_t>(qrow) * a.ldo + head * D;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int d = db * 32 + 8 * g + 4 * lh;
+                        bf16x4 pk;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) pk[e] = static_cast<__bf16>(o[qb][db][4 * g + e] * inv);
+                        *reinterpret_cast<bf16x4*>(op + d) = pk;
+                    }
+            } else {
+                // partial result: unnormalised O, running max (log2 domain) and sum
+                const int64_t prow = ranged ? static_cast<int64_t>(slot) * QW + (qrow - q_tile * QW) : (static_cast<int64_t>(slot) * a.heads + head) * a.n_q_pad + qrow;
+                float* pp = a.part + prow * (D + 4);
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int d = db * 32 + 8 * g + 4 * lh;
+                        *reinterpret_cast<f32x4*>(pp + d) = f32x4{o[qb][db][4 * g], o[qb][db][4 * g + 1], o[qb][db][4 * g + 2], o[qb][db][4 * g + 3]};
+                    }
+                if (lh == 0) { pp[D] = m_run[qb] * c; pp[D + 1] = l_tot; }   // maximum in the log2 domain, as the merge kernel expects
+            }
+        }    left -= tile_end - tile_begin;
+        if (!ranged || left <= 0) break;
+        __syncthreads();   // every wave has read its last tile before the next query tile's first copies
+        slot |= 1;         // only the last query tile of a range can be partial from here on
+        tile_begin = 0;
+        tile_end = left < n_tiles ? left : n_tiles;
+        if (++q_tile == a.q_tiles) { q_tile = a.q_full; ++head; }
     }
 }
 
-// Merges the split-KV partial results: out = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s.
-template <int D>
+// Merges the split-KV partial results: out = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s.  RANGED: of the even ranges
+// that met in a query tile (QW rows, tiles from q_full on; n_q counts the rows from there), in key order; query tiles
+// that one range covered are finished already.
+template <int D, int QW, bool RANGED>
 __global__ void __launch_bounds__(kThreads)
-attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n_q, int n_q_pad, bf16_t* __restrict__ out, int ldo) {
+attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n_q, int n_q_pad, bf16_t* __restrict__ out, int ldo,
+                    int q_full, int q_rest, int n_tiles, int range) {
     // one thread per (query, head, 4 d's)
     constexpr int G = D / 4;
     const int64_t gid = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
@@ -436,6 +476,14 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
     const int g = static_cast<int>(gid % G);
     const int head = static_cast<int>((gid / G) % heads);
     const int qrow = static_cast<int>(gid / (static_cast<int64_t>(G) * heads));
+    int w0 = 0, w0_slot = 0;
+    if (RANGED) {
+        const int first = (head * q_rest + qrow / QW) * n_tiles;      // this query tile's place in the list of key tiles
+        w0 = first / range;
+        splits = (first + n_tiles - 1) / range - w0 + 1;
+        if (splits == 1) return;
+        w0_slot = 2 * w0 + (w0 * range / n_tiles == first / n_tiles ? 0 : 1);   // later ranges start inside this query tile: slot 0
+    }
     // every split's row is requested before the first value is used; a wave's loads of one split are contiguous
     constexpr int kMaxSplits = 8;
     float ms[kMaxSplits], ls[kMaxSplits];
@@ -443,7 +491,8 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
 #pragma unroll
     for (int s = 0; s < kMaxSplits; ++s)
         if (s < splits) {
-            const float* pp = part + ((static_cast<int64_t>(s) * heads + head) * n_q_pad + qrow) * (D + 4);
+            const int64_t prow = RANGED ? static_cast<int64_t>(s == 0 ? w0_slot : 2 * (w0 + s)) * QW + qrow % QW : (static_cast<int64_t>(s) * heads + head) * n_q_pad + qrow;
+            const float* pp = part + prow * (D + 4);
             const float2 ml = *reinterpret_cast<const float2*>(pp + D);
             ms[s] = ml.x; ls[s] = ml.y;
             val[s] = *reinterpret_cast<const f32x4*>(pp + 4 * g);
@@ -465,7 +514,7 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
     bf16x4 pk;
 #pragma unroll
     for (int e = 0; e < 4; ++e) pk[e] = static_cast<__bf16>(acc[e] * inv);
-    *reinterpret_cast<bf16x4*>(out + static_cast<int64_t>(qrow) * ldo + head * D + 4 * g) = pk;
+    *reinterpret_cast<bf16x4*>(out + static_cast<int64_t>(qrow + (RANGED ? q_full * QW : 0)) * ldo + head * D + 4 * g) = pk;
 }
 
 template <int D, int NW, int QB, int NSTAGE, int WPE>
@@ -500,26 +549,65 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
     a.part = ctx->attn_part;
     a.q_tiles = q_tiles;
     const int groups_per_xcd = (a.heads * splits + 7) / 8;
-    const dim3 grid(static_cast<unsigned>(groups_per_xcd) * q_tiles * 8);
+    a.full_blocks = groups_per_xcd * q_tiles * 8;
+    a.q_full = q_tiles;
+    // Equal splits leave the chip idle where the workgroups do not fill its last pass (264 query tiles x heads: 0.52 or
+    // 1.03 passes of 512).  Even ranges give each of the last `slots` workgroups the same number of consecutive key tiles
+    // of what whole passes of unsplit query tiles leave over.  Their workgroups start at different keys and share less
+    // of what an L2 holds: fitted to measurements a tile costs 2.3 us there against 1.9 in a whole pass, and the model
+    // above is 10 % high.  Equal splits -> even ranges (us; queries x keys, 24 heads of 128): 1024 x 8704 141 -> 127,
+    // 1332 x 8704 by index list 247 -> 218, 8704 x 8704 913 -> 865, 3000 x 3000 144 -> 130, with 8 heads 8704 x 8704
+    // 388 -> 296; taken for all it would be 2560 x 8704 267 -> 298, 4096 x 8704 417 -> 440, 205 x 8704 47 -> 53.
+    // At most eight ranges meet in a query tile (range >= n_tiles / 7), as many as the merge kernel takes.
+    if (D == 128 && ctx->attn_force_splits == 0) {
+        const int whole = a.heads % 8 == 0 ? static_cast<int>(wgs / slots) : 0;    // other head counts: unsplit tiles would fill the XCDs unevenly
+        const int q_full = static_cast<int>(whole * slots) / a.heads;
+        const int64_t units = static_cast<int64_t>(a.heads) * (q_tiles - q_full) * n_tiles;
+        int64_t range = (units + static_cast<int64_t>(slots) - 1) / static_cast<int64_t>(slots);
+        const int64_t least = (n_tiles + 6) / 7 > 4 ? (n_tiles + 6) / 7 : 4;
+        if (range < least) range = least;
+        const int64_t range_wgs = (units + range - 1) / range;
+        const size_t need = static_cast<size_t>(range_wgs) * 2 * QW * (D + 4) * sizeof(float);
+        const double t = 1.9 * whole * (n_tiles + 4) + 2.3 * static_cast<double>(range) + 16.0;
+        if (units > 0 && units < (1 << 30) && need <= ctx->attn_part_bytes && t < 0.97 * 0.9 * best) {
+            a.splits = splits = 1;
+            a.tiles_per_split = n_tiles;
+            a.q_full = q_full;
+            a.full_blocks = (a.heads + 7) / 8 * q_full * 8;
+            a.range = static_cast<int>(range);
+            a.range_wgs = static_cast<int>(range_wgs);
+        }
+    }
+    const dim3 grid(static_cast<unsigned>(a.full_blocks + (a.range_wgs + 7) / 8 * 8));
     constexpr size_t lds_bytes = static_cast<size_t>(NSTAGE) * 2 * KT * D * sizeof(bf16_t);
     constexpr uint32_t grant_bit = 1u << (24 + (D == 128 ? 1 : 0));   // bits 0-23 belong to the GEMM kernels
+    using Kernel = void (*)(AttnArgs);
+    // by source, then with and without even ranges
+    static constexpr Kernel kernels[3][2] = {
+        {attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_CONTIG, false>, attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_CONTIG, D == 128>},
+        {attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_TWO, false>, attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_TWO, D == 128>},
+        {attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_INDEXED, false>, attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_INDEXED, D == 128>}};
     if (!(ctx->lds_grant_mask & grant_bit)) {   // per instantiation: more than 64 KiB of LDS has to be granted explicitly
-        RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_INDEXED>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes)));
-        RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_TWO>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes)));
-        RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_CONTIG>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes)));
+        for (const auto& by_source : kernels)
+            for (Kernel k : by_source)
+                RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes)));
         ctx->lds_grant_mask |= grant_bit;
     }
     // a lane's byte offset inside a tile of a contiguous source has to fit 32 bits
     const int64_t src_ld = a.n0 > 0 ? a.ldkv0 : a.ldkv1;
     const bool contig = !a.idx1 && (a.n0 == 0 || a.n1 == 0) && (KT * src_ld + a.heads * D) * 2 < (int64_t{1} << 31);
-    if (a.idx1) hipLaunchKernelGGL((attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_INDEXED>), grid, dim3(NW * 64), lds_bytes, ctx->stream, a);
-    else if (contig) hipLaunchKernelGGL((attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_CONTIG>), grid, dim3(NW * 64), lds_bytes, ctx->stream, a);
-    else hipLaunchKernelGGL((attn_kvcache_kernel<D, NW, QB, NSTAGE, WPE, SRC_TWO>), grid, dim3(NW * 64), lds_bytes, ctx->stream, a);
+    hipLaunchKernelGGL(kernels[a.idx1 ? SRC_INDEXED : contig ? SRC_CONTIG : SRC_TWO][a.range_wgs > 0], grid, dim3(NW * 64), lds_bytes, ctx->stream, a);
     RG_LAUNCH_CHECK();
-    if (splits > 1) {
-        const int64_t total = static_cast<int64_t>(a.n_q) * a.heads * (D / 4);
-        hipLaunchKernelGGL((attn_combine_kernel<D>), dim3(static_cast<unsigned>((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, ctx->stream,
-                           a.part, splits, a.heads, a.n_q, a.n_q_pad, a.out, a.ldo);
+    if (splits > 1 || a.range_wgs > 0) {
+        const int rows = a.n_q - (a.range_wgs > 0 ? a.q_full * QW : 0);
+        const int64_t total = static_cast<int64_t>(rows) * a.heads * (D / 4);
+        const dim3 merge_grid(static_cast<unsigned>((total + kThreads - 1) / kThreads));
+        if (a.range_wgs > 0)
+            hipLaunchKernelGGL((attn_combine_kernel<D, QW, true>), merge_grid, dim3(kThreads), 0, ctx->stream,
+                               a.part, 0, a.heads, rows, 0, a.out, a.ldo, a.q_full, q_tiles - a.q_full, n_tiles, a.range);
+        else
+            hipLaunchKernelGGL((attn_combine_kernel<D, QW, false>), merge_grid, dim3(kThreads), 0, ctx->stream,
+                               a.part, splits, a.heads, a.n_q, a.n_q_pad, a.out, a.ldo, 0, 0, 0, 0);
         RG_LAUNCH_CHECK();
     }
     return REGIONE_OK;
