@@ -624,9 +624,9 @@ def main():
         a_ms = prof["attention"][0] / args.steps
         ach = gemm_flops / (g_ms * 1e-3) / 1e12
         traffic = profiled_traffic() if n == 820 else {}     # the committed counter summaries were taken on the default workload
-        out["roofline"] = {"kernel": "gemm_bf16_kernel (QKV, attention output, MLP up, MLP down) + gemm_skinny_kernel (velocity head): 5 launches per step",
+        out["roofline"] = {"kernel": "gemm_kg_kernel / gemm_pp_kernel (QKV, attention output, MLP up, MLP down) + gemm_skinny_kernel (velocity head): 5 launches per step",
                            "bound": "mfma", "achieved": ach, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_BF16_TFLOPS,
-                           "traffic": traffic.get("gemm_bf16_kernel"),
+                           "traffic": traffic.get("step_gemm_kernels"),
                            "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE/WRITE_SIZE at the L2-fabric boundary, from profiles/*_hbm_traffic.txt)",
                            "algorithmic_flops_per_launch": gemm_flops / 5, "avg_launch_ms": prof["gemm"][0] / max(prof["gemm"][1], 1),
                            "measured_in": f"a second timed region of the same {args.steps} steps with HIP event pairs ({ms_profiled:.4f} ms per step there)"}
