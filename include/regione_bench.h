@@ -17,7 +17,7 @@ extern "C" {
  * choice. */
 int regione_tune_gemm(regione_ctx* ctx, int32_t wave_tile_blocks, int32_t k_splits);
 
-/* Tuning knob for experiments: forces the number of key-range splits (1..8) of every later
+/* Tuning knob for experiments: forces the number of key-range splits (1..32) of every later
  * attention call of this context; 0 restores the automatic choice. */
 int regione_tune_attention(regione_ctx* ctx, int32_t key_splits);
 

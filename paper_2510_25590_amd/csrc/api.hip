@@ -55,7 +55,10 @@ extern "C" int regione_create(regione_ctx** out, const regione_dims* dims, void*
     const size_t es = c->f32 ? 4 : 2;   // bytes per activation element
     c->part_counts_cap = rg_partition_scratch_ints(dims->max_tokens);   // per-block counts and one decision bit per token
     const size_t split_rows = n < 2048 ? n : 2048;
-    c->attn_part_bytes = static_cast<size_t>(8) * dims->heads * split_rows * (dims->head_dim + 4) * sizeof(float);
+    // partial rows of an attention: eight key ranges for up to 2048 queries, and for few queries up to 32 of at most 8192 rows together
+    size_t part_rows = 8 * split_rows;
+    if (part_rows < 8192) part_rows = 32 * split_rows < 8192 ? 32 * split_rows : 8192;
+    c->attn_part_bytes = part_rows * dims->heads * (dims->head_dim + 4) * sizeof(float);
     int rc = dev_alloc(&c->part_counts, static_cast<size_t>(c->part_counts_cap));
     if (rc == REGIONE_OK) rc = dev_alloc(&c->u, n * H * es);
     if (rc == REGIONE_OK) rc = dev_alloc(&c->q, n * H * es);

@@ -28,6 +28,7 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int kThreads = 256;
 constexpr int KT = 64;  // keys per tile
+constexpr int kMaxSplits = 32;   // key ranges of a query tile
 
 struct AttnArgs {
     const bf16_t* q; int ldq; int n_q;
@@ -464,7 +465,7 @@ attn_kvcache_kernel(AttnArgs a) {
 // Merges the split-KV partial results: out = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s.  RANGED: of the even ranges
 // that met in a query tile (QW rows, tiles from q_full on; n_q counts the rows from there), in key order; query tiles
 // that one range covered are finished already.
-template <int D, int QW, bool RANGED>
+template <int D, int QW, bool RANGED, int MAXS>
 __global__ void __launch_bounds__(kThreads)
 attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n_q, int n_q_pad, bf16_t* __restrict__ out, int ldo,
                     int q_full, int q_rest, int n_tiles, int range) {
@@ -485,11 +486,10 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
         w0_slot = 2 * w0 + (w0 * range / n_tiles == first / n_tiles ? 0 : 1);   // later ranges start inside this query tile: slot 0
     }
     // every split's row is requested before the first value is used; a wave's loads of one split are contiguous
-    constexpr int kMaxSplits = 8;
-    float ms[kMaxSplits], ls[kMaxSplits];
-    f32x4 val[kMaxSplits];
+    float ms[MAXS], ls[MAXS];
+    f32x4 val[MAXS];
 #pragma unroll
-    for (int s = 0; s < kMaxSplits; ++s)
+    for (int s = 0; s < MAXS; ++s)
         if (s < splits) {
             const int64_t prow = RANGED ? static_cast<int64_t>(s == 0 ? w0_slot : 2 * (w0 + s)) * QW + qrow % QW : (static_cast<int64_t>(s) * heads + head) * n_q_pad + qrow;
             const float* pp = part + prow * (D + 4);
@@ -499,12 +499,12 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
         }
     float m = -INFINITY;
 #pragma unroll
-    for (int s = 0; s < kMaxSplits; ++s)
+    for (int s = 0; s < MAXS; ++s)
         if (s < splits && ls[s] > 0.f) m = fmaxf(m, ms[s]);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     float l = 0.f;
 #pragma unroll
-    for (int s = 0; s < kMaxSplits; ++s)
+    for (int s = 0; s < MAXS; ++s)
         if (s < splits && ls[s] > 0.f) {   // a split with l = 0 saw no key
             const float w = fast_exp2(ms[s] - m);
             l += w * ls[s];
@@ -515,6 +515,25 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
 #pragma unroll
     for (int e = 0; e < 4; ++e) pk[e] = static_cast<__bf16>(acc[e] * inv);
     *reinterpret_cast<bf16x4*>(out + static_cast<int64_t>(qrow + (RANGED ? q_full * QW : 0)) * ldo + head * D + 4 * g) = pk;
+}
+
+// Microseconds of an attention with `s` equal key ranges where the unsplit query tiles leave CUs empty.  Fitted to forced
+// ranges of 1-32 over 105 shapes (16-1024 queries, 544-19456 keys, 24 and 8 heads of 128, 4 of 64): a key tile costs `alone` on a CU that holds one
+// workgroup, `pair` and more where an XCD's 32 CUs hold up to two each, `pass` in a full pass of 64; then the merge launch, the partial rows'
+// way out and back, and 1.2 us of the merge kernel for more than eight ranges.  The choice is 1 % behind the best range count
+// on average; eight ranges at most, with one cost for all fills, was 9 % behind, up to 1.7 times.
+// us, 24 heads: 512 x 8704 84.9 -> 67.6, 384 x 8704 63.4 -> 54.9, 16 x 19456 52.7 -> 42.6; 8 heads, 16 x 19456 47.7 -> 28.0;
+// 4 heads of 64, 1024 x 19456 40.9 -> 37.8.
+template <int D>
+double split_time(int q_tiles, int heads, int n_q, int n_tiles, int s) {
+    struct Cost { double fixed, alone, pair, more, pass, merge, mb, range; };
+    constexpr Cost c = D == 128 ? Cost{6.1, 1.0, 1.47, 0.39, 1.6, 3.4, 0.33, 0.28} : Cost{3.9, 0.68, 0.95, -0.05, 0.64, 1.3, 0.58, 0.35};
+    const int per = (n_tiles + s - 1) / s;
+    const int per_xcd = (heads * s + 7) / 8 * q_tiles, full = per_xcd / 64, rem = per_xcd % 64;
+    double t = c.fixed + full * c.pass * (per + 2);
+    if (rem > 0) t += per * (rem <= 32 ? c.alone : c.pair + c.more * (rem - 32) / 32.0);
+    if (s > 1) t += c.merge + c.mb * (s * 4.0e-6 * n_q * heads * (D + 4)) + c.range * s + (s > 8 ? 1.2 : 0.0);
+    return t;
 }
 
 template <int D, int NW, int QB, int NSTAGE, int WPE>
@@ -530,7 +549,13 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
     const double wgs = static_cast<double>(q_tiles) * a.heads;
     int splits = 1;
     double best = 0.0;
-    for (int s = 1; s <= 8 && (s == 1 || s * 4 <= n_tiles); ++s) {
+    const bool few = static_cast<int64_t>(q_tiles) * a.heads <= 256;   // at most one workgroup per CU before the split: a model of its own
+    const size_t part_row_set = static_cast<size_t>(a.heads) * a.n_q * (D + 4) * sizeof(float);
+    for (int s = 1; few && s <= kMaxSplits && (s == 1 || (s * 2 <= n_tiles && s * part_row_set <= ctx->attn_part_bytes)); ++s) {
+        const double t = split_time<D>(q_tiles, a.heads, a.n_q, n_tiles, s);
+        if (s == 1 || t < best) { best = t; splits = s; }
+    }
+    for (int s = 1; !few && s <= 8 && (s == 1 || s * 4 <= n_tiles); ++s) {
         const double load = wgs * s / slots;
         const double passes = load <= 1.0 ? 1.0 : 0.5 * (ceil(load) + load);   // a last, partly filled pass runs faster
         const double fill = wgs * s <= 256.0 ? 0.68 : 1.0;                      // a CU with one workgroup runs it faster
@@ -555,9 +580,9 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
     // 1.03 passes of 512).  Even ranges give each of the last `slots` workgroups the same number of consecutive key tiles
     // of what whole passes of unsplit query tiles leave over.  Their workgroups start at different keys and share less
     // of what an L2 holds: fitted to measurements a tile costs 2.3 us there against 1.9 in a whole pass, and the model
-    // above is 10 % high.  Equal splits -> even ranges (us; queries x keys, 24 heads of 128): 1024 x 8704 141 -> 127,
+    // for many query tiles is 10 % high.  Equal splits -> even ranges (us; queries x keys, 24 heads of 128): 1024 x 8704 141 -> 127,
     // 1332 x 8704 by index list 247 -> 218, 8704 x 8704 913 -> 865, 3000 x 3000 144 -> 130, with 8 heads 8704 x 8704
-    // 388 -> 296; taken for all it would be 2560 x 8704 267 -> 298, 4096 x 8704 417 -> 440, 205 x 8704 47 -> 53.
+    // 388 -> 296 (with up to 256 query tiles x heads split_time finds equal ranges as fast: 1024 x 8704 122.5 in four); taken for all it would be 2560 x 8704 267 -> 298, 4096 x 8704 417 -> 440, 205 x 8704 47 -> 53.
     // At most eight ranges meet in a query tile (range >= n_tiles / 7), as many as the merge kernel takes.
     if (D == 128 && ctx->attn_force_splits == 0) {
         const int whole = a.heads % 8 == 0 ? static_cast<int>(wgs / slots) : 0;    // other head counts: unsplit tiles would fill the XCDs unevenly
@@ -569,7 +594,7 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
         const int64_t range_wgs = (units + range - 1) / range;
         const size_t need = static_cast<size_t>(range_wgs) * 2 * QW * (D + 4) * sizeof(float);
         const double t = 1.9 * whole * (n_tiles + 4) + 2.3 * static_cast<double>(range) + 16.0;
-        if (units > 0 && units < (1 << 30) && need <= ctx->attn_part_bytes && t < 0.97 * 0.9 * best) {
+        if (units > 0 && units < (1 << 30) && need <= ctx->attn_part_bytes && t < 0.97 * (few ? 1.0 : 0.9) * best) {
             a.splits = splits = 1;
             a.tiles_per_split = n_tiles;
             a.q_full = q_full;
@@ -580,7 +605,7 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
     }
     const dim3 grid(static_cast<unsigned>(a.full_blocks + (a.range_wgs + 7) / 8 * 8));
     constexpr size_t lds_bytes = static_cast<size_t>(NSTAGE) * 2 * KT * D * sizeof(bf16_t);
-    constexpr uint32_t grant_bit = 1u << (24 + (D == 128 ? 1 : 0));   // bits 0-23 belong to the GEMM kernels
+    constexpr uint32_t grant_bit = D == 128 ? 2u : 1u;
     using Kernel = void (*)(AttnArgs);
     // by source, then with and without even ranges
     static constexpr Kernel kernels[3][2] = {
@@ -603,10 +628,10 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
         const int64_t total = static_cast<int64_t>(rows) * a.heads * (D / 4);
         const dim3 merge_grid(static_cast<unsigned>((total + kThreads - 1) / kThreads));
         if (a.range_wgs > 0)
-            hipLaunchKernelGGL((attn_combine_kernel<D, QW, true>), merge_grid, dim3(kThreads), 0, ctx->stream,
+            hipLaunchKernelGGL((attn_combine_kernel<D, QW, true, 8>), merge_grid, dim3(kThreads), 0, ctx->stream,
                                a.part, 0, a.heads, rows, 0, a.out, a.ldo, a.q_full, q_tiles - a.q_full, n_tiles, a.range);
         else
-            hipLaunchKernelGGL((attn_combine_kernel<D, QW, false>), merge_grid, dim3(kThreads), 0, ctx->stream,
+            hipLaunchKernelGGL((splits > 8 ? attn_combine_kernel<D, QW, false, kMaxSplits> : attn_combine_kernel<D, QW, false, 8>), merge_grid, dim3(kThreads), 0, ctx->stream,
                                a.part, splits, a.heads, a.n_q, a.n_q_pad, a.out, a.ldo, 0, 0, 0, 0);
         RG_LAUNCH_CHECK();
     }
@@ -617,7 +642,7 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
 
 extern "C" int regione_tune_attention(regione_ctx* ctx, int32_t key_splits) {
     if (!ctx) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_attention: null context");
-    if (key_splits < 0 || key_splits > 8) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_attention: key_splits=%d must be 0..8", key_splits);
+    if (key_splits < 0 || key_splits > kMaxSplits) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_attention: key_splits=%d must be 0..32", key_splits);
     ctx->attn_force_splits = key_splits;
     return REGIONE_OK;
 }
