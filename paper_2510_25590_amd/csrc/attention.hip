@@ -14,6 +14,7 @@
 // of gfx950.  The k-slot of the second product pairs lane-half h, slot s of both operands, so the
 // only requirement is that both sides enumerate keys identically: slot s of half h of MFMA (kb,j)
 // is key kb*32 + 16*j + 8*(s/4) + 4*h + s%4, which is exactly the row order of the S^T accumulator.
+#include <cfloat>
 #include <cmath>
 #include "common.h"
 
@@ -218,10 +219,10 @@ __device__ __forceinline__ void attn_tile(const bf16_t* smem, int t, int n_keys,
         // maximum exceeds it by more than kRescaleSlack (in the log2 domain), so exp2((s - m_run) c) <= 2^kRescaleSlack
         // and the 64-multiplication rescale of the accumulators becomes rare.  Any reference gives the same quotient
         // O / l; the probabilities keep their relative precision in bf16 whatever their scale.
-        const bool move = (mx - m_run[qb]) * c > kRescaleSlack;     // the first tile: m_run = -inf, always true
+        const bool move = (mx - m_run[qb]) * c > kRescaleSlack;     // the first tile: m_run is the most negative reference
         float m_new = m_run[qb];
         if (__builtin_amdgcn_ballot_w64(move) != 0) {               // wave-uniform branch
-            m_new = move ? mx : m_run[qb];                          // finite: every tile holds at least one live key
+            m_new = move ? mx : m_run[qb];
             const float alpha = move ? fast_exp2((m_run[qb] - m_new) * c) : 1.0f;
             l_run[qb] *= alpha;
 #pragma unroll
@@ -337,6 +338,9 @@ attn_kvcache_kernel(AttnArgs a) {
     }
 
     const float c = a.scale_log2e;
+    // the reference of a row that has met no score above -inf: finite and finite times c, so that such keys weigh exp2(-inf) = 0
+    // (with a reference of -inf they would weigh exp2(-inf + inf) = NaN), and no larger than any finite score worth keeping
+    const float m_floor = c <= 1.0f ? -FLT_MAX : -FLT_MAX * 0.999999f / c;
 
     // Two LDS stages, copies one tile ahead.  Per tile: wait until this tile's copies have landed, barrier (publishes
     // them and retires the stage read one tile ago), issue the copies of the next tile into that retired stage, compute.
@@ -391,7 +395,7 @@ attn_kvcache_kernel(AttnArgs a) {
         float m_run[QB], l_run[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            m_run[qb] = -INFINITY;
+            m_run[qb] = m_floor;
             l_run[qb] = 0.f;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
@@ -497,15 +501,17 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
             ms[s] = ml.x; ls[s] = ml.y;
             val[s] = *reinterpret_cast<const f32x4*>(pp + 4 * g);
         }
+    // No partial result is left out: one without keys, or whose scores are all -inf, has a sum of zero under a finite maximum and
+    // adds nothing, and one whose sum is NaN (a NaN key, an overflowing score) has to make the row NaN as it does unsplit.
     float m = -INFINITY;
 #pragma unroll
     for (int s = 0; s < MAXS; ++s)
-        if (s < splits && ls[s] > 0.f) m = fmaxf(m, ms[s]);
+        if (s < splits) m = fmaxf(m, ms[s]);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     float l = 0.f;
 #pragma unroll
     for (int s = 0; s < MAXS; ++s)
-        if (s < splits && ls[s] > 0.f) {   // a split with l = 0 saw no key
+        if (s < splits) {
             const float w = fast_exp2(ms[s] - m);
             l += w * ls[s];
             acc[0] += w * val[s][0]; acc[1] += w * val[s][1]; acc[2] += w * val[s][2]; acc[3] += w * val[s][3];
