@@ -30,6 +30,32 @@ void free_all(regione_ctx* c) {
     }
     delete[] c->prof_class;
 }
+
+__global__ void clear_counters_kernel(int* counters, int n) {
+    for (int i = static_cast<int>(threadIdx.x); i < n; i += static_cast<int>(blockDim.x)) counters[i] = 0;
+}
+// Clears the arrival counters ahead of the context's first launch, in the order of its stream: nothing waits, least of all for
+// other streams.  A stream that is being captured would only clear them when the graph runs; a stream of its own does it then.
+int clear_counters(regione_ctx* c, int n) {
+    hipStream_t stream = c->stream, own = nullptr;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {       // the default stream while another one is captured
+        (void)hipGetLastError();
+        capture = hipStreamCaptureStatusActive;
+    }
+    if (capture != hipStreamCaptureStatusNone) {
+        RG_HIP(hipStreamCreateWithFlags(&own, hipStreamNonBlocking));
+        stream = own;
+    }
+    hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(256), 0, stream, c->gemm_arrived, n);
+    hipError_t e = hipGetLastError();
+    if (own) {
+        if (e == hipSuccess) e = hipStreamSynchronize(own);
+        (void)hipStreamDestroy(own);
+    }
+    RG_HIP(e);
+    return REGIONE_OK;
+}
 }  // namespace
 
 extern "C" int regione_create(regione_ctx** out, const regione_dims* dims, void* hip_stream) {
@@ -73,10 +99,7 @@ extern "C" int regione_create(regione_ctx** out, const regione_dims* dims, void*
     c->gemm_part_bytes = n > 0 ? static_cast<size_t>(128) << 20 : 0;
     if (rc == REGIONE_OK) rc = dev_alloc(reinterpret_cast<char**>(&c->gemm_part), c->gemm_part_bytes);
     if (rc == REGIONE_OK) rc = dev_alloc(&c->gemm_arrived, 2 * kMaxSplitTiles);
-    if (rc == REGIONE_OK && (hipMemset(c->gemm_arrived, 0, 2 * kMaxSplitTiles * sizeof(int)) != hipSuccess || hipDeviceSynchronize() != hipSuccess)) {
-        regione_set_error("create: cannot clear the arrival counters");
-        rc = REGIONE_ERR_HIP;
-    }
+    if (rc == REGIONE_OK) rc = clear_counters(c, 2 * kMaxSplitTiles);
     if (rc == REGIONE_OK) {   // pinned, device-visible host word for the edited-token count (saves the device-to-host copy)
         void* host = nullptr; void* dev = nullptr;
         if (hipHostMalloc(&host, 64, hipHostMallocMapped) != hipSuccess || hipHostGetDevicePointer(&dev, host, 0) != hipSuccess) {
