@@ -31,7 +31,7 @@ EXPORTS = (
     "regione_quantize_rows_fp8", "regione_pack_weight_fp8", "regione_linear_fp8", "regione_mfma_peak_probe",
     "regione_partition_static", "regione_rel_decision_host", "regione_rel_update_host", "regione_fresh_slots", "regione_time_bias",
     "regione_euler_rows", "regione_gather_pair", "regione_scatter_pair", "regione_velocity_head", "regione_region_step",
-    "regione_block_forward_fp8",
+    "regione_block_forward_fp8", "regione_gemm_plan_host",
 )
 STEP_FULL, STEP_FULL_STORE, STEP_REGION = 0, 1, 2
 PROF_NAMES = ("partition", "rows", "layernorm", "gemm", "attention", "velocity")
@@ -498,6 +498,16 @@ def regione_linear_fp8(ctx, xq, x_scale, wq_packed, w_scale, b, m, n, k, act, ou
 
 def regione_tune_gemm(ctx, wave_tile_blocks: int, k_splits: int):
     _check(lib().regione_tune_gemm(ctx.handle, wave_tile_blocks, k_splits))
+
+
+GEMM_BF16, GEMM_E4M3 = 0, 1
+
+
+def regione_gemm_plan_host(m: int, n: int, k: int, kind: int, workspace_bytes: int = 128 << 20):
+    """(tile code, K splits) that a product gets by itself."""
+    tile, splits = C.c_int32(0), C.c_int32(0)
+    _check(lib().regione_gemm_plan_host(m, n, k, kind, C.c_int64(workspace_bytes), C.byref(tile), C.byref(splits)))
+    return tile.value, splits.value
 
 
 def regione_tune_attention(ctx, key_splits: int):

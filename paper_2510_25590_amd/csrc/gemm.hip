@@ -43,15 +43,13 @@ pack_weight_kernel(const bf16_t* __restrict__ w, int n, int k, bf16_t* __restric
 // first copies and epilogue per round of workgroups.  A K split adds its partial sums' way out and back (padded tiles).
 // Against the best of all plans, timed over 126 shapes (36-8704 rows, 256-21504 columns, k 256-15360), the choice loses 1.1 %
 // on average and 13 % at most.
-struct TileShape { int code, rows, cols, lds_kb; };
+struct TileShape { int code, rows, cols, lds_kb, form; };   // form: kTilesFp8 only
 constexpr TileShape kTiles[] = {{222, 64, 64, 64},    {224, 64, 128, 96},   {242, 128, 64, 96},   {244, 128, 128, 128}, {274, 224, 128, 132}, {284, 256, 128, 144},
                                 {426, 128, 96, 112},  {436, 192, 96, 144},  {446, 256, 96, 132},  {44, 128, 256, 144},  {64, 192, 256, 136},  {74, 224, 256, 148},
                                 {84, 256, 256, 160}};
-constexpr TileShape kTilesFp8[] = {{42, 128, 128, 96}, {62, 192, 128, 120}, {82, 256, 128, 144}, {44, 128, 256, 144}};
-
 struct GemmPlan { int tile; int splits; };
 
-double plan_time(const TileShape& t, int m, int n, int steps, int splits) {
+double plan_time_bf16(const TileShape& t, int m, int n, int steps, int splits) {
     const int m_tiles = (m + t.rows - 1) / t.rows, n_tiles = (n + t.cols - 1) / t.cols;
     const long units = static_cast<long>(m_tiles) * n_tiles * splits;
     const int per = (steps + splits - 1) / splits;
@@ -78,8 +76,50 @@ double plan_time(const TileShape& t, int m, int n, int steps, int splits) {
     return us;
 }
 
-template <size_t N>
-GemmPlan plan_over(const TileShape (&tiles)[N], const regione_ctx* ctx, int m, int n, int steps) {
+// The E4M3 tiles by kernel: rows of their own for each group, a ring of three or four phases (gemm_pp_kernel); the same with
+// a ring of two steps (gemm_pp8_kernel); groups that take turns at the steps (gemm_kg8_kernel).
+enum { F8_PP = 0, F8_PP8 = 1, F8_KG8 = 2 };
+constexpr TileShape kTilesFp8[] = {{42, 128, 128, 96, F8_PP},    {62, 192, 128, 120, F8_PP},  {82, 256, 128, 144, F8_PP},   {44, 128, 256, 144, F8_PP},
+                                   {54, 160, 256, 104, F8_PP8},  {64, 192, 256, 112, F8_PP8}, {74, 224, 256, 120, F8_PP8},  {84, 256, 256, 128, F8_PP8},
+                                   {222, 64, 64, 80, F8_KG8},    {224, 64, 128, 120, F8_KG8}, {274, 224, 128, 132, F8_KG8}, {426, 128, 96, 140, F8_KG8},
+                                   {446, 256, 96, 132, F8_KG8}};
+
+// The same estimate for E4M3 (a step is 128 values of K).  The MFMAs of a tile's step take as many cycles as in bf16 for twice the work, so
+// that the LDS bounds most tiles: 128 bytes a cycle for the fragments that all waves read and for the copies.  The constants are
+// fitted to every tile and K split, warm and with cold caches, over 201 shapes (1-19456 rows, 65-21504 columns, k 256-15360): the
+// choice is 0.45 % behind the best plan on average and 9 % at most.  With the bf16 constants, and none but tiles of 32 columns
+// per wave and 128 x 256, it was 13 % behind the kernel before at 8704 rows.
+// us (warm caches; K 3072 unless stated), kernel before / bf16 constants / now: 8704 x 12288 298 / 330 / 287, 8704 x 9216 236 / 269 / 216,
+// 8704 x 3072 of K 12288 312 / 316 / 253, 6000 x 12288 204 / 257 / 213, 820 x 12288 46 / 45 / 38, 820 x 3072 of K 12288 54 / 45 / 39,
+// 12 x 9216 13 / 16 / 10; over 130 shapes now 1.21 times the kernel before (1.27 with cold caches), 0.95 and 0.89 at the least.
+double plan_time_fp8(const TileShape& t, int m, int n, int steps, int splits) {
+    const int m_tiles = (m + t.rows - 1) / t.rows, n_tiles = (n + t.cols - 1) / t.cols;
+    const long units = static_cast<long>(m_tiles) * n_tiles * splits;
+    const int per = (steps + splits - 1) / splits;
+    const double barriers[] = {160.0, 55.0, 310.0}, latency[] = {900.0, 1970.0, 0.0}, fixed[] = {3.7, 7.3, 4.4};
+    const double mfma = t.rows * t.cols / 32.0;
+    const double fragment_rows = (t.form == F8_KG8 ? 4 : 8) * 16.0 * (t.code / 10 % 10 + t.code % 10);
+    double step = mfma + barriers[t.form];
+    const double lds = 1.066 * (fragment_rows + t.rows + t.cols);
+    if (step < lds) step = lds;
+    if (step < latency[t.form]) step = latency[t.form];
+    const double active = units < 256 ? units / 256.0 : 1.0, live = static_cast<double>(m) / (static_cast<double>(m_tiles) * t.rows);
+    const double mhz = 2200.0 - 450.0 * (mfma / step * active * live);
+    const double tile_mb = t.rows * t.cols * 4.0 / 1e6;
+    const long slots = t.lds_kb <= 80 ? 512 : 256;
+    const long full = units / slots, rem = units % slots;
+    const double one = per * step / mhz, fix = fixed[t.form] + 22.0 * tile_mb;
+    auto round_time = [&](long u) { return one * (slots > 256 && u > 256 ? 2.65 : 1.0) + fix; };
+    double us = full * round_time(slots) + (rem > 0 ? round_time(rem) : 0.0);
+    const double hbm = static_cast<double>(n) * steps * 128.0 / 5.4e6 + fix;      // the weights once from HBM
+    if (us < hbm) us = hbm;
+    us += 2.5 + static_cast<double>(m) * n * 2.0 / 14.4e6;
+    if (splits > 1) us += 1.2 + 0.26 * units * tile_mb + 9.5 * splits * tile_mb;
+    return us;
+}
+
+template <size_t N, typename Time>
+GemmPlan plan_over(const TileShape (&tiles)[N], Time time, size_t part_bytes, int m, int n, int steps) {
     GemmPlan best = {tiles[0].code, 1};
     double best_t = 1e30;
     for (const TileShape& t : tiles) {
@@ -87,21 +127,23 @@ GemmPlan plan_over(const TileShape (&tiles)[N], const regione_ctx* ctx, int m, i
         for (int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
             if (s > 1) {
                 if (count * s > 640 || steps / s < 3) break;
-                if (count > kMaxSplitTiles || static_cast<size_t>(count) * s * t.rows * t.cols * sizeof(float) > ctx->gemm_part_bytes) break;
+                if (count > kMaxSplitTiles || static_cast<size_t>(count) * s * t.rows * t.cols * sizeof(float) > part_bytes) break;
                 const int per = (steps + s - 1) / s;
                 if ((steps + per - 1) / per != s) continue;       // another split count in disguise
             }
-            const double us = plan_time(t, m, n, steps, s);
+            const double us = time(t, m, n, steps, s);
             if (us < best_t) { best_t = us; best = {t.code, s}; }
         }
     }
     return best;
 }
+GemmPlan choose_plan(int m, int n, int k, bool fp8, size_t part_bytes) {
+    return fp8 ? plan_over(kTilesFp8, plan_time_fp8, part_bytes, m, n, k / BK) : plan_over(kTiles, plan_time_bf16, part_bytes, m, n, k / BK);
+}
 
 // The plan of a product, remembered per context (a direct-mapped table: a forward repeats a handful of shapes, and trying all
 // plans takes the host about as long as a small product takes the GPU).
 GemmPlan plan_gemm(regione_ctx* ctx, int m, int n, int k, bool fp8) {
-    const int steps = k / BK;
     if (ctx->gemm_force_tn > 0) {
         const int by_size[7] = {0, 222, 244, 426, 44, 74, 84}, by_size_fp8[7] = {0, 42, 44, 62, 82, 42, 44};
         const int tile = ctx->gemm_force_tn <= 6 ? (fp8 ? by_size_fp8 : by_size)[ctx->gemm_force_tn] : ctx->gemm_force_tn;
@@ -110,7 +152,7 @@ GemmPlan plan_gemm(regione_ctx* ctx, int m, int n, int k, bool fp8) {
     const uint32_t h = (static_cast<uint32_t>(m) * 2654435761u) ^ (static_cast<uint32_t>(n) * 2246822519u) ^ (static_cast<uint32_t>(k) * 3266489917u);
     GemmPlanSlot& slot = ctx->gemm_plans[(h >> 16) % kGemmPlanSlots];
     if (slot.m == m && slot.n == n && slot.k == k && slot.fp8 == fp8 && slot.part_bytes == ctx->gemm_part_bytes) return {slot.tile, slot.splits};
-    const GemmPlan p = fp8 ? plan_over(kTilesFp8, ctx, m, n, steps) : plan_over(kTiles, ctx, m, n, steps);
+    const GemmPlan p = choose_plan(m, n, k, fp8, ctx->gemm_part_bytes);
     slot = {m, n, k, fp8, p.tile, p.splits, ctx->gemm_part_bytes};
     return p;
 }
@@ -122,7 +164,7 @@ GemmPlan plan_gemm(regione_ctx* ctx, int m, int n, int k, bool fp8) {
 // in flight at once (four waves per workgroup, twelve round trips each: 25 us at 820 x 64 x 3072 inside the step,
 // slower than the general kernel's K split + merge launch, 15 + 5 us).
 // KIND: EPI_PLAIN, or EPI_VELOCITY (the fresh region step's velocity cache, Euler update and latent merge).
-constexpr int kSkinnyWaves = 16;
+constexpr int kSkinnyWaves = 16, kSkinnyColumns = 64;
 template <int KIND>
 __global__ void __launch_bounds__(kSkinnyWaves * 64)
 gemm_skinny_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ Wp, int M, int N, int K, GemmEpilogue ep) {
@@ -178,7 +220,7 @@ int launch_gemm_skinny(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t*
     return REGIONE_OK;
 }
 // the shapes the small-N kernel takes: narrow results, unless a comparison forces a plan of the general kernels
-bool skinny_shape(const regione_ctx* ctx, int n) { return n <= 64 && ctx->gemm_force_tn == 0 && ctx->gemm_force_splits == 0; }
+bool skinny_shape(const regione_ctx* ctx, int n) { return n <= kSkinnyColumns && ctx->gemm_force_tn == 0 && ctx->gemm_force_splits == 0; }
 
 // the wide epilogue needs every eight-column group whole (n % 8, checked by the caller) and every touched row 16-byte aligned
 bool wide_epilogue_ok(const GemmEpilogue& ep, int n) {
@@ -267,6 +309,19 @@ extern "C" int regione_tune_gemm(regione_ctx* ctx, int32_t wave_tile_blocks, int
     if (wave_tile_blocks < 0 || wave_tile_blocks > 499 || k_splits < 0 || k_splits > 16) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_gemm: wave_tile_blocks in 0..499, k_splits in 0..16");
     ctx->gemm_force_tn = wave_tile_blocks;
     ctx->gemm_force_splits = k_splits;
+    return REGIONE_OK;
+}
+
+extern "C" int regione_gemm_plan_host(int32_t m, int32_t n, int32_t k, int32_t kind, int64_t workspace_bytes, int32_t* tile, int32_t* k_splits) {
+    if (!tile || !k_splits) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm_plan: null argument");
+    if (m <= 0 || n <= 0 || k <= 0 || workspace_bytes < 0) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm_plan: m=%d n=%d k=%d", m, n, k);
+    if (kind != REGIONE_GEMM_BF16 && kind != REGIONE_GEMM_E4M3) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm_plan: kind %d", kind);
+    const bool fp8 = kind == REGIONE_GEMM_E4M3;
+    if (k % (fp8 ? 2 * BK : BK)) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "gemm_plan: k=%d must be a multiple of %d", k, fp8 ? 2 * BK : BK);
+    GemmPlan p = {0, 1};
+    if (fp8 || n > kSkinnyColumns) p = choose_plan(m, n, fp8 ? k / 2 : k, fp8, static_cast<size_t>(workspace_bytes));
+    *tile = p.tile;
+    *k_splits = p.splits;
     return REGIONE_OK;
 }
 

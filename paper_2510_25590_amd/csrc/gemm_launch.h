@@ -29,9 +29,17 @@ int launch_tile(regione_ctx* ctx, Kernel kernel, std::atomic<uint64_t>& granted,
     return REGIONE_OK;
 }
 template <int RF, int CF, int KIND, bool FP8>
-int launch_pp(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
+int launch_pp_any(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
     static std::atomic<uint64_t> granted{0};
     return launch_tile<PpTile<RF, CF>>(ctx, gemm_pp_kernel<RF, CF, KIND, FP8>, granted, a, lda, wp, m, n, k, splits, ep);
+}
+template <int RF, int CF, int KIND>
+int launch_pp(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
+    return launch_pp_any<RF, CF, KIND, false>(ctx, a, lda, wp, m, n, k, splits, ep);
+}
+template <int RF, int CF, int KIND>
+int launch_pp_fp8(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
+    return launch_pp_any<RF, CF, KIND, true>(ctx, a, lda, wp, m, n, k, splits, ep);
 }
 template <int RF, int CF, int WM, int KIND>
 int launch_kg(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
@@ -39,4 +47,23 @@ int launch_kg(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int 
     return launch_tile<KgTile<RF, CF, WM>>(ctx, gemm_kg_kernel<RF, CF, WM, KIND>, granted, a, lda, wp, m, n, k, splits, ep);
 }
 
+template <int RF, int CF, int WM, int KIND>
+int launch_kg8(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
+    static std::atomic<uint64_t> granted{0};
+    return launch_tile<Kg8Tile<RF, CF, WM>>(ctx, gemm_kg8_kernel<RF, CF, WM, KIND>, granted, a, lda, wp, m, n, k, splits, ep);
+}
+template <int RF, int KIND>
+int launch_pp8(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
+    static std::atomic<uint64_t> granted{0};
+    return launch_tile<Pp8Tile<RF>>(ctx, gemm_pp8_kernel<RF, KIND>, granted, a, lda, wp, m, n, k, splits, ep);
+}
+
 }  // namespace
+
+// One entry of a list of tiles: the launch of tile CODE through LAUNCH<tile parameters, epilogue kind>.
+#define RG_TILE(CODE, LAUNCH, ...)                                                                              \
+    if (tile == CODE) {                                                                                         \
+        if (ep.kind == EPI_QKV) return LAUNCH<__VA_ARGS__, EPI_QKV>(ctx, a, lda, wp, m, n, k, splits, ep);      \
+        if (ep.kind == EPI_RESID) return LAUNCH<__VA_ARGS__, EPI_RESID>(ctx, a, lda, wp, m, n, k, splits, ep);  \
+        return LAUNCH<__VA_ARGS__, EPI_PLAIN>(ctx, a, lda, wp, m, n, k, splits, ep);                            \
+    }

@@ -288,6 +288,35 @@ gemm_pp_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__
                                         M, N, m0_wg + wm * (RF * 16), n0 + wn * (16 * CF), ep);
 }
 
+// Where two groups hold partial sums of the same fragments they exchange halves of them through LDS (see KG_FINISH): rows [I0, I1) of a
+// wave's fragments on their way out and in.
+template <int I0, int I1, int RF, int CF> __device__ __forceinline__ void kg_put(const f32x4 (&acc)[RF][CF], f32x4* ex) {
+#pragma unroll
+    for (int i = I0; i < I1; ++i)
+#pragma unroll
+        for (int j = 0; j < CF; ++j) ex[(i * CF + j) * 64] = acc[i][j];
+}
+template <int I0, int I1, int RF, int CF> __device__ __forceinline__ void kg_add(f32x4 (&acc)[RF][CF], const f32x4* ex) {
+#pragma unroll
+    for (int i = I0; i < I1; ++i)
+#pragma unroll
+        for (int j = 0; j < CF; ++j) acc[i][j] += ex[(i * CF + j) * 64];
+}
+// The end of a tile: rows [0, H) of the fragments are finished by group 0, the rest by group 1.  A macro: through a function that
+// holds both groups' branches the accumulators end up in scratch memory.
+#define KG_FINISH(FP8)                                                                                      \
+    {                                                                                                       \
+        constexpr int H = (RF + 1) / 2;                                                                     \
+        f32x4* ex = reinterpret_cast<f32x4*>(lds_raw) + static_cast<unsigned>(w4) * (RF * CF * 64) + lane;  \
+        const int tile = n_tile * m_tiles + m_tile, m0 = m0_wg + wm * (RF * 16), n0w = n0 + wn * (16 * CF); \
+        if (kg == 1) kg_put<0, H>(acc, ex); else kg_put<H, RF>(acc, ex);                                    \
+        __syncthreads();                                                                                    \
+        if (kg == 0) kg_add<0, H>(acc, ex); else kg_add<H, RF>(acc, ex);                                    \
+        if (splits > 1) __syncthreads();   /* the area is read before the arrival flag is written into it */ \
+        if (kg == 0) pp_finish<0, H, RF, CF, KIND, FP8>(acc, lds_raw, w4, T::PART_FLOATS, tile, split, splits, partial, arrived, M, N, m0, n0w, ep); \
+        else pp_finish<H, RF, RF, CF, KIND, FP8>(acc, lds_raw, w4, T::PART_FLOATS, tile, split, splits, partial, arrived, M, N, m0, n0w, ep); \
+    }
+
 // Narrow tiles: the two wave groups take the two 32-k halves of every K-step of the SAME tile, so that a wave of a 128-column
 // tile still owns 64 columns (half the LDS bytes per MFMA of the form above) and a 96-column tile has whole waves; the
 // groups' sums meet in LDS at the end.  WM x WN waves per group: 16*RF*WM rows x 16*CF*WN columns.
@@ -402,36 +431,244 @@ gemm_kg_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__
     if (kg == 0) pp_barrier();
     pp_wait<0>();
     __syncthreads();
-    // the groups exchange halves of their fragments (rows [0, H) are finished by group 0, the rest by group 1)
-    constexpr int H = (RF + 1) / 2;
-    f32x4* ex = reinterpret_cast<f32x4*>(lds_raw) + static_cast<unsigned>(w4) * (RF * CF * 64) + lane;
-    const int tile = n_tile * m_tiles + m_tile, m0 = m0_wg + wm * (RF * 16), n0w = n0 + wn * (16 * CF);
-    if (kg == 1) {
+    KG_FINISH(false)
+}
+
+// E4M3 form of the narrow tiles: the instruction takes a whole K-step (128 values) at once, so the groups take turns: group
+// g owns the steps g, g + 2, ..., copies them itself and reads them while the other group runs its MFMAs on the step before.
+// A wave owns the rows and columns of a bf16 one (128 x 64 at 256 x 128: 96 KiB of fragment reads per step where two groups
+// with rows of their own read 160, more than the LDS delivers during the step's MFMAs).
+template <int RF, int CF, int WM> struct Kg8Tile {
+    static constexpr int WN = 4 / WM, ROWS = 16 * RF * WM, COLS = 16 * CF * WN, THREADS = 512;
+    static constexpr int AC = ROWS / 32, WC = COLS / 32;           // 1 KiB copies per wave of the group and step
+    static constexpr unsigned STEP = (ROWS + COLS) * 128u, W_BASE = ROWS * 128u;
+    static constexpr int LOOK = 5 * STEP <= 163840u ? 2 : 1;        // own steps that the copies run ahead
+    static constexpr int NS = 2 * LOOK + 1;                         // steps in LDS
+    static constexpr unsigned ACC_BYTES = ROWS * COLS * 4u;         // the exchange at the end
+    static constexpr unsigned LDS_BYTES = NS * STEP > ACC_BYTES ? NS * STEP : ACC_BYTES;
+    static constexpr int64_t PART_FLOATS = static_cast<int64_t>(ROWS) * COLS;
+    static_assert(COLS % 32 == 0 && ROWS % 32 == 0 && LDS_BYTES <= 163840u, "whole weight blocks, and what a CU has");
+};
+
+template <int RF, int CF, int WM, int KIND>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+gemm_kg8_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ Wp,
+                int M, int N, int K, int m_tiles, int n_tiles, int units_per_xcd, int group_rows,
+                int splits, int steps_per_split, float* __restrict__ partial, int* __restrict__ arrived, GemmEpilogue ep) {
+    using T = Kg8Tile<RF, CF, WM>;
+    constexpr int AC = T::AC, WC = T::WC, LOOK = T::LOOK;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) void*)(lds_raw)));
+    int n_tile, m_tile, split;
+    if (!pp_unit(m_tiles, n_tiles, units_per_xcd, group_rows, splits, m_tile, n_tile, split)) return;
+    const int m0_wg = m_tile * T::ROWS, n0 = n_tile * T::COLS;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, kc = lane >> 4;
+    const int kg = wave >> 2, w4 = wave & 3, wm = w4 / T::WN, wn = w4 % T::WN;
+
+    const int ks_begin = split * steps_per_split;
+    int n_steps = K / 64 - ks_begin;
+    n_steps = n_steps < steps_per_split ? n_steps : steps_per_split;
+
+    // Copy sources of a step: wave w of the group takes A rows [w * 8 * AC, + 8 * AC) and k-block w of every weight block of the tile.
+    unsigned a_voff[AC];
 #pragma unroll
-        for (int i = 0; i < H; ++i)
-#pragma unroll
-            for (int j = 0; j < CF; ++j) ex[(i * CF + j) * 64] = acc[i][j];
-    } else {
-#pragma unroll
-        for (int i = H; i < RF; ++i)
-#pragma unroll
-            for (int j = 0; j < CF; ++j) ex[(i * CF + j) * 64] = acc[i][j];
+    for (int i = 0; i < AC; ++i) {
+        const int row = (w4 * AC + i) * 8 + (lane >> 3);
+        int r = m0_wg + row;
+        r = r < M ? r : M - 1;                                      // rows past M repeat the last row; never stored
+        a_voff[i] = static_cast<unsigned>(r - m0_wg) * static_cast<unsigned>(lda) * 2u + static_cast<unsigned>(((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
+    const int a_live = (M - m0_wg - w4 * (8 * AC) + 7) >> 3;        // rows past M are not copied
+    const char* a_base = reinterpret_cast<const char*>(A + static_cast<int64_t>(m0_wg) * lda + static_cast<int64_t>(ks_begin) * 64);
+    const int n_blocks = (N + 31) >> 5;
+    const char* w_base = reinterpret_cast<const char*>(Wp + (static_cast<int64_t>(ks_begin) * 4 + w4) * 512);
+    const int64_t w_block = static_cast<int64_t>(K >> 4) * 1024;    // bytes of a 32-column block
+    const unsigned w_voff = pp_w_source(lane);
+    const unsigned a_dst = lds0 + static_cast<unsigned>(w4) * (AC * 1024u), w_dst = lds0 + T::W_BASE + static_cast<unsigned>(w4) * 1024u;
+
+    unsigned a_off[2], w_off[2];                                    // [k half], [fragment parity]
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        a_off[h] = static_cast<unsigned>(wm * (RF * 16) + l16) * 128u + static_cast<unsigned>(((4 * h + kc) ^ ((l16 >> 1) & 7)) << 4);
+#pragma unroll
+    for (int jl = 0; jl < 2; ++jl) w_off[jl] = T::W_BASE + static_cast<unsigned>(wn * (CF / 2)) * 4096u + pp_w_slot(lane, jl);
+    static_assert(CF % 2 == 0, "a wave's columns are whole weight blocks");
+
+    f32x4 acc[RF][CF];
+#pragma unroll
+    for (int i = 0; i < RF; ++i)
+#pragma unroll
+        for (int j = 0; j < CF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // Step s sits in slot s % NS.  A group reads step s, then issues the copies of its step s + NS - 1 into the slot of step s - 1, which
+    // the other group has finished reading one barrier ago; what it reads next has landed when LOOK - 1 packets are in flight.
+    // Steps past the end repeat the last one (their slots are never multiplied).
+    auto copy = [&](int step, unsigned slot) __attribute__((always_inline)) {
+        const int st = step < n_steps ? step : n_steps - 1;
+        pp_copies_if<0, AC>(a_voff, a_base + static_cast<int64_t>(st) * 128, a_dst + slot, a_live);
+#pragma unroll
+        for (int i = 0; i < WC; ++i) {
+            int nb = (n0 >> 5) + i;
+            nb = nb < n_blocks ? nb : n_blocks - 1;                 // blocks past N repeat the last block
+            pp_copy16(w_voff, w_base + nb * w_block + static_cast<int64_t>(st) * 4096, w_dst + slot + i * 4096u);
+        }
+    };
+#pragma unroll
+    for (int p = 0; p < LOOK; ++p) copy(kg + 2 * p, (kg + 2 * p) * T::STEP);
+    if (kg == 1) pp_barrier();     // the second group runs one half phase behind the first
+    pp_wait<(LOOK - 1) * (AC + WC)>();
+    pp_barrier();
+    unsigned rd = kg * T::STEP;
+    bf16x8 af[2][RF], wf[2][CF];
+    int live = (M - m0_wg - wm * (RF * 16) + 15) >> 4;
+    live = live < 0 ? 0 : (live < RF ? live : RF);
+#define KG8_LOOP(LIVE)                                                                                      \
+    for (int s = kg; s < n_steps + kg; s += 2) {                                                            \
+        _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                     \
+            _Pragma("unroll") for (int j = 0; j < CF; ++j) wf[h][j] = *reinterpret_cast<const bf16x8*>(lds_raw + (w_off[j & 1] + rd) + (j >> 1) * 4096 + h * 2048); \
+            _Pragma("unroll") for (int i = 0; i < RF; ++i) if (i < (LIVE)) af[h][i] = *reinterpret_cast<const bf16x8*>(lds_raw + (a_off[h] + rd) + i * 2048); \
+        }                                                                                                   \
+        __builtin_amdgcn_sched_barrier(0);                                                                  \
+        copy(s + 2 * LOOK, rd == 0 ? (T::NS - 1) * T::STEP : rd - T::STEP);                                 \
+        rd += 2 * T::STEP;                                                                                  \
+        rd = rd >= T::NS * T::STEP ? rd - T::NS * T::STEP : rd;                                             \
+        pp_wait<LOOK * (AC + WC)>();                                                                        \
+        __builtin_amdgcn_sched_barrier(0);                                                                  \
+        pp_barrier();                                                                                       \
+        if (s < n_steps) {                                                                                  \
+            __builtin_amdgcn_s_setprio(1);                                                                  \
+            _Pragma("unroll") for (int i = 0; i < RF; ++i)                                                  \
+                if (i < (LIVE)) _Pragma("unroll") for (int j = 0; j < CF; ++j)                              \
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(pp_pair(wf[0][j], wf[1][j]), pp_pair(af[0][i], af[1][i]), acc[i][j], 0, 0, 0, 0, 0, 0); \
+            __builtin_amdgcn_s_setprio(0);                                                                  \
+        }                                                                                                   \
+        __builtin_amdgcn_sched_barrier(0);                                                                  \
+        pp_wait<(LOOK - 1) * (AC + WC)>();                                                                  \
+        pp_barrier();                                                                                       \
+    }
+    if (live == RF) { KG8_LOOP(RF) } else { KG8_LOOP(live) }
+#undef KG8_LOOP
+    if (kg == 0) pp_barrier();
+    pp_wait<0>();
     __syncthreads();
-    if (kg == 0) {
+    KG_FINISH(true)
+}
+
+// E4M3 form of the wide tiles: 256 columns, a wave owns 16*RF rows x 64 columns, the two groups the upper and lower rows.  Only two
+// steps fit into LDS at 256 x 256, which is enough because nothing is waited for before a whole phase has passed: a group
+// copies its own rows, and the first group, whose phase begins first, all the weights.  The MFMAs of a step take 2048 cycles
+// at 256 x 256, and the LDS as long for the step's 192 KiB of fragment reads and 64 KiB of copies.
+template <int RF> struct Pp8Tile {
+    static constexpr int CF = 4, ROWS = 32 * RF, COLS = 256, THREADS = 512;
+    static constexpr int AC = (2 * RF + 3) / 4, WC = 8;             // 1 KiB copies per wave and step: of its group's rows, of the weights
+    static constexpr unsigned STEP = (ROWS + COLS) * 128u, W_BASE = ROWS * 128u, LDS_BYTES = 2 * STEP;
+    static constexpr int64_t PART_FLOATS = static_cast<int64_t>(ROWS) * COLS;
+};
+
+template <int RF, int KIND>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+gemm_pp8_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ Wp,
+                int M, int N, int K, int m_tiles, int n_tiles, int units_per_xcd, int group_rows,
+                int splits, int steps_per_split, float* __restrict__ partial, int* __restrict__ arrived, GemmEpilogue ep) {
+    using T = Pp8Tile<RF>;
+    constexpr int CF = T::CF, AC = T::AC, WC = T::WC;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) void*)(lds_raw)));
+    int n_tile, m_tile, split;
+    if (!pp_unit(m_tiles, n_tiles, units_per_xcd, group_rows, splits, m_tile, n_tile, split)) return;
+    const int m0_wg = m_tile * T::ROWS, n0 = n_tile * T::COLS;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, kc = lane >> 4;
+    const int wm = wave >> 2, wn = wave & 3;
+
+    const int ks_begin = split * steps_per_split;
+    int n_steps = K / 64 - ks_begin;
+    n_steps = n_steps < steps_per_split ? n_steps : steps_per_split;
+
+    // Copy sources of a step: wave wn of group wm takes rows [wn * 8 * AC, + 8 * AC) of the group's, and in the first group k-block wn of
+    // every weight block of the tile.
+    const int m0 = m0_wg + wm * (RF * 16);
+    unsigned a_voff[AC];
 #pragma unroll
-        for (int i = 0; i < H; ++i)
-#pragma unroll
-            for (int j = 0; j < CF; ++j) acc[i][j] += ex[(i * CF + j) * 64];
-    } else {
-#pragma unroll
-        for (int i = H; i < RF; ++i)
-#pragma unroll
-            for (int j = 0; j < CF; ++j) acc[i][j] += ex[(i * CF + j) * 64];
+    for (int i = 0; i < AC; ++i) {
+        const int row = (wn * AC + i) * 8 + (lane >> 3);
+        int r = m0 + row;
+        r = r < M ? r : M - 1;                                      // rows past M repeat the last row; never stored
+        a_voff[i] = static_cast<unsigned>(r - m0_wg) * static_cast<unsigned>(lda) * 2u + static_cast<unsigned>(((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
-    if (splits > 1) __syncthreads();   // the exchange area is read before the arrival flag is written into it
-    if (kg == 0) pp_finish<0, H, RF, CF, KIND, false>(acc, lds_raw, w4, T::PART_FLOATS, tile, split, splits, partial, arrived, M, N, m0, n0w, ep);
-    else pp_finish<H, RF, RF, CF, KIND, false>(acc, lds_raw, w4, T::PART_FLOATS, tile, split, splits, partial, arrived, M, N, m0, n0w, ep);
+    int a_live = (M - m0 - wn * (8 * AC) + 7) >> 3;                 // neither rows past M are copied nor rows past the group's
+    a_live = a_live < 2 * RF - wn * AC ? a_live : 2 * RF - wn * AC;
+    const char* a_base = reinterpret_cast<const char*>(A + static_cast<int64_t>(m0_wg) * lda + static_cast<int64_t>(ks_begin) * 64);
+    const int n_blocks = (N + 31) >> 5;
+    const char* w_base = reinterpret_cast<const char*>(Wp + (static_cast<int64_t>(ks_begin) * 4 + wn) * 512);
+    const int64_t w_block = static_cast<int64_t>(K >> 4) * 1024;    // bytes of a 32-column block
+    const unsigned w_voff = pp_w_source(lane);
+    const unsigned a_dst = lds0 + static_cast<unsigned>(wm * (RF * 16)) * 128u + static_cast<unsigned>(wn) * (AC * 1024u);
+    const unsigned w_dst = lds0 + T::W_BASE + static_cast<unsigned>(wn) * 1024u;
+    const int w_live = wm == 0 ? WC : 0;
+
+    unsigned a_off[2], w_off[2];                                    // [k half], [fragment parity]
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        a_off[h] = static_cast<unsigned>(wm * (RF * 16) + l16) * 128u + static_cast<unsigned>(((4 * h + kc) ^ ((l16 >> 1) & 7)) << 4);
+#pragma unroll
+    for (int jl = 0; jl < 2; ++jl) w_off[jl] = T::W_BASE + static_cast<unsigned>(wn * (CF / 2)) * 4096u + pp_w_slot(lane, jl);
+
+    f32x4 acc[RF][CF];
+#pragma unroll
+    for (int i = 0; i < RF; ++i)
+#pragma unroll
+        for (int j = 0; j < CF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // Step s sits in slot s % 2.  The copies of step s + 1 go into the slot of step s - 1, which both groups have finished reading: a group
+    // its own rows one phase ago, the weights are written by the first group after the second group's last barrier.
+    auto copy = [&](int step, unsigned slot) __attribute__((always_inline)) {
+        const int st = step < n_steps ? step : n_steps - 1;         // steps past the end repeat the last one (their slot is never read)
+        pp_copies_if<0, AC>(a_voff, a_base + static_cast<int64_t>(st) * 128, a_dst + slot, a_live);
+#pragma unroll
+        for (int i = 0; i < WC; ++i) {
+            int nb = (n0 >> 5) + i;
+            nb = nb < n_blocks ? nb : n_blocks - 1;                 // blocks past N repeat the last block
+            pp_copy16_if<0>(w_voff, w_base + nb * w_block + static_cast<int64_t>(st) * 4096, w_dst + slot + i * 4096u, w_live);
+        }
+    };
+    copy(0, 0);
+    pp_wait<0>();
+    pp_barrier();
+    if (wm == 1) pp_barrier();     // the second group runs one half phase behind the first
+    unsigned rd = 0;
+    bf16x8 af[2][RF], wf[2][CF];
+    int live = (M - m0 + 15) >> 4;
+    live = live < 0 ? 0 : (live < RF ? live : RF);
+#define PP8_LOOP(LIVE)                                                                                      \
+    for (int s = 0; s < n_steps; ++s) {                                                                     \
+        _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                     \
+            _Pragma("unroll") for (int j = 0; j < CF; ++j) wf[h][j] = *reinterpret_cast<const bf16x8*>(lds_raw + (w_off[j & 1] + rd) + (j >> 1) * 4096 + h * 2048); \
+            _Pragma("unroll") for (int i = 0; i < RF; ++i) if (i < (LIVE)) af[h][i] = *reinterpret_cast<const bf16x8*>(lds_raw + (a_off[h] + rd) + i * 2048); \
+        }                                                                                                   \
+        __builtin_amdgcn_sched_barrier(0);                                                                  \
+        rd = T::STEP - rd;                                                                                  \
+        copy(s + 1, rd);                                                                                    \
+        pp_wait<AC + WC>();                                                                                 \
+        __builtin_amdgcn_sched_barrier(0);                                                                  \
+        pp_barrier();                                                                                       \
+        __builtin_amdgcn_s_setprio(1);                                                                      \
+        _Pragma("unroll") for (int i = 0; i < RF; ++i)                                                      \
+            if (i < (LIVE)) _Pragma("unroll") for (int j = 0; j < CF; ++j)                                  \
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(pp_pair(wf[0][j], wf[1][j]), pp_pair(af[0][i], af[1][i]), acc[i][j], 0, 0, 0, 0, 0, 0); \
+        __builtin_amdgcn_s_setprio(0);                                                                      \
+        __builtin_amdgcn_sched_barrier(0);                                                                  \
+        pp_wait<0>();                                                                                       \
+        pp_barrier();                                                                                       \
+    }
+    if (live == RF) { PP8_LOOP(RF) } else { PP8_LOOP(live) }
+#undef PP8_LOOP
+    if (wm == 0) pp_barrier();
+    pp_finish<0, RF, RF, CF, KIND, true>(acc, lds_raw, wave, T::PART_FLOATS, n_tile * m_tiles + m_tile, split, splits, partial, arrived,
+                                         M, N, m0, n0 + wn * (16 * CF), ep);
 }
 
 }  // namespace

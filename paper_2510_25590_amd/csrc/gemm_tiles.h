@@ -1,5 +1,6 @@
 // The tile shapes of the two-group GEMM kernels (gemm_pp.h), each set in a translation unit of its own.  A tile's code is
-// 10*RF + CF for gemm_pp_kernel and 100*WM + 10*RF + CF for gemm_kg_kernel; ep.kind picks the epilogue.
+// 10*RF + CF for gemm_pp_kernel and gemm_pp8_kernel and 100*WM + 10*RF + CF for gemm_kg_kernel and gemm_kg8_kernel; ep.kind picks the
+// epilogue.
 #pragma once
 #include "common.h"
 

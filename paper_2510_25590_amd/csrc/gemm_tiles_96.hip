@@ -2,15 +2,8 @@
 #include "gemm_launch.h"
 
 int rg_gemm_tile_96(regione_ctx* ctx, int tile, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
-#define RG_TILE(CODE, ...)                                                                                                  \
-    if (tile == CODE) {                                                                                                     \
-        if (ep.kind == EPI_QKV) return launch_kg<__VA_ARGS__, EPI_QKV>(ctx, a, lda, wp, m, n, k, splits, ep);     \
-        if (ep.kind == EPI_RESID) return launch_kg<__VA_ARGS__, EPI_RESID>(ctx, a, lda, wp, m, n, k, splits, ep); \
-        return launch_kg<__VA_ARGS__, EPI_PLAIN>(ctx, a, lda, wp, m, n, k, splits, ep);                           \
-    }
-    RG_TILE(426, 2, 6, 4)
-    RG_TILE(436, 3, 6, 4)
-    RG_TILE(446, 4, 6, 4)
-#undef RG_TILE
+    RG_TILE(426, launch_kg, 2, 6, 4)
+    RG_TILE(436, launch_kg, 3, 6, 4)
+    RG_TILE(446, launch_kg, 4, 6, 4)
     RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm: no tile %d here", tile);
 }

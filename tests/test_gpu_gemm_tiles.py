@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 TILES = {222: (64, 64), 224: (64, 128), 242: (128, 64), 244: (128, 128), 274: (224, 128), 284: (256, 128), 426: (128, 96), 436: (192, 96), 446: (256, 96),
          44: (128, 256), 64: (192, 256), 74: (224, 256), 84: (256, 256)}
-TILES_FP8 = {42: (128, 128), 62: (192, 128), 82: (256, 128), 44: (128, 256)}
+TILES_FP8 = {42: (128, 128), 62: (192, 128), 82: (256, 128), 44: (128, 256),
+             222: (64, 64), 224: (64, 128), 274: (224, 128), 426: (128, 96), 446: (256, 96),
+             54: (160, 256), 64: (192, 256), 74: (224, 256), 84: (256, 256)}
 
 
 @pytest.fixture(scope="module")
