@@ -24,7 +24,7 @@ EXPORTS = (
     "regione_last_error", "regione_create", "regione_destroy", "regione_partition", "regione_gather",
     "regione_scatter", "regione_attn_kvcache", "regione_linear", "regione_block_forward",
     "regione_velocity_decision_host", "regione_velocity_cache", "regione_profile_enable", "regione_profile_read",
-    "regione_packed_weight_elems", "regione_pack_weight", "regione_tune_gemm", "regione_tune_attention",
+    "regione_packed_weight_elems", "regione_pack_weight", "regione_tune_gemm", "regione_tune_attention", "regione_attention_plan",
     "regione_layernorm", "regione_stage_plan_host", "regione_cast", "regione_mask_cleanup", "regione_rope_table",
     "regione_vec_linear", "regione_timestep_embedding", "regione_block_forward_batched",
     "regione_sq_norms", "regione_gamma_fit_host", "regione_guidance_combine", "regione_rel_change",
@@ -152,6 +152,7 @@ def lib() -> C.CDLL:
             "regione_linear_fp8": [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp],
             "regione_tune_gemm": [vp, i32, i32],
             "regione_tune_attention": [vp, i32],
+            "regione_attention_plan": [vp, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)],
             "regione_layernorm": [vp, vp, i32, i32, i32, vp, vp, vp],
             "regione_cast": [vp, vp, i32, vp, i32, i64],
             "regione_rope_table": [vp, vp, i64, i32, C.POINTER(i32), f32, vp],
@@ -512,6 +513,13 @@ def regione_gemm_plan_host(m: int, n: int, k: int, kind: int, workspace_bytes: i
 
 def regione_tune_attention(ctx, key_splits: int):
     _check(lib().regione_tune_attention(ctx.handle, key_splits))
+
+
+def regione_attention_plan(ctx, n_q: int, n_keys: int, heads: int, d: int):
+    """(equal key ranges per query tile, key tiles of an even range or 0, unsplit query tiles in front) of a bf16 attention."""
+    splits, tiles, whole = C.c_int32(0), C.c_int32(0), C.c_int32(0)
+    _check(lib().regione_attention_plan(ctx.handle, n_q, n_keys, heads, d, C.byref(splits), C.byref(tiles), C.byref(whole)))
+    return splits.value, tiles.value, whole.value
 
 
 def pack_weight(ctx, w):

@@ -542,46 +542,37 @@ double split_time(int q_tiles, int heads, int n_q, int n_tiles, int s) {
     return t;
 }
 
-template <int D, int NW, int QB, int NSTAGE, int WPE>
-int launch_attention(regione_ctx* ctx, AttnArgs a) {
-    constexpr int QW = NW * QB * 32;
-    const int q_tiles = (a.n_q + QW - 1) / QW;
-    const int n_tiles = (a.n0 + a.n1 + KT - 1) / KT;
+// How a call is dealt to workgroups: `splits` equal key ranges per query tile, or (range > 0) even ranges of `range` key tiles behind
+// the first q_full query tiles of every head.
+struct AttnPlan { int splits, range, range_wgs, q_full; };
+
+template <int D, int QW, int WG_PER_CU>
+AttnPlan plan_attention(int n_q, int n_keys, int heads, int force_splits, size_t part_bytes) {
+    const int q_tiles = (n_q + QW - 1) / QW;
+    const int n_tiles = (n_keys + KT - 1) / KT;
+    AttnPlan plan = {1, 0, 0, q_tiles};
     // Key-range splits: the choice that minimises a small cost model.  The chip holds `slots` workgroups at a time;
     // a pass of workgroups costs its tiles plus a fixed prologue/epilogue (in tile times, about 2 us each with a full
     // CU); partial results cost their write and re-read.
-    constexpr int wg_per_cu = WPE * 4 / NW;
-    const double slots = 256.0 * wg_per_cu;
-    const double wgs = static_cast<double>(q_tiles) * a.heads;
-    int splits = 1;
+    const double slots = 256.0 * WG_PER_CU;
+    const double wgs = static_cast<double>(q_tiles) * heads;
     double best = 0.0;
-    const bool few = static_cast<int64_t>(q_tiles) * a.heads <= 256;   // at most one workgroup per CU before the split: a model of its own
-    const size_t part_row_set = static_cast<size_t>(a.heads) * a.n_q * (D + 4) * sizeof(float);
-    for (int s = 1; few && s <= kMaxSplits && (s == 1 || (s * 2 <= n_tiles && s * part_row_set <= ctx->attn_part_bytes)); ++s) {
-        const double t = split_time<D>(q_tiles, a.heads, a.n_q, n_tiles, s);
-        if (s == 1 || t < best) { best = t; splits = s; }
+    const bool few = static_cast<int64_t>(q_tiles) * heads <= 256;   // at most one workgroup per CU before the split: a model of its own
+    const size_t part_row_set = static_cast<size_t>(heads) * n_q * (D + 4) * sizeof(float);
+    for (int s = 1; few && s <= kMaxSplits && (s == 1 || (s * 2 <= n_tiles && s * part_row_set <= part_bytes)); ++s) {
+        const double t = split_time<D>(q_tiles, heads, n_q, n_tiles, s);
+        if (s == 1 || t < best) { best = t; plan.splits = s; }
     }
     for (int s = 1; !few && s <= 8 && (s == 1 || s * 4 <= n_tiles); ++s) {
         const double load = wgs * s / slots;
         const double passes = load <= 1.0 ? 1.0 : 0.5 * (ceil(load) + load);   // a last, partly filled pass runs faster
         const double fill = wgs * s <= 256.0 ? 0.68 : 1.0;                      // a CU with one workgroup runs it faster
         double t = passes * ((n_tiles + s - 1) / s + 4) * 2.0 * fill;
-        if (s > 1) t += 3.0 + 1.5 * static_cast<double>(s) * a.n_q * a.heads * (D + 4) * 8.0 / 4.0e6;
-        if (s == 1 || t < best) { best = t; splits = s; }
+        if (s > 1) t += 3.0 + 1.5 * static_cast<double>(s) * n_q * heads * (D + 4) * 8.0 / 4.0e6;
+        if (s == 1 || t < best) { best = t; plan.splits = s; }
     }
-    if (ctx->attn_force_splits > 0 && ctx->attn_force_splits * 2 <= n_tiles) splits = ctx->attn_force_splits;
-    a.n_q_pad = a.n_q;
-    if (splits > 1) {
-        const size_t need = static_cast<size_t>(splits) * a.heads * a.n_q_pad * (D + 4) * sizeof(float);
-        if (need > ctx->attn_part_bytes) splits = 1;
-    }
-    a.splits = splits;
-    a.tiles_per_split = (n_tiles + splits - 1) / splits;
-    a.part = ctx->attn_part;
-    a.q_tiles = q_tiles;
-    const int groups_per_xcd = (a.heads * splits + 7) / 8;
-    a.full_blocks = groups_per_xcd * q_tiles * 8;
-    a.q_full = q_tiles;
+    if (force_splits > 0 && force_splits * 2 <= n_tiles) plan.splits = force_splits;
+    if (plan.splits > 1 && plan.splits * part_row_set > part_bytes) plan.splits = 1;
     // Equal splits leave the chip idle where the workgroups do not fill its last pass (264 query tiles x heads: 0.52 or
     // 1.03 passes of 512).  Even ranges give each of the last `slots` workgroups the same number of consecutive key tiles
     // of what whole passes of unsplit query tiles leave over.  Their workgroups start at different keys and share less
@@ -590,25 +581,46 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
     // 1332 x 8704 by index list 247 -> 218, 8704 x 8704 913 -> 865, 3000 x 3000 144 -> 130, with 8 heads 8704 x 8704
     // 388 -> 296 (with up to 256 query tiles x heads split_time finds equal ranges as fast: 1024 x 8704 122.5 in four); taken for all it would be 2560 x 8704 267 -> 298, 4096 x 8704 417 -> 440, 205 x 8704 47 -> 53.
     // At most eight ranges meet in a query tile (range >= n_tiles / 7), as many as the merge kernel takes.
-    if (D == 128 && ctx->attn_force_splits == 0) {
-        const int whole = a.heads % 8 == 0 ? static_cast<int>(wgs / slots) : 0;    // other head counts: unsplit tiles would fill the XCDs unevenly
-        const int q_full = static_cast<int>(whole * slots) / a.heads;
-        const int64_t units = static_cast<int64_t>(a.heads) * (q_tiles - q_full) * n_tiles;
+    if (D == 128 && force_splits == 0) {
+        const int whole = heads % 8 == 0 ? static_cast<int>(wgs / slots) : 0;    // other head counts: unsplit tiles would fill the XCDs unevenly
+        const int q_full = static_cast<int>(whole * slots) / heads;
+        const int64_t units = static_cast<int64_t>(heads) * (q_tiles - q_full) * n_tiles;
         int64_t range = (units + static_cast<int64_t>(slots) - 1) / static_cast<int64_t>(slots);
         const int64_t least = (n_tiles + 6) / 7 > 4 ? (n_tiles + 6) / 7 : 4;
         if (range < least) range = least;
         const int64_t range_wgs = (units + range - 1) / range;
         const size_t need = static_cast<size_t>(range_wgs) * 2 * QW * (D + 4) * sizeof(float);
         const double t = 1.9 * whole * (n_tiles + 4) + 2.3 * static_cast<double>(range) + 16.0;
-        if (units > 0 && units < (1 << 30) && need <= ctx->attn_part_bytes && t < 0.97 * (few ? 1.0 : 0.9) * best) {
-            a.splits = splits = 1;
-            a.tiles_per_split = n_tiles;
-            a.q_full = q_full;
-            a.full_blocks = (a.heads + 7) / 8 * q_full * 8;
-            a.range = static_cast<int>(range);
-            a.range_wgs = static_cast<int>(range_wgs);
-        }
+        if (units > 0 && units < (1 << 30) && need <= part_bytes && t < 0.97 * (few ? 1.0 : 0.9) * best)
+            plan = {1, static_cast<int>(range), static_cast<int>(range_wgs), q_full};
     }
+    return plan;
+}
+
+// the shapes of the two instantiations: four waves of 32 queries, two workgroups per CU
+constexpr int kWaves = 4, kQueryBlocks = 1, kWavesPerEu = 2, kQueriesPerTile = kWaves * kQueryBlocks * 32;
+AttnPlan plan_attention(const regione_ctx* ctx, int n_q, int n_keys, int heads, int d) {
+    constexpr int per_cu = kWavesPerEu * 4 / kWaves;
+    return d == 64 ? plan_attention<64, kQueriesPerTile, per_cu>(n_q, n_keys, heads, ctx->attn_force_splits, ctx->attn_part_bytes)
+                   : plan_attention<128, kQueriesPerTile, per_cu>(n_q, n_keys, heads, ctx->attn_force_splits, ctx->attn_part_bytes);
+}
+
+template <int D, int NW, int QB, int NSTAGE, int WPE>
+int launch_attention(regione_ctx* ctx, AttnArgs a) {
+    constexpr int QW = NW * QB * 32;
+    const int q_tiles = (a.n_q + QW - 1) / QW;
+    const int n_tiles = (a.n0 + a.n1 + KT - 1) / KT;
+    const AttnPlan plan = plan_attention(ctx, a.n_q, a.n0 + a.n1, a.heads, D);
+    const int splits = plan.splits;
+    a.n_q_pad = a.n_q;
+    a.splits = splits;
+    a.tiles_per_split = (n_tiles + splits - 1) / splits;
+    a.part = ctx->attn_part;
+    a.q_tiles = q_tiles;
+    a.q_full = plan.q_full;
+    a.full_blocks = (a.heads * splits + 7) / 8 * plan.q_full * 8;
+    a.range = plan.range;
+    a.range_wgs = plan.range_wgs;
     const dim3 grid(static_cast<unsigned>(a.full_blocks + (a.range_wgs + 7) / 8 * 8));
     constexpr size_t lds_bytes = static_cast<size_t>(NSTAGE) * 2 * KT * D * sizeof(bf16_t);
     constexpr uint32_t grant_bit = D == 128 ? 2u : 1u;
@@ -653,6 +665,17 @@ extern "C" int regione_tune_attention(regione_ctx* ctx, int32_t key_splits) {
     return REGIONE_OK;
 }
 
+extern "C" int regione_attention_plan(regione_ctx* ctx, int32_t n_q, int32_t n_keys, int32_t heads, int32_t d, int32_t* key_splits, int32_t* range_tiles, int32_t* whole_query_tiles) {
+    if (!ctx || !key_splits || !range_tiles || !whole_query_tiles) RG_FAIL(REGIONE_ERR_INVALID_ARG, "attention_plan: null argument");
+    if (n_q <= 0 || n_keys <= 0 || heads <= 0) RG_FAIL(REGIONE_ERR_INVALID_ARG, "attention_plan: n_q=%d n_keys=%d heads=%d", n_q, n_keys, heads);
+    if (ctx->f32 || (d != 64 && d != 128)) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "attention_plan: bf16 contexts and head dimensions of 64 or 128 (%d) only", d);
+    const AttnPlan plan = plan_attention(ctx, n_q, n_keys, heads, d);
+    *key_splits = plan.splits;
+    *range_tiles = plan.range;
+    *whole_query_tiles = plan.q_full;
+    return REGIONE_OK;
+}
+
 int rg_attention(regione_ctx* ctx, const void* q_any, int ldq, int n_q,
                  const void* k0_any, const void* v0_any, int ldkv0, int n0,
                  const void* k1_any, const void* v1_any, int ldkv1, int n1, const int32_t* idx1,
@@ -677,8 +700,8 @@ int rg_attention(regione_ctx* ctx, const void* q_any, int ldq, int n_q,
     a.heads = heads;
     a.scale_log2e = (scale > 0.f ? scale : 1.0f / sqrtf(static_cast<float>(d))) * 1.4426950408889634f;
     a.out = out; a.ldo = ldo;
-    if (d == 64) return launch_attention<64, 4, 1, 2, 2>(ctx, a);
-    return launch_attention<128, 4, 1, 2, 2>(ctx, a);
+    if (d == 64) return launch_attention<64, kWaves, kQueryBlocks, 2, kWavesPerEu>(ctx, a);
+    return launch_attention<128, kWaves, kQueryBlocks, 2, kWavesPerEu>(ctx, a);
 }
 
 extern "C" int regione_attn_kvcache(regione_ctx* ctx, const void* q, int32_t n_q,

@@ -39,6 +39,8 @@ def test_nonfinite_scores(kind, heads, d, n_q, n_keys, splits):
     assert torch.equal(want.isnan().any(-1), hit) and torch.equal(want.isnan().all(-1), hit)
     ctx = rg.Context(heads * d, heads, d, 256, max(n_q, 2048), 16)
     rg.regione_tune_attention(ctx, splits)
+    plan = rg.regione_attention_plan(ctx, n_q, n_keys, heads, d)
+    assert plan[0] == splits if splits else plan[1] > 0 and plan[2] > 0
     out = torch.full((n_q + 1, heads, d), 7.0, dtype=torch.bfloat16, device="cuda")
     rg.regione_attn_kvcache(ctx, q, n_q, None, None, 0, k, v, n_keys, None, 0, heads, d, 0.0, out)
     torch.cuda.synchronize()

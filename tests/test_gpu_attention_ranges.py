@@ -18,13 +18,14 @@ def _reference(q, k, v, d):
 
 
 @pytest.mark.parametrize("source", ["contiguous", "two", "indexed"])
-@pytest.mark.parametrize("heads,n_q,n_keys", [
-    (24, 1000, 8700),     # 0.38 of a pass: ranges shorter than a query tile's keys
-    (12, 5450, 2499),     # heads not a multiple of the XCDs; a range longer than a query tile's keys, no whole pass
-    (8, 8700, 2497),      # one whole pass, the rest in ranges
-    (24, 2900, 3001),     # one whole pass that the heads do not divide
+@pytest.mark.parametrize("heads,n_q,n_keys,whole,short", [
+    (24, 1409, 3001, 0, True),      # 0.56 of a pass, no query tile in front: ranges shorter than a query tile's keys
+    (8, 1461, 3001, 0, True),       # 0.19 of a pass: up to seven ranges meet in a query tile
+    (12, 5450, 2499, 0, False),     # heads not a multiple of the XCDs; a range longer than a query tile's keys, no whole pass
+    (8, 8700, 2497, 64, True),      # one whole pass, the rest in ranges
+    (24, 2900, 3001, 21, True),     # one whole pass that the heads do not divide
 ])
-def test_even_ranges(source, heads, n_q, n_keys):
+def test_even_ranges(source, heads, n_q, n_keys, whole, short):
     d = 128
     g = torch.Generator(device="cuda")
     g.manual_seed(n_q)
@@ -35,6 +36,8 @@ def test_even_ranges(source, heads, n_q, n_keys):
     idx = torch.arange(n_keys - n_fresh, dtype=torch.int32, device="cuda").flip(0).contiguous() if source == "indexed" else None
     kc, vc = k[n_fresh:].contiguous(), v[n_fresh:].contiguous()
     ctx = rg.Context(heads * d, heads, d, 256, max(n_q, 2048), 16)
+    splits, tiles, in_front = rg.regione_attention_plan(ctx, n_q, n_keys, heads, d)
+    assert (splits, in_front) == (1, whole) and tiles > 0 and (tiles < (n_keys + 63) // 64) == short      # even ranges, of the case's kind
     outs = []
     for splits in (0, 0, 1):
         rg.regione_tune_attention(ctx, splits)
