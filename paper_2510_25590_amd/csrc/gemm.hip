@@ -228,13 +228,13 @@ bool wide_epilogue_ok(const GemmEpilogue& ep, int n) {
     if (ep.kind == EPI_QKV) return (ep.hidden % 8 == 0) && (ep.ldq % 8 == 0) && (ep.ldkv % 8 == 0) && rg_aligned16(ep.q) && rg_aligned16(ep.k) && rg_aligned16(ep.v) &&
                                    (n <= 3 * ep.hidden || ((ep.ldy % 8 == 0) && (ep.y_col0 % 8 == 0) && rg_aligned16(ep.y)));
     if (ep.kind == EPI_RESID) return (ep.ldy % 8 == 0) && (ep.ldr % 8 == 0) && rg_aligned16(ep.y) && rg_aligned16(ep.resid);
+    if (ep.kind == EPI_VELOCITY) return (ep.ldy % 8 == 0) && rg_aligned16(ep.y) && rg_aligned16(ep.vel_ca) && rg_aligned16(ep.vel_xe) && rg_aligned16(ep.vel_xfull);
     return false;
 }
 
 }  // namespace
 
 static int gemm_tile(regione_ctx* ctx, const GemmPlan& p, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, const GemmEpilogue& ep) {
-    if (ep.kind == EPI_VELOCITY) return rg_gemm_tile_velocity(ctx, a, lda, wp, m, n, k, p.splits, ep);
     if (p.tile >= 400) return rg_gemm_tile_96(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
     if (p.tile >= 200) return rg_gemm_tile_128(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
     return rg_gemm_tile_wide(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
@@ -261,12 +261,14 @@ int rg_gemm_velocity(regione_ctx* ctx, const void* a_any, int lda, const void* w
     if (!rg_aligned16(a_any) || !rg_aligned16(wp_any)) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm: operands must be 16-byte aligned");
     ProfScope prof(ctx, REGIONE_PROF_GEMM);
     GemmEpilogue ep = ep_in;
-    ep.kind = EPI_VELOCITY; ep.vec_ok = 0;
+    ep.kind = EPI_VELOCITY;
+    ep.vec_ok = (n % 8 == 0) && wide_epilogue_ok(ep, n);
     const bf16_t* a = static_cast<const bf16_t*>(a_any);
     const bf16_t* wp = static_cast<const bf16_t*>(wp_any);
     if (skinny_shape(ctx, n)) return launch_gemm_skinny<EPI_VELOCITY>(ctx, a, lda, wp, m, n, k, ep);
-    const int splits = ctx->gemm_force_splits > 0 ? ctx->gemm_force_splits : 1;
-    return gemm_tile(ctx, {222, splits}, a, lda, wp, m, n, k, ep);
+    // The plan of the product alone: the sums are then those of rg_gemm bit for bit.  Tile 222 with one K split for all such heads took
+    // (us, kernel before the two-group ones / 222 / now; hidden 3072) VELTIMES
+    return gemm_tile(ctx, plan_gemm(ctx, m, n, k, false), a, lda, wp, m, n, k, ep);
 }
 
 int rg_gemm(regione_ctx* ctx, const void* a_any, int lda, const void* wp_any, int m, int n, int k, const GemmEpilogue& ep_in) {

@@ -88,6 +88,55 @@ __device__ __forceinline__ void store8(void* base, int64_t elem, int as_f32, con
     }
 }
 
+__device__ __forceinline__ void load8(const void* base, int64_t elem, int as_f32, float (&v)[8]) {
+    if (as_f32) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const f32x4 a = *reinterpret_cast<const f32x4*>(static_cast<const float*>(base) + elem + 4 * h);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * h + e] = a[e];
+        }
+    } else {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(static_cast<const bf16_t*>(base) + elem);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = static_cast<float>(a[e]);
+    }
+}
+
+// The velocity step (see epilogue_store) on columns col0..col0+n-1 of a row, n <= 8.  WIDE: all eight, in whole pieces.  Otherwise one
+// at a time, but the row's place is looked up once and every element of x_e requested before the first store.
+template <bool WIDE>
+__device__ __forceinline__ void epilogue_velocity(const GemmEpilogue& ep, int row, int col0, int n, float (&val)[8]) {
+    const int64_t o = static_cast<int64_t>(row) * ep.ldy + col0;
+    const int64_t full = ep.vel_index ? static_cast<int64_t>(ep.vel_index[row]) * ep.ldy + col0 : o;
+    float x[8];
+    if (WIDE) {
+        load8(ep.vel_xe, o, ep.y_f32, x);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (e < n) x[e] = ep.y_f32 ? static_cast<const float*>(ep.vel_xe)[o + e] : bf16_to_f32(static_cast<const bf16_t*>(ep.vel_xe)[o + e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        if (!ep.y_f32) val[e] = static_cast<float>(static_cast<__bf16>(val[e]));
+        x[e] = __fsub_rn(x[e], __fmul_rn(ep.vel_dt, val[e]));
+    }
+    auto put = [&](void* base, int64_t at, const float (&v)[8]) __attribute__((always_inline)) {
+        if (WIDE) { store8(base, at, ep.y_f32, v); return; }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (e < n) {
+                if (ep.y_f32) static_cast<float*>(base)[at + e] = v[e];
+                else static_cast<bf16_t*>(base)[at + e] = f32_to_bf16(v[e]);
+            }
+    };
+    if (ep.y) put(ep.y, o, val);
+    put(ep.vel_ca, o, val);
+    put(ep.vel_xe, o, x);
+    if (ep.vel_xfull) put(ep.vel_xfull, full, x);
+}
+
 // Epilogue for the eight consecutive columns col0..col0+7 of one row (all inside N, col0 a multiple of 8; the
 // wide-epilogue conditions hold, so a group never straddles two destinations): wide loads and stores only.
 template <int KIND>
@@ -96,7 +145,9 @@ __device__ __forceinline__ void epilogue_store8(const GemmEpilogue& ep, int row,
     float val[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) val[e] = acc[e] + bias[e];
-    if (KIND == EPI_PLAIN) {
+    if (KIND == EPI_VELOCITY) {
+        epilogue_velocity<true>(ep, row, col0, 8, val);
+    } else if (KIND == EPI_PLAIN) {
         if (ep.act == REGIONE_ACT_GELU_TANH) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) if (col0 + e >= ep.act_from) val[e] = gelu_tanh_f32(val[e]);
@@ -118,20 +169,8 @@ __device__ __forceinline__ void epilogue_store8(const GemmEpilogue& ep, int row,
             store8(ep.y, static_cast<int64_t>(row) * ep.ldy + ep.y_col0 + (col0 - 3 * H), 0, val);
         }
     } else {  // EPI_RESID
-        const int64_t ri = static_cast<int64_t>(row) * ep.ldr + col0;
         float res[8];
-        if (ep.resid_f32) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const f32x4 a = *reinterpret_cast<const f32x4*>(static_cast<const float*>(ep.resid) + ri + 4 * h);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) res[4 * h + e] = a[e];
-            }
-        } else {
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(static_cast<const bf16_t*>(ep.resid) + ri);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) res[e] = static_cast<float>(a[e]);
-        }
+        load8(ep.resid, static_cast<int64_t>(row) * ep.ldr + col0, ep.resid_f32, res);
 #pragma unroll
         for (int e = 0; e < 8; ++e) val[e] = res[e] + gate[e] * val[e];
         store8(ep.y, static_cast<int64_t>(row) * ep.ldy + col0, ep.y_f32, val);
@@ -171,6 +210,13 @@ __device__ __forceinline__ void gemm_epilogue16_pair(f32x4 (&acc)[RF][CF], int M
         for (int i = I0; i < I1; ++i) {
             const int row = m0 + 16 * i + l16;
             if (row < M) {
+                if (KIND == EPI_VELOCITY) {
+                    float v[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] = acc[i][2 * B + (e >> 2)][e & 3] + (ep.bias && col0 + e < N ? ep.bias[col0 + e] : 0.f);
+                    epilogue_velocity<false>(ep, row, col0, N - col0, v);
+                    continue;
+                }
                 const float rs = SCALED ? ep.row_scale[row] : 1.f;
                 const int64_t kv_row = epilogue_kv_row<KIND>(ep, row);
 #pragma unroll

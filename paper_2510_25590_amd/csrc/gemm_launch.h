@@ -60,10 +60,14 @@ int launch_pp8(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int
 
 }  // namespace
 
-// One entry of a list of tiles: the launch of tile CODE through LAUNCH<tile parameters, epilogue kind>.
-#define RG_TILE(CODE, LAUNCH, ...)                                                                              \
+// One entry of a list of tiles: the launch of tile CODE through LAUNCH<tile parameters, epilogue kind>.  The bf16 tiles also finish the
+// velocity head.
+#define RG_TILE_FP8(CODE, LAUNCH, ...)                                                                          \
     if (tile == CODE) {                                                                                         \
         if (ep.kind == EPI_QKV) return LAUNCH<__VA_ARGS__, EPI_QKV>(ctx, a, lda, wp, m, n, k, splits, ep);      \
         if (ep.kind == EPI_RESID) return LAUNCH<__VA_ARGS__, EPI_RESID>(ctx, a, lda, wp, m, n, k, splits, ep);  \
         return LAUNCH<__VA_ARGS__, EPI_PLAIN>(ctx, a, lda, wp, m, n, k, splits, ep);                            \
     }
+#define RG_TILE(CODE, LAUNCH, ...)                                                                              \
+    if (tile == CODE && ep.kind == EPI_VELOCITY) return LAUNCH<__VA_ARGS__, EPI_VELOCITY>(ctx, a, lda, wp, m, n, k, splits, ep); \
+    RG_TILE_FP8(CODE, LAUNCH, __VA_ARGS__)

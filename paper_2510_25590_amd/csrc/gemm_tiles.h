@@ -9,5 +9,3 @@ int rg_gemm_tile_128(regione_ctx* ctx, int tile, const bf16_t* a, int lda, const
 int rg_gemm_tile_96(regione_ctx* ctx, int tile, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep);
 // E4M3 operands; lda and k count pairs of values
 int rg_gemm_tile_fp8(regione_ctx* ctx, int tile, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep);
-// the tile (222) that has the velocity step as its epilogue, for heads of more than 64 channels
-int rg_gemm_tile_velocity(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep);

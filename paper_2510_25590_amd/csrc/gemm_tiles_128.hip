@@ -10,7 +10,3 @@ int rg_gemm_tile_128(regione_ctx* ctx, int tile, const bf16_t* a, int lda, const
     RG_TILE(284, launch_kg, 8, 4, 2)
     RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm: no tile %d here", tile);
 }
-
-int rg_gemm_tile_velocity(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int splits, const GemmEpilogue& ep) {
-    return launch_kg<2, 2, 2, EPI_VELOCITY>(ctx, a, lda, wp, m, n, k, splits, ep);
-}

@@ -277,6 +277,38 @@ def test_pair_gather_and_scatter_equal_the_single_calls(ctx, elems_a, elems_b, d
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,c,hidden", [(1, 72, 256), (36, 65, 3072), (820, 128, 3072), (820, 100, 1024), (2048, 264, 3072), (2500, 1024, 256)])
+def test_velocity_head_of_many_channels(dtype, n, c, hidden):
+    """More than 64 channels: the tile and K splits of the product alone, so that the fused head stays equal to the three calls
+    it stands for (bit for bit), with channels that fill whole groups of eight and others, and updates in place."""
+    rng = np.random.default_rng(hidden + c)
+    ctx2 = rg.Context(hidden, hidden // 128, 128, 4 * hidden, n, 16)
+    r = lambda *shape: rng.standard_normal(shape).astype(np.float32)
+    code = rg.BF16 if dtype == "bf16" else rg.FP32
+    h, w, b = inputs.bf16_round(r(n, hidden)), inputs.bf16_round(0.02 * r(c, hidden)), 0.02 * r(c)
+    idx = rng.permutation(n + 5)[:n].astype(np.int32)
+    x_e, x_full = dev(r(n, c), dtype), dev(r(n + 5, c), dtype)
+    wp = rg.pack_weight(ctx2, dev(w, "bf16")); db = torch.from_numpy(b).cuda(); dh = dev(h, "bf16"); didx = torch.from_numpy(idx).cuda()
+    outs = []
+    for fused in (True, True, False):
+        v, ca, xe, xf = torch.zeros_like(x_e), torch.ones_like(x_e), x_e.clone(), x_full.clone()
+        if fused:
+            rg.regione_velocity_head(ctx2, dh, wp, db, n, c, hidden, 1.0 / 28.0, v, ca, xe, xf, didx, code)
+        else:
+            rg.regione_linear(ctx2, dh, wp, db, n, c, hidden, rg.ACT_NONE, code, v)
+            rg.regione_velocity_cache(ctx2, False, 1.0, 1.0 / 28.0, v, ca, None, xe, None, n, c, code)
+            rg.regione_scatter(ctx2, xf, c, code, didx, None, n, xe)
+        outs.append((v, ca, xe, xf))
+    for name, p, again, q in zip(("v", "c_a", "x_e", "x_full"), *outs):
+        assert torch.equal(p, q) and torch.equal(p, again), name
+    want = h.astype(np.float64) @ w.T.astype(np.float64) + b
+    # float32 sums of exact products over at most 3072 terms, and a rounding to bf16 where that is the storage type
+    bound = (np.abs(h.astype(np.float64)) @ np.abs(w.T) + np.abs(b)) * 2.0 ** -19 + (np.abs(want) * 2.0 ** -8 if dtype == "bf16" else 0.0)
+    assert np.all(np.abs(host(outs[0][0]) - want) <= bound)
+    ctx2.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n", [1, 36, 820])
 def test_velocity_head_equals_linear_cache_and_scatter(dtype, n):
     """The fused head of a fresh region step against the three calls it stands for (bit for bit), and against the oracle."""
