@@ -13,8 +13,9 @@ extern "C" {
 #endif
 
 /* Tuning knob for experiments: forces the tile (1..6: six tiles from 64 x 64 to 256 x 256; larger numbers are the tile
- * codes of csrc/gemm_tiles.h) and the number of K splits of every later GEMM of this context; 0 restores the automatic
- * choice. */
+ * codes of csrc/gemm_tiles.h, any other is refused) and the number of K splits of every later GEMM of this context; 0 leaves
+ * either to the library.  K splits without a tile split the tile that the product gets by itself.  A product fails that
+ * has no such tile (some are bf16 or E4M3 only) or whose split does not fit the workspace. */
 int regione_tune_gemm(regione_ctx* ctx, int32_t wave_tile_blocks, int32_t k_splits);
 
 /* The tile and the number of K splits that a product of m rows, n columns and k elements gets by itself, with a K-split workspace

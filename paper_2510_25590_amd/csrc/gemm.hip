@@ -12,7 +12,6 @@
 
 namespace {
 
-
 constexpr int BK = 64;        // k elements per step
 constexpr int kThreads = 256;
 
@@ -149,6 +148,7 @@ GemmPlan plan_gemm(regione_ctx* ctx, int m, int n, int k, bool fp8) {
         const int tile = ctx->gemm_force_tn <= 6 ? (fp8 ? by_size_fp8 : by_size)[ctx->gemm_force_tn] : ctx->gemm_force_tn;
         return {tile, ctx->gemm_force_splits > 0 ? ctx->gemm_force_splits : 1};
     }
+    if (ctx->gemm_force_splits > 0) return {choose_plan(m, n, k, fp8, ctx->gemm_part_bytes).tile, ctx->gemm_force_splits};
     const uint32_t h = (static_cast<uint32_t>(m) * 2654435761u) ^ (static_cast<uint32_t>(n) * 2246822519u) ^ (static_cast<uint32_t>(k) * 3266489917u);
     GemmPlanSlot& slot = ctx->gemm_plans[(h >> 16) % kGemmPlanSlots];
     if (slot.m == m && slot.n == n && slot.k == k && slot.fp8 == fp8 && slot.part_bytes == ctx->gemm_part_bytes) return {slot.tile, slot.splits};
@@ -308,7 +308,10 @@ extern "C" int regione_pack_weight(regione_ctx* ctx, const void* w, int32_t n, i
 
 extern "C" int regione_tune_gemm(regione_ctx* ctx, int32_t wave_tile_blocks, int32_t k_splits) {
     if (!ctx) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_gemm: null context");
-    if (wave_tile_blocks < 0 || wave_tile_blocks > 499 || k_splits < 0 || k_splits > 16) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_gemm: wave_tile_blocks in 0..499, k_splits in 0..16");
+    bool known = wave_tile_blocks >= 0 && wave_tile_blocks <= 6;
+    for (const TileShape& t : kTiles) known = known || t.code == wave_tile_blocks;
+    for (const TileShape& t : kTilesFp8) known = known || t.code == wave_tile_blocks;
+    if (!known || k_splits < 0 || k_splits > 16) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_gemm: tile %d is none of 0..6 and no tile code, or k_splits=%d is not in 0..16", wave_tile_blocks, k_splits);
     ctx->gemm_force_tn = wave_tile_blocks;
     ctx->gemm_force_splits = k_splits;
     return REGIONE_OK;
