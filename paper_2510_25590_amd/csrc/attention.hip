@@ -5,7 +5,7 @@
 //
 // Flash-style streaming with an online softmax.  A workgroup of NW waves owns NW*QB*32 query rows of
 // one head; each wave owns QB blocks of 32 queries, whose Q fragments stay in registers.  Keys and
-// values are staged 64 rows at a time in LDS by asynchronous global->LDS copies, three stages deep.  The scores are computed
+// values are staged 64 rows at a time in LDS by asynchronous global->LDS copies, in two stages.  The scores are computed
 // TRANSPOSED, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: a lane then holds, for ONE query
 // (column lane%32), 16 of every 32 keys, so the running maximum and the rescaling factor are
 // per-lane scalars, and the exponentiated scores are already in the register layout of the "B"
@@ -42,7 +42,7 @@ struct AttnArgs {
     int splits; int tiles_per_split; float* part;  // [splits][heads][n_q_pad][D + 4] when splits > 1: O, maximum, sum, two unused (rows stay 16-byte aligned)
     int n_q_pad;
     int q_tiles;
-    // Even ranges (see launch_attention): after `full_blocks` workgroups, each with one key range of one of the first
+    // Even ranges (see plan_attention): after `full_blocks` workgroups, each with one key range of one of the first
     // q_full query tiles of a head, range_wgs workgroups take `range` consecutive key tiles each of the list (head, query tile >= q_full,
     // key tile).  A range that covers a query tile's keys only in part leaves its partial result in slot 2 w (the range's
     // first query tile) or 2 w + 1 (its last), rows of the query tile, D + 4 floats each as above.
@@ -456,7 +456,8 @@ attn_kvcache_kernel(AttnArgs a) {
                     }
                 if (lh == 0) { pp[D] = m_run[qb] * c; pp[D + 1] = l_tot; }   // maximum in the log2 domain, as the merge kernel expects
             }
-        }    left -= tile_end - tile_begin;
+        }
+        left -= tile_end - tile_begin;
         if (!ranged || left <= 0) break;
         __syncthreads();   // every wave has read its last tile before the next query tile's first copies
         slot |= 1;         // only the last query tile of a range can be partial from here on
@@ -578,7 +579,7 @@ AttnPlan plan_attention(int n_q, int n_keys, int heads, int force_splits, size_t
     // of what whole passes of unsplit query tiles leave over.  Their workgroups start at different keys and share less
     // of what an L2 holds: fitted to measurements a tile costs 2.3 us there against 1.9 in a whole pass, and the model
     // for many query tiles is 10 % high.  Equal splits -> even ranges (us; queries x keys, 24 heads of 128): 1024 x 8704 141 -> 127,
-    // 1332 x 8704 by index list 247 -> 218, 8704 x 8704 913 -> 865, 3000 x 3000 144 -> 130, with 8 heads 8704 x 8704
+    // 1332 x 8704 by index list 226 -> 214, 8704 x 8704 913 -> 865, 3000 x 3000 144 -> 130, with 8 heads 8704 x 8704
     // 388 -> 296 (with up to 256 query tiles x heads split_time finds equal ranges as fast: 1024 x 8704 122.5 in four); taken for all it would be 2560 x 8704 267 -> 298, 4096 x 8704 417 -> 440, 205 x 8704 47 -> 53.
     // At most eight ranges meet in a query tile (range >= n_tiles / 7), as many as the merge kernel takes.
     if (D == 128 && force_splits == 0) {

@@ -4,7 +4,8 @@ The kernels issue global-to-LDS copies as inline assembly and wait for them by h
 neither knows what the counts stand for nor waits itself.  `check_asm` proves on the generated code that (1) the K loops hold
 no vector-memory instruction besides the counted copies and no kernel with such copies spills to scratch memory (spills share
 the counter); (2) no wide store's data registers are overwritten by the next instruction; (3) registers that are the
-destination of an assembly load are left alone until a wait covers them (`check_function`).
+destination of an assembly load are left alone until a wait covers them (`check_function`).  The kernels' assembly copies write LDS
+only; (3) guards the step back to loads into registers, whose destinations the compiler takes as written at once.
 
 Model of (3): loads complete in issue order.  Every destination register of an asm load is "pending" with an age = number
 of vector-memory loads issued after it.  `s_waitcnt vmcnt(N)` lands every register whose age is at least N.  At a
