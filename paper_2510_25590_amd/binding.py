@@ -152,7 +152,7 @@ def lib() -> C.CDLL:
             "regione_linear_fp8": [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp],
             "regione_tune_gemm": [vp, i32, i32],
             "regione_tune_attention": [vp, i32],
-            "regione_attention_plan": [vp, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)],
+            "regione_attention_plan": [vp, i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)],
             "regione_layernorm": [vp, vp, i32, i32, i32, vp, vp, vp],
             "regione_cast": [vp, vp, i32, vp, i32, i64],
             "regione_rope_table": [vp, vp, i64, i32, C.POINTER(i32), f32, vp],
@@ -515,10 +515,13 @@ def regione_tune_attention(ctx, key_splits: int):
     _check(lib().regione_tune_attention(ctx.handle, key_splits))
 
 
-def regione_attention_plan(ctx, n_q: int, n_keys: int, heads: int, d: int):
+KEYS_CONTIGUOUS, KEYS_TWO, KEYS_INDEXED = 0, 1, 2
+
+
+def regione_attention_plan(ctx, n_q: int, n_keys: int, heads: int, d: int, source: int = KEYS_CONTIGUOUS):
     """(equal key ranges per query tile, key tiles of an even range or 0, unsplit query tiles in front) of a bf16 attention."""
     splits, tiles, whole = C.c_int32(0), C.c_int32(0), C.c_int32(0)
-    _check(lib().regione_attention_plan(ctx.handle, n_q, n_keys, heads, d, C.byref(splits), C.byref(tiles), C.byref(whole)))
+    _check(lib().regione_attention_plan(ctx.handle, n_q, n_keys, heads, d, source, C.byref(splits), C.byref(tiles), C.byref(whole)))
     return splits.value, tiles.value, whole.value
 
 

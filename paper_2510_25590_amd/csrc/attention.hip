@@ -524,22 +524,28 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
     *reinterpret_cast<bf16x4*>(out + static_cast<int64_t>(qrow + (RANGED ? q_full * QW : 0)) * ldo + head * D + 4 * g) = pk;
 }
 
-// Microseconds of an attention with `s` equal key ranges where the unsplit query tiles leave CUs empty.  Fitted to forced
-// ranges of 1-32 over 105 shapes (16-1024 queries, 544-19456 keys, 24 and 8 heads of 128, 4 of 64): a key tile costs `alone` on a CU that holds one
+// Microseconds of an attention with `s` equal key ranges where the unsplit query tiles leave CUs empty: a key tile costs `alone` on a CU that holds one
 // workgroup, `pair` and more where an XCD's 32 CUs hold up to two each, `pass` in a full pass of 64; then the merge launch, the partial rows'
-// way out and back, and 1.2 us of the merge kernel for more than eight ranges.  The choice is 1 % behind the best range count
-// on average; eight ranges at most, with one cost for all fills, was 9 % behind, up to 1.7 times.
-// us, 24 heads: 512 x 8704 84.9 -> 67.6, 384 x 8704 63.4 -> 54.9, 16 x 19456 52.7 -> 42.6; 8 heads, 16 x 19456 47.7 -> 28.0;
-// 4 heads of 64, 1024 x 19456 40.9 -> 37.8.
+// way out and back, and what more ranges cost the merge kernel.
+// Rows in one or two arrays: fitted to forced ranges of 1-32 over 105 shapes (16-1024 queries, 544-19456 keys, 24 and 8 heads of 128, 4 of
+// 64), 1 % behind the best range count there on average and 3 to 7 % over 496 wider ones; eight ranges at most, with one cost for all fills, was
+// 9 % behind, up to 1.7 times.  us, 24 heads: 512 x 8704 84.9 -> 67.6, 384 x 8704 63.4 -> 54.9, 16 x 19456 52.7 -> 42.6; 8 heads, 16 x 19456
+// 47.7 -> 28.0; 4 heads of 64, 1024 x 19456 40.9 -> 37.8.
+// Rows named by an index list lie apart, so that a tile waits longer where no other workgroup fills the CU: costs of their own, fitted to 409
+// calls (16-4096 queries, 98-19456 keys, 8 to 24 heads of 128, 4 and 16 of 64): 1.1 % behind the best range count on average and 17 % at most.
+// With the costs of contiguous rows it was 6.2 % behind and slower than one cost for all fills in some: 1719 queries on 5982 keys, 8 heads,
+// 79.6 us before, 92.9 in the two ranges chosen then, 71 in four; 595 on 6591, 24 heads, 1.19 times.
 template <int D>
-double split_time(int q_tiles, int heads, int n_q, int n_tiles, int s) {
-    struct Cost { double fixed, alone, pair, more, pass, merge, mb, range; };
-    constexpr Cost c = D == 128 ? Cost{6.1, 1.0, 1.47, 0.39, 1.6, 3.4, 0.33, 0.28} : Cost{3.9, 0.68, 0.95, -0.05, 0.64, 1.3, 0.58, 0.35};
+double split_time(int source, int q_tiles, int heads, int n_q, int n_tiles, int s) {
+    struct Cost { double fixed, alone, pair, more, pass, merge, mb, range, many; };
+    constexpr Cost costs[2][2] = {{{3.9, 0.68, 0.95, -0.05, 0.64, 1.3, 0.58, 0.35, 1.2}, {4.5, 0.91, 1.24, 0.23, 0.93, 2.9, 0.60, 0.0, 0.0}},      // D = 64
+                                  {{6.1, 1.00, 1.47, 0.39, 1.60, 3.4, 0.33, 0.28, 1.2}, {6.0, 1.50, 2.19, 0.16, 1.68, 2.5, 0.43, 0.0, 0.0}}};    // D = 128
+    const Cost& c = costs[D == 128][source == SRC_INDEXED];
     const int per = (n_tiles + s - 1) / s;
     const int per_xcd = (heads * s + 7) / 8 * q_tiles, full = per_xcd / 64, rem = per_xcd % 64;
     double t = c.fixed + full * c.pass * (per + 2);
     if (rem > 0) t += per * (rem <= 32 ? c.alone : c.pair + c.more * (rem - 32) / 32.0);
-    if (s > 1) t += c.merge + c.mb * (s * 4.0e-6 * n_q * heads * (D + 4)) + c.range * s + (s > 8 ? 1.2 : 0.0);
+    if (s > 1) t += c.merge + c.mb * (s * 4.0e-6 * n_q * heads * (D + 4)) + c.range * s + (s > 8 ? c.many : 0.0);
     return t;
 }
 
@@ -548,7 +554,7 @@ double split_time(int q_tiles, int heads, int n_q, int n_tiles, int s) {
 struct AttnPlan { int splits, range, range_wgs, q_full; };
 
 template <int D, int QW, int WG_PER_CU>
-AttnPlan plan_attention(int n_q, int n_keys, int heads, int force_splits, size_t part_bytes) {
+AttnPlan plan_attention(int source, int n_q, int n_keys, int heads, int force_splits, size_t part_bytes) {
     const int q_tiles = (n_q + QW - 1) / QW;
     const int n_tiles = (n_keys + KT - 1) / KT;
     AttnPlan plan = {1, 0, 0, q_tiles};
@@ -561,8 +567,8 @@ AttnPlan plan_attention(int n_q, int n_keys, int heads, int force_splits, size_t
     const bool few = static_cast<int64_t>(q_tiles) * heads <= 256;   // at most one workgroup per CU before the split: a model of its own
     const size_t part_row_set = static_cast<size_t>(heads) * n_q * (D + 4) * sizeof(float);
     for (int s = 1; few && s <= kMaxSplits && (s == 1 || (s * 2 <= n_tiles && s * part_row_set <= part_bytes)); ++s) {
-        const double t = split_time<D>(q_tiles, heads, n_q, n_tiles, s);
-        if (s == 1 || t < best) { best = t; plan.splits = s; }
+        const double t = split_time<D>(source, q_tiles, heads, n_q, n_tiles, s);
+        if (s == 1 || t < (source == SRC_INDEXED ? 0.97 : 1.0) * best) { best = t; plan.splits = s; }   // no cost per range there: nearly equal goes to fewer
     }
     for (int s = 1; !few && s <= 8 && (s == 1 || s * 4 <= n_tiles); ++s) {
         const double load = wgs * s / slots;
@@ -578,9 +584,11 @@ AttnPlan plan_attention(int n_q, int n_keys, int heads, int force_splits, size_t
     // 1.03 passes of 512).  Even ranges give each of the last `slots` workgroups the same number of consecutive key tiles
     // of what whole passes of unsplit query tiles leave over.  Their workgroups start at different keys and share less
     // of what an L2 holds: fitted to measurements a tile costs 2.3 us there against 1.9 in a whole pass, and the model
-    // for many query tiles is 10 % high.  Equal splits -> even ranges (us; queries x keys, 24 heads of 128): 1024 x 8704 141 -> 127,
-    // 1332 x 8704 by index list 226 -> 214, 8704 x 8704 913 -> 865, 3000 x 3000 144 -> 130, with 8 heads 8704 x 8704
-    // 388 -> 296 (with up to 256 query tiles x heads split_time finds equal ranges as fast: 1024 x 8704 122.5 in four); taken for all it would be 2560 x 8704 267 -> 298, 4096 x 8704 417 -> 440, 205 x 8704 47 -> 53.
+    // for many query tiles is 10 % high.  Equal splits -> even ranges (us; queries x keys, 24 heads of 128): 1332 x 8704 by index
+    // list 226 -> 214, 8704 x 8704 913 -> 865, 3000 x 3000 144 -> 130, with 8 heads 8704 x 8704 388 -> 296; taken for all it would be
+    // 2560 x 8704 267 -> 298, 4096 x 8704 417 -> 440, 205 x 8704 47 -> 53.  With up to 256 query tiles x heads equal ranges are as fast
+    // (1024 x 8704 122.5 in four, 127 even) and are mostly taken; by index list a tile costs 3.0 there (at 2.3 even ranges were taken in
+    // 39 of 200 such calls and cost up to 1.23 times the best plan).
     // At most eight ranges meet in a query tile (range >= n_tiles / 7), as many as the merge kernel takes.
     if (D == 128 && force_splits == 0) {
         const int whole = heads % 8 == 0 ? static_cast<int>(wgs / slots) : 0;    // other head counts: unsplit tiles would fill the XCDs unevenly
@@ -591,7 +599,7 @@ AttnPlan plan_attention(int n_q, int n_keys, int heads, int force_splits, size_t
         if (range < least) range = least;
         const int64_t range_wgs = (units + range - 1) / range;
         const size_t need = static_cast<size_t>(range_wgs) * 2 * QW * (D + 4) * sizeof(float);
-        const double t = 1.9 * whole * (n_tiles + 4) + 2.3 * static_cast<double>(range) + 16.0;
+        const double t = 1.9 * whole * (n_tiles + 4) + (few && source == SRC_INDEXED ? 3.0 : 2.3) * static_cast<double>(range) + 16.0;
         if (units > 0 && units < (1 << 30) && need <= part_bytes && t < 0.97 * (few ? 1.0 : 0.9) * best)
             plan = {1, static_cast<int>(range), static_cast<int>(range_wgs), q_full};
     }
@@ -600,10 +608,10 @@ AttnPlan plan_attention(int n_q, int n_keys, int heads, int force_splits, size_t
 
 // the shapes of the two instantiations: four waves of 32 queries, two workgroups per CU
 constexpr int kWaves = 4, kQueryBlocks = 1, kWavesPerEu = 2, kQueriesPerTile = kWaves * kQueryBlocks * 32;
-AttnPlan plan_attention(const regione_ctx* ctx, int n_q, int n_keys, int heads, int d) {
+AttnPlan plan_attention(const regione_ctx* ctx, int source, int n_q, int n_keys, int heads, int d) {
     constexpr int per_cu = kWavesPerEu * 4 / kWaves;
-    return d == 64 ? plan_attention<64, kQueriesPerTile, per_cu>(n_q, n_keys, heads, ctx->attn_force_splits, ctx->attn_part_bytes)
-                   : plan_attention<128, kQueriesPerTile, per_cu>(n_q, n_keys, heads, ctx->attn_force_splits, ctx->attn_part_bytes);
+    return d == 64 ? plan_attention<64, kQueriesPerTile, per_cu>(source, n_q, n_keys, heads, ctx->attn_force_splits, ctx->attn_part_bytes)
+                   : plan_attention<128, kQueriesPerTile, per_cu>(source, n_q, n_keys, heads, ctx->attn_force_splits, ctx->attn_part_bytes);
 }
 
 template <int D, int NW, int QB, int NSTAGE, int WPE>
@@ -611,7 +619,11 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
     constexpr int QW = NW * QB * 32;
     const int q_tiles = (a.n_q + QW - 1) / QW;
     const int n_tiles = (a.n0 + a.n1 + KT - 1) / KT;
-    const AttnPlan plan = plan_attention(ctx, a.n_q, a.n0 + a.n1, a.heads, D);
+    // a lane's byte offset inside a tile of a contiguous source has to fit 32 bits
+    const int64_t src_ld = a.n0 > 0 ? a.ldkv0 : a.ldkv1;
+    const bool contig = !a.idx1 && (a.n0 == 0 || a.n1 == 0) && (KT * src_ld + a.heads * D) * 2 < (int64_t{1} << 31);
+    const int source = a.idx1 ? SRC_INDEXED : contig ? SRC_CONTIG : SRC_TWO;
+    const AttnPlan plan = plan_attention(ctx, source, a.n_q, a.n0 + a.n1, a.heads, D);
     const int splits = plan.splits;
     a.n_q_pad = a.n_q;
     a.splits = splits;
@@ -637,10 +649,7 @@ int launch_attention(regione_ctx* ctx, AttnArgs a) {
                 RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes)));
         ctx->lds_grant_mask |= grant_bit;
     }
-    // a lane's byte offset inside a tile of a contiguous source has to fit 32 bits
-    const int64_t src_ld = a.n0 > 0 ? a.ldkv0 : a.ldkv1;
-    const bool contig = !a.idx1 && (a.n0 == 0 || a.n1 == 0) && (KT * src_ld + a.heads * D) * 2 < (int64_t{1} << 31);
-    hipLaunchKernelGGL(kernels[a.idx1 ? SRC_INDEXED : contig ? SRC_CONTIG : SRC_TWO][a.range_wgs > 0], grid, dim3(NW * 64), lds_bytes, ctx->stream, a);
+    hipLaunchKernelGGL(kernels[source][a.range_wgs > 0], grid, dim3(NW * 64), lds_bytes, ctx->stream, a);
     RG_LAUNCH_CHECK();
     if (splits > 1 || a.range_wgs > 0) {
         const int rows = a.n_q - (a.range_wgs > 0 ? a.q_full * QW : 0);
@@ -666,11 +675,14 @@ extern "C" int regione_tune_attention(regione_ctx* ctx, int32_t key_splits) {
     return REGIONE_OK;
 }
 
-extern "C" int regione_attention_plan(regione_ctx* ctx, int32_t n_q, int32_t n_keys, int32_t heads, int32_t d, int32_t* key_splits, int32_t* range_tiles, int32_t* whole_query_tiles) {
+extern "C" int regione_attention_plan(regione_ctx* ctx, int32_t n_q, int32_t n_keys, int32_t heads, int32_t d, int32_t source, int32_t* key_splits,
+                                      int32_t* range_tiles, int32_t* whole_query_tiles) {
     if (!ctx || !key_splits || !range_tiles || !whole_query_tiles) RG_FAIL(REGIONE_ERR_INVALID_ARG, "attention_plan: null argument");
     if (n_q <= 0 || n_keys <= 0 || heads <= 0) RG_FAIL(REGIONE_ERR_INVALID_ARG, "attention_plan: n_q=%d n_keys=%d heads=%d", n_q, n_keys, heads);
     if (ctx->f32 || (d != 64 && d != 128)) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "attention_plan: bf16 contexts and head dimensions of 64 or 128 (%d) only", d);
-    const AttnPlan plan = plan_attention(ctx, n_q, n_keys, heads, d);
+    if (source != REGIONE_KEYS_CONTIGUOUS && source != REGIONE_KEYS_TWO && source != REGIONE_KEYS_INDEXED) RG_FAIL(REGIONE_ERR_INVALID_ARG, "attention_plan: source %d", source);
+    static_assert(REGIONE_KEYS_CONTIGUOUS == SRC_CONTIG && REGIONE_KEYS_TWO == SRC_TWO && REGIONE_KEYS_INDEXED == SRC_INDEXED, "the same order");
+    const AttnPlan plan = plan_attention(ctx, source, n_q, n_keys, heads, d);
     *key_splits = plan.splits;
     *range_tiles = plan.range;
     *whole_query_tiles = plan.q_full;
