@@ -268,6 +268,7 @@ int rg_gemm_velocity(regione_ctx* ctx, const void* a_any, int lda, const void* w
     if (skinny_shape(ctx, n)) return launch_gemm_skinny<EPI_VELOCITY>(ctx, a, lda, wp, m, n, k, ep);
     // The plan of the product alone: the sums are then those of rg_gemm bit for bit.  Tile 222 with one K split for all such heads took
     // (us, kernel before the two-group ones / 222 / now; hidden 3072): 820 x 128 14.1 / 19.3 / 10.6, 36 x 256 11.4 / 16.7 / 9.0, 8704 x 1024 122 / 139 / 60.
+    // Odd widths (see the epilogue): 8704 x 65 22 / 28 / 27, 8704 x 100 23.5 / - / 27, 4096 x 65 16.5 / - / 17.3, 2048 x 66 15.4 / - / 12.4.
     return gemm_tile(ctx, plan_gemm(ctx, m, n, k, false), a, lda, wp, m, n, k, ep);
 }
 

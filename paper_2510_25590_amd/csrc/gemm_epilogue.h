@@ -74,30 +74,38 @@ __device__ __forceinline__ void epilogue_store(const GemmEpilogue& ep, int row, 
     }
 }
 
-// eight consecutive elements: 32 bytes (float32) or 16 (bf16)
+// eight consecutive elements: 32 bytes (float32) or 16 (bf16), of which only an element's own alignment is promised unless ALIGNED
+template <bool ALIGNED> struct Pieces { typedef f32x4 f32; typedef bf16x8 b16; };
+template <> struct Pieces<false> {
+    typedef f32x4 __attribute__((aligned(4))) f32;
+    typedef bf16x8 __attribute__((aligned(2))) b16;
+};
+template <bool ALIGNED>
 __device__ __forceinline__ void store8(void* base, int64_t elem, int as_f32, const float (&v)[8]) {
     if (as_f32) {
+        typedef typename Pieces<ALIGNED>::f32 piece;
         float* p = static_cast<float*>(base) + elem;
-        *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
-        *reinterpret_cast<f32x4*>(p + 4) = f32x4{v[4], v[5], v[6], v[7]};
+        *reinterpret_cast<piece*>(p) = f32x4{v[0], v[1], v[2], v[3]};
+        *reinterpret_cast<piece*>(p + 4) = f32x4{v[4], v[5], v[6], v[7]};
     } else {
         bf16x8 o;
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(v[e]);
-        *reinterpret_cast<bf16x8*>(static_cast<bf16_t*>(base) + elem) = o;
+        *reinterpret_cast<typename Pieces<ALIGNED>::b16*>(static_cast<bf16_t*>(base) + elem) = o;
     }
 }
 
+template <bool ALIGNED>
 __device__ __forceinline__ void load8(const void* base, int64_t elem, int as_f32, float (&v)[8]) {
     if (as_f32) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(static_cast<const float*>(base) + elem + 4 * h);
+            const f32x4 a = *reinterpret_cast<const typename Pieces<ALIGNED>::f32*>(static_cast<const float*>(base) + elem + 4 * h);
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[4 * h + e] = a[e];
         }
     } else {
-        const bf16x8 a = *reinterpret_cast<const bf16x8*>(static_cast<const bf16_t*>(base) + elem);
+        const bf16x8 a = *reinterpret_cast<const typename Pieces<ALIGNED>::b16*>(static_cast<const bf16_t*>(base) + elem);
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = static_cast<float>(a[e]);
     }
@@ -105,13 +113,13 @@ __device__ __forceinline__ void load8(const void* base, int64_t elem, int as_f32
 
 // The velocity step (see epilogue_store) on columns col0..col0+n-1 of a row, n <= 8.  WIDE: all eight, in whole pieces.  Otherwise one
 // at a time, but the row's place is looked up once and every element of x_e requested before the first store.
-template <bool WIDE>
+template <bool WIDE, bool ALIGNED>
 __device__ __forceinline__ void epilogue_velocity(const GemmEpilogue& ep, int row, int col0, int n, float (&val)[8]) {
     const int64_t o = static_cast<int64_t>(row) * ep.ldy + col0;
     const int64_t full = ep.vel_index ? static_cast<int64_t>(ep.vel_index[row]) * ep.ldy + col0 : o;
     float x[8];
     if (WIDE) {
-        load8(ep.vel_xe, o, ep.y_f32, x);
+        load8<ALIGNED>(ep.vel_xe, o, ep.y_f32, x);
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
@@ -123,7 +131,7 @@ __device__ __forceinline__ void epilogue_velocity(const GemmEpilogue& ep, int ro
         x[e] = __fsub_rn(x[e], __fmul_rn(ep.vel_dt, val[e]));
     }
     auto put = [&](void* base, int64_t at, const float (&v)[8]) __attribute__((always_inline)) {
-        if (WIDE) { store8(base, at, ep.y_f32, v); return; }
+        if (WIDE) { store8<ALIGNED>(base, at, ep.y_f32, v); return; }
 #pragma unroll
         for (int e = 0; e < 8; ++e)
             if (e < n) {
@@ -137,43 +145,43 @@ __device__ __forceinline__ void epilogue_velocity(const GemmEpilogue& ep, int ro
     if (ep.vel_xfull) put(ep.vel_xfull, full, x);
 }
 
-// Epilogue for the eight consecutive columns col0..col0+7 of one row (all inside N, col0 a multiple of 8; the
-// wide-epilogue conditions hold, so a group never straddles two destinations): wide loads and stores only.
-template <int KIND>
+// Epilogue for the eight consecutive columns col0..col0+7 of one row (all inside N, col0 a multiple of 8; a group never
+// straddles two destinations): wide loads and stores only, of whole 16-byte pieces if ALIGNED.
+template <int KIND, bool ALIGNED>
 __device__ __forceinline__ void epilogue_store8(const GemmEpilogue& ep, int row, int col0, const float (&acc)[8],
                                                 const float (&bias)[8], const float (&gate)[8]) {
     float val[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) val[e] = acc[e] + bias[e];
     if (KIND == EPI_VELOCITY) {
-        epilogue_velocity<true>(ep, row, col0, 8, val);
+        epilogue_velocity<true, ALIGNED>(ep, row, col0, 8, val);
     } else if (KIND == EPI_PLAIN) {
         if (ep.act == REGIONE_ACT_GELU_TANH) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) if (col0 + e >= ep.act_from) val[e] = gelu_tanh_f32(val[e]);
         }
-        store8(ep.y, static_cast<int64_t>(row) * ep.ldy + col0, ep.y_f32, val);
+        store8<ALIGNED>(ep.y, static_cast<int64_t>(row) * ep.ldy + col0, ep.y_f32, val);
     } else if (KIND == EPI_QKV) {
         const int H = ep.hidden;   // a multiple of 8
         if (col0 < H) {
-            store8(ep.q, static_cast<int64_t>(row) * ep.ldq + col0, 0, val);
+            store8<ALIGNED>(ep.q, static_cast<int64_t>(row) * ep.ldq + col0, 0, val);
         } else if (col0 < 3 * H) {
             const int64_t kv_row = epilogue_kv_row<KIND>(ep, row);
-            if (col0 < 2 * H) store8(ep.k, kv_row * ep.ldkv + (col0 - H), 0, val);
-            else store8(ep.v, kv_row * ep.ldkv + (col0 - 2 * H), 0, val);
+            if (col0 < 2 * H) store8<ALIGNED>(ep.k, kv_row * ep.ldkv + (col0 - H), 0, val);
+            else store8<ALIGNED>(ep.v, kv_row * ep.ldkv + (col0 - 2 * H), 0, val);
         } else {
             if (ep.act == REGIONE_ACT_GELU_TANH) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) val[e] = gelu_tanh_f32(val[e]);
             }
-            store8(ep.y, static_cast<int64_t>(row) * ep.ldy + ep.y_col0 + (col0 - 3 * H), 0, val);
+            store8<ALIGNED>(ep.y, static_cast<int64_t>(row) * ep.ldy + ep.y_col0 + (col0 - 3 * H), 0, val);
         }
     } else {  // EPI_RESID
         float res[8];
-        load8(ep.resid, static_cast<int64_t>(row) * ep.ldr + col0, ep.resid_f32, res);
+        load8<ALIGNED>(ep.resid, static_cast<int64_t>(row) * ep.ldr + col0, ep.resid_f32, res);
 #pragma unroll
         for (int e = 0; e < 8; ++e) val[e] = res[e] + gate[e] * val[e];
-        store8(ep.y, static_cast<int64_t>(row) * ep.ldy + col0, ep.y_f32, val);
+        store8<ALIGNED>(ep.y, static_cast<int64_t>(row) * ep.ldy + col0, ep.y_f32, val);
     }
 }
 // Writes a wave's accumulators, those of 16x16 matrix instructions whose FIRST operand were the weights: acc[i][j] of a lane
@@ -181,30 +189,39 @@ __device__ __forceinline__ void epilogue_store8(const GemmEpilogue& ep, int row,
 // the caller presents the weight columns), i.e. eight consecutive columns per pair j = 2b, 2b+1.  A lane writes 16 bytes
 // (bf16) of its row per pair, the four lanes of a row 64 contiguous bytes: no transposition, no LDS, no barrier.
 // SCALED (the 8-bit GEMM): every sum is first multiplied by ep.row_scale[row] * ep.col_scale[column].
+template <int KIND, bool SCALED, int I0, int I1, int RF, int CF, int B, bool ALIGNED>
+__device__ __forceinline__ void gemm_epilogue16_wide(f32x4 (&acc)[RF][CF], int M, int m0, int col0, const GemmEpilogue& ep) {
+    const int l16 = threadIdx.x & 15;
+    float bias[8], gate[8], cscale[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        bias[e] = ep.bias ? ep.bias[col0 + e] : 0.f;
+        gate[e] = (KIND == EPI_RESID && ep.gate) ? ep.gate[col0 + e] : 1.f;
+        cscale[e] = SCALED ? ep.col_scale[col0 + e] : 1.f;
+    }
+#pragma unroll
+    for (int i = I0; i < I1; ++i) {
+        const int row = m0 + 16 * i + l16;
+        if (row < M) {
+            const float rs = SCALED ? ep.row_scale[row] : 1.f;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = SCALED ? acc[i][2 * B + (e >> 2)][e & 3] * (rs * cscale[e]) : acc[i][2 * B + (e >> 2)][e & 3];
+            epilogue_store8<KIND, ALIGNED>(ep, row, col0, v, bias, gate);
+        }
+    }
+}
 template <int KIND, bool SCALED, int I0, int I1, int RF, int CF, int B>
 __device__ __forceinline__ void gemm_epilogue16_pair(f32x4 (&acc)[RF][CF], int M, int N, int m0, int n0w, const GemmEpilogue& ep) {
     const int lane = threadIdx.x & 63, l16 = lane & 15;
     const int col0 = n0w + 32 * B + 8 * (lane >> 4);
     if (ep.vec_ok) {
-        if (col0 >= N) return;            // N is a multiple of 8 on this path
-        float bias[8], gate[8], cscale[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            bias[e] = ep.bias ? ep.bias[col0 + e] : 0.f;
-            gate[e] = (KIND == EPI_RESID && ep.gate) ? ep.gate[col0 + e] : 1.f;
-            cscale[e] = SCALED ? ep.col_scale[col0 + e] : 1.f;
-        }
-#pragma unroll
-        for (int i = I0; i < I1; ++i) {
-            const int row = m0 + 16 * i + l16;
-            if (row < M) {
-                const float rs = SCALED ? ep.row_scale[row] : 1.f;
-                float v[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = SCALED ? acc[i][2 * B + (e >> 2)][e & 3] * (rs * cscale[e]) : acc[i][2 * B + (e >> 2)][e & 3];
-                epilogue_store8<KIND>(ep, row, col0, v, bias, gate);
-            }
-        }
+        if (col0 < N) gemm_epilogue16_wide<KIND, SCALED, I0, I1, RF, CF, B, true>(acc, M, m0, col0, ep);    // N is a multiple of 8 on this path
+    } else if (KIND != EPI_QKV && col0 + 8 <= N) {
+        // odd widths or unaligned tensors: the same pieces without their alignment, which the memory path takes as it is.  One element at
+        // a time cost as much as the product (us): 11844 x 9156 x 832 358 -> 171, 543 x 9522 x 384 24 -> 13, 10605 x 201 x 5568 55 -> 45;
+        // velocity heads on 8704 rows of 65 channels 37 -> 27, of 100 45 -> 27
+        gemm_epilogue16_wide<KIND, SCALED, I0, I1, RF, CF, B, false>(acc, M, m0, col0, ep);
     } else {
 #pragma unroll
         for (int i = I0; i < I1; ++i) {
@@ -214,7 +231,7 @@ __device__ __forceinline__ void gemm_epilogue16_pair(f32x4 (&acc)[RF][CF], int M
                     float v[8];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) v[e] = acc[i][2 * B + (e >> 2)][e & 3] + (ep.bias && col0 + e < N ? ep.bias[col0 + e] : 0.f);
-                    epilogue_velocity<false>(ep, row, col0, N - col0, v);
+                    epilogue_velocity<false, false>(ep, row, col0, N - col0, v);
                     continue;
                 }
                 const float rs = SCALED ? ep.row_scale[row] : 1.f;
