@@ -29,8 +29,10 @@ int regione_gemm_plan_host(int32_t m, int32_t n, int32_t k, int32_t kind, int64_
 int regione_tune_attention(regione_ctx* ctx, int32_t key_splits);
 
 /* How an attention of n_q queries on n_keys keys is dealt to workgroups in this bf16 context, with its workspace and what
- * regione_tune_attention forces, for keys in one array, in two (fresh rows, then cache rows) or named by an index list: *key_splits equal key ranges per query tile (128 queries), or, where *range_tiles > 0, even ranges of
- * that many key tiles (64 keys) each behind the first *whole_query_tiles query tiles of every head, which stay unsplit.  Host only. */
+ * regione_tune_attention forces, for keys in one array, in two (fresh rows, then cache rows) or named by an index list: *key_splits equal key ranges per
+ * query tile, or, where *range_tiles > 0, even ranges of that many key tiles (64 keys) each behind the first *whole_query_tiles query tiles
+ * (counted in 128 queries) of every head, which stay unsplit; workgroups of 256 queries take them in pairs and leave an odd last one to the
+ * ranges.  A forced number of equal ranges is taken in workgroups of 128 queries.  Host only. */
 enum { REGIONE_KEYS_CONTIGUOUS = 0, REGIONE_KEYS_TWO = 1, REGIONE_KEYS_INDEXED = 2 };
 int regione_attention_plan(regione_ctx* ctx, int32_t n_q, int32_t n_keys, int32_t heads, int32_t d, int32_t source, int32_t* key_splits,
                            int32_t* range_tiles, int32_t* whole_query_tiles);

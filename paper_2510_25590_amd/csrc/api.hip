@@ -84,7 +84,10 @@ extern "C" int regione_create(regione_ctx** out, const regione_dims* dims, void*
     // partial rows of an attention: eight key ranges for up to 2048 queries, and for few queries up to 32 of at most 8192 rows together
     size_t part_rows = 8 * split_rows;
     if (part_rows < 8192) part_rows = 32 * split_rows < 8192 ? 32 * split_rows : 8192;
-    c->attn_part_bytes = part_rows * dims->heads * (dims->head_dim + 4) * sizeof(float);
+    c->attn_range_bytes = part_rows * dims->heads * (dims->head_dim + 4) * sizeof(float);
+    // even ranges on 256 workgroups of 256 queries, two partial results each
+    const size_t even_bytes = dims->head_dim == 128 && n > 128 ? 256 * 2 * 256 * static_cast<size_t>(128 + 4) * sizeof(float) : 0;
+    c->attn_part_bytes = c->attn_range_bytes > even_bytes ? c->attn_range_bytes : even_bytes;
     int rc = dev_alloc(&c->part_counts, static_cast<size_t>(c->part_counts_cap));
     if (rc == REGIONE_OK) rc = dev_alloc(&c->u, n * H * es);
     if (rc == REGIONE_OK) rc = dev_alloc(&c->q, n * H * es);
@@ -448,10 +451,11 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
 
     // ---- attention (Eq.6).  With a flag set the fresh K,V already sit in their cache slots, so the
     // key list is the whole cached sequence; without a flag it is the fresh rows only.
+    const bool keep_ranges = w8 && dbl && H > 1024;
     for (int b = 0; b < n_branches; ++b) {
         const size_t r0 = static_cast<size_t>(b) * n_fresh * es, c0 = static_cast<size_t>(b) * n_all * H * es;
-        if (flags) rc = rg_attention(ctx, ctx->q + r0 * H, H, n_fresh, nullptr, nullptr, H, 0, kc + c0, vc + c0, H, n_all, nullptr, heads, D, 0.f, ctx->a + r0 * lda_attn, lda_attn);
-        else rc = rg_attention(ctx, ctx->q + r0 * H, H, n_fresh, ctx->kf + r0 * H, ctx->vf + r0 * H, H, n_fresh, nullptr, nullptr, H, 0, nullptr, heads, D, 0.f, ctx->a + r0 * lda_attn, lda_attn);
+        if (flags) rc = rg_attention(ctx, ctx->q + r0 * H, H, n_fresh, nullptr, nullptr, H, 0, kc + c0, vc + c0, H, n_all, nullptr, 0, heads, D, 0.f, ctx->a + r0 * lda_attn, lda_attn, keep_ranges);
+        else rc = rg_attention(ctx, ctx->q + r0 * H, H, n_fresh, ctx->kf + r0 * H, ctx->vf + r0 * H, H, n_fresh, nullptr, nullptr, H, 0, nullptr, 0, heads, D, 0.f, ctx->a + r0 * lda_attn, lda_attn, keep_ranges);
         if (rc != REGIONE_OK) return rc;
     }
 

@@ -35,6 +35,7 @@ struct regione_ctx {
     char* m;       // [max_fresh, M]     activated MLP hidden rows
     float* attn_part;  // split-KV partial results
     size_t attn_part_bytes;
+    size_t attn_range_bytes;   // how much of it plan_ranges counts on
     int32_t* slot_all; // [max_fresh] slot list of all branches of a batched block call
     float* mod_ws;     // [2][6H] modulation vectors of the two streams when a block call forms them itself
     // workspace of the 8-bit block (allocated by its first call): codes of one projection's input rows and their scales
@@ -129,8 +130,8 @@ int rg_qk_norm_rope(regione_ctx* ctx, bf16_t* q, int ldq, bf16_t* k, int ldkv, c
 int rg_expand_slots(regione_ctx* ctx, const int32_t* slot, int n, int n_branches, int branch_rows, int32_t* out);
 int rg_attention(regione_ctx* ctx, const void* q, int ldq, int n_q,
                  const void* k0, const void* v0, int ldkv0, int n0,
-                 const void* k1, const void* v1, int ldkv1, int n1, const int32_t* idx1,
-                 int heads, int d, float scale, void* out, int ldo);
+                 const void* k1, const void* v1, int ldkv1, int n1, const int32_t* idx1, int rows1,   // rows1: rows of the array that idx1 picks from
+                 int heads, int d, float scale, void* out, int ldo, bool keep_ranges);       // keep_ranges: for wide E4M3 blocks, see plan_ranges
 int rg_attention_f32(regione_ctx* ctx, const float* q, int ldq, int n_q,
                      const float* k0, const float* v0, int ldkv0, int n0,
                      const float* k1, const float* v1, int ldkv1, int n1, const int32_t* idx1,

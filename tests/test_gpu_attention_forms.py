@@ -1,0 +1,66 @@
+"""The forms of attention workgroups at the sizes where each can go wrong: 32-query tiles that deal their keys to the waves (none, one, two and more
+blocks per wave, in one key range and in several), 128-query tiles whose two wave groups take a range each or one in turns, and 256-query tiles, unsplit and
+in even ranges; query and key counts around the tiles' edges, the place where the cache rows begin inside a tile, every key source.  The oracle
+is float32 attention on the same bf16 inputs."""
+import pytest
+import torch
+
+from paper_2510_25590_amd import binding as rg
+from test_gpu_attention_ranges import _reference
+
+pytestmark = pytest.mark.gpu
+
+
+def _call(heads, d, n_q, n_fresh, n_cached, source, splits=0):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1000 * n_q + n_cached)
+    r = lambda n: torch.empty((n, heads, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    rows = n_cached if source != "indexed" else n_cached + 77
+    q, kf, vf, kc, vc = r(n_q) * 2.0, r(n_fresh), r(n_fresh), r(max(rows, 1)), r(max(rows, 1))
+    idx = torch.randperm(rows, generator=g, device="cuda")[:n_cached].int().contiguous() if source == "indexed" else None
+    ctx = rg.Context(heads * d, heads, d, 256, max(n_q, 512), 16)
+    rg.regione_tune_attention(ctx, splits)
+    outs = []
+    for _ in range(2):
+        out = torch.full((n_q + 1, heads, d), 7.0, dtype=torch.bfloat16, device="cuda")
+        rg.regione_attn_kvcache(ctx, q, n_q, kf if n_fresh else None, vf if n_fresh else None, n_fresh, kc, vc, rows, idx, n_cached if source == "indexed" else 0,
+                                heads, d, 0.0, out)
+        torch.cuda.synchronize()
+        outs.append(out)
+    ctx.close()
+    assert torch.equal(outs[0], outs[1])                 # no order that depends on timing
+    used = (kc[idx.long()], vc[idx.long()]) if source == "indexed" else (kc[:n_cached], vc[:n_cached])
+    k, v = torch.cat([kf, used[0]]), torch.cat([vf, used[1]])
+    want, got = _reference(q, k, v, d), outs[0].float()
+    assert torch.all(got[n_q] == 7.0)
+    # weights and result in bf16: 2^-9 relative each, on rows whose weights add up to one
+    assert float((got[:n_q] - want).norm() / want.norm()) <= 2.0 ** -8
+    assert float((got[:n_q] - want).abs().max()) <= 2.0 ** -7 * float(v.float().abs().max())
+
+
+@pytest.mark.parametrize("source", ["one", "two", "indexed"])
+@pytest.mark.parametrize("heads,d,n_q,n_keys", [
+    (3, 128, 1, 1), (2, 64, 31, 32), (8, 128, 32, 33), (4, 64, 33, 65), (8, 128, 65, 257), (4, 64, 36, 544), (4, 64, 257, 575),
+    (24, 128, 64, 513), (5, 128, 100, 1023), (24, 128, 17, 3500), (4, 64, 40, 4100),
+])
+def test_few_queries(source, heads, d, n_q, n_keys):
+    n_fresh = 0 if source == "one" else min(n_q, n_keys // 2)
+    _call(heads, d, n_q, n_fresh, n_keys - n_fresh, source)
+
+
+@pytest.mark.parametrize("source", ["one", "two", "indexed"])
+@pytest.mark.parametrize("heads,n_q,n_keys", [
+    (24, 257, 1500), (24, 820, 4097),                    # 128-query tiles, ranges in pairs
+    (24, 2500, 1217), (8, 6500, 700),                    # 256-query tiles, unsplit; the last one with a few rows
+    (24, 1400, 5001), (24, 3100, 2050),                  # ... in even ranges, alone and behind whole passes
+])
+def test_many_queries(source, heads, n_q, n_keys):
+    n_fresh = 0 if source == "one" else 333
+    _call(heads, 128, n_q, n_fresh, n_keys - n_fresh, source)
+
+
+@pytest.mark.parametrize("splits", [1, 2, 3, 4, 7])
+def test_forced_ranges(splits):
+    """One range and odd numbers are taken by the wave groups in turns, even numbers a range to each group; the last ones are short or empty."""
+    for n_keys in (128 * splits + 1, 128 * splits + 129, 2000):
+        _call(2, 128, 150, 50, n_keys - 50, "indexed", splits)
