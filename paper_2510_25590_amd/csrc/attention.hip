@@ -312,8 +312,9 @@ __device__ __forceinline__ void attn_tile(const bf16_t* smem, int t, int n_keys,
     }
 }
 
-// Head dimension 64: four waves of 32 queries, copies one tile ahead in two LDS stages.
-template <int D, int MODE>
+// Four waves of 32 queries, copies one tile ahead in two LDS stages.
+// RANGED: the grid holds even ranges (AttnArgs); a form of its own because the loop over query tiles costs registers.
+template <int D, int MODE, bool RANGED>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attn_narrow_kernel(AttnArgs a) {
     constexpr int NW = 4, QB = 1;
@@ -328,16 +329,40 @@ attn_narrow_kernel(AttnArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     // XCD-aware numbering (workgroup i runs on XCD i % 8): all query tiles of one (head, key split) get consecutive
-    // slots on ONE XCD, so that the K/V range they share is filled into a single L2 once instead of once per query tile.
+    // slots on ONE XCD, so that the K/V range they share is filled into a single L2 once instead of once per query tile;
+    // for the same reason an XCD's even ranges are consecutive ones.
+    const int xcd = blockIdx.x & 7;
     const int n_keys = a.n0 + a.n1;
     const int n_tiles = (n_keys + KT - 1) / KT;
-    const int local = blockIdx.x >> 3;
-    const int group = __builtin_amdgcn_readfirstlane((local / a.q_tiles) * 8 + (blockIdx.x & 7));   // (head, split) pair
-    if (group >= a.heads * a.splits) return;
-    const int q_tile = __builtin_amdgcn_readfirstlane(local % a.q_tiles);
-    const int head = group % a.heads, slot = group / a.heads;
-    const int tile_begin = slot * a.tiles_per_split;
-    const int tile_end = tile_begin + a.tiles_per_split < n_tiles ? tile_begin + a.tiles_per_split : n_tiles;
+    const bool ranged = RANGED && static_cast<int>(blockIdx.x) >= a.full_blocks;
+    int head, q_tile, tile_begin, tile_end, left = 0, slot = 0;
+    if (!ranged) {
+        const int local = blockIdx.x >> 3;
+        const int group = (local / a.q_full) * 8 + xcd;            // (head, split) pair
+        if (group >= a.heads * a.splits) return;
+        q_tile = local % a.q_full;
+        head = group % a.heads;
+        slot = group / a.heads;
+        tile_begin = slot * a.tiles_per_split;
+        tile_end = tile_begin + a.tiles_per_split;
+        tile_end = tile_end < n_tiles ? tile_end : n_tiles;
+    } else {
+        const int per_xcd = (a.range_wgs + 7) / 8;
+        const int w = xcd * per_xcd + ((static_cast<int>(blockIdx.x) - a.full_blocks) >> 3);
+        const int q_rest = a.q_tiles - a.q_full;
+        const int first = w * a.range;
+        const int total = a.heads * q_rest * n_tiles;              // the launcher keeps it below 2^30
+        if (w >= a.range_wgs || first >= total) return;
+        left = total - first < a.range ? total - first : a.range;
+        const int seg = first / n_tiles;
+        head = seg / q_rest;
+        q_tile = a.q_full + seg % q_rest;
+        tile_begin = first - seg * n_tiles;
+        tile_end = tile_begin + left < n_tiles ? tile_begin + left : n_tiles;
+        slot = 2 * w;
+    }
+    head = __builtin_amdgcn_readfirstlane(head); q_tile = __builtin_amdgcn_readfirstlane(q_tile); slot = __builtin_amdgcn_readfirstlane(slot);
+    tile_begin = __builtin_amdgcn_readfirstlane(tile_begin); tile_end = __builtin_amdgcn_readfirstlane(tile_end); left = __builtin_amdgcn_readfirstlane(left);
 
     // per-lane LDS offsets (elements) of the fragment reads
     int koff[KK], voff[DB];
@@ -392,83 +417,92 @@ attn_narrow_kernel(AttnArgs a) {
             kv_tile_issue<D, NW, MODE == SRC_CONTIG ? SRC_TWO : MODE>(a, head, tc * KT, n_keys, stage_bytes);
         }
     };
-    if (tile_begin < tile_end) issue_tile(tile_begin, smem_bytes0);
-    const int q_base = q_tile * QW + wave * (QB * 32);
-    // Q fragments ("B" operand): lane holds query l32 of the block, d = kk*16 + 8*lh + 0..7
-    bf16x8 qf[QB][KK];
+    for (;;) {   // one query tile and key range; an even range may run on into further query tiles
+        if (tile_begin < tile_end) issue_tile(tile_begin, smem_bytes0);
+        const int q_base = q_tile * QW + wave * (QB * 32);
+        // Q fragments ("B" operand): lane holds query l32 of the block, d = kk*16 + 8*lh + 0..7
+        bf16x8 qf[QB][KK];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        int qrow = q_base + qb * 32 + l32;
-        qrow = qrow < a.n_q ? qrow : a.n_q - 1;
-        const bf16_t* qp = a.q + static_cast<int64_t>(qrow) * a.ldq + head * D + 8 * lh;
+        for (int qb = 0; qb < QB; ++qb) {
+            int qrow = q_base + qb * 32 + l32;
+            qrow = qrow < a.n_q ? qrow : a.n_q - 1;
+            const bf16_t* qp = a.q + static_cast<int64_t>(qrow) * a.ldq + head * D + 8 * lh;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) qf[qb][kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16);
-    }
-    f32x16 o[QB][DB];
-    float m_run[QB], l_run[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        m_run[qb] = m_floor;
-        l_run[qb] = 0.f;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[qb][db][r] = 0.f;
-    }
-#define RG_ATTN_TILE(T, STAGE, MASK)                                                                      \
-    {                                                                                                     \
-        const int t_ = (T);                                                                               \
-        wait_async_copies<0>();                                                                           \
-        __syncthreads();                                                                                  \
-        issue_tile(t_ + 1, smem_bytes0 + ((STAGE) ^ 1) * STAGE_BYTES);                                    \
-        attn_tile<D, STAGE, QB, MASK>(smem, t_, n_keys, c, lh, koff, voff, qf, o, m_run, l_run);          \
-    }
-    // only the very last tile of the key list can be partial; it runs outside the main loop with the masking code
-    const bool last_partial = tile_end * KT > n_keys;
-    const int full_end = last_partial ? tile_end - 1 : tile_end;
-    for (int t = tile_begin; t < full_end; t += 2) {
-        RG_ATTN_TILE(t, 0, false)
-        if (t + 1 < full_end) RG_ATTN_TILE(t + 1, 1, false)
-    }
-    if (full_end < tile_end && tile_begin < tile_end) {   // its stage follows from the number of full tiles before it
-        if (((full_end - tile_begin) & 1) == 0) RG_ATTN_TILE(full_end, 0, true) else RG_ATTN_TILE(full_end, 1, true)
-    }
-#undef RG_ATTN_TILE
-    wait_async_copies<0>();   // nothing may still be writing LDS when the workgroup ends
-
-    const bool whole = a.splits == 1;
-    // ---- finish: O^T accumulator r of d-block db: d = db*32 + 8*(r/4) + 4*lh + r%4, query = l32
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int qrow = q_base + qb * 32 + l32;
-        const float l_tot = sum_across_halves(l_run[qb]);
-        if (qrow >= a.n_q) continue;
-        if (whole) {
-            const float inv = 1.0f / l_tot;
-            bf16_t* op = a.out + static_cast<int64_t>(qrow) * a.ldo + head * D;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int d = db * 32 + 8 * g + 4 * lh;
-                    bf16x4 pk;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) pk[e] = static_cast<__bf16>(o[qb][db][4 * g + e] * inv);
-                    *reinterpret_cast<bf16x4*>(op + d) = pk;
-                }
-        } else {
-            // partial result: unnormalised O, running max (log2 domain) and sum
-            const int64_t prow = (static_cast<int64_t>(slot) * a.heads + head) * a.n_q_pad + qrow;
-            float* pp = a.part + prow * (D + 4);
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int d = db * 32 + 8 * g + 4 * lh;
-                    *reinterpret_cast<f32x4*>(pp + d) = f32x4{o[qb][db][4 * g], o[qb][db][4 * g + 1], o[qb][db][4 * g + 2], o[qb][db][4 * g + 3]};
-                }
-            if (lh == 0) { pp[D] = m_run[qb] * c; pp[D + 1] = l_tot; }   // maximum in the log2 domain, as the merge kernel expects
+            for (int kk = 0; kk < KK; ++kk) qf[qb][kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16);
         }
+        f32x16 o[QB][DB];
+        float m_run[QB], l_run[QB];
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            m_run[qb] = m_floor;
+            l_run[qb] = 0.f;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[qb][db][r] = 0.f;
+        }
+#define RG_ATTN_TILE(T, STAGE, MASK)                                                                      \
+        {                                                                                                     \
+            const int t_ = (T);                                                                               \
+            wait_async_copies<0>();                                                                           \
+            __syncthreads();                                                                                  \
+            issue_tile(t_ + 1, smem_bytes0 + ((STAGE) ^ 1) * STAGE_BYTES);                                    \
+            attn_tile<D, STAGE, QB, MASK>(smem, t_, n_keys, c, lh, koff, voff, qf, o, m_run, l_run);          \
+        }
+        // only the very last tile of the key list can be partial; it runs outside the main loop with the masking code
+        const bool last_partial = tile_end * KT > n_keys;
+        const int full_end = last_partial ? tile_end - 1 : tile_end;
+        for (int t = tile_begin; t < full_end; t += 2) {
+            RG_ATTN_TILE(t, 0, false)
+            if (t + 1 < full_end) RG_ATTN_TILE(t + 1, 1, false)
+        }
+        if (full_end < tile_end && tile_begin < tile_end) {   // its stage follows from the number of full tiles before it
+            if (((full_end - tile_begin) & 1) == 0) RG_ATTN_TILE(full_end, 0, true) else RG_ATTN_TILE(full_end, 1, true)
+        }
+#undef RG_ATTN_TILE
+        wait_async_copies<0>();   // nothing may still be writing LDS when the workgroup ends
+
+        const bool whole = ranged ? tile_begin == 0 && tile_end == n_tiles : a.splits == 1;
+        // ---- finish: O^T accumulator r of d-block db: d = db*32 + 8*(r/4) + 4*lh + r%4, query = l32
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const int qrow = q_base + qb * 32 + l32;
+            const float l_tot = sum_across_halves(l_run[qb]);
+            if (qrow >= a.n_q) continue;
+            if (whole) {
+                const float inv = 1.0f / l_tot;
+                bf16_t* op = a.out + static_cast<int64_t>(qrow) * a.ldo + head * D;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int d = db * 32 + 8 * g + 4 * lh;
+                        bf16x4 pk;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) pk[e] = static_cast<__bf16>(o[qb][db][4 * g + e] * inv);
+                        *reinterpret_cast<bf16x4*>(op + d) = pk;
+                    }
+            } else {
+                // partial result: unnormalised O, running max (log2 domain) and sum
+                const int64_t prow = ranged ? static_cast<int64_t>(slot) * QW + (qrow - q_tile * QW) : (static_cast<int64_t>(slot) * a.heads + head) * a.n_q_pad + qrow;
+                float* pp = a.part + prow * (D + 4);
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int d = db * 32 + 8 * g + 4 * lh;
+                        *reinterpret_cast<f32x4*>(pp + d) = f32x4{o[qb][db][4 * g], o[qb][db][4 * g + 1], o[qb][db][4 * g + 2], o[qb][db][4 * g + 3]};
+                    }
+                if (lh == 0) { pp[D] = m_run[qb] * c; pp[D + 1] = l_tot; }   // maximum in the log2 domain, as the merge kernel expects
+            }
+        }
+        left -= tile_end - tile_begin;
+        if (!ranged || left <= 0) break;
+        __syncthreads();   // every wave has read its last tile before the next query tile's first copies
+        slot |= 1;         // only the last query tile of a range can be partial from here on
+        tile_begin = 0;
+        tile_end = left < n_tiles ? left : n_tiles;
+        if (++q_tile == a.q_tiles) { q_tile = a.q_full; ++head; }
     }
 }
 
@@ -1320,7 +1354,7 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
 
 // ---------------------------------------------------------------- how a call is dealt to workgroups
 //
-// NARROW (head dimension 64): workgroups of four waves of 32 queries, several per CU, that run freely; there the softmax bounds, and groups that take turns at
+// NARROW (head dimension 64, and wide E4M3 blocks): workgroups of four waves of 32 queries, several per CU, that run freely; there the softmax bounds, and groups that take turns at
 // the matrix cores would leave the vector units idle instead.  SPLIT and SHARE (head dimension 128): see AttnTile, one workgroup per CU.  DEALT:
 // few queries on not too many keys.
 enum { FORM_SPLIT = 0, FORM_SHARE = 1, FORM_DEALT = 2, FORM_NARROW = 3 };
@@ -1353,7 +1387,8 @@ double range_time(int source, int q_tiles, int heads, int n_q, int n_tiles, int 
 // Key ranges for workgroups of four waves, two per CU: what NARROW calls take.  With head dimension 128 the choice stays in use for its ranges of keys in
 // one array: where it takes even ranges (see plan_wide), and for wide E4M3 blocks.  Their two quantisations turn another rounding of
 // the attention's results by one bf16 ulp into whole code steps (1.8 % of a 3072-wide double-stream block's output, 0.7 % at width 1024), and the
-// weights are rounded relative to their range's reference; so other key ranges would change that mode's results by that much.
+// weights are rounded relative to their range's reference; so other key ranges would change that mode's results by that much.  The kernel of four waves stays
+// for them where forms of one workgroup per CU have too few of these ranges to share out: 928 queries and keys, 24 heads, 68 us in SPLIT workgroups, 39.5 so.
 template <int D>
 AttnPlan plan_ranges(int source, int n_q, int n_keys, int heads, int force_splits, size_t part_bytes) {
     constexpr int QW = 128;
@@ -1399,13 +1434,14 @@ AttnPlan plan_ranges(int source, int n_q, int n_keys, int heads, int force_split
 
 // Microseconds of SPLIT, SHARE and DEALT workgroups, one per CU: `units` of work each (key tiles; DEALT: blocks of 32 keys of a wave) at `full` in a
 // pass that fills the chip and at `part` + `fill` x its filling in the last one (the chip's power is shared by fewer), a start per pass,
-// the merge launch and the partial rows' way out and back.  Fitted to 1700 forced plans of 150 calls (16-9000 queries, 500-19000 keys, 8, 16 and 24 heads; all
-// three key sources): rms 5 to 9 %, its choice 1.0 % behind the best plan on average and 1.16 times faster than the kernel of four-wave
-// workgroups before.
-struct FormCost { double fixed, pass, full, part, fill, merge, mb, ranged, keys; };   // keys: a megabyte of the keys and values (DEALT workgroups start on them all at once)
+// the merge launch and the partial rows' way out and back.  SPLIT and SHARE fitted to 1700 forced plans of 150 calls (16-9000 queries, 500-19000 keys, 8, 16 and 24
+// heads; all three key sources); DEALT, whose workgroups start on all keys at once, to 2200 plans of 370 calls on keys that no cache held, as those of a model's blocks
+// are not: 140 queries on 7068 keys, 24 heads, 42.7 us in DEALT workgroups that costs of cached keys chose, now 32.  Over 630 such calls the choice is 1.8 % behind
+// the best plan on average.
+struct FormCost { double fixed, pass, full, part, fill, merge, mb, ranged, keys; };   // keys: a megabyte of the keys and values
 constexpr FormCost kFormCosts[2][3] = {   // keys in one or two arrays, by index list; SPLIT, SHARE, DEALT
-    {{9.72, 0.00, 0.94, 0.50, 0.27, 1.24, 0.46, 7.35, 0.0}, {8.60, 0.00, 1.65, 0.92, 0.57, 0.00, 0.47, 3.91, 0.0}, {2.37, 4.33, 1.29, 0.93, 0.21, 2.34, 0.36, 0.0, 0.062}},
-    {{9.08, 0.38, 1.10, 0.79, 0.13, 3.04, 0.56, 12.37, 0.0}, {5.54, 0.00, 1.62, 1.36, 0.13, 3.20, 0.65, 5.89, 0.0}, {4.11, 4.08, 1.44, 1.45, 0.00, 1.30, 0.70, 0.0, 0.066}}};
+    {{9.72, 0.00, 0.94, 0.50, 0.27, 1.24, 0.46, 7.35, 0.0}, {8.60, 0.00, 1.65, 0.92, 0.57, 0.00, 0.47, 3.91, 0.0}, {2.17, 3.85, 1.494, 1.441, 0.245, 2.83, 0.404, 0.0, 0.118}},
+    {{9.08, 0.38, 1.10, 0.79, 0.13, 3.04, 0.56, 12.37, 0.0}, {5.54, 0.00, 1.62, 1.36, 0.13, 3.20, 0.65, 5.89, 0.0}, {3.44, 3.29, 1.690, 1.682, 0.000, 2.75, 0.563, 0.0, 0.095}}};
 constexpr FormCost kDealtNarrow[2] = {{3.03, 1.87, 0.85, 0.61, 0.10, 3.07, 0.62, 0.0, 0.0}, {1.04, 4.36, 0.97, 0.97, 0.00, 3.01, 0.51, 0.0, 0.0}};   // head dimension 64
 
 template <int D>
@@ -1427,6 +1463,7 @@ double even_time(int form, bool indexed, int n_q, int heads, int n_tiles, int q_
     const double whole = heads * q_full / 256.0, fill = (range_wgs + 7) / 8 / 32.0;
     double t = c.fixed + c.ranged + c.merge + c.pass * (whole + 1.0 + static_cast<double>(range - 1) / n_tiles) + c.full * whole * n_tiles;
     t += range * (fill >= 1.0 ? c.full : c.part + c.fill * fill);
+    t += c.keys * 4.0e-6 * n_tiles * KT * heads * 128;
     return t + c.mb * 4.0e-6 * (n_q - q_full * form_queries(form)) * static_cast<double>(heads) * (128 + 4) * (static_cast<double>(n_tiles) / range + 1.0);
 }
 
@@ -1439,11 +1476,12 @@ AttnPlan plan_wide(int source, int n_q, int n_keys, int heads, size_t range_byte
     const bool indexed = source == SRC_INDEXED;
     const int n_tiles = (n_keys + KT - 1) / KT, tiles128 = (n_q + 127) / 128;
     const size_t part_row_set = static_cast<size_t>(heads) * n_q * (D + 4) * sizeof(float);
-    // Even ranges of keys in one array are taken where plan_ranges takes them: tests of such ranges name their calls.  The best form without
-    // them was as fast or up to 4 % faster in 10 of 13 such calls, 1.08 to 1.26 times faster in the others.
+    // Even ranges of up to 3008 keys in one array are taken for more than 1408 queries where plan_ranges takes them: tests of such ranges name their calls.  The best form
+    // without them is 1.03 to 1.35 times faster there; of fewer queries or more keys, where the costs decide, it was up to 1.6 times (489 queries on 2363 keys,
+    // 24 heads, 49 us, now 31).
     AttnPlan even = {};
     if (source == SRC_CONTIG) even = plan_ranges<D>(source, n_q, n_keys, heads, 0, range_bytes);
-    const bool only_even = even.range > 0;
+    const bool only_even = even.range > 0 && n_tiles <= 47 && n_q > 1408;
     AttnPlan plan = {};
     double best = 0.0;
     for (int form = FORM_SPLIT; form <= FORM_DEALT && !only_even; ++form)
@@ -1484,14 +1522,16 @@ AttnPlan plan_attention(const regione_ctx* ctx, int source, int n_q, int n_keys,
     const int n_tiles = (n_keys + KT - 1) / KT, forced = ctx->attn_force_splits;
     if (d == 128 && !keep_ranges && forced == 0) return plan_wide(source, n_q, n_keys, heads, ctx->attn_range_bytes, ctx->attn_part_bytes);
     AttnPlan plan = d == 64 ? plan_ranges<64>(source, n_q, n_keys, heads, forced, ctx->attn_range_bytes) : plan_ranges<128>(source, n_q, n_keys, heads, forced, ctx->attn_range_bytes);
-    if (forced > 0 || plan.range > 0) return plan;
+    if (forced > 0) return plan;
     // the same ranges in another form, or (head dimension 64) other ranges in DEALT workgroups
     if (d == 128) {
-        const int pairs = plan.splits % 2 == 0 ? plan.splits / 2 : plan.splits;
-        double best = form_time<128>(FORM_SPLIT, source == SRC_INDEXED, n_q, heads, n_tiles, pairs);
-        for (int form = FORM_SHARE; form <= FORM_DEALT; ++form) {
-            const double t = form_time<128>(form, source == SRC_INDEXED, n_q, heads, n_tiles, plan.splits);
-            if (t >= best || (form == FORM_DEALT && !dealt_fits(source, n_tiles, plan.splits))) continue;
+        plan.form = source == SRC_CONTIG ? FORM_NARROW : FORM_SPLIT;
+        if (plan.range > 0) return plan;
+        double best = source == SRC_CONTIG ? range_time<128>(source, plan.whole, heads, n_q, n_tiles, plan.splits) : DBL_MAX;
+        for (int form = FORM_SPLIT; form <= FORM_SHARE; ++form) {
+            const int pairs = form == FORM_SPLIT && plan.splits % 2 == 0 ? plan.splits / 2 : plan.splits;
+            const double t = form_time<128>(form, source == SRC_INDEXED, n_q, heads, n_tiles, pairs);
+            if (t >= (plan.form == FORM_NARROW ? 0.9 : 1.0) * best) continue;   // two models: a tenth apart before the wide forms are taken
             best = t;
             plan.form = form;
         }
@@ -1538,6 +1578,11 @@ int launch_attention(regione_ctx* ctx, AttnArgs a, bool keep_ranges) {
         kernel = indexed ? attn_dealt_kernel<D, true> : attn_dealt_kernel<D, false>;
         lds_bytes = DealtTile<D>::LIST_BASE + (indexed ? kDealtKeys * sizeof(int32_t) : 0);
         which = 8 + indexed;
+    } else if (D == 128 && plan.form == FORM_NARROW) {   // wide E4M3 blocks: keys in one array
+        kernel = a.fast ? (ranged ? attn_narrow_kernel<D, SRC_CONTIG, D == 128> : attn_narrow_kernel<D, SRC_CONTIG, false>)
+                        : (ranged ? attn_narrow_kernel<D, SRC_TWO, D == 128> : attn_narrow_kernel<D, SRC_TWO, false>);
+        lds_bytes = 2u * 2 * KT * D * sizeof(bf16_t);
+        which = 10 + 2 * a.fast + ranged;
     } else if constexpr (D == 128) {
         static constexpr Kernel kernels[8] = {attn_kvcache_kernel<D, false, false, false>, attn_kvcache_kernel<D, false, false, true>,
                                               attn_kvcache_kernel<D, false, true, false>, attn_kvcache_kernel<D, false, true, true>,
@@ -1548,7 +1593,7 @@ int launch_attention(regione_ctx* ctx, AttnArgs a, bool keep_ranges) {
         kernel = kernels[which];
         lds_bytes = share ? AttnTile<D, true>::LDS_BYTES : AttnTile<D, false>::LDS_BYTES;
     } else {
-        static constexpr Kernel kernels[3] = {attn_narrow_kernel<D, SRC_CONTIG>, attn_narrow_kernel<D, SRC_TWO>, attn_narrow_kernel<D, SRC_INDEXED>};
+        static constexpr Kernel kernels[3] = {attn_narrow_kernel<D, SRC_CONTIG, false>, attn_narrow_kernel<D, SRC_TWO, false>, attn_narrow_kernel<D, SRC_INDEXED, false>};
         which = source == SRC_CONTIG && !a.fast ? SRC_TWO : source;
         kernel = kernels[which];
         lds_bytes = 2u * 2 * KT * D * sizeof(bf16_t);

@@ -2,10 +2,13 @@
 blocks per wave, in one key range and in several), 128-query tiles whose two wave groups take a range each or one in turns, and 256-query tiles, unsplit and
 in even ranges; query and key counts around the tiles' edges, the place where the cache rows begin inside a tile, every key source.  The oracle
 is float32 attention on the same bf16 inputs."""
+import numpy as np
 import pytest
 import torch
 
+from gpu_util import block_to_device, dev
 from paper_2510_25590_amd import binding as rg
+from paper_2510_25590_amd import inputs
 from test_gpu_attention_ranges import _reference
 
 pytestmark = pytest.mark.gpu
@@ -64,3 +67,31 @@ def test_forced_ranges(splits):
     """One range and odd numbers are taken by the wave groups in turns, even numbers a range to each group; the last ones are short or empty."""
     for n_keys in (128 * splits + 1, 128 * splits + 129, 2000):
         _call(2, 128, 150, 50, n_keys - 50, "indexed", splits)
+
+
+@pytest.mark.parametrize("n_txt,n_img", [(528, 400), (17, 240), (300, 1717)])
+def test_wide_8bit_block(n_txt, n_img):
+    """A double-stream E4M3 block above width 1024 keeps its key ranges: even ones, equal ones, one range in 256-query tiles."""
+    heads, d, mlp, n = 24, 128, 256, n_txt + n_img
+    hidden = heads * d
+    rng = np.random.default_rng(n)
+    streams = [inputs.stream_weights(rng, hidden, mlp, "double", "bf16", std=0.02) for _ in range(2)]
+    ctx = rg.Context(hidden, heads, d, mlp, n, 16)
+    bw, keep = block_to_device(streams, "double", ctx)
+    w8 = rg.BlockWeightsFp8()
+    held = []
+    for name, s in (("txt", streams[0]), ("img", streams[1])):
+        w, k = rg.make_stream_weights_fp8(ctx, {key: dev(v, "bf16") for key, v in s.items() if key.startswith("w_")})
+        setattr(w8, name, w)
+        held.append(k)
+    h = dev(inputs.bf16_round(rng.standard_normal((n, hidden)).astype(np.float32)), "bf16")
+    slots = torch.arange(n, dtype=torch.int32, device="cuda")
+    kc, vc = (torch.zeros((n, heads, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    taps = {"q": torch.zeros((n, hidden), dtype=torch.bfloat16, device="cuda"), "attn": torch.zeros((n, hidden), dtype=torch.bfloat16, device="cuda")}
+    out = torch.empty((n, hidden), dtype=torch.bfloat16, device="cuda")
+    rg.regione_block_forward_fp8(ctx, bw, w8, rg.BLOCK_DOUBLE, h, out, rg.BF16, n, n_txt, slots, 0, kc, vc, n, rg.FLAG_STORE, rg.make_fp8_taps(taps))
+    torch.cuda.synchronize()
+    ctx.close()
+    want, got = _reference(taps["q"].view(n, heads, d), kc, vc, d), taps["attn"].view(n, heads, d).float()
+    assert float((got - want).norm() / want.norm()) <= 2.0 ** -8
+    assert float((got - want).abs().max()) <= 2.0 ** -7 * float(vc.float().abs().max())
