@@ -252,6 +252,14 @@ int lane_join(regione_ctx* ctx) {
     RG_HIP(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0));
     return REGIONE_OK;
 }
+// Fork and join cost 10 to 40 us of events and leave the second group waiting; what they buy is that the text group's products fill the last round of the
+// image group's.  That pays where the work is large and the text rows few.  us, two lanes -> one: width 3072, 2048 image + 512 text rows 908 -> 896,
+// 100 + 512 402 -> 391, but 8192 + 512 2440 -> 2453, 2 x (2048 + 400) 1367 -> 1407, 800 + 100 344 -> 348, 512 + 32 290 -> 285; width 1024, 8192 + 500 601 -> 604, 800 + 60
+// 115 -> 106; width 256, 512 + 32 93 -> 54, 8192 + 500 341 -> 333.
+bool lanes_pay(int n_txt, int n_img, int hidden, int mlp) {
+    const double products = static_cast<double>(n_txt + n_img) * hidden * (4.0 * hidden + 2.0 * mlp);
+    return n_txt > 0 && n_img > 0 && 6 * static_cast<int64_t>(n_txt) <= n_txt + n_img && products >= 9e10;
+}
 // While alive, launches through the context go to the side lane: its stream and the upper half of the K-split workspace
 // (the main lane is left the lower half for the same time by LaneHalf).
 struct LaneSwap {
@@ -392,10 +400,10 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
     }
 
     // Text and image rows of a double-stream block go through different weights: until the attention joins them, and
-    // again after it, the two groups are independent, so the text group runs on the context's second lane and the
+    // again after it, the two groups are independent, so the text group may run on the context's second lane and the
     // workgroups of both fill the chip together (each group alone leaves part of its last round of tiles empty).
     // (the 8-bit form keeps one lane: its groups share the workspace of the codes)
-    const bool two_lanes = groups[0].n > 0 && groups[1].n > 0 && !ctx->prof_on && !w8;
+    const bool two_lanes = lanes_pay(groups[0].n, groups[1].n, H, M) && !ctx->prof_on && !w8;
     if (w8 && (rc = ensure_fp8_workspace(ctx)) != REGIONE_OK) return rc;
     // copy of an intermediate into the caller's tap (8-bit form only), rows of the group at their place
     auto tap = [&](void* dst, const void* src, size_t row0, size_t rows, size_t row_bytes) -> int {
