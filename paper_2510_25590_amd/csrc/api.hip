@@ -422,9 +422,7 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
         const char* hin = static_cast<const char*>(h_in) + static_cast<size_t>(g.r0) * H * h_elem;
         char* u = ctx->u + static_cast<size_t>(g.r0) * H * es;
         const regione_stream_weights_fp8* g8 = w8 ? (&g == &groups[0] ? &w8->txt : &w8->img) : nullptr;
-        if (g8) rc = rg_layernorm_mod_fp8(ctx, hin, h_f32, g.n, H, g.w->shift1, g.w->scale1, ctx->q8, ctx->q8_scale);
-        else rc = rg_layernorm_mod(ctx, hin, h_f32, g.n, H, g.w->shift1, g.w->scale1, u);
-        if (rc != REGIONE_OK) return rc;
+        if (g8 && (rc = rg_layernorm_mod_fp8(ctx, hin, h_f32, g.n, H, g.w->shift1, g.w->scale1, ctx->q8, ctx->q8_scale)) != REGIONE_OK) return rc;
         if (g8 && taps && ((rc = tap(taps->u1_codes, ctx->q8, g.r0, g.n, H)) != REGIONE_OK || (rc = tap(taps->u1_scale, ctx->q8_scale, g.r0, g.n, 4)) != REGIONE_OK)) return rc;
         GemmEpilogue ep = {};
         ep.kind = EPI_QKV; ep.hidden = H;
@@ -441,11 +439,11 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
             rc = rg_gemm_fp8(ctx, ctx->q8, H, static_cast<const uint8_t*>(g8->w_1), g.n, 3 * H + M, H, ep);
         } else if (dbl) {
             ep.bias = g.w->b_qkv;
-            rc = rg_gemm(ctx, u, H, g.w->w_qkv, g.n, 3 * H, H, ep);
+            rc = rg_layernorm_gemm(ctx, hin, h_f32, g.w->shift1, g.w->scale1, u, g.w->w_qkv, g.n, 3 * H, H, ep);
         } else {
             ep.bias = g.w->b_1; ep.act = REGIONE_ACT_GELU_TANH;
             ep.y = ctx->a + static_cast<size_t>(g.r0) * lda_attn * es; ep.ldy = lda_attn; ep.y_col0 = H; ep.y_f32 = ctx->f32;
-            rc = rg_gemm(ctx, u, H, g.w->w_1, g.n, 3 * H + M, H, ep);
+            rc = rg_layernorm_gemm(ctx, hin, h_f32, g.w->shift1, g.w->scale1, u, g.w->w_1, g.n, 3 * H + M, H, ep);
         }
         if (rc != REGIONE_OK) return rc;
         // extras: normalised and rotated queries and keys, in place where the projection wrote them (bf16 contexts only)
@@ -529,8 +527,7 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
             continue;
         }
         if ((rc = rg_gemm(ctx, a, H, g.w->w_o, g.n, H, H, ep)) != REGIONE_OK) return rc;
-        if ((rc = rg_layernorm_mod(ctx, h1, 1, g.n, H, g.w->shift2, g.w->scale2, u)) != REGIONE_OK) return rc;
-        if ((rc = rg_gemm(ctx, u, H, g.w->w_1, g.n, M, H, up)) != REGIONE_OK) return rc;
+        if ((rc = rg_layernorm_gemm(ctx, h1, 1, g.w->shift2, g.w->scale2, u, g.w->w_1, g.n, M, H, up)) != REGIONE_OK) return rc;
         if ((rc = rg_gemm(ctx, m, M, g.w->w_2, g.n, H, M, dn)) != REGIONE_OK) return rc;
     }
     if (two_lanes && (rc = lane_join(ctx)) != REGIONE_OK) return rc;

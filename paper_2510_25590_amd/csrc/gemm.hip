@@ -5,10 +5,10 @@
 //
 // The packed layout: block (n/32, k/16) is 64 lanes x 16 bytes, lane l holding W[32*(n/32) + l%32][16*(k/16) + 8*(l/32) .. +8].
 // The tile kernels (gemm_pp.h) copy such blocks whole into LDS and read the columns of a fragment from there; the kernel
-// for results of at most 64 columns (below) reads them as they lie.
+// for few rows and for results of at most 64 columns (gemm_small.h) reads them as they lie.
 #include "gemm_epilogue.h"
+#include "gemm_small.h"
 #include "gemm_tiles.h"
-#include <type_traits>
 
 namespace {
 
@@ -157,70 +157,28 @@ GemmPlan plan_gemm(regione_ctx* ctx, int m, int n, int k, bool fp8) {
     return p;
 }
 
-// Results of at most 64 columns (the velocity head: hidden -> latent channels): a workgroup owns 32 rows x 32 columns,
-// its sixteen waves split K, fragments come straight from global memory (A rows as the MFMA's row operand, the packed
-// weights as they lie), the partial tiles meet in LDS and are added in wave order, and the epilogue runs on the sums.
-// Such a launch is a chain of memory round trips, not arithmetic: with K over sixteen waves a wave has all its loads
-// in flight at once (four waves per workgroup, twelve round trips each: 25 us at 820 x 64 x 3072 inside the step,
-// slower than the general kernel's K split + merge launch, 15 + 5 us).
-// KIND: EPI_PLAIN, or EPI_VELOCITY (the fresh region step's velocity cache, Euler update and latent merge).
-constexpr int kSkinnyWaves = 16, kSkinnyColumns = 64;
-template <int KIND>
-__global__ void __launch_bounds__(kSkinnyWaves * 64)
-gemm_skinny_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ Wp, int M, int N, int K, GemmEpilogue ep) {
-    constexpr int LDR = 32;                      // row stride of a partial tile in LDS
-    __shared__ float red[kSkinnyWaves][32 * LDR];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int l32 = lane & 31, lh = lane >> 5;
-    const int m0 = blockIdx.x * 32, nb = blockIdx.y;
-    const int steps = K >> 4, per = (steps + kSkinnyWaves - 1) / kSkinnyWaves;
-    const int s0 = wave * per;
-    const int s1 = s0 + per < steps ? s0 + per : steps;
-    int row = m0 + l32;
-    row = row < M ? row : M - 1;                 // rows past the end repeat the last one; their sums are not stored
-    const bf16_t* ap = A + static_cast<int64_t>(row) * lda + 8 * lh;
-    const bf16_t* wp = Wp + (static_cast<int64_t>(nb) * steps * 64 + lane) * 8;
-    f32x16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    // all loads of a chunk of ten K-steps are issued before its first MFMA: one memory round trip per chunk
-    constexpr int CH = 10;
-    for (int base = s0; base < s1; base += CH) {
-        bf16x8 a[CH], w[CH];
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const int sidx = base + i < s1 ? base + i : s1 - 1;     // past the end: a valid address, the product is dropped below
-            a[i] = *reinterpret_cast<const bf16x8*>(ap + sidx * 16);
-            w[i] = *reinterpret_cast<const bf16x8*>(wp + static_cast<int64_t>(sidx) * 512);
-        }
-#pragma unroll
-        for (int i = 0; i < CH; ++i)
-            if (base + i < s1) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], w[i], acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) red[wave][(8 * (r >> 2) + 4 * lh + (r & 3)) * LDR + l32] = acc[r];
-    __syncthreads();
-    {
-        const int i = threadIdx.x;               // 32 x 32 sums, one per thread
-        const int rr = i >> 5, cc = i & 31;
-        const int at = rr * LDR + cc;
-        float sum = red[0][at];
-#pragma unroll
-        for (int w = 1; w < kSkinnyWaves; ++w) sum += red[w][at];
-        const int grow = m0 + rr, gcol = nb * 32 + cc;
-        if (grow < M && gcol < N) epilogue_store<KIND>(ep, grow, grow, gcol, sum, ep.bias ? ep.bias[gcol] : 0.f, 1.f);
-    }
+// Which products the kernel of 16-row tiles takes (gemm_small.h), and in tiles of how many columns; 0: the tile kernels.  Its workgroups hold a CU each, and
+// every row tile reads all weights from L2 again: it wins where one round of 256 workgroups does.  Times in us, tile kernels -> 32 / 64 columns, where
+// a call by itself takes 4.4: rows x columns x K 544 x 256 x 1024 6.9 -> 5.7 / 4.4, 64 x 3072 x 1024 6.9 -> 5.8 / 4.7, 100 x 3072 x 1024 7.0 -> 7.8 / 7.0 (336
+// workgroups), 820 x 768 x 256 4.6 -> 7.2 / 5.3; 100 x 1024 x 5120 10.6 -> 9.5 / 11.4, 160 x 1024 x 5120 10.5 -> 16.8 / 11.5; 1 x 3072 x 12288 15.9 -> 16.1 / 23.7.
+// Narrow results (at most 64 columns: the velocity head) all go there: 820 x 64 x 3072 13.3 -> 6.4 / 8.0 against a kernel of 32 x 32 tiles, 2560 rows 14.4 -> 11.7
+// / 8.1, 8704 rows 44 -> 28 / 23.
+// After a LayerNorm (k <= 1024) a launch of about 3.5 us goes away as well, which pays for a second round, as K <= 256 does; 838 x 768 x 256 after a LayerNorm in
+// three rounds took 10.9 where LayerNorm and tile kernel take 9.3, 838 x 1024 in four 16.3 for 9.5.
+constexpr int kNarrowColumns = 64;
+int small_columns(int m, int n, int k, bool after_ln) {
+    const int64_t row_tiles = (m + 15) / 16, wgs32 = row_tiles * ((n + 31) / 32), wgs64 = row_tiles * ((n + 63) / 64);
+    if (row_tiles > 65535) return 0;
+    if (n <= kNarrowColumns) return wgs32 <= 256 ? 32 : 64;
+    if (k > 5120) return 0;
+    if (wgs32 <= 256) return 32;
+    const int64_t most = k <= 256 || after_ln ? 512 : 256;
+    return k <= 3072 && wgs64 <= most ? 64 : 0;
 }
-
-template <int KIND>
-int launch_gemm_skinny(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, const GemmEpilogue& ep) {
-    hipLaunchKernelGGL((gemm_skinny_kernel<KIND>), dim3(static_cast<unsigned>((m + 31) / 32), static_cast<unsigned>((n + 31) / 32)), dim3(kSkinnyWaves * 64), 0, ctx->stream,
-                       a, lda, wp, m, n, k, ep);
-    RG_LAUNCH_CHECK();
-    return REGIONE_OK;
+// ... unless a comparison forces a plan of the tile kernels
+int small_columns(const regione_ctx* ctx, int m, int n, int k, bool after_ln = false) {
+    return ctx->gemm_force_tn == 0 && ctx->gemm_force_splits == 0 ? small_columns(m, n, k, after_ln) : 0;
 }
-// the shapes the small-N kernel takes: narrow results, unless a comparison forces a plan of the general kernels
-bool skinny_shape(const regione_ctx* ctx, int n) { return n <= kSkinnyColumns && ctx->gemm_force_tn == 0 && ctx->gemm_force_splits == 0; }
 
 // the wide epilogue needs every eight-column group whole (n % 8, checked by the caller) and every touched row 16-byte aligned
 bool wide_epilogue_ok(const GemmEpilogue& ep, int n) {
@@ -265,7 +223,7 @@ int rg_gemm_velocity(regione_ctx* ctx, const void* a_any, int lda, const void* w
     ep.vec_ok = (n % 8 == 0) && wide_epilogue_ok(ep, n);
     const bf16_t* a = static_cast<const bf16_t*>(a_any);
     const bf16_t* wp = static_cast<const bf16_t*>(wp_any);
-    if (skinny_shape(ctx, n)) return launch_gemm_skinny<EPI_VELOCITY>(ctx, a, lda, wp, m, n, k, ep);
+    if (const int columns = small_columns(ctx, m, n, k)) return gemm_small(ctx, a, lda, wp, m, n, k, columns, ep);
     // The plan of the product alone: the sums are then those of rg_gemm bit for bit.  Tile 222 with one K split for all such heads took
     // (us, kernel before the two-group ones / 222 / now; hidden 3072): 820 x 128 14.1 / 19.3 / 10.6, 36 x 256 11.4 / 16.7 / 9.0, 8704 x 1024 122 / 139 / 60.
     // Odd widths (see the epilogue): 8704 x 65 22 / 28 / 27, 8704 x 100 23.5 / - / 27, 4096 x 65 16.5 / - / 17.3, 2048 x 66 15.4 / - / 12.4.
@@ -283,8 +241,21 @@ int rg_gemm(regione_ctx* ctx, const void* a_any, int lda, const void* wp_any, in
     ProfScope prof(ctx, REGIONE_PROF_GEMM);
     GemmEpilogue ep = ep_in;
     ep.vec_ok = (n % 8 == 0) && wide_epilogue_ok(ep, n);
-    if (ep.kind == EPI_PLAIN && skinny_shape(ctx, n)) return launch_gemm_skinny<EPI_PLAIN>(ctx, a, lda, wp, m, n, k, ep);
+    if (const int columns = small_columns(ctx, m, n, k)) return gemm_small(ctx, a, lda, wp, m, n, k, columns, ep);
     return gemm_tile(ctx, plan_gemm(ctx, m, n, k, false), a, lda, wp, m, n, k, ep);
+}
+
+int rg_layernorm_gemm(regione_ctx* ctx, const void* h, int h_f32, const float* shift, const float* scale, void* u, const void* wp, int m, int n, int k, const GemmEpilogue& ep_in) {
+    if (m <= 0 || n <= 0) return REGIONE_OK;
+    const int columns = !ctx->f32 && k <= 1024 && (k % BK) == 0 && rg_aligned16(h) && rg_aligned16(wp) && rg_aligned16(shift) && rg_aligned16(scale) ? small_columns(ctx, m, n, k, true) : 0;
+    if (columns && (ep_in.kind == EPI_PLAIN || ep_in.kind == EPI_QKV)) {
+        ProfScope prof(ctx, REGIONE_PROF_GEMM);
+        GemmEpilogue ep = ep_in;
+        ep.vec_ok = (n % 8 == 0) && wide_epilogue_ok(ep, n);
+        return gemm_small_ln(ctx, h, h_f32, shift, scale, static_cast<const bf16_t*>(wp), m, n, k, columns, ep);
+    }
+    if (int rc = rg_layernorm_mod(ctx, h, h_f32, m, k, shift, scale, u)) return rc;
+    return rg_gemm(ctx, u, k, wp, m, n, k, ep_in);
 }
 
 extern "C" int64_t regione_packed_weight_elems(int32_t n, int32_t k) {
@@ -325,7 +296,7 @@ extern "C" int regione_gemm_plan_host(int32_t m, int32_t n, int32_t k, int32_t k
     const bool fp8 = kind == REGIONE_GEMM_E4M3;
     if (k % (fp8 ? 2 * BK : BK)) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "gemm_plan: k=%d must be a multiple of %d", k, fp8 ? 2 * BK : BK);
     GemmPlan p = {0, 1};
-    if (fp8 || n > kSkinnyColumns) p = choose_plan(m, n, fp8 ? k / 2 : k, fp8, static_cast<size_t>(workspace_bytes));
+    if (fp8 || !small_columns(m, n, k, false)) p = choose_plan(m, n, fp8 ? k / 2 : k, fp8, static_cast<size_t>(workspace_bytes));
     *tile = p.tile;
     *k_splits = p.splits;
     return REGIONE_OK;

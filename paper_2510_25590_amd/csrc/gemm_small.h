@@ -1,0 +1,151 @@
+// Products of few rows, and results of at most 64 columns (the velocity head): launches that are chains of memory latencies rather than arithmetic.
+//
+// A workgroup owns 16 rows x 32 or 64 columns; its eight waves split K, request all their fragments (activation rows as they lie, the packed
+// weights as they lie) before the first MFMA, and meet in LDS, where the sums are formed in wave order.  16x16x32 MFMAs with the weights as the
+// first operand, as in the tile kernels, so that a lane holds eight consecutive columns of a row and their epilogue serves here too.
+// A product that follows a LayerNorm takes the rows before it: the waves normalise the tile's rows into LDS while the weights are on their way, one
+// launch and one trip through memory less.
+// Which products come here, and what they took before: small_columns (gemm.hip).  In a block of width 256 and 36 rows the launch of a LayerNorm and that of
+// its product took 3.4 + 5.4 us, one launch now 3.7; two such blocks with everything around them 85 -> 62 us.
+#pragma once
+#include "gemm_epilogue.h"
+#include "layernorm_row.h"
+
+namespace {
+
+constexpr int kSmallWaves = 8, kSmallRows = 16;
+constexpr int kLnColumns = 1024;         // longest row that is normalised here
+enum { LN_NONE = 0, LN_BF16 = 1, LN_F32 = 2 };
+
+template <int CF> struct SmallTile {
+    static constexpr int CHUNK = CF == 2 ? 12 : 6;              // K-steps of 32 whose loads are in flight together
+    static constexpr unsigned SUM_BYTES = kSmallWaves * CF * 1024u;  // the waves' partial tiles
+};
+__host__ __device__ constexpr unsigned ln_row_bytes(int k) { return static_cast<unsigned>(k) * 2u + 16u; }   // 16 bytes on: the rows of a fragment start in different banks
+
+template <int CF, int KIND, int LN>
+__global__ void __launch_bounds__(kSmallWaves * 64) __attribute__((amdgpu_waves_per_eu(2)))
+gemm_small_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict__ Wp, int M, int N, int K,
+                  const float* __restrict__ shift, const float* __restrict__ scale, GemmEpilogue ep) {
+    constexpr int CHUNK = SmallTile<CF>::CHUNK;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, quad = lane >> 4;
+    const int n0 = blockIdx.x * (16 * CF), m0 = blockIdx.y * kSmallRows;
+    const int steps = K >> 5, per = (steps + kSmallWaves - 1) / kSmallWaves;
+    const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
+
+    // weight fragment 2 b + jl of a lane: column 8*(l16/4) + 4*jl + l16%4 of the tile's block b (see gemm_epilogue16)
+    const int n_blocks = (N + 31) >> 5;
+    const bf16_t* wp[CF / 2];
+#pragma unroll
+    for (int b = 0; b < CF / 2; ++b) {
+        int nb = (n0 >> 5) + b;
+        nb = nb < n_blocks ? nb : n_blocks - 1;                 // blocks past N repeat the last one; their sums are not stored
+        wp[b] = Wp + ((static_cast<int64_t>(nb) * (K >> 4) + (quad >> 1)) * 64 + (quad & 1) * 32 + 8 * (l16 >> 2) + (l16 & 3)) * 8;
+    }
+    int row = m0 + l16;
+    row = row < M ? row : M - 1;                                // rows past the end repeat the last one
+    const bf16_t* ap = LN == LN_NONE ? static_cast<const bf16_t*>(A) + static_cast<int64_t>(row) * lda + 8 * quad : nullptr;
+    const unsigned a_lds = SmallTile<CF>::SUM_BYTES + static_cast<unsigned>(l16) * ln_row_bytes(K) + 16u * quad;
+
+    f32x4 acc[1][CF];
+#pragma unroll
+    for (int j = 0; j < CF; ++j) acc[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 a[CHUNK], w[CHUNK][CF];
+    auto load_w = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < CHUNK; ++i)
+            if (base + i < s1) {
+#pragma unroll
+                for (int j = 0; j < CF; ++j) w[i][j] = *reinterpret_cast<const bf16x8*>(wp[j >> 1] + static_cast<int64_t>(base + i) * 1024 + (j & 1) * 32);
+            }
+    };
+    auto load_a = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < CHUNK; ++i)
+            if (base + i < s1) {
+                if (LN == LN_NONE) a[i] = *reinterpret_cast<const bf16x8*>(ap + (base + i) * 32);
+                else a[i] = *reinterpret_cast<const bf16x8*>(lds + a_lds + static_cast<unsigned>(base + i) * 64u);
+            }
+    };
+    if (LN != LN_NONE) {
+        load_w(s0);
+#pragma unroll
+        for (int r = 0; r < kSmallRows / kSmallWaves; ++r) {
+            const int lr = wave * (kSmallRows / kSmallWaves) + r;
+            int hr = m0 + lr;
+            hr = hr < M ? hr : M - 1;
+            unsigned char* to = lds + SmallTile<CF>::SUM_BYTES + static_cast<unsigned>(lr) * ln_row_bytes(K);
+            auto put = [&](int g, const ln_bf16x8& o) { *reinterpret_cast<ln_bf16x8*>(to + g * 16) = o; };
+            if (LN == LN_BF16) layernorm_row<bf16_t, kLnColumns / 512>(static_cast<const bf16_t*>(A) + static_cast<int64_t>(hr) * lda, K, shift, scale, put);
+            else layernorm_row<float, kLnColumns / 512>(static_cast<const float*>(A) + static_cast<int64_t>(hr) * lda, K, shift, scale, put);
+        }
+        __syncthreads();
+    }
+    for (int base = s0; base < s1; base += CHUNK) {
+        if (LN == LN_NONE || base > s0) load_w(base);
+        load_a(base);
+#pragma unroll
+        for (int i = 0; i < CHUNK; ++i)
+            if (base + i < s1) {
+#pragma unroll
+                for (int j = 0; j < CF; ++j) acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i][j], a[i], acc[0][j], 0, 0, 0);
+            }
+    }
+    f32x4* sums = reinterpret_cast<f32x4*>(lds) + lane;
+#pragma unroll
+    for (int j = 0; j < CF; ++j) sums[(wave * CF + j) * 64] = acc[0][j];
+    __syncthreads();
+    if (wave >= CF / 2) return;
+    // wave b finishes block b of 32 columns
+#pragma unroll
+    for (int b = 0; b < CF / 2; ++b)
+        if (wave == b) {
+#pragma unroll
+            for (int jl = 0; jl < 2; ++jl) {
+                f32x4 s = sums[(2 * b + jl) * 64];
+#pragma unroll
+                for (int v = 1; v < kSmallWaves; ++v) s += sums[(v * CF + 2 * b + jl) * 64];
+                acc[0][2 * b + jl] = s;
+            }
+        }
+    if (wave == 0) gemm_epilogue16_pair<KIND, false, 0, 1, 1, CF, 0>(acc, M, N, m0, n0, ep);
+    if constexpr (CF >= 4) { if (wave == 1) gemm_epilogue16_pair<KIND, false, 0, 1, 1, CF, 1>(acc, M, N, m0, n0, ep); }
+}
+
+template <int CF, int KIND, int LN>
+int launch_small(regione_ctx* ctx, const void* a, int lda, const bf16_t* wp, int m, int n, int k, const float* shift, const float* scale, const GemmEpilogue& ep) {
+    const unsigned bytes = SmallTile<CF>::SUM_BYTES + (LN == LN_NONE ? 0u : kSmallRows * ln_row_bytes(k));
+    static_assert(SmallTile<4>::SUM_BYTES + kSmallRows * ln_row_bytes(kLnColumns) <= 65536u + 16384u, "a CU holds a workgroup, mostly two");
+    hipLaunchKernelGGL((gemm_small_kernel<CF, KIND, LN>), dim3(static_cast<unsigned>((n + 16 * CF - 1) / (16 * CF)), static_cast<unsigned>((m + kSmallRows - 1) / kSmallRows)), dim3(kSmallWaves * 64), bytes,
+                       ctx->stream, a, lda, wp, m, n, k, shift, scale, ep);
+    RG_LAUNCH_CHECK();
+    return REGIONE_OK;
+}
+template <int CF, int LN>
+int launch_small_kind(regione_ctx* ctx, const void* a, int lda, const bf16_t* wp, int m, int n, int k, const float* shift, const float* scale, const GemmEpilogue& ep) {
+    if (ep.kind == EPI_QKV) return launch_small<CF, EPI_QKV, LN>(ctx, a, lda, wp, m, n, k, shift, scale, ep);
+    if (ep.kind == EPI_PLAIN) return launch_small<CF, EPI_PLAIN, LN>(ctx, a, lda, wp, m, n, k, shift, scale, ep);
+    if constexpr (LN == LN_NONE) {
+        if (ep.kind == EPI_VELOCITY) return launch_small<CF, EPI_VELOCITY, LN>(ctx, a, lda, wp, m, n, k, shift, scale, ep);
+        return launch_small<CF, EPI_RESID, LN>(ctx, a, lda, wp, m, n, k, shift, scale, ep);
+    }
+    RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm_small: epilogue kind %d", ep.kind);
+}
+
+// tiles of 16 rows x `columns` (32 or 64); every epilogue kind
+int gemm_small(regione_ctx* ctx, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, int columns, const GemmEpilogue& ep) {
+    if ((m + kSmallRows - 1) / kSmallRows > 65535) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "gemm_small: %d rows", m);
+    return columns == 32 ? launch_small_kind<2, LN_NONE>(ctx, a, lda, wp, m, n, k, nullptr, nullptr, ep) : launch_small_kind<4, LN_NONE>(ctx, a, lda, wp, m, n, k, nullptr, nullptr, ep);
+}
+
+// the product of layernorm_mod(h), rows h of k <= 1024 values (bf16 or float32, 16-byte aligned like shift and scale); QKV and plain epilogues
+int gemm_small_ln(regione_ctx* ctx, const void* h, int h_f32, const float* shift, const float* scale, const bf16_t* wp, int m, int n, int k, int columns, const GemmEpilogue& ep) {
+    if (k > kLnColumns || (m + kSmallRows - 1) / kSmallRows > 65535) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "gemm_small_ln: %d rows of %d", m, k);
+    if (h_f32) return columns == 32 ? launch_small_kind<2, LN_F32>(ctx, h, k, wp, m, n, k, shift, scale, ep) : launch_small_kind<4, LN_F32>(ctx, h, k, wp, m, n, k, shift, scale, ep);
+    return columns == 32 ? launch_small_kind<2, LN_BF16>(ctx, h, k, wp, m, n, k, shift, scale, ep) : launch_small_kind<4, LN_BF16>(ctx, h, k, wp, m, n, k, shift, scale, ep);
+}
+
+}  // namespace
