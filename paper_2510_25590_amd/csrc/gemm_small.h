@@ -78,7 +78,7 @@ gemm_small_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict_
             int hr = m0 + lr;
             hr = hr < M ? hr : M - 1;
             unsigned char* to = lds + SmallTile<CF>::SUM_BYTES + static_cast<unsigned>(lr) * ln_row_bytes(K);
-            auto put = [&](int g, const ln_bf16x8& o) { *reinterpret_cast<ln_bf16x8*>(to + g * 16) = o; };
+            auto put = [&](int g, const float (&o)[8]) { st8<bf16_t>(reinterpret_cast<bf16_t*>(to + g * 16), o); };
             if (LN == LN_BF16) layernorm_row<bf16_t, kLnColumns / 512>(static_cast<const bf16_t*>(A) + static_cast<int64_t>(hr) * lda, K, shift, scale, put);
             else layernorm_row<float, kLnColumns / 512>(static_cast<const float*>(A) + static_cast<int64_t>(hr) * lda, K, shift, scale, put);
         }

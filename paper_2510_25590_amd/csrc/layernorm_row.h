@@ -20,7 +20,7 @@ template <> __device__ __forceinline__ void ld8<float>(const float* p, float (&v
     for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
 }
 
-// put(group, values): takes the eight bf16 results of columns 8*group..8*group+7
+// put(group, values): takes the eight results, as float32, of columns 8*group..8*group+7
 template <typename T, int MAXV, typename Put>
 __device__ __forceinline__ void layernorm_row(const T* hr, int hidden, const float* shift, const float* scale, Put put) {
     const int lane = threadIdx.x & 63;
@@ -64,16 +64,28 @@ __device__ __forceinline__ void layernorm_row(const T* hr, int hidden, const flo
     for (int i = 0; i < MAXV; ++i) {
         const int g = lane + 64 * i;
         if (g < groups) {
-            ln_bf16x8 o;
+            float o[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float y = (x[i][e] - mean) * rstd;
                 y = y * (1.f + (scale ? sc[i][e] : 0.f)) + (shift ? sh[i][e] : 0.f);
-                o[e] = static_cast<__bf16>(y);
+                o[e] = y;
             }
             put(g, o);
         }
     }
+}
+
+template <typename T> __device__ __forceinline__ void st8(T* p, const float (&v)[8]);
+template <> __device__ __forceinline__ void st8<bf16_t>(bf16_t* p, const float (&v)[8]) {
+    ln_bf16x8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(v[e]);
+    *reinterpret_cast<ln_bf16x8*>(p) = o;
+}
+template <> __device__ __forceinline__ void st8<float>(float* p, const float (&v)[8]) {
+    *reinterpret_cast<ln_f32x4*>(p) = ln_f32x4{v[0], v[1], v[2], v[3]};
+    *reinterpret_cast<ln_f32x4*>(p + 4) = ln_f32x4{v[4], v[5], v[6], v[7]};
 }
 
 }  // namespace
