@@ -1531,7 +1531,7 @@ AttnPlan plan_attention(const regione_ctx* ctx, int source, int n_q, int n_keys,
         for (int form = FORM_SPLIT; form <= FORM_SHARE; ++form) {
             const int pairs = form == FORM_SPLIT && plan.splits % 2 == 0 ? plan.splits / 2 : plan.splits;
             const double t = form_time<128>(form, source == SRC_INDEXED, n_q, heads, n_tiles, pairs);
-            if (t >= (plan.form == FORM_NARROW ? 0.9 : 1.0) * best) continue;   // two models: a tenth apart before the wide forms are taken
+            if (t >= best - (plan.form == FORM_NARROW ? 1.75 : 0.0)) continue;   // the two models' fixed costs agree to about 1.75 us
             best = t;
             plan.form = form;
         }
