@@ -1,0 +1,80 @@
+"""Scores whose weights outgrow the reference of the exponentials, which is the maximum of a range's first keys: later keys that score 3 to 5 above
+those (weights of 20 to 150, whose sum meets the limit where no single weight does), a reference that moves with every tile and one that moves late, in every
+kind of workgroup.  The oracle is float32 attention on the same bf16 inputs; and keys like the first kind take no longer than level ones."""
+import pytest
+import torch
+
+from paper_2510_25590_amd import binding as rg
+from test_gpu_attention_ranges import _reference
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(heads, d, n_q, n_keys, lift):
+    """q, k, v; lift: float32 [n_keys], what is added to every query's score of a key (of spread 0.5)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_q + n_keys)
+    r = lambda n: torch.empty((n, heads, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    q, k, v = r(n_q) * 0.5, r(n_keys), r(n_keys)
+    q[..., 0] = 8.0
+    k[..., 0] = (lift * d ** 0.5 / 8.0).to(torch.bfloat16)[:, None]
+    return q, k, v
+
+
+def _runner(heads, d, q, k, v, source):
+    """A call of the attention on these tensors; n_fresh of its keys come as fresh rows, the others as cache rows."""
+    n_q, n_keys = q.shape[0], k.shape[0]
+    n_fresh = 0 if source == "one" else min(n_keys // 3, 333)
+    kf, vf, kc, vc = k[:n_fresh].contiguous(), v[:n_fresh].contiguous(), k[n_fresh:].contiguous(), v[n_fresh:].contiguous()
+    idx = torch.arange(n_keys - n_fresh, dtype=torch.int32, device="cuda") if source == "indexed" else None
+    ctx = rg.Context(heads * d, heads, d, 256, max(n_q, 2048), 16)
+    out = torch.full((n_q + 1, heads, d), 7.0, dtype=torch.bfloat16, device="cuda")
+
+    def call():
+        rg.regione_attn_kvcache(ctx, q, n_q, kf if n_fresh else None, vf if n_fresh else None, n_fresh, kc, vc, n_keys - n_fresh, idx,
+                                n_keys - n_fresh if source == "indexed" else 0, heads, d, 0.0, out)
+    return ctx, out, call
+
+
+@pytest.mark.parametrize("lift", ["step", "climb", "late"])
+@pytest.mark.parametrize("source", ["one", "two", "indexed"])
+@pytest.mark.parametrize("heads,d,n_q,n_keys", [
+    (24, 128, 820, 4097), (8, 128, 6500, 700), (24, 128, 2500, 1217), (24, 128, 3100, 2050), (24, 128, 64, 513), (5, 128, 100, 1023), (24, 128, 17, 3500), (4, 64, 36, 544), (4, 64, 820, 2000),
+])
+def test_scores_above_the_reference(lift, source, heads, d, n_q, n_keys):
+    at = torch.arange(n_keys, device="cuda").float()
+    lifts = {"step": 4.0 * (at >= 64), "climb": 2.0 * (at // 64).clamp(max=12), "late": 12.0 * (at >= n_keys * 0.9)}
+    q, k, v = _inputs(heads, d, n_q, n_keys, lifts[lift])
+    ctx, out, call = _runner(heads, d, q, k, v, source)
+    call()
+    torch.cuda.synchronize()
+    ctx.close()
+    want, got = _reference(q, k, v, d), out.float()
+    assert torch.all(got[n_q] == 7.0)
+    # weights and result in bf16: 2^-9 relative each, on rows whose weights add up to one
+    assert float((got[:n_q] - want).norm() / want.norm()) <= 2.0 ** -8
+    assert float((got[:n_q] - want).abs().max()) <= 2.0 ** -7 * float(v.float().abs().max())
+
+
+@pytest.mark.parametrize("heads,n_q,n_keys,source", [(24, 2560, 8704, "one"), (24, 1332, 8704, "indexed")])
+def test_time_does_not_depend_on_the_scores(heads, n_q, n_keys, source):
+    """Forming every weight twice took 1.3 times as long; the same work differs by a few percent at most (clock, one rescale)."""
+    d, calls, held = 128, [], []
+    for step in (0.0, 4.0):
+        q, k, v = _inputs(heads, d, n_q, n_keys, step * (torch.arange(n_keys, device="cuda") >= 64))
+        held.append(_runner(heads, d, q, k, v, source))
+        calls.append(held[-1][2])
+    best = [1e9, 1e9]
+    for _ in range(8):
+        for i, call in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            call()
+            a.record()
+            for _ in range(10):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b))
+    for ctx, _, _ in held:
+        ctx.close()
+    assert best[1] <= 1.12 * best[0], best
