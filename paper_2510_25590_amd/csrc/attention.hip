@@ -518,7 +518,7 @@ template <int D> struct DealtTile {
     static constexpr int COPY_ROWS = 64 / CPR;              // rows per copy
     static constexpr unsigned BLOCK = 32u * D * 2u;         // K (or V) rows of a block
     static constexpr unsigned WAVE = 2u * BLOCK;            // a wave's LDS: K block, V block; its accumulators at the end
-    static constexpr unsigned ML_BASE = 8u * WAVE;          // reference and sum of every wave and query; before, the first tile's maxima
+    static constexpr unsigned ML_BASE = 8u * WAVE;          // reference and sum of every wave and query
     static constexpr unsigned LIST_BASE = ML_BASE + 8u * 32u * 8u;
     static_assert(WAVE == DB * 4096u, "a wave's accumulators fit where its blocks were");
 };
@@ -626,7 +626,6 @@ attn_dealt_kernel(AttnArgs a) {
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[db] = zero;
     float m_run = m_floor, l_run = 0.f;
-    float* maxima = reinterpret_cast<float*>(lds + T::ML_BASE);
 
     // S^T = K Q^T of block i, whose K rows leave LDS for registers first, so that the next block's can follow
 #define RG_DEALT_SCORES(I, AHEAD, NTH)                                                                                  \
@@ -658,19 +657,18 @@ attn_dealt_kernel(AttnArgs a) {
         }                                                                                                   \
         psum = sum_[0] + sum_[1];                                                                           \
     }
-    // One reference for the range, the maximum of its first 64 keys (waves 0 and 1 hold their scores); see the kernel below for what a
-    // reference is and when it moves.
+    // A wave's reference is the maximum of its own first block; see the kernel below for what a reference is and when it moves.  The weight of a reference's
+    // key is exactly one, so eight references of 32 keys each round fewer of the large weights than one of 64 keys for all waves did, and no wave waits for another
+    // one's scores.  Error against 64 bits (2-norm; scores of spread 2), shared reference -> own ones: 95 queries on 759 keys by index list, 24 heads of 128,
+    // 2.31e-3 -> 2.11e-3 (key ranges of four waves 2.03e-3), 100 x 3000, 8 heads of 128, 2.21e-3 -> 1.89e-3, 36 x 544, 4 heads of 64, 2.24e-3 -> 2.05e-3 (2.09e-3).
+    // us: 64 x 513, 24 heads, 9.85 -> 8.45; 100 x 3000 14.5 -> 13.75; 36 x 544 6.4 -> 6.0.
     if (mine > 0) {
         wait_async_copies<0>();
         RG_DEALT_SCORES(0, mine > 1, 1)
+        RG_DEALT_MAX(mx)
+        m_run = fmaxf(m_floor, mx);
     }
-    if (wave < 2) {
-        float mx = m_floor;
-        if (mine > 0) { RG_DEALT_MAX(m) mx = m; }
-        if (lh == 0) maxima[wave * 32 + l32] = mx;
-    }
-    __syncthreads();
-    m_run = fmaxf(m_floor, fmaxf(maxima[l32], maxima[32 + l32]));
+    if (INDEXED) __syncthreads();                                    // the list is complete
     for (int i = 0; i < mine; ++i) {
         bf16x8 pf[2];
         float psum;
@@ -720,7 +718,6 @@ attn_dealt_kernel(AttnArgs a) {
 
     // ---- the waves' results meet in LDS: every wave sums its share of the accumulators over all waves
     l_run = sum_across_halves(l_run);
-    __syncthreads();                                                 // the first tile's maxima have been read
     float2* ml = reinterpret_cast<float2*>(lds + T::ML_BASE);
     if (lh == 0) ml[wave * 32 + l32] = float2{m_run, l_run};
     f32x4* mine4 = reinterpret_cast<f32x4*>(lds + wave * T::WAVE) + lane;

@@ -51,6 +51,34 @@ def test_few_queries(source, heads, d, n_q, n_keys):
     _call(heads, d, n_q, n_fresh, n_keys - n_fresh, source)
 
 
+@pytest.mark.parametrize("indexed", [False, True])
+@pytest.mark.parametrize("heads,d", [(24, 128), (4, 64)])
+def test_few_queries_weigh_their_largest_scores_exactly(heads, d, indexed):
+    """Keys of a workgroup that deals them to its waves, 32 a wave: one key in every wave's block carries all the block's weight.  Each is its wave's reference, whose
+    weight is exactly one; the waves are joined in float32, so that only the result's own rounding is left."""
+    n_q, n_keys = 40, 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    r = lambda *s: torch.empty(s, dtype=torch.float32, device="cuda").normal_(generator=g)
+    q, k, v = torch.zeros((n_q, heads, d), device="cuda"), torch.zeros((n_keys, heads, d), device="cuda"), r(n_keys, heads, d).to(torch.bfloat16)
+    q[..., 0], q[..., 1] = 8.0, 1.0 + r(n_q, heads).abs()
+    k[..., 0] = -100.0 * d ** 0.5 / 8.0                   # scores of -100 ...
+    live = torch.arange(8, device="cuda") * 32 + torch.randint(0, 32, (8,), generator=g, device="cuda")
+    k[live, :, 0], k[live, :, 1] = 0.0, r(8, heads) * d ** 0.5      # ... but for one key in 32, of about -5 to 5
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    out = torch.empty_like(q)
+    ctx = rg.Context(heads * d, heads, d, 256, 512, 16)
+    idx = torch.arange(n_keys, dtype=torch.int32, device="cuda") if indexed else None
+    rg.regione_attn_kvcache(ctx, q, n_q, None, None, 0, k, v, n_keys, idx, n_keys if indexed else 0, heads, d, 0.0, out)
+    torch.cuda.synchronize()
+    ctx.close()
+    p = torch.softmax(torch.einsum("qhd,khd->hqk", q.cpu().double(), k.cpu().double()) / d ** 0.5, dim=-1)
+    want = torch.einsum("hqk,khd->qhd", p, v.cpu().double())
+    sizes = torch.einsum("hqk,khd->qhd", p, v.cpu().double().abs())
+    # the nearest bf16 value, or where float32 scores (up to 20, scaled), exponentials and sums of eight terms (2^-17 of the terms' sizes) reach across a tie its neighbour
+    assert torch.all((out.cpu().double() - want).abs() <= (want.to(torch.bfloat16).double() - want).abs() + 2.0 ** -16 * sizes)
+
+
 @pytest.mark.parametrize("source", ["one", "two", "indexed"])
 @pytest.mark.parametrize("heads,n_q,n_keys", [
     (24, 257, 1500), (24, 820, 4097),                    # 128-query tiles, ranges in pairs
