@@ -22,6 +22,12 @@ template <int CF> struct SmallTile {
     static constexpr unsigned SUM_BYTES = kSmallWaves * CF * 1024u;  // the waves' partial tiles
 };
 __host__ __device__ constexpr unsigned ln_row_bytes(int k) { return static_cast<unsigned>(k) * 2u + 16u; }   // 16 bytes on: the rows of a fragment start in different banks
+// The partial tiles take the place of the normalised rows, which all waves have read by then.
+template <int CF> constexpr unsigned small_lds_bytes(bool ln, int k) {
+    const unsigned rows = ln ? kSmallRows * ln_row_bytes(k) : 0u;
+    return rows > SmallTile<CF>::SUM_BYTES ? rows : SmallTile<CF>::SUM_BYTES;
+}
+static_assert(small_lds_bytes<4>(true, kLnColumns) <= 65536u, "what a launch may ask for without hipFuncSetAttribute");
 
 template <int CF, int KIND, int LN>
 __global__ void __launch_bounds__(kSmallWaves * 64) __attribute__((amdgpu_waves_per_eu(2)))
@@ -48,7 +54,7 @@ gemm_small_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict_
     int row = m0 + l16;
     row = row < M ? row : M - 1;                                // rows past the end repeat the last one
     const bf16_t* ap = LN == LN_NONE ? static_cast<const bf16_t*>(A) + static_cast<int64_t>(row) * lda + 8 * quad : nullptr;
-    const unsigned a_lds = SmallTile<CF>::SUM_BYTES + static_cast<unsigned>(l16) * ln_row_bytes(K) + 16u * quad;
+    const unsigned a_lds = static_cast<unsigned>(l16) * ln_row_bytes(K) + 16u * quad;
 
     f32x4 acc[1][CF];
 #pragma unroll
@@ -77,7 +83,7 @@ gemm_small_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict_
             const int lr = wave * (kSmallRows / kSmallWaves) + r;
             int hr = m0 + lr;
             hr = hr < M ? hr : M - 1;
-            unsigned char* to = lds + SmallTile<CF>::SUM_BYTES + static_cast<unsigned>(lr) * ln_row_bytes(K);
+            unsigned char* to = lds + static_cast<unsigned>(lr) * ln_row_bytes(K);
             auto put = [&](int g, const float (&o)[8]) { st8<bf16_t>(reinterpret_cast<bf16_t*>(to + g * 16), o); };
             if (LN == LN_BF16) layernorm_row<bf16_t, kLnColumns / 512>(static_cast<const bf16_t*>(A) + static_cast<int64_t>(hr) * lda, K, shift, scale, put);
             else layernorm_row<float, kLnColumns / 512>(static_cast<const float*>(A) + static_cast<int64_t>(hr) * lda, K, shift, scale, put);
@@ -94,6 +100,7 @@ gemm_small_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict_
                 for (int j = 0; j < CF; ++j) acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i][j], a[i], acc[0][j], 0, 0, 0);
             }
     }
+    if (LN != LN_NONE) __syncthreads();                         // the rows have been read
     f32x4* sums = reinterpret_cast<f32x4*>(lds) + lane;
 #pragma unroll
     for (int j = 0; j < CF; ++j) sums[(wave * CF + j) * 64] = acc[0][j];
@@ -117,10 +124,8 @@ gemm_small_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict_
 
 template <int CF, int KIND, int LN>
 int launch_small(regione_ctx* ctx, const void* a, int lda, const bf16_t* wp, int m, int n, int k, const float* shift, const float* scale, const GemmEpilogue& ep) {
-    const unsigned bytes = SmallTile<CF>::SUM_BYTES + (LN == LN_NONE ? 0u : kSmallRows * ln_row_bytes(k));
-    static_assert(SmallTile<4>::SUM_BYTES + kSmallRows * ln_row_bytes(kLnColumns) <= 65536u + 16384u, "a CU holds a workgroup, mostly two");
-    hipLaunchKernelGGL((gemm_small_kernel<CF, KIND, LN>), dim3(static_cast<unsigned>((n + 16 * CF - 1) / (16 * CF)), static_cast<unsigned>((m + kSmallRows - 1) / kSmallRows)), dim3(kSmallWaves * 64), bytes,
-                       ctx->stream, a, lda, wp, m, n, k, shift, scale, ep);
+    hipLaunchKernelGGL((gemm_small_kernel<CF, KIND, LN>), dim3(static_cast<unsigned>((n + 16 * CF - 1) / (16 * CF)), static_cast<unsigned>((m + kSmallRows - 1) / kSmallRows)), dim3(kSmallWaves * 64),
+                       small_lds_bytes<CF>(LN != LN_NONE, k), ctx->stream, a, lda, wp, m, n, k, shift, scale, ep);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }
