@@ -24,6 +24,10 @@ int regione_tune_gemm(regione_ctx* ctx, int32_t wave_tile_blocks, int32_t k_spli
 enum { REGIONE_GEMM_BF16 = 0, REGIONE_GEMM_E4M3 = 1 };
 int regione_gemm_plan_host(int32_t m, int32_t n, int32_t k, int32_t kind, int64_t workspace_bytes, int32_t* tile, int32_t* k_splits);
 
+/* How many lanes (streams) the projections of a double-stream block run on with that many fresh text and image rows: 2 where the two groups run
+ * side by side, else 1.  While per-class timing is on, and in the 8-bit form, it is always one.  A pure host function. */
+int regione_block_lanes_host(int32_t n_txt, int32_t n_img, int32_t hidden, int32_t mlp, int32_t compute_dtype, int32_t* lanes);
+
 /* Tuning knob for experiments: forces the number of key-range splits (1..32) of every later
  * attention call of this context; 0 restores the automatic choice. */
 int regione_tune_attention(regione_ctx* ctx, int32_t key_splits);

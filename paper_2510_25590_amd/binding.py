@@ -31,7 +31,7 @@ EXPORTS = (
     "regione_quantize_rows_fp8", "regione_pack_weight_fp8", "regione_linear_fp8", "regione_mfma_peak_probe",
     "regione_partition_static", "regione_rel_decision_host", "regione_rel_update_host", "regione_fresh_slots", "regione_time_bias",
     "regione_euler_rows", "regione_gather_pair", "regione_scatter_pair", "regione_velocity_head", "regione_region_step",
-    "regione_block_forward_fp8", "regione_gemm_plan_host",
+    "regione_block_forward_fp8", "regione_gemm_plan_host", "regione_block_lanes_host",
 )
 STEP_FULL, STEP_FULL_STORE, STEP_REGION = 0, 1, 2
 PROF_NAMES = ("partition", "rows", "layernorm", "gemm", "attention", "velocity")
@@ -151,6 +151,7 @@ def lib() -> C.CDLL:
             "regione_pack_weight_fp8": [vp, vp, i32, i32, vp],
             "regione_linear_fp8": [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp],
             "regione_tune_gemm": [vp, i32, i32],
+            "regione_block_lanes_host": [i32, i32, i32, i32, i32, C.POINTER(i32)],
             "regione_tune_attention": [vp, i32],
             "regione_attention_plan": [vp, i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)],
             "regione_layernorm": [vp, vp, i32, i32, i32, vp, vp, vp],
@@ -509,6 +510,13 @@ def regione_gemm_plan_host(m: int, n: int, k: int, kind: int, workspace_bytes: i
     tile, splits = C.c_int32(0), C.c_int32(0)
     _check(lib().regione_gemm_plan_host(m, n, k, kind, C.c_int64(workspace_bytes), C.byref(tile), C.byref(splits)))
     return tile.value, splits.value
+
+
+def regione_block_lanes_host(n_txt: int, n_img: int, hidden: int, mlp: int, compute_dtype: int = BF16) -> int:
+    """Lanes that the projections of a double-stream block run on."""
+    lanes = C.c_int32(0)
+    _check(lib().regione_block_lanes_host(n_txt, n_img, hidden, mlp, compute_dtype, C.byref(lanes)))
+    return lanes.value
 
 
 def regione_tune_attention(ctx, key_splits: int):

@@ -253,12 +253,15 @@ int lane_join(regione_ctx* ctx) {
     return REGIONE_OK;
 }
 // Fork and join cost 10 to 40 us of events and leave the second group waiting; what they buy is that the text group's products fill the last round of the
-// image group's.  That pays where the work is large and the text rows few.  us, two lanes -> one: width 3072, 2048 image + 512 text rows 908 -> 896,
+// image group's.  That pays where the work is large and, in bf16, the text rows few.  us, two lanes -> one (image + text rows): bf16, width 3072, 2048 + 512 908 -> 896,
 // 100 + 512 402 -> 391, but 8192 + 512 2440 -> 2453, 2 x (2048 + 400) 1367 -> 1407, 800 + 100 344 -> 348, 512 + 32 290 -> 285; width 1024, 8192 + 500 601 -> 604, 800 + 60
-// 115 -> 106; width 256, 512 + 32 93 -> 54, 8192 + 500 341 -> 333.
-bool lanes_pay(int n_txt, int n_img, int hidden, int mlp) {
+// 115 -> 106; width 256, 512 + 32 93 -> 54, 8192 + 500 341 -> 333.  float32, whose products take some ten times as long: width 3072, 256 + 32 1030 -> 1073, 820 + 512 3631 -> 3634;
+// width 1024, 4096 + 500 2543 -> 2590, 820 + 512 654 -> 674, 256 + 32 189 -> 190; width 512, 2048 + 512 516 -> 530, 512 + 64 138 -> 133; width 256, 8000 + 100
+// 1143 -> 1143, 1000 + 64 123 -> 114.
+bool lanes_pay(int n_txt, int n_img, int hidden, int mlp, bool f32) {
     const double products = static_cast<double>(n_txt + n_img) * hidden * (4.0 * hidden + 2.0 * mlp);
-    return n_txt > 0 && n_img > 0 && 6 * static_cast<int64_t>(n_txt) <= n_txt + n_img && products >= 9e10;
+    if (n_txt <= 0 || n_img <= 0) return false;
+    return f32 ? products >= 8e9 : 6 * static_cast<int64_t>(n_txt) <= n_txt + n_img && products >= 9e10;
 }
 // While alive, launches through the context go to the side lane: its stream and the upper half of the K-split workspace
 // (the main lane is left the lower half for the same time by LaneHalf).
@@ -403,7 +406,7 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
     // again after it, the two groups are independent, so the text group may run on the context's second lane and the
     // workgroups of both fill the chip together (each group alone leaves part of its last round of tiles empty).
     // (the 8-bit form keeps one lane: its groups share the workspace of the codes)
-    const bool two_lanes = lanes_pay(groups[0].n, groups[1].n, H, M) && !ctx->prof_on && !w8;
+    const bool two_lanes = lanes_pay(groups[0].n, groups[1].n, H, M, ctx->f32) && !ctx->prof_on && !w8;
     if (w8 && (rc = ensure_fp8_workspace(ctx)) != REGIONE_OK) return rc;
     // copy of an intermediate into the caller's tap (8-bit form only), rows of the group at their place
     auto tap = [&](void* dst, const void* src, size_t row0, size_t rows, size_t row_bytes) -> int {
@@ -531,6 +534,14 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
         if ((rc = rg_gemm(ctx, m, M, g.w->w_2, g.n, H, M, dn)) != REGIONE_OK) return rc;
     }
     if (two_lanes && (rc = lane_join(ctx)) != REGIONE_OK) return rc;
+    return REGIONE_OK;
+}
+
+extern "C" int regione_block_lanes_host(int32_t n_txt, int32_t n_img, int32_t hidden, int32_t mlp, int32_t compute_dtype, int32_t* lanes) {
+    if (!lanes) RG_FAIL(REGIONE_ERR_INVALID_ARG, "block_lanes: null argument");
+    if (n_txt < 0 || n_img < 0 || hidden <= 0 || mlp <= 0) RG_FAIL(REGIONE_ERR_INVALID_ARG, "block_lanes: n_txt=%d n_img=%d hidden=%d mlp=%d", n_txt, n_img, hidden, mlp);
+    if (compute_dtype != REGIONE_BF16 && compute_dtype != REGIONE_FP32) RG_FAIL(REGIONE_ERR_INVALID_ARG, "block_lanes: compute_dtype %d", compute_dtype);
+    *lanes = lanes_pay(n_txt, n_img, hidden, mlp, compute_dtype == REGIONE_FP32) ? 2 : 1;
     return REGIONE_OK;
 }
 
