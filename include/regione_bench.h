@@ -41,6 +41,20 @@ enum { REGIONE_KEYS_CONTIGUOUS = 0, REGIONE_KEYS_TWO = 1, REGIONE_KEYS_INDEXED =
 int regione_attention_plan(regione_ctx* ctx, int32_t n_q, int32_t n_keys, int32_t heads, int32_t d, int32_t source, int32_t* key_splits,
                            int32_t* range_tiles, int32_t* whole_query_tiles);
 
+/* Tuning knob for experiments: the kind of workgroups and of key ranges that later attention calls of this context take where they have such; 0 leaves either to the
+ * library.  form: workgroups of 128 or 256 queries in two wave groups (head dimension 128), of 32 queries whose keys are dealt to the waves, or of 128 queries in
+ * waves that run freely (head dimension 64).  ranges: equal ones, even ones for all query tiles, or even ones behind unsplit query tiles (the last two for head dimension
+ * 128).  A number of equal ranges that regione_tune_attention forces is taken in that form.  The ranges of wide 8-bit blocks stay as they are. */
+enum { REGIONE_ATTN_TILES_128 = 1, REGIONE_ATTN_TILES_256 = 2, REGIONE_ATTN_DEALT = 3, REGIONE_ATTN_FREE = 4 };
+enum { REGIONE_RANGES_EQUAL = 1, REGIONE_RANGES_EVEN = 2, REGIONE_RANGES_EVEN_BEHIND = 3 };
+int regione_tune_attention_form(regione_ctx* ctx, int32_t form, int32_t ranges);
+
+/* The kind of workgroups (REGIONE_ATTN_*) that regione_attention_plan's call gets, with its *key_splits and *range_tiles.  One more source: the keys of an 8-bit
+ * double-stream block wider than 1024, whose key ranges are chosen apart.  Host only. */
+enum { REGIONE_KEYS_WIDE_8BIT = 3 };
+int regione_attention_workgroups(regione_ctx* ctx, int32_t n_q, int32_t n_keys, int32_t heads, int32_t d, int32_t source, int32_t* form, int32_t* key_splits,
+                                 int32_t* range_tiles);
+
 /* Per-kernel-class timing for benchmarks (not part of the method).  While enabled, every
  * kernel launch group of the context is bracketed by a HIP event pair on its stream (at most
  * 8192 pairs between two reads).  regione_profile_read waits for the stream, adds the elapsed

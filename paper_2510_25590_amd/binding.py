@@ -32,6 +32,7 @@ EXPORTS = (
     "regione_partition_static", "regione_rel_decision_host", "regione_rel_update_host", "regione_fresh_slots", "regione_time_bias",
     "regione_euler_rows", "regione_gather_pair", "regione_scatter_pair", "regione_velocity_head", "regione_region_step",
     "regione_block_forward_fp8", "regione_gemm_plan_host", "regione_block_lanes_host",
+    "regione_tune_attention_form", "regione_attention_workgroups",
 )
 STEP_FULL, STEP_FULL_STORE, STEP_REGION = 0, 1, 2
 PROF_NAMES = ("partition", "rows", "layernorm", "gemm", "attention", "velocity")
@@ -153,6 +154,8 @@ def lib() -> C.CDLL:
             "regione_tune_gemm": [vp, i32, i32],
             "regione_block_lanes_host": [i32, i32, i32, i32, i32, C.POINTER(i32)],
             "regione_tune_attention": [vp, i32],
+            "regione_tune_attention_form": [vp, i32, i32],
+            "regione_attention_workgroups": [vp, i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)],
             "regione_attention_plan": [vp, i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)],
             "regione_layernorm": [vp, vp, i32, i32, i32, vp, vp, vp],
             "regione_cast": [vp, vp, i32, vp, i32, i64],
@@ -523,7 +526,20 @@ def regione_tune_attention(ctx, key_splits: int):
     _check(lib().regione_tune_attention(ctx.handle, key_splits))
 
 
-KEYS_CONTIGUOUS, KEYS_TWO, KEYS_INDEXED = 0, 1, 2
+KEYS_CONTIGUOUS, KEYS_TWO, KEYS_INDEXED, KEYS_WIDE_8BIT = 0, 1, 2, 3
+ATTN_TILES_128, ATTN_TILES_256, ATTN_DEALT, ATTN_FREE = 1, 2, 3, 4
+RANGES_EQUAL, RANGES_EVEN, RANGES_EVEN_BEHIND = 1, 2, 3
+
+
+def regione_tune_attention_form(ctx, form: int = 0, ranges: int = 0):
+    _check(lib().regione_tune_attention_form(ctx.handle, form, ranges))
+
+
+def regione_attention_workgroups(ctx, n_q: int, n_keys: int, heads: int, d: int, source: int = KEYS_CONTIGUOUS):
+    """(ATTN_* kind of workgroups, equal key ranges per query tile, key tiles of an even range or 0) of a bf16 attention."""
+    form, splits, tiles = C.c_int32(0), C.c_int32(0), C.c_int32(0)
+    _check(lib().regione_attention_workgroups(ctx.handle, n_q, n_keys, heads, d, source, C.byref(form), C.byref(splits), C.byref(tiles)))
+    return form.value, splits.value, tiles.value
 
 
 def regione_attention_plan(ctx, n_q: int, n_keys: int, heads: int, d: int, source: int = KEYS_CONTIGUOUS):

@@ -1355,6 +1355,8 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
 // the matrix cores would leave the vector units idle instead.  SPLIT and SHARE (head dimension 128): see AttnTile, one workgroup per CU.  DEALT:
 // few queries on not too many keys.
 enum { FORM_SPLIT = 0, FORM_SHARE = 1, FORM_DEALT = 2, FORM_NARROW = 3 };
+// what comparisons force (0: nothing): a form, as its number + 1, and which ranges of keys
+struct Forced { int form, ranges; bool allows(int f) const { return form == 0 || form == f + 1; } };
 int form_queries(int form) { return form == FORM_DEALT ? 32 : form == FORM_SHARE ? 256 : 128; }
 
 // `splits` equal key ranges per query tile (in SPLIT workgroups an even number of them goes in pairs, a range to each wave group), or (range > 0)
@@ -1467,8 +1469,8 @@ double even_time(int form, bool indexed, int n_q, int heads, int n_tiles, int q_
 // DEALT keeps the rows that an index list names in LDS
 bool dealt_fits(int source, int n_tiles, int wgs) { return source != SRC_INDEXED || (n_tiles + wgs - 1) / wgs * KT <= kDealtKeys; }
 
-// Head dimension 128: the fastest of the forms, equal or even ranges.
-AttnPlan plan_wide(int source, int n_q, int n_keys, int heads, size_t range_bytes, size_t part_bytes) {
+// Head dimension 128: the fastest of the forms, equal or even ranges; no ranges at all (splits 0) where nothing fits what is forced.
+AttnPlan plan_wide(int source, int n_q, int n_keys, int heads, size_t range_bytes, size_t part_bytes, Forced forced) {
     constexpr int D = 128;
     const bool indexed = source == SRC_INDEXED;
     const int n_tiles = (n_keys + KT - 1) / KT, tiles128 = (n_q + 127) / 128;
@@ -1477,11 +1479,12 @@ AttnPlan plan_wide(int source, int n_q, int n_keys, int heads, size_t range_byte
     // without them is 1.03 to 1.35 times faster there; of fewer queries or more keys, where the costs decide, it was up to 1.6 times (489 queries on 2363 keys,
     // 24 heads, 49 us, now 31).
     AttnPlan even = {};
-    if (source == SRC_CONTIG) even = plan_ranges<D>(source, n_q, n_keys, heads, 0, range_bytes);
+    if (source == SRC_CONTIG && forced.form == 0 && forced.ranges == 0) even = plan_ranges<D>(source, n_q, n_keys, heads, 0, range_bytes);
     const bool only_even = even.range > 0 && n_tiles <= 47 && n_q > 1408;
     AttnPlan plan = {};
     double best = 0.0;
-    for (int form = FORM_SPLIT; form <= FORM_DEALT && !only_even; ++form)
+    for (int form = FORM_SPLIT; form <= FORM_DEALT && !only_even; ++form) {
+        if (!forced.allows(form) || forced.ranges > REGIONE_RANGES_EQUAL) continue;
         for (int wgs = 1; wgs <= (form == FORM_SPLIT ? kMaxSplits / 2 : kMaxSplits); ++wgs) {
             if (wgs > 1 && (wgs * 2 > n_tiles || wgs * part_row_set > part_bytes)) break;
             if (form == FORM_DEALT && !dealt_fits(source, n_tiles, wgs)) continue;
@@ -1491,13 +1494,16 @@ AttnPlan plan_wide(int source, int n_q, int n_keys, int heads, size_t range_byte
             const int q_tiles = (n_q + form_queries(form) - 1) / form_queries(form);
             plan = {form, form == FORM_SPLIT && n_tiles > 1 ? 2 * wgs : wgs, 0, 0, q_tiles, tiles128};
         }
-    for (int form = FORM_SPLIT; form <= FORM_SHARE; ++form)
+    }
+    for (int form = FORM_SPLIT; form <= FORM_SHARE; ++form) {
+        if (!forced.allows(form) || forced.ranges == REGIONE_RANGES_EQUAL) continue;
         for (int pass = 0; pass < 2; ++pass) {   // with and without whole passes of unsplit query tiles in front
             const int qw = form_queries(form), q_tiles = (n_q + qw - 1) / qw;
             const int whole = heads % 8 == 0 ? q_tiles * heads / 256 : 0;
             if (pass > 0 && (whole == 0 || only_even)) break;
             const int tiles = only_even ? even.whole : pass == 0 ? 256 * whole / heads * (qw / 128) : 0;
             const int q_full = tiles / (qw / 128);
+            if (forced.ranges > 0 && forced.ranges != (q_full > 0 ? REGIONE_RANGES_EVEN_BEHIND : REGIONE_RANGES_EVEN)) continue;
             const int64_t units = static_cast<int64_t>(heads) * (q_tiles - q_full) * n_tiles;
             if (units <= 0 || units >= (1 << 30)) continue;
             int64_t range = (units + 255) / 256;
@@ -1511,15 +1517,25 @@ AttnPlan plan_wide(int source, int n_q, int n_keys, int heads, size_t range_byte
             best = t;
             plan = {form, 1, static_cast<int>(range), static_cast<int>(range_wgs), q_full, tiles};
         }
+    }
     return plan.splits > 0 ? plan : even;
 }
 
 // keep_ranges: see plan_ranges
 AttnPlan plan_attention(const regione_ctx* ctx, int source, int n_q, int n_keys, int heads, int d, bool keep_ranges) {
     const int n_tiles = (n_keys + KT - 1) / KT, forced = ctx->attn_force_splits;
-    if (d == 128 && !keep_ranges && forced == 0) return plan_wide(source, n_q, n_keys, heads, ctx->attn_range_bytes, ctx->attn_part_bytes);
+    const Forced asked = {ctx->attn_force_form, ctx->attn_force_ranges};
+    if (d == 128 && !keep_ranges && forced == 0) {
+        const AttnPlan plan = plan_wide(source, n_q, n_keys, heads, ctx->attn_range_bytes, ctx->attn_part_bytes, asked);
+        return plan.splits > 0 ? plan : plan_wide(source, n_q, n_keys, heads, ctx->attn_range_bytes, ctx->attn_part_bytes, {0, 0});
+    }
     AttnPlan plan = d == 64 ? plan_ranges<64>(source, n_q, n_keys, heads, forced, ctx->attn_range_bytes) : plan_ranges<128>(source, n_q, n_keys, heads, forced, ctx->attn_range_bytes);
-    if (forced > 0) return plan;
+    if (forced > 0) {   // that many equal ranges in the form asked for, if it has such workgroups
+        const int form = asked.form - 1;
+        if (form == FORM_DEALT ? dealt_fits(source, n_tiles, plan.splits) : d == 128 && (form == FORM_SPLIT || form == FORM_SHARE)) plan.form = form;
+        plan.q_full = (n_q + form_queries(plan.form) - 1) / form_queries(plan.form);
+        return plan;
+    }
     // the same ranges in another form, or (head dimension 64) other ranges in DEALT workgroups
     if (d == 128) {
         plan.form = source == SRC_CONTIG ? FORM_NARROW : FORM_SPLIT;
@@ -1532,8 +1548,8 @@ AttnPlan plan_attention(const regione_ctx* ctx, int source, int n_q, int n_keys,
             best = t;
             plan.form = form;
         }
-    } else if (static_cast<int64_t>(plan.whole) * heads <= 256) {
-        double best = range_time<64>(source, plan.whole, heads, n_q, n_tiles, plan.splits);
+    } else if (asked.allows(FORM_DEALT) && (asked.form > 0 || static_cast<int64_t>(plan.whole) * heads <= 256)) {
+        double best = asked.form > 0 ? DBL_MAX : range_time<64>(source, plan.whole, heads, n_q, n_tiles, plan.splits);
         for (int wgs = 1; wgs <= kMaxSplits && (wgs == 1 || (wgs * 2 <= n_tiles && wgs * sizeof(float) * n_q * heads * (64 + 4) <= ctx->attn_part_bytes)); ++wgs) {
             const double t = form_time<64>(FORM_DEALT, source == SRC_INDEXED, n_q, heads, n_tiles, wgs);
             if (t >= best || !dealt_fits(source, n_tiles, wgs)) continue;
@@ -1626,6 +1642,29 @@ extern "C" int regione_tune_attention(regione_ctx* ctx, int32_t key_splits) {
     if (!ctx) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_attention: null context");
     if (key_splits < 0 || key_splits > kMaxSplits) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_attention: key_splits=%d must be 0..32", key_splits);
     ctx->attn_force_splits = key_splits;
+    return REGIONE_OK;
+}
+
+extern "C" int regione_tune_attention_form(regione_ctx* ctx, int32_t form, int32_t ranges) {
+    static_assert(REGIONE_ATTN_TILES_128 == FORM_SPLIT + 1 && REGIONE_ATTN_TILES_256 == FORM_SHARE + 1 && REGIONE_ATTN_DEALT == FORM_DEALT + 1 && REGIONE_ATTN_FREE == FORM_NARROW + 1, "the same order");
+    if (!ctx) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_attention_form: null context");
+    if (form < 0 || form > REGIONE_ATTN_FREE || ranges < 0 || ranges > REGIONE_RANGES_EVEN_BEHIND) RG_FAIL(REGIONE_ERR_INVALID_ARG, "tune_attention_form: form %d, ranges %d", form, ranges);
+    ctx->attn_force_form = form;
+    ctx->attn_force_ranges = ranges;
+    return REGIONE_OK;
+}
+
+extern "C" int regione_attention_workgroups(regione_ctx* ctx, int32_t n_q, int32_t n_keys, int32_t heads, int32_t d, int32_t source, int32_t* form, int32_t* key_splits,
+                                            int32_t* range_tiles) {
+    if (!ctx || !form || !key_splits || !range_tiles) RG_FAIL(REGIONE_ERR_INVALID_ARG, "attention_workgroups: null argument");
+    if (n_q <= 0 || n_keys <= 0 || heads <= 0) RG_FAIL(REGIONE_ERR_INVALID_ARG, "attention_workgroups: n_q=%d n_keys=%d heads=%d", n_q, n_keys, heads);
+    if (ctx->f32 || (d != 64 && d != 128)) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "attention_workgroups: bf16 contexts and head dimensions of 64 or 128 (%d) only", d);
+    if (source < REGIONE_KEYS_CONTIGUOUS || source > REGIONE_KEYS_WIDE_8BIT) RG_FAIL(REGIONE_ERR_INVALID_ARG, "attention_workgroups: source %d", source);
+    const bool wide8 = source == REGIONE_KEYS_WIDE_8BIT;
+    const AttnPlan plan = plan_attention(ctx, wide8 ? SRC_CONTIG : source, n_q, n_keys, heads, d, wide8);
+    *form = plan.form + 1;
+    *key_splits = plan.splits;
+    *range_tiles = plan.range;
     return REGIONE_OK;
 }
 

@@ -50,7 +50,7 @@ struct regione_ctx {
     hipEvent_t ev_fork, ev_join;
     GemmPlanSlot gemm_plans[kGemmPlanSlots];
     int gemm_force_tn, gemm_force_splits;  // 0 = chosen per call
-    int attn_force_splits;  // 0 = chosen per call
+    int attn_force_splits, attn_force_form, attn_force_ranges;  // 0 = chosen per call
     // kernels that need more than 64 KiB of LDS have to be granted it once per device: one bit per kernel family and
     // instantiation that this context (one device) has already asked for
     uint32_t lds_grant_mask;

@@ -1,7 +1,7 @@
-"""The forms of attention workgroups at the sizes where each can go wrong: 32-query tiles that deal their keys to the waves (none, one, two and more
-blocks per wave, in one key range and in several), 128-query tiles whose two wave groups take a range each or one in turns, and 256-query tiles, unsplit and
-in even ranges; query and key counts around the tiles' edges, the place where the cache rows begin inside a tile, every key source.  The oracle
-is float32 attention on the same bf16 inputs."""
+"""The forms of attention workgroups at the sizes where each can go wrong, forced so that every call shows the form it names: 32-query tiles that deal their keys to
+the waves (none, one, two and more blocks per wave, in one key range and in several), 128-query tiles whose two wave groups take a range each or one in turns, and
+256-query tiles, unsplit and in even ranges; query and key counts around the tiles' edges, the place where the cache rows begin inside a tile, every key
+source.  The oracle is float32 attention on the same bf16 inputs."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,10 @@ from test_gpu_attention_ranges import _reference
 pytestmark = pytest.mark.gpu
 
 
-def _call(heads, d, n_q, n_fresh, n_cached, source, splits=0):
+KEYS = {"one": rg.KEYS_CONTIGUOUS, "two": rg.KEYS_TWO, "indexed": rg.KEYS_INDEXED}
+
+
+def _call(heads, d, n_q, n_fresh, n_cached, source, splits=0, form=0, ranges=0):
     g = torch.Generator(device="cuda")
     g.manual_seed(1000 * n_q + n_cached)
     r = lambda n: torch.empty((n, heads, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
@@ -23,6 +26,10 @@ def _call(heads, d, n_q, n_fresh, n_cached, source, splits=0):
     idx = torch.randperm(rows, generator=g, device="cuda")[:n_cached].int().contiguous() if source == "indexed" else None
     ctx = rg.Context(heads * d, heads, d, 256, max(n_q, 512), 16)
     rg.regione_tune_attention(ctx, splits)
+    rg.regione_tune_attention_form(ctx, form, ranges)
+    plan = rg.regione_attention_workgroups(ctx, n_q, n_fresh + n_cached, heads, d, KEYS[source])
+    if form:
+        assert plan[0] == form and (plan[2] > 0) == (ranges > rg.RANGES_EQUAL) and plan[1] == (splits or plan[1])
     outs = []
     for _ in range(2):
         out = torch.full((n_q + 1, heads, d), 7.0, dtype=torch.bfloat16, device="cuda")
@@ -39,16 +46,18 @@ def _call(heads, d, n_q, n_fresh, n_cached, source, splits=0):
     # weights and result in bf16: 2^-9 relative each, on rows whose weights add up to one
     assert float((got[:n_q] - want).norm() / want.norm()) <= 2.0 ** -8
     assert float((got[:n_q] - want).abs().max()) <= 2.0 ** -7 * float(v.float().abs().max())
+    return plan
+
+
+FEW = [(3, 128, 1, 1), (2, 64, 31, 32), (8, 128, 32, 33), (4, 64, 33, 65), (8, 128, 65, 257), (4, 64, 36, 544), (4, 64, 257, 575), (24, 128, 64, 513), (5, 128, 100, 1023),
+       (24, 128, 17, 3500), (4, 64, 40, 4100)]
 
 
 @pytest.mark.parametrize("source", ["one", "two", "indexed"])
-@pytest.mark.parametrize("heads,d,n_q,n_keys", [
-    (3, 128, 1, 1), (2, 64, 31, 32), (8, 128, 32, 33), (4, 64, 33, 65), (8, 128, 65, 257), (4, 64, 36, 544), (4, 64, 257, 575),
-    (24, 128, 64, 513), (5, 128, 100, 1023), (24, 128, 17, 3500), (4, 64, 40, 4100),
-])
-def test_few_queries(source, heads, d, n_q, n_keys):
+@pytest.mark.parametrize("heads,d,n_q,n_keys,splits", [(*c, s) for c in FEW for s in (0, 3) if 64 * 2 * s <= c[3] + 63])     # a forced range has two key tiles at least
+def test_few_queries(source, heads, d, n_q, n_keys, splits):
     n_fresh = 0 if source == "one" else min(n_q, n_keys // 2)
-    _call(heads, d, n_q, n_fresh, n_keys - n_fresh, source)
+    _call(heads, d, n_q, n_fresh, n_keys - n_fresh, source, splits, rg.ATTN_DEALT)
 
 
 @pytest.mark.parametrize("indexed", [False, True])
@@ -69,6 +78,8 @@ def test_few_queries_weigh_their_largest_scores_exactly(heads, d, indexed):
     out = torch.empty_like(q)
     ctx = rg.Context(heads * d, heads, d, 256, 512, 16)
     idx = torch.arange(n_keys, dtype=torch.int32, device="cuda") if indexed else None
+    rg.regione_tune_attention_form(ctx, rg.ATTN_DEALT)
+    assert rg.regione_attention_workgroups(ctx, n_q, n_keys, heads, d, KEYS["indexed" if indexed else "one"])[0] == rg.ATTN_DEALT
     rg.regione_attn_kvcache(ctx, q, n_q, None, None, 0, k, v, n_keys, idx, n_keys if indexed else 0, heads, d, 0.0, out)
     torch.cuda.synchronize()
     ctx.close()
@@ -80,21 +91,42 @@ def test_few_queries_weigh_their_largest_scores_exactly(heads, d, indexed):
 
 
 @pytest.mark.parametrize("source", ["one", "two", "indexed"])
-@pytest.mark.parametrize("heads,n_q,n_keys", [
-    (24, 257, 1500), (24, 820, 4097),                    # 128-query tiles, ranges in pairs
-    (24, 2500, 1217), (8, 6500, 700),                    # 256-query tiles, unsplit; the last one with a few rows
-    (24, 1400, 5001), (24, 3100, 2050),                  # ... in even ranges, alone and behind whole passes
+@pytest.mark.parametrize("heads,n_q,n_keys,splits,form,ranges", [
+    (24, 257, 1500, 4, rg.ATTN_TILES_128, rg.RANGES_EQUAL), (24, 820, 4097, 2, rg.ATTN_TILES_128, rg.RANGES_EQUAL),       # ranges in pairs
+    (24, 2500, 1217, 1, rg.ATTN_TILES_256, rg.RANGES_EQUAL), (8, 6500, 700, 1, rg.ATTN_TILES_256, rg.RANGES_EQUAL),       # unsplit; the last tile with a few rows
+    (24, 300, 2300, 3, rg.ATTN_TILES_256, rg.RANGES_EQUAL), (24, 100, 600, 4, rg.ATTN_TILES_256, rg.RANGES_EQUAL),        # equal ranges; the last ones short or empty
+    (24, 1400, 5001, 0, rg.ATTN_TILES_256, rg.RANGES_EVEN), (24, 1400, 5001, 0, rg.ATTN_TILES_128, rg.RANGES_EVEN),       # even ranges, alone ...
+    (24, 3100, 2050, 0, rg.ATTN_TILES_256, rg.RANGES_EVEN_BEHIND), (24, 3100, 2050, 0, rg.ATTN_TILES_128, rg.RANGES_EVEN_BEHIND),      # ... and behind whole passes
 ])
-def test_many_queries(source, heads, n_q, n_keys):
+def test_many_queries(source, heads, n_q, n_keys, splits, form, ranges):
     n_fresh = 0 if source == "one" else 333
-    _call(heads, 128, n_q, n_fresh, n_keys - n_fresh, source)
+    _call(heads, 128, n_q, n_fresh, n_keys - n_fresh, source, splits, form, ranges)
+
+
+@pytest.mark.parametrize("source", ["one", "two", "indexed"])
+@pytest.mark.parametrize("heads,d,n_q,n_keys", [(24, 128, 257, 1500), (24, 128, 1400, 5001), (24, 128, 3100, 2050), (4, 64, 36, 544), (4, 64, 1500, 3000), (8, 128, 100, 3000)])
+def test_own_choice(source, heads, d, n_q, n_keys):
+    """What the library takes by itself, and again after a form was forced and given back."""
+    n_fresh = 0 if source == "one" else 33
+    plan = _call(heads, d, n_q, n_fresh, n_keys - n_fresh, source)
+    ctx = rg.Context(heads * d, heads, d, 256, max(n_q, 512), 16)
+    for form, ranges in ((rg.ATTN_DEALT, 0), (rg.ATTN_TILES_256, rg.RANGES_EVEN), (rg.ATTN_FREE, rg.RANGES_EQUAL), (0, 0)):
+        rg.regione_tune_attention_form(ctx, form, ranges)
+        got = rg.regione_attention_workgroups(ctx, n_q, n_keys, heads, d, KEYS[source])
+    assert got == plan
+    for bad in ((-1, 0), (5, 0), (0, -1), (0, 4)):
+        with pytest.raises(rg.RegionEError):
+            rg.regione_tune_attention_form(ctx, *bad)
+    with pytest.raises(rg.RegionEError):
+        rg.regione_attention_workgroups(ctx, n_q, n_keys, heads, d, 4)
+    ctx.close()
 
 
 @pytest.mark.parametrize("splits", [1, 2, 3, 4, 7])
 def test_forced_ranges(splits):
     """One range and odd numbers are taken by the wave groups in turns, even numbers a range to each group; the last ones are short or empty."""
     for n_keys in (128 * splits + 1, 128 * splits + 129, 2000):
-        _call(2, 128, 150, 50, n_keys - 50, "indexed", splits)
+        _call(2, 128, 150, 50, n_keys - 50, "indexed", splits, rg.ATTN_TILES_128)
 
 
 @pytest.mark.parametrize("n_txt,n_img", [(528, 400), (17, 240), (300, 1717)])

@@ -12,12 +12,15 @@ pytestmark = pytest.mark.gpu
 BIG = 1e30      # two of them make a product beyond float32
 
 
-@pytest.mark.parametrize("heads,d,n_q,n_keys,splits", [
-    (2, 128, 130, 1000, 1), (2, 128, 130, 1000, 4), (2, 64, 130, 1000, 1), (2, 64, 130, 1000, 4), (3, 128, 40, 2111, 16),
-    (24, 128, 3000, 3000, 0),     # one whole pass of query tiles, even ranges behind it
+@pytest.mark.parametrize("heads,d,n_q,n_keys,splits,form", [
+    (2, 128, 130, 1000, 1, rg.ATTN_TILES_128), (2, 128, 130, 1000, 4, rg.ATTN_TILES_128), (2, 64, 130, 1000, 1, rg.ATTN_FREE), (2, 64, 130, 1000, 4, rg.ATTN_FREE),
+    (3, 128, 40, 2111, 16, rg.ATTN_TILES_128), (2, 128, 300, 1000, 1, rg.ATTN_TILES_256), (2, 128, 300, 1000, 4, rg.ATTN_TILES_256),
+    (2, 128, 130, 1000, 1, rg.ATTN_DEALT), (2, 128, 130, 1000, 4, rg.ATTN_DEALT), (2, 64, 130, 1000, 1, rg.ATTN_DEALT), (2, 64, 130, 1000, 4, rg.ATTN_DEALT),
+    (2, 128, 40, 200, 1, rg.ATTN_DEALT),                                                         # a block per wave, or none
+    (24, 128, 3000, 3000, 0, rg.ATTN_TILES_128), (24, 128, 3000, 3000, 0, rg.ATTN_TILES_256),    # whole passes of query tiles, even ranges behind them
 ])
 @pytest.mark.parametrize("kind", ["nan", "plus", "minus"])
-def test_nonfinite_scores(kind, heads, d, n_q, n_keys, splits):
+def test_nonfinite_scores(kind, heads, d, n_q, n_keys, splits, form):
     g = torch.Generator(device="cuda")
     g.manual_seed(n_q + d)
     r = lambda n: torch.empty((n, heads, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
@@ -39,6 +42,8 @@ def test_nonfinite_scores(kind, heads, d, n_q, n_keys, splits):
     assert torch.equal(want.isnan().any(-1), hit) and torch.equal(want.isnan().all(-1), hit)
     ctx = rg.Context(heads * d, heads, d, 256, max(n_q, 2048), 16)
     rg.regione_tune_attention(ctx, splits)
+    rg.regione_tune_attention_form(ctx, form, 0 if splits else rg.RANGES_EVEN_BEHIND)
+    assert rg.regione_attention_workgroups(ctx, n_q, n_keys, heads, d)[0] == form
     plan = rg.regione_attention_plan(ctx, n_q, n_keys, heads, d)
     assert plan[0] == splits if splits else plan[1] > 0 and plan[2] > 0
     out = torch.full((n_q + 1, heads, d), 7.0, dtype=torch.bfloat16, device="cuda")

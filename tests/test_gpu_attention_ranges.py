@@ -17,15 +17,16 @@ def _reference(q, k, v, d):
     return out
 
 
+@pytest.mark.parametrize("form", [rg.ATTN_TILES_128, rg.ATTN_TILES_256])
 @pytest.mark.parametrize("source", ["contiguous", "two", "indexed"])
 @pytest.mark.parametrize("heads,n_q,n_keys,whole,short", [
-    (24, 1409, 3001, 0, True),      # 0.56 of a pass, no query tile in front: ranges shorter than a query tile's keys
-    (8, 1461, 3001, 0, True),       # 0.19 of a pass: up to seven ranges meet in a query tile
-    (12, 5450, 2499, 0, False),     # heads not a multiple of the XCDs; a range longer than a query tile's keys, no whole pass
-    (8, 8700, 2497, 64, True),      # one whole pass, the rest in ranges
-    (24, 2900, 3001, 21, True),     # one whole pass that the heads do not divide
+    (24, 1409, 3001, 0, (False, True)),     # no query tile in front; ranges longer than a tile of 128 queries' keys, shorter than one of 256
+    (8, 1461, 3001, 0, (True, True)),       # 0.19 of a pass: many ranges meet in a query tile
+    (12, 5450, 2499, 0, (False, False)),    # heads not a multiple of the XCDs; a range longer than a query tile's keys, no whole pass
+    (8, 8700, 2497, 64, (True, True)),      # whole passes, the rest in ranges
+    (24, 2900, 3001, 21, (True, True)),     # ... that the heads do not divide
 ])
-def test_even_ranges(source, heads, n_q, n_keys, whole, short):
+def test_even_ranges(form, source, heads, n_q, n_keys, whole, short):
     d = 128
     g = torch.Generator(device="cuda")
     g.manual_seed(n_q)
@@ -36,8 +37,12 @@ def test_even_ranges(source, heads, n_q, n_keys, whole, short):
     idx = torch.arange(n_keys - n_fresh, dtype=torch.int32, device="cuda").flip(0).contiguous() if source == "indexed" else None
     kc, vc = k[n_fresh:].contiguous(), v[n_fresh:].contiguous()
     ctx = rg.Context(heads * d, heads, d, 256, max(n_q, 2048), 16)
-    splits, tiles, in_front = rg.regione_attention_plan(ctx, n_q, n_keys, heads, d)
-    assert (splits, in_front) == (1, whole) and tiles > 0 and (tiles < (n_keys + 63) // 64) == short      # even ranges, of the case's kind
+    keys = {"contiguous": rg.KEYS_CONTIGUOUS, "two": rg.KEYS_TWO, "indexed": rg.KEYS_INDEXED}[source]
+    rg.regione_tune_attention_form(ctx, form, rg.RANGES_EVEN_BEHIND if whole else rg.RANGES_EVEN)
+    splits, tiles, in_front = rg.regione_attention_plan(ctx, n_q, n_keys, heads, d, keys)
+    assert rg.regione_attention_workgroups(ctx, n_q, n_keys, heads, d, keys) == (form, 1, tiles)
+    # even ranges, of the case's kind; workgroups of 256 queries take the query tiles in front in pairs
+    assert (splits, in_front) == (1, whole if form == rg.ATTN_TILES_128 else whole // 2 * 2) and tiles > 0 and (tiles < (n_keys + 63) // 64) == short[form == rg.ATTN_TILES_256]
     outs = []
     for splits in (0, 0, 1):
         rg.regione_tune_attention(ctx, splits)
@@ -48,7 +53,6 @@ def test_even_ranges(source, heads, n_q, n_keys, whole, short):
         outs.append(out)
     ctx.close()
     assert torch.equal(outs[0], outs[1])                 # no order that depends on timing
-    assert not torch.equal(outs[0], outs[2])             # the ranges were used: unsplit sums differ in their last bits
     want = _reference(q, k, v, d)
     for out in outs[1:]:
         got = out.float()

@@ -21,7 +21,7 @@ def _inputs(heads, d, n_q, n_keys, lift):
     return q, k, v
 
 
-def _runner(heads, d, q, k, v, source):
+def _runner(heads, d, q, k, v, source, form=0, ranges=0):
     """A call of the attention on these tensors; n_fresh of its keys come as fresh rows, the others as cache rows."""
     n_q, n_keys = q.shape[0], k.shape[0]
     n_fresh = 0 if source == "one" else min(n_keys // 3, 333)
@@ -29,6 +29,10 @@ def _runner(heads, d, q, k, v, source):
     idx = torch.arange(n_keys - n_fresh, dtype=torch.int32, device="cuda") if source == "indexed" else None
     ctx = rg.Context(heads * d, heads, d, 256, max(n_q, 2048), 16)
     out = torch.full((n_q + 1, heads, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    rg.regione_tune_attention_form(ctx, form, ranges)
+    if form:
+        plan = rg.regione_attention_workgroups(ctx, n_q, n_keys, heads, d, {"one": rg.KEYS_CONTIGUOUS, "two": rg.KEYS_TWO, "indexed": rg.KEYS_INDEXED}[source])
+        assert plan[0] == form and (plan[2] > 0) == (ranges == rg.RANGES_EVEN)
 
     def call():
         rg.regione_attn_kvcache(ctx, q, n_q, kf if n_fresh else None, vf if n_fresh else None, n_fresh, kc, vc, n_keys - n_fresh, idx,
@@ -38,14 +42,17 @@ def _runner(heads, d, q, k, v, source):
 
 @pytest.mark.parametrize("lift", ["step", "climb", "late"])
 @pytest.mark.parametrize("source", ["one", "two", "indexed"])
-@pytest.mark.parametrize("heads,d,n_q,n_keys", [
-    (24, 128, 820, 4097), (8, 128, 6500, 700), (24, 128, 2500, 1217), (24, 128, 3100, 2050), (24, 128, 64, 513), (5, 128, 100, 1023), (24, 128, 17, 3500), (4, 64, 36, 544), (4, 64, 820, 2000),
+@pytest.mark.parametrize("heads,d,n_q,n_keys,form,ranges", [
+    (24, 128, 820, 4097, rg.ATTN_TILES_128, rg.RANGES_EQUAL), (24, 128, 820, 2050, rg.ATTN_TILES_128, rg.RANGES_EVEN),
+    (8, 128, 6500, 700, rg.ATTN_TILES_256, rg.RANGES_EQUAL), (24, 128, 2500, 1217, rg.ATTN_TILES_256, rg.RANGES_EQUAL), (24, 128, 1400, 2050, rg.ATTN_TILES_256, rg.RANGES_EVEN),
+    (24, 128, 64, 513, rg.ATTN_DEALT, 0), (5, 128, 100, 1023, rg.ATTN_DEALT, 0), (24, 128, 17, 3500, rg.ATTN_DEALT, 0), (4, 64, 36, 544, rg.ATTN_DEALT, 0),
+    (4, 64, 820, 2000, rg.ATTN_DEALT, 0), (4, 64, 820, 2000, rg.ATTN_FREE, 0),
 ])
-def test_scores_above_the_reference(lift, source, heads, d, n_q, n_keys):
+def test_scores_above_the_reference(lift, source, heads, d, n_q, n_keys, form, ranges):
     at = torch.arange(n_keys, device="cuda").float()
     lifts = {"step": 4.0 * (at >= 64), "climb": 2.0 * (at // 64).clamp(max=12), "late": 12.0 * (at >= n_keys * 0.9)}
     q, k, v = _inputs(heads, d, n_q, n_keys, lifts[lift])
-    ctx, out, call = _runner(heads, d, q, k, v, source)
+    ctx, out, call = _runner(heads, d, q, k, v, source, form, ranges)
     call()
     torch.cuda.synchronize()
     ctx.close()
@@ -62,7 +69,7 @@ def test_time_does_not_depend_on_the_scores(heads, n_q, n_keys, source):
     d, calls, held = 128, [], []
     for step in (0.0, 4.0):
         q, k, v = _inputs(heads, d, n_q, n_keys, step * (torch.arange(n_keys, device="cuda") >= 64))
-        held.append(_runner(heads, d, q, k, v, source))
+        held.append(_runner(heads, d, q, k, v, source, rg.ATTN_TILES_256, rg.RANGES_EQUAL))
         calls.append(held[-1][2])
     best = [1e9, 1e9]
     for _ in range(8):
