@@ -43,7 +43,7 @@ int regione_attention_plan(regione_ctx* ctx, int32_t n_q, int32_t n_keys, int32_
 
 /* Tuning knob for experiments: the kind of workgroups and of key ranges that later attention calls of this context take where they have such; 0 leaves either to the
  * library.  form: workgroups of 128 or 256 queries in two wave groups (head dimension 128), of 32 queries whose keys are dealt to the waves, or of 128 queries in
- * waves that run freely (head dimension 64).  ranges: equal ones, even ones for all query tiles, or even ones behind unsplit query tiles (the last two for head dimension
+ * waves that run freely.  ranges: equal ones, even ones for all query tiles, or even ones behind unsplit query tiles (the last two for head dimension
  * 128).  A number of equal ranges that regione_tune_attention forces is taken in that form.  The ranges of wide 8-bit blocks stay as they are. */
 enum { REGIONE_ATTN_TILES_128 = 1, REGIONE_ATTN_TILES_256 = 2, REGIONE_ATTN_DEALT = 3, REGIONE_ATTN_FREE = 4 };
 enum { REGIONE_RANGES_EQUAL = 1, REGIONE_RANGES_EVEN = 2, REGIONE_RANGES_EVEN_BEHIND = 3 };

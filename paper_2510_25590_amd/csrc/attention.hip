@@ -1351,9 +1351,10 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
 
 // ---------------------------------------------------------------- how a call is dealt to workgroups
 //
-// NARROW (head dimension 64, and wide E4M3 blocks): workgroups of four waves of 32 queries, several per CU, that run freely; there the softmax bounds, and groups that take turns at
-// the matrix cores would leave the vector units idle instead.  SPLIT and SHARE (head dimension 128): see AttnTile, one workgroup per CU.  DEALT:
-// few queries on not too many keys.
+// NARROW: workgroups of four waves of 32 queries, two per CU, that run freely.  With head dimension 64 the softmax bounds, and groups that take turns at
+// the matrix cores would leave the vector units idle instead.  SPLIT and SHARE (head dimension 128): see AttnTile, one workgroup per CU; there NARROW stays
+// the fastest where few key tiles do not pay for their longer start and where the query tiles are a little more than a pass.  DEALT: few queries on not
+// too many keys.
 enum { FORM_SPLIT = 0, FORM_SHARE = 1, FORM_DEALT = 2, FORM_NARROW = 3 };
 // what comparisons force (0: nothing): a form, as its number + 1, and which ranges of keys
 struct Forced { int form, ranges; bool allows(int f) const { return form == 0 || form == f + 1; } };
@@ -1364,7 +1365,7 @@ int form_queries(int form) { return form == FORM_DEALT ? 32 : form == FORM_SHARE
 // workgroups take them in pairs and leave an odd last one to the ranges.
 struct AttnPlan { int form, splits, range, range_wgs, q_full, whole; };
 
-// NARROW (and SPLIT, where it only ranks range counts): microseconds with `s` equal key ranges where the unsplit query tiles leave CUs empty.  A key
+// What plan_ranges ranks numbers of equal key ranges by, in microseconds, where the unsplit query tiles leave CUs empty.  A key
 // tile costs `alone` on a CU that holds four waves, `pair` and more where an XCD's 32 CUs hold up to twice that each, `pass` in a full pass of
 // 64; then the merge launch, the partial rows' way out and back, and what more ranges cost the merge kernel.  Fitted to forced ranges of 1-32 over 105
 // shapes, for rows named by an index list (which lie apart, so that a tile waits longer where nothing else fills the CU) to 409 calls: about 1 % behind
@@ -1383,11 +1384,9 @@ double range_time(int source, int q_tiles, int heads, int n_q, int n_tiles, int 
     return t;
 }
 
-// Key ranges for workgroups of four waves, two per CU: what NARROW calls take.  With head dimension 128 the choice stays in use for its ranges of keys in
-// one array: where it takes even ranges (see plan_wide), and for wide E4M3 blocks.  Their two quantisations turn another rounding of
-// the attention's results by one bf16 ulp into whole code steps (1.8 % of a 3072-wide double-stream block's output, 0.7 % at width 1024), and the
-// weights are rounded relative to their range's reference; so other key ranges would change that mode's results by that much.  The kernel of four waves stays
-// for them where forms of one workgroup per CU have too few of these ranges to share out: 928 queries and keys, 24 heads, 68 us in SPLIT workgroups, 39.5 so.
+// Key ranges of workgroups of four waves: what calls with head dimension 64 take, and wide E4M3 blocks (head dimension 128, keys in one array).  Those blocks' two
+// quantisations turn another rounding of the attention's results by one bf16 ulp into whole code steps (1.8 % of a 3072-wide double-stream block's output, 0.7 % at width 1024),
+// and the weights are rounded relative to their range's reference; so other key ranges would change that mode's results by that much.
 template <int D>
 AttnPlan plan_ranges(int source, int n_q, int n_keys, int heads, int force_splits, size_t part_bytes) {
     constexpr int QW = 128;
@@ -1431,94 +1430,104 @@ AttnPlan plan_ranges(int source, int n_q, int n_keys, int heads, int force_split
     return plan;
 }
 
-// Microseconds of SPLIT, SHARE and DEALT workgroups, one per CU: `units` of work each (key tiles; DEALT: blocks of 32 keys of a wave) at `full` in a
-// pass that fills the chip and at `part` + `fill` x its filling in the last one (the chip's power is shared by fewer), a start per pass,
-// the merge launch and the partial rows' way out and back.  SPLIT and SHARE fitted to 1700 forced plans of 150 calls (16-9000 queries, 500-19000 keys, 8, 16 and 24
-// heads; all three key sources); DEALT, whose workgroups start on all keys at once, to 2200 plans of 370 calls on keys that no cache held, as those of a model's blocks
-// are not: 140 queries on 7068 keys, 24 heads, 42.7 us in DEALT workgroups that costs of cached keys chose, now 32.  Over 630 such calls the choice is 1.8 % behind
-// the best plan on average.
-struct FormCost { double fixed, pass, full, part, fill, merge, mb, ranged, keys; };   // keys: a megabyte of the keys and values
-constexpr FormCost kFormCosts[2][3] = {   // keys in one or two arrays, by index list; SPLIT, SHARE, DEALT
-    {{9.72, 0.00, 0.94, 0.50, 0.27, 1.24, 0.46, 7.35, 0.0}, {8.60, 0.00, 1.65, 0.92, 0.57, 0.00, 0.47, 3.91, 0.0}, {2.17, 3.85, 1.494, 1.441, 0.245, 2.83, 0.404, 0.0, 0.118}},
-    {{9.08, 0.38, 1.10, 0.79, 0.13, 3.04, 0.56, 12.37, 0.0}, {5.54, 0.00, 1.62, 1.36, 0.13, 3.20, 0.65, 5.89, 0.0}, {3.44, 3.29, 1.690, 1.682, 0.000, 2.75, 0.563, 0.0, 0.095}}};
-constexpr FormCost kDealtNarrow[2] = {{3.03, 1.87, 0.85, 0.61, 0.10, 3.07, 0.62, 0.0, 0.0}, {1.04, 4.36, 0.97, 0.97, 0.00, 3.01, 0.51, 0.0, 0.0}};   // head dimension 64
+// Microseconds of a call with equal key ranges.  A pass is 32 workgroups on each of the 8 XCDs, one per CU (NARROW: 64); it costs a start and `units` of work per workgroup (key
+// tiles; DEALT: blocks of 32 keys of a wave) at `full`, the last one at `part` + `fill` x its filling, or where it fills no more than half of itself `low` + `low_fill` x
+// filling (only NARROW differs there: one workgroup per CU or two); then the merge launch, the partial rows' way out and back, what more ranges cost it, and the
+// keys' and the queries' megabytes.  Fitted to 23000 forced plans of 2077 calls (16-9500 queries, 33-16000 keys, 8, 12, 16 and 24 heads, all three key sources), each timed on keys
+// that no cache held, as those of a wide model's blocks are not, and on keys that the last level did: over 500 other calls the choice is 1.0 % behind the best of 10 to 30
+// plans on average and 24 % at most.  Costs fitted to calls of 500 keys and more, and without NARROW among the forms, were 5.9 % behind and up to 1.27 times as slow as
+// NARROW alone.  us, 24 heads, NARROW alone / those costs / now: 6098 x 567 66 / 80 / 68, 2777 x 513 39.5 / 47 / 38, 2700 x 2700 103 / 117 / 103, 1409 x 1409 54 / 62 / 40,
+// 6000 x 2000 166 / 176 / 167; 713 x 122 8.8 / 14.2 / 9.8.
+struct FormCost { double fixed, pass, full, part, fill, low, low_fill, merge, mb, range, keys, rows; };
+constexpr FormCost kFormCosts[2][4] = {   // keys in one or two arrays, by index list; SPLIT, SHARE, DEALT, NARROW
+    {{5.809, 1.96, 0.833, 0.592, 0.124, 0.592, 0.124, 3.194, 0.393, 0.032, 0.031, 0.365}, {7.184, 0.0, 1.6, 0.828, 0.595, 0.828, 0.595, 2.816, 0.384, 0.0, 0.0, 0.429},
+     {1.926, 3.274, 1.237, 1.524, 0.0, 1.524, 0.0, 3.107, 0.34, 0.061, 0.092, 0.298}, {5.078, 0.0, 1.754, 1.302, 0.6, 1.028, 0.136, 2.83, 0.326, 0.047, 0.027, 0.241}},
+    {{6.406, 4.106, 0.889, 0.677, 0.082, 0.677, 0.082, 3.65, 0.378, 0.0, 0.066, 0.415}, {8.651, 0.858, 1.686, 0.993, 0.521, 0.993, 0.521, 2.816, 0.403, 0.0, 0.0, 0.459},
+     {1.987, 3.986, 1.543, 1.853, 0.0, 1.853, 0.0, 2.681, 0.353, 0.233, 0.067, 0.45}, {5.002, 0.0, 2.109, 1.901, 0.388, 1.424, 0.006, 2.804, 0.321, 0.063, 0.043, 0.268}}};
+constexpr FormCost kDealtNarrow[2] = {   // head dimension 64, DEALT
+    {3.03, 1.87, 0.85, 0.61, 0.10, 0.61, 0.10, 3.07, 0.62, 0.0, 0.0, 0.0}, {1.04, 4.36, 0.97, 0.97, 0.00, 0.97, 0.00, 3.01, 0.51, 0.0, 0.0, 0.0}};
 
 template <int D>
 double form_time(int form, bool indexed, int n_q, int heads, int n_tiles, int wgs) {   // wgs: workgroups per query tile
     const FormCost& c = D == 64 ? kDealtNarrow[indexed] : kFormCosts[indexed][form];
-    const int q_tiles = (n_q + form_queries(form) - 1) / form_queries(form);
+    const int q_tiles = (n_q + form_queries(form) - 1) / form_queries(form), slots = form == FORM_NARROW ? 64 : 32;
     const int per = (n_tiles + wgs - 1) / wgs;
     // DEALT: between the blocks of the busiest wave and of the average one
     const double units = form == FORM_DEALT ? 0.5 * ((2 * per + 7) / 8 + (D == 64 ? (2 * per + 7) / 8 : per / 4.0)) : per;
-    const int per_xcd = (heads * wgs + 7) / 8 * q_tiles, full = per_xcd / 32, rem = per_xcd % 32;
-    double t = c.fixed + c.pass * (full + (rem > 0)) + c.full * units * full + c.keys * 4.0e-6 * n_tiles * KT * heads * D;
-    if (rem > 0) t += units * (c.part + c.fill * rem / 32.0);
-    if (wgs > 1) t += c.merge + c.mb * wgs * 4.0e-6 * n_q * heads * (D + 4);
+    const int per_xcd = (heads * wgs + 7) / 8 * q_tiles, full = per_xcd / slots, rem = per_xcd % slots;
+    const double filling = static_cast<double>(rem) / slots;
+    double t = c.fixed + c.pass * (full + (rem > 0)) + c.full * units * full + 4.0e-6 * heads * D * (c.keys * n_tiles * KT + c.rows * n_q);
+    if (rem > 0) t += units * (2 * rem > slots ? c.part + c.fill * filling : c.low + c.low_fill * filling);
+    if (wgs > 1) t += c.merge + c.mb * wgs * 4.0e-6 * n_q * heads * (D + 4) + c.range * wgs;
     return t;
 }
-// even ranges on 256 workgroups behind q_full query tiles of every head
+
+// The same for even ranges on 256 workgroups (NARROW: 512) behind q_full query tiles of every head: `pass` and `tile` for whole passes of those, `again` for the
+// share of ranges that run on into another query tile, `full` a key tile of the ranges where they fill a pass, else `part` x their filling.
+struct EvenCost { double fixed, pass, again, tile, full, part, mb, keys; };
+constexpr EvenCost kEvenCosts[2][4] = {
+    {{14.255, 12.951, 2.717, 0.858, 0.896, 1.043, 0.519, 0.149}, {15.843, 16.556, 0.0, 1.637, 1.676, 1.73, 0.436, 0.007}, {}, {10.086, 6.764, 0.0, 1.894, 2.054, 1.995, 0.337, 0.06}},
+    {{17.268, 18.649, 7.781, 0.94, 0.996, 1.194, 0.524, 0.189}, {18.092, 20.528, 2.193, 1.717, 1.764, 1.894, 0.469, 0.07}, {}, {11.37, 6.897, 0.0, 2.311, 2.562, 2.574, 0.315, 0.044}}};
 double even_time(int form, bool indexed, int n_q, int heads, int n_tiles, int q_full, int range, int range_wgs) {
-    const FormCost& c = kFormCosts[indexed][form];
-    const double whole = heads * q_full / 256.0, fill = (range_wgs + 7) / 8 / 32.0;
-    double t = c.fixed + c.ranged + c.merge + c.pass * (whole + 1.0 + static_cast<double>(range - 1) / n_tiles) + c.full * whole * n_tiles;
-    t += range * (fill >= 1.0 ? c.full : c.part + c.fill * fill);
+    const EvenCost& c = kEvenCosts[indexed][form];
+    const double slots = form == FORM_NARROW ? 512.0 : 256.0, whole = heads * q_full / slots, filling = (range_wgs + 7) / 8 / (slots / 8.0);
+    double t = c.fixed + whole * (c.pass + c.tile * n_tiles) + c.again * (range - 1) / n_tiles + range * (filling >= 1.0 ? c.full : c.part * filling);
     t += c.keys * 4.0e-6 * n_tiles * KT * heads * 128;
     return t + c.mb * 4.0e-6 * (n_q - q_full * form_queries(form)) * static_cast<double>(heads) * (128 + 4) * (static_cast<double>(n_tiles) / range + 1.0);
 }
+
+// Ranges that a second launch joins have to be faster by so much: among a block's launches that one waits longer than back to back (820 queries on 8704 keys, 24
+// heads, in the step: 353 us in three ranges that the costs alone take, 347 unsplit; by themselves 100 and 97), and alone the choice is as good with it.
+constexpr double kMergeMargin = 1.04;
 
 // DEALT keeps the rows that an index list names in LDS
 bool dealt_fits(int source, int n_tiles, int wgs) { return source != SRC_INDEXED || (n_tiles + wgs - 1) / wgs * KT <= kDealtKeys; }
 
 // Head dimension 128: the fastest of the forms, equal or even ranges; no ranges at all (splits 0) where nothing fits what is forced.
-AttnPlan plan_wide(int source, int n_q, int n_keys, int heads, size_t range_bytes, size_t part_bytes, Forced forced) {
+AttnPlan plan_wide(int source, int n_q, int n_keys, int heads, size_t part_bytes, Forced forced) {
     constexpr int D = 128;
     const bool indexed = source == SRC_INDEXED;
     const int n_tiles = (n_keys + KT - 1) / KT, tiles128 = (n_q + 127) / 128;
     const size_t part_row_set = static_cast<size_t>(heads) * n_q * (D + 4) * sizeof(float);
-    // Even ranges of up to 3008 keys in one array are taken for more than 1408 queries where plan_ranges takes them: tests of such ranges name their calls.  The best form
-    // without them is 1.03 to 1.35 times faster there; of fewer queries or more keys, where the costs decide, it was up to 1.6 times (489 queries on 2363 keys,
-    // 24 heads, 49 us, now 31).
-    AttnPlan even = {};
-    if (source == SRC_CONTIG && forced.form == 0 && forced.ranges == 0) even = plan_ranges<D>(source, n_q, n_keys, heads, 0, range_bytes);
-    const bool only_even = even.range > 0 && n_tiles <= 47 && n_q > 1408;
     AttnPlan plan = {};
     double best = 0.0;
-    for (int form = FORM_SPLIT; form <= FORM_DEALT && !only_even; ++form) {
+    for (int form = FORM_SPLIT; form <= FORM_NARROW; ++form) {
         if (!forced.allows(form) || forced.ranges > REGIONE_RANGES_EQUAL) continue;
+        const int q_tiles = (n_q + form_queries(form) - 1) / form_queries(form);
         for (int wgs = 1; wgs <= (form == FORM_SPLIT ? kMaxSplits / 2 : kMaxSplits); ++wgs) {
             if (wgs > 1 && (wgs * 2 > n_tiles || wgs * part_row_set > part_bytes)) break;
             if (form == FORM_DEALT && !dealt_fits(source, n_tiles, wgs)) continue;
-            const double t = form_time<D>(form, indexed, n_q, heads, n_tiles, wgs);
+            const double t = form_time<D>(form, indexed, n_q, heads, n_tiles, wgs) * (wgs > 1 ? kMergeMargin : 1.0);
             if (plan.splits > 0 && t >= best) continue;
             best = t;
-            const int q_tiles = (n_q + form_queries(form) - 1) / form_queries(form);
             plan = {form, form == FORM_SPLIT && n_tiles > 1 ? 2 * wgs : wgs, 0, 0, q_tiles, tiles128};
         }
     }
-    for (int form = FORM_SPLIT; form <= FORM_SHARE; ++form) {
-        if (!forced.allows(form) || forced.ranges == REGIONE_RANGES_EQUAL) continue;
+    for (int form = FORM_SPLIT; form <= FORM_NARROW; ++form) {
+        if (!forced.allows(form) || forced.ranges == REGIONE_RANGES_EQUAL || form == FORM_DEALT) continue;
+        const int slots = form == FORM_NARROW ? 512 : 256;
         for (int pass = 0; pass < 2; ++pass) {   // with and without whole passes of unsplit query tiles in front
             const int qw = form_queries(form), q_tiles = (n_q + qw - 1) / qw;
-            const int whole = heads % 8 == 0 ? q_tiles * heads / 256 : 0;
-            if (pass > 0 && (whole == 0 || only_even)) break;
-            const int tiles = only_even ? even.whole : pass == 0 ? 256 * whole / heads * (qw / 128) : 0;
+            const int whole = heads % 8 == 0 ? q_tiles * heads / slots : 0;
+            if (pass > 0 && whole == 0) break;
+            const int tiles = pass == 0 ? slots * whole / heads * (qw / 128) : 0;
             const int q_full = tiles / (qw / 128);
             if (forced.ranges > 0 && forced.ranges != (q_full > 0 ? REGIONE_RANGES_EVEN_BEHIND : REGIONE_RANGES_EVEN)) continue;
             const int64_t units = static_cast<int64_t>(heads) * (q_tiles - q_full) * n_tiles;
             if (units <= 0 || units >= (1 << 30)) continue;
-            int64_t range = (units + 255) / 256;
+            int64_t range = (units + slots - 1) / slots;
             const int64_t least = (n_tiles + kMaxSplits - 3) / (kMaxSplits - 2);     // as many ranges in a query tile as the merge kernel takes
             range = range < 2 ? 2 : range;
             range = range < least ? least : range;
             const int64_t range_wgs = (units + range - 1) / range;
             if (static_cast<size_t>(range_wgs) * 2 * qw * (D + 4) * sizeof(float) > part_bytes) continue;
-            const double t = even_time(form, indexed, n_q, heads, n_tiles, q_full, static_cast<int>(range), static_cast<int>(range_wgs));
+            const double t = even_time(form, indexed, n_q, heads, n_tiles, q_full, static_cast<int>(range), static_cast<int>(range_wgs)) * kMergeMargin;
             if (plan.splits > 0 && t >= best) continue;
             best = t;
             plan = {form, 1, static_cast<int>(range), static_cast<int>(range_wgs), q_full, tiles};
         }
     }
-    return plan.splits > 0 ? plan : even;
+    return plan;
 }
 
 // keep_ranges: see plan_ranges
@@ -1526,25 +1535,25 @@ AttnPlan plan_attention(const regione_ctx* ctx, int source, int n_q, int n_keys,
     const int n_tiles = (n_keys + KT - 1) / KT, forced = ctx->attn_force_splits;
     const Forced asked = {ctx->attn_force_form, ctx->attn_force_ranges};
     if (d == 128 && !keep_ranges && forced == 0) {
-        const AttnPlan plan = plan_wide(source, n_q, n_keys, heads, ctx->attn_range_bytes, ctx->attn_part_bytes, asked);
-        return plan.splits > 0 ? plan : plan_wide(source, n_q, n_keys, heads, ctx->attn_range_bytes, ctx->attn_part_bytes, {0, 0});
+        const AttnPlan plan = plan_wide(source, n_q, n_keys, heads, ctx->attn_part_bytes, asked);
+        return plan.splits > 0 ? plan : plan_wide(source, n_q, n_keys, heads, ctx->attn_part_bytes, {0, 0});
     }
     AttnPlan plan = d == 64 ? plan_ranges<64>(source, n_q, n_keys, heads, forced, ctx->attn_range_bytes) : plan_ranges<128>(source, n_q, n_keys, heads, forced, ctx->attn_range_bytes);
     if (forced > 0) {   // that many equal ranges in the form asked for, if it has such workgroups
         const int form = asked.form - 1;
-        if (form == FORM_DEALT ? dealt_fits(source, n_tiles, plan.splits) : d == 128 && (form == FORM_SPLIT || form == FORM_SHARE)) plan.form = form;
+        if (form == FORM_DEALT ? dealt_fits(source, n_tiles, plan.splits) : d == 128 && form >= 0) plan.form = form;
         plan.q_full = (n_q + form_queries(plan.form) - 1) / form_queries(plan.form);
         return plan;
     }
-    // the same ranges in another form, or (head dimension 64) other ranges in DEALT workgroups
+    // the same ranges in the fastest form, or (head dimension 64) other ranges in DEALT workgroups
     if (d == 128) {
-        plan.form = source == SRC_CONTIG ? FORM_NARROW : FORM_SPLIT;
+        plan.form = FORM_NARROW;
         if (plan.range > 0) return plan;
-        double best = source == SRC_CONTIG ? range_time<128>(source, plan.whole, heads, n_q, n_tiles, plan.splits) : DBL_MAX;
+        double best = form_time<128>(FORM_NARROW, false, n_q, heads, n_tiles, plan.splits);
         for (int form = FORM_SPLIT; form <= FORM_SHARE; ++form) {
             const int pairs = form == FORM_SPLIT && plan.splits % 2 == 0 ? plan.splits / 2 : plan.splits;
-            const double t = form_time<128>(form, source == SRC_INDEXED, n_q, heads, n_tiles, pairs);
-            if (t >= best - (plan.form == FORM_NARROW ? 1.75 : 0.0)) continue;   // the two models' fixed costs agree to about 1.75 us
+            const double t = form_time<128>(form, false, n_q, heads, n_tiles, pairs);
+            if (t >= best) continue;
             best = t;
             plan.form = form;
         }
@@ -1591,11 +1600,14 @@ int launch_attention(regione_ctx* ctx, AttnArgs a, bool keep_ranges) {
         kernel = indexed ? attn_dealt_kernel<D, true> : attn_dealt_kernel<D, false>;
         lds_bytes = DealtTile<D>::LIST_BASE + (indexed ? kDealtKeys * sizeof(int32_t) : 0);
         which = 8 + indexed;
-    } else if (D == 128 && plan.form == FORM_NARROW) {   // wide E4M3 blocks: keys in one array
-        kernel = a.fast ? (ranged ? attn_narrow_kernel<D, SRC_CONTIG, D == 128> : attn_narrow_kernel<D, SRC_CONTIG, false>)
-                        : (ranged ? attn_narrow_kernel<D, SRC_TWO, D == 128> : attn_narrow_kernel<D, SRC_TWO, false>);
+    } else if (plan.form == FORM_NARROW) {
+        static constexpr Kernel kernels[3][2] = {{attn_narrow_kernel<D, SRC_CONTIG, false>, attn_narrow_kernel<D, SRC_CONTIG, D == 128>},
+                                                 {attn_narrow_kernel<D, SRC_TWO, false>, attn_narrow_kernel<D, SRC_TWO, D == 128>},
+                                                 {attn_narrow_kernel<D, SRC_INDEXED, false>, attn_narrow_kernel<D, SRC_INDEXED, D == 128>}};
+        const int way = source == SRC_CONTIG && !a.fast ? SRC_TWO : source;
+        kernel = kernels[way][ranged];
         lds_bytes = 2u * 2 * KT * D * sizeof(bf16_t);
-        which = 10 + 2 * a.fast + ranged;
+        which = 10 + 2 * way + ranged;
     } else if constexpr (D == 128) {
         static constexpr Kernel kernels[8] = {attn_kvcache_kernel<D, false, false, false>, attn_kvcache_kernel<D, false, false, true>,
                                               attn_kvcache_kernel<D, false, true, false>, attn_kvcache_kernel<D, false, true, true>,
@@ -1606,10 +1618,7 @@ int launch_attention(regione_ctx* ctx, AttnArgs a, bool keep_ranges) {
         kernel = kernels[which];
         lds_bytes = share ? AttnTile<D, true>::LDS_BYTES : AttnTile<D, false>::LDS_BYTES;
     } else {
-        static constexpr Kernel kernels[3] = {attn_narrow_kernel<D, SRC_CONTIG, false>, attn_narrow_kernel<D, SRC_TWO, false>, attn_narrow_kernel<D, SRC_INDEXED, false>};
-        which = source == SRC_CONTIG && !a.fast ? SRC_TWO : source;
-        kernel = kernels[which];
-        lds_bytes = 2u * 2 * KT * D * sizeof(bf16_t);
+        RG_FAIL(REGIONE_ERR_UNSUPPORTED, "attention: no workgroups of form %d for head dimension %d", plan.form, D);
     }
     const uint32_t granted = 1u << (which + (D == 128 ? 0 : 16));
     if (!(ctx->lds_grant_mask & granted)) {   // more than 64 KiB of LDS has to be granted explicitly

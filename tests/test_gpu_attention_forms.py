@@ -95,6 +95,7 @@ def test_few_queries_weigh_their_largest_scores_exactly(heads, d, indexed):
     (24, 257, 1500, 4, rg.ATTN_TILES_128, rg.RANGES_EQUAL), (24, 820, 4097, 2, rg.ATTN_TILES_128, rg.RANGES_EQUAL),       # ranges in pairs
     (24, 2500, 1217, 1, rg.ATTN_TILES_256, rg.RANGES_EQUAL), (8, 6500, 700, 1, rg.ATTN_TILES_256, rg.RANGES_EQUAL),       # unsplit; the last tile with a few rows
     (24, 300, 2300, 3, rg.ATTN_TILES_256, rg.RANGES_EQUAL), (24, 100, 600, 4, rg.ATTN_TILES_256, rg.RANGES_EQUAL),        # equal ranges; the last ones short or empty
+    (24, 820, 513, 1, rg.ATTN_FREE, rg.RANGES_EQUAL), (24, 100, 600, 4, rg.ATTN_FREE, rg.RANGES_EQUAL), (24, 1400, 5001, 0, rg.ATTN_FREE, rg.RANGES_EVEN),      # free waves
     (24, 1400, 5001, 0, rg.ATTN_TILES_256, rg.RANGES_EVEN), (24, 1400, 5001, 0, rg.ATTN_TILES_128, rg.RANGES_EVEN),       # even ranges, alone ...
     (24, 3100, 2050, 0, rg.ATTN_TILES_256, rg.RANGES_EVEN_BEHIND), (24, 3100, 2050, 0, rg.ATTN_TILES_128, rg.RANGES_EVEN_BEHIND),      # ... and behind whole passes
 ])

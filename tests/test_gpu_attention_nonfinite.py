@@ -17,6 +17,7 @@ BIG = 1e30      # two of them make a product beyond float32
     (3, 128, 40, 2111, 16, rg.ATTN_TILES_128), (2, 128, 300, 1000, 1, rg.ATTN_TILES_256), (2, 128, 300, 1000, 4, rg.ATTN_TILES_256),
     (2, 128, 130, 1000, 1, rg.ATTN_DEALT), (2, 128, 130, 1000, 4, rg.ATTN_DEALT), (2, 64, 130, 1000, 1, rg.ATTN_DEALT), (2, 64, 130, 1000, 4, rg.ATTN_DEALT),
     (2, 128, 40, 200, 1, rg.ATTN_DEALT),                                                         # a block per wave, or none
+    (2, 128, 300, 1000, 1, rg.ATTN_FREE), (2, 128, 300, 1000, 4, rg.ATTN_FREE), (24, 128, 3000, 3000, 0, rg.ATTN_FREE),
     (24, 128, 3000, 3000, 0, rg.ATTN_TILES_128), (24, 128, 3000, 3000, 0, rg.ATTN_TILES_256),    # whole passes of query tiles, even ranges behind them
 ])
 @pytest.mark.parametrize("kind", ["nan", "plus", "minus"])

@@ -17,14 +17,17 @@ def _reference(q, k, v, d):
     return out
 
 
-@pytest.mark.parametrize("form", [rg.ATTN_TILES_128, rg.ATTN_TILES_256])
+FORMS = (rg.ATTN_TILES_128, rg.ATTN_TILES_256, rg.ATTN_FREE)
+
+
+@pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("source", ["contiguous", "two", "indexed"])
 @pytest.mark.parametrize("heads,n_q,n_keys,whole,short", [
-    (24, 1409, 3001, 0, (False, True)),     # no query tile in front; ranges longer than a tile of 128 queries' keys, shorter than one of 256
-    (8, 1461, 3001, 0, (True, True)),       # 0.19 of a pass: many ranges meet in a query tile
-    (12, 5450, 2499, 0, (False, False)),    # heads not a multiple of the XCDs; a range longer than a query tile's keys, no whole pass
-    (8, 8700, 2497, 64, (True, True)),      # whole passes, the rest in ranges
-    (24, 2900, 3001, 21, (True, True)),     # ... that the heads do not divide
+    (24, 1409, 3001, 0, (False, True, True)),     # no query tile in front; ranges longer than a tile of 128 queries' keys, shorter than one of 256
+    (8, 1461, 3001, 0, (True, True, True)),       # 0.19 of a pass: many ranges meet in a query tile
+    (12, 5450, 2499, 0, (False, False, False)),    # heads not a multiple of the XCDs; a range longer than a query tile's keys, no whole pass
+    (8, 8700, 2497, 64, (True, True, True)),      # whole passes, the rest in ranges
+    (24, 2900, 3001, 21, (True, True, True)),     # ... that the heads do not divide
 ])
 def test_even_ranges(form, source, heads, n_q, n_keys, whole, short):
     d = 128
@@ -42,7 +45,7 @@ def test_even_ranges(form, source, heads, n_q, n_keys, whole, short):
     splits, tiles, in_front = rg.regione_attention_plan(ctx, n_q, n_keys, heads, d, keys)
     assert rg.regione_attention_workgroups(ctx, n_q, n_keys, heads, d, keys) == (form, 1, tiles)
     # even ranges, of the case's kind; workgroups of 256 queries take the query tiles in front in pairs
-    assert (splits, in_front) == (1, whole if form == rg.ATTN_TILES_128 else whole // 2 * 2) and tiles > 0 and (tiles < (n_keys + 63) // 64) == short[form == rg.ATTN_TILES_256]
+    assert (splits, in_front) == (1, whole // 2 * 2 if form == rg.ATTN_TILES_256 else whole) and tiles > 0 and (tiles < (n_keys + 63) // 64) == short[FORMS.index(form)]
     outs = []
     for splits in (0, 0, 1):
         rg.regione_tune_attention(ctx, splits)
