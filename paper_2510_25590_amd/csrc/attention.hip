@@ -1632,14 +1632,16 @@ int launch_attention(regione_ctx* ctx, AttnArgs a, bool keep_ranges) {
         const int64_t total = static_cast<int64_t>(rows) * a.heads * (D / 4);
         const dim3 merge_grid(static_cast<unsigned>((total + kThreads - 1) / kThreads));
         const bool many = (ranged ? (n_tiles - 1) / a.range + 2 : a.splits) > 8;
-        if (ranged) {
-            const auto merge = qw == 256 ? (many ? attn_combine_kernel<D, 256, true, kMaxSplits> : attn_combine_kernel<D, 256, true, 8>)
-                                         : (many ? attn_combine_kernel<D, 128, true, kMaxSplits> : attn_combine_kernel<D, 128, true, 8>);
-            hipLaunchKernelGGL(merge, merge_grid, dim3(kThreads), 0, ctx->stream, a.part, 0, a.heads, rows, 0, a.out, a.ldo, a.q_full, a.q_tiles - a.q_full, n_tiles, a.range);
-        } else {
+        if constexpr (D == 128) {
+            if (ranged) {
+                const auto merge = qw == 256 ? (many ? attn_combine_kernel<D, 256, true, kMaxSplits> : attn_combine_kernel<D, 256, true, 8>)
+                                             : (many ? attn_combine_kernel<D, 128, true, kMaxSplits> : attn_combine_kernel<D, 128, true, 8>);
+                hipLaunchKernelGGL(merge, merge_grid, dim3(kThreads), 0, ctx->stream, a.part, 0, a.heads, rows, 0, a.out, a.ldo, a.q_full, a.q_tiles - a.q_full, n_tiles, a.range);
+            }
+        }
+        if (!ranged)
             hipLaunchKernelGGL((many ? attn_combine_kernel<D, 128, false, kMaxSplits> : attn_combine_kernel<D, 128, false, 8>), merge_grid, dim3(kThreads), 0, ctx->stream,
                                a.part, a.splits, a.heads, a.n_q, a.n_q_pad, a.out, a.ldo, 0, 0, 0, 0);
-        }
         RG_LAUNCH_CHECK();
     }
     return REGIONE_OK;

@@ -130,14 +130,19 @@ def test_forced_ranges(splits):
         _call(2, 128, 150, 50, n_keys - 50, "indexed", splits, rg.ATTN_TILES_128)
 
 
-@pytest.mark.parametrize("n_txt,n_img", [(528, 400), (17, 240), (300, 1717)])
-def test_wide_8bit_block(n_txt, n_img):
-    """A double-stream E4M3 block above width 1024 keeps its key ranges: even ones, equal ones, one range in 256-query tiles."""
+@pytest.mark.parametrize("n_txt,n_img,n_all,plan", [
+    (528, 400, 928, (rg.ATTN_TILES_128, 1, 0)), (17, 240, 257, (rg.ATTN_FREE, 1, 0)), (300, 1717, 2017, (rg.ATTN_TILES_256, 1, 0)),      # one range
+    (20, 80, 1000, (rg.ATTN_FREE, 4, 0)), (0, 300, 3000, (rg.ATTN_TILES_128, 3, 0)),                     # equal ranges
+    (60, 1272, 3000, (rg.ATTN_FREE, 1, 25)), (500, 1000, 1500, (rg.ATTN_FREE, 1, 14)), (100, 2600, 2700, (rg.ATTN_FREE, 1, 7)),      # even ranges, the last behind whole passes
+])
+def test_wide_8bit_block(n_txt, n_img, n_all, plan):
+    """A double-stream E4M3 block above width 1024 keeps its key ranges, equal and even ones, in whatever form is the fastest for them."""
     heads, d, mlp, n = 24, 128, 256, n_txt + n_img
     hidden = heads * d
     rng = np.random.default_rng(n)
     streams = [inputs.stream_weights(rng, hidden, mlp, "double", "bf16", std=0.02) for _ in range(2)]
     ctx = rg.Context(hidden, heads, d, mlp, n, 16)
+    assert rg.regione_attention_workgroups(ctx, n, n_all, heads, d, rg.KEYS_WIDE_8BIT) == plan
     bw, keep = block_to_device(streams, "double", ctx)
     w8 = rg.BlockWeightsFp8()
     held = []
@@ -147,10 +152,11 @@ def test_wide_8bit_block(n_txt, n_img):
         held.append(k)
     h = dev(inputs.bf16_round(rng.standard_normal((n, hidden)).astype(np.float32)), "bf16")
     slots = torch.arange(n, dtype=torch.int32, device="cuda")
-    kc, vc = (torch.zeros((n, heads, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    kc, vc = (torch.randn((n_all, heads, d), device="cuda").to(torch.bfloat16) for _ in range(2))
     taps = {"q": torch.zeros((n, hidden), dtype=torch.bfloat16, device="cuda"), "attn": torch.zeros((n, hidden), dtype=torch.bfloat16, device="cuda")}
     out = torch.empty((n, hidden), dtype=torch.bfloat16, device="cuda")
-    rg.regione_block_forward_fp8(ctx, bw, w8, rg.BLOCK_DOUBLE, h, out, rg.BF16, n, n_txt, slots, 0, kc, vc, n, rg.FLAG_STORE, rg.make_fp8_taps(taps))
+    rg.regione_block_forward_fp8(ctx, bw, w8, rg.BLOCK_DOUBLE, h, out, rg.BF16, n, n_txt, slots, 0, kc, vc, n_all, rg.FLAG_STORE if n == n_all else rg.FLAG_RETRIEVE,
+                                 rg.make_fp8_taps(taps))
     torch.cuda.synchronize()
     ctx.close()
     want, got = _reference(taps["q"].view(n, heads, d), kc, vc, d), taps["attn"].view(n, heads, d).float()
