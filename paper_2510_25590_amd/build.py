@@ -17,8 +17,9 @@ LIB = os.path.join(HERE, "libregione.so")
 SOURCES = ["api.hip", "partition.hip", "rows.hip", "gemm.hip", "gemm_tiles_wide.hip", "gemm_tiles_128.hip", "gemm_tiles_96.hip", "gemm_tiles_fp8.hip",
            "attention.hip", "block_extras.hip", "fp8.hip", "peaks.hip", "fp32.hip", "host_logic.cpp"]
 
-# sources whose machine code is checked (isa_check.py)
-CHECKED = ("gemm.hip", "gemm_tiles_wide.hip", "gemm_tiles_128.hip", "gemm_tiles_96.hip", "gemm_tiles_fp8.hip")
+# sources whose machine code is checked, and by which function of isa_check.py
+CHECKED = {**dict.fromkeys(("gemm.hip", "gemm_tiles_wide.hip", "gemm_tiles_128.hip", "gemm_tiles_96.hip", "gemm_tiles_fp8.hip"), "check_asm"),
+           "attention.hip": "check_attention_asm"}
 
 
 def flags() -> list[str]:
@@ -61,7 +62,7 @@ def build(verbose: bool = False, only=None) -> str:
             # hand-counted copies are only correct if the compiler left them alone: proved on the machine code just made
             from . import isa_check
             asm = os.path.join(OBJ, stem + "-hip-amdgcn-amd-amdhsa-gfx950.s")
-            isa_check.check_asm(open(asm).read())
+            getattr(isa_check, CHECKED[src])(open(asm).read())
             for f in os.listdir(OBJ):
                 if f.startswith((stem + "-hip", stem + "-host", stem + ".hip", stem + ".bc")) or f in (stem + ".s", stem + ".cui"):
                     os.remove(os.path.join(OBJ, f))

@@ -1,4 +1,4 @@
-"""Static checks of the GEMM kernels' machine code, run by every build.
+"""Static checks of the GEMM and attention kernels' machine code, run by every build.
 
 The kernels issue global-to-LDS copies as inline assembly and wait for them by hand with `s_waitcnt vmcnt(N)`: the compiler
 neither knows what the counts stand for nor waits itself.  `check_asm` proves on the generated code that (1) the K loops hold
@@ -256,6 +256,46 @@ def check_asm(asm: str) -> None:
         problems.append("no GEMM kernel found in the assembly")
     if problems:
         raise RuntimeError("GEMM machine-code check failed:\n  " + "\n  ".join(problems[:20]))
+
+
+def check_rounds(name: str, lines) -> list[str]:
+    """The full rounds of the attention's two wave groups: basic blocks that run MFMAs and issue copies of key tiles.  What they wait for is counted by hand; spills and
+    further loads share the counter and would make the waits stricter, never laxer, but a round with them is not the one that was measured.  So: no
+    scratch access; no vector-memory access besides the copies but single index entries; and no wait that leaves more in flight than the
+    copies of one round (the loop may be rotated, so that a round's wait opens the next block)."""
+    short = name[:70]
+    errors, rounds = [], 0
+    for k, b in enumerate(_blocks(lines)):
+        instrs = [i for i, _ in b[1]]
+        copies = sum(i.startswith(_COPY) for i in instrs)
+        if not copies or sum(i.startswith("v_mfma") for i in instrs) < 32:
+            continue
+        rounds += 1
+        for instr in instrs:
+            op = instr.split()[0]
+            if re.match(r"^(global|buffer|flat|scratch)_(load|store|atomic)", op) and op not in (_COPY, "global_load_dword"):
+                errors.append(f"{short} block {b[0] or k}: '{instr}' in a full round")
+        left = [int(m.group(1)) for m in (_VMCNT.search(i) for i in instrs if i.startswith("s_waitcnt")) if m]
+        if not left or max(left) > copies:
+            errors.append(f"{short} block {b[0] or k}: {copies} copies, and waits that leave {left} in flight")
+    if rounds == 0:
+        errors.append(f"{short}: no full round found")
+    return errors
+
+
+def check_attention_asm(asm: str) -> None:
+    """Checks every attention kernel of one translation unit's assembly; raises RuntimeError on a violation."""
+    n = 0
+    problems: list[str] = []
+    for name, lines in _kernel_bodies(asm, "attn_"):
+        n += 1
+        problems += check_wide_stores(name, lines)
+        if "attn_kvcache_kernel" in name:
+            problems += check_rounds(name, lines)
+    if n == 0:
+        problems.append("no attention kernel found in the assembly")
+    if problems:
+        raise RuntimeError("attention machine-code check failed:\n  " + "\n  ".join(problems[:20]))
 
 
 def check_gemm(hipcc: str, flags: list[str], source: str) -> None:

@@ -1,5 +1,7 @@
-"""The build's checks of the two-group GEMM kernels' machine code: foreign vector-memory instructions among hand-counted
-copies, and wide stores whose data the next instruction overwrites."""
+"""The build's checks of the two-group kernels' machine code: foreign vector-memory instructions among hand-counted
+copies, wide stores whose data the next instruction overwrites, and what a full round of the attention may hold."""
+import pytest
+
 from paper_2510_25590_amd import isa_check as ic
 
 LOOP = """
@@ -30,3 +32,24 @@ def test_foreign_load_in_the_loop_is_found():
 def test_overwritten_store_data_is_found():
     errs = ic.check_wide_stores("store", LOOP.replace("\ts_nop 0\n", "").strip().splitlines())
     assert errs and "v_add_u32_e32 v4" in errs[0]
+
+
+ROUND = (".LBB0_1:\n\tglobal_load_dword v30, v[2:3], off\n" + "\tv_mfma_f32_32x32x16_bf16 v[4:19], v[20:23], v[24:27], v[4:19]\n" * 16
+         + "\t;;#ASMSTART\n\tglobal_load_lds_dwordx4 v1, s[2:3]\n\t;;#ASMEND\n" * 4 + "\ts_waitcnt vmcnt(4)\n"
+         + "\tv_mfma_f32_32x32x16_bf16 v[4:19], v[20:23], v[24:27], v[4:19]\n" * 16 + "\ts_cbranch_scc1 .LBB0_1\n\ts_endpgm\n")
+
+
+def test_full_round_passes():
+    assert ic.check_rounds("round", ROUND.splitlines()) == []
+
+
+@pytest.mark.parametrize("was,now,found", [
+    ("\ts_waitcnt vmcnt(4)\n", "\tscratch_load_dword v40, off, s32\n\ts_waitcnt vmcnt(4)\n", "scratch_load_dword"),
+    ("\ts_waitcnt vmcnt(4)\n", "\tglobal_store_dwordx4 v[2:3], v[4:7], off\n\ts_waitcnt vmcnt(4)\n", "global_store_dwordx4"),
+    ("vmcnt(4)", "vmcnt(5)", "leave [5]"),
+    ("\ts_waitcnt vmcnt(4)\n", "", "leave []"),
+    ("global_load_lds_dwordx4", "ds_nop", "no full round"),
+])
+def test_faults_of_a_full_round_are_found(was, now, found):
+    errs = ic.check_rounds("round", ROUND.replace(was, now).splitlines())
+    assert len(errs) == 1 and found in errs[0]
