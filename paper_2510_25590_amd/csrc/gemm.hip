@@ -160,11 +160,14 @@ GemmPlan plan_gemm(regione_ctx* ctx, int m, int n, int k, bool fp8) {
 // Which products the kernel of 16-row tiles takes (gemm_small.h), and in tiles of how many columns; 0: the tile kernels.  Its workgroups hold a CU each, and
 // every row tile reads all weights from L2 again: it wins where one round of 256 workgroups does.  Times in us, tile kernels -> 32 / 64 columns, where
 // a call by itself takes 4.4: rows x columns x K 544 x 256 x 1024 6.9 -> 5.7 / 4.4, 64 x 3072 x 1024 6.9 -> 5.8 / 4.7, 100 x 3072 x 1024 7.0 -> 7.8 / 7.0 (336
-// workgroups), 820 x 768 x 256 4.6 -> 7.2 / 5.3; 100 x 1024 x 5120 10.6 -> 9.5 / 11.4, 160 x 1024 x 5120 10.5 -> 16.8 / 11.5; 1 x 3072 x 12288 15.9 -> 16.1 / 23.7.
+// workgroups), 820 x 768 x 256 4.6 -> 7.2 / 5.3.  Long K costs it chains of loads, most of all on weights that no cache holds: the tile kernels' time over this
+// kernel's, mean of 580 products of up to 2400 rows, cached / uncached weights: 32 columns, K 2048 1.46 / 1.43, 3072 1.38 / 1.21, 4096 1.31 / 1.08, 5120 1.17 / 0.95; 64
+// columns, K 1280 1.26 / 1.21, 1792 1.24 / 1.09, 2304 1.16 / 0.99, 3072 1.09 / 0.92; the last lengths are those of narrow models, whose weights the caches hold.
 // Narrow results (at most 64 columns: the velocity head) all go there: 820 x 64 x 3072 13.3 -> 6.4 / 8.0 against a kernel of 32 x 32 tiles, 2560 rows 14.4 -> 11.7
 // / 8.1, 8704 rows 44 -> 28 / 23.
-// After a LayerNorm (k <= 1024) a launch of about 3.5 us goes away as well, which pays for a second round, as K <= 256 does; 838 x 768 x 256 after a LayerNorm in
-// three rounds took 10.9 where LayerNorm and tile kernel take 9.3, 838 x 1024 in four 16.3 for 9.5.
+// With K <= 256 a second round pays.  After a LayerNorm (k <= 1024), whose launch goes away too, one round is the limit all the same, since every workgroup normalises
+// its rows again: us per block with up to two rounds -> one, tile kernels and LayerNorm before: width 256, 400 rows 37.0 -> 33.7 (41.4), single-stream 150 rows 22.0 -> 20.4 (26.3);
+// width 768, single-stream 50 rows 33.2 -> 30.0 (32.4); width 1024, 100 rows 52.5 -> 48.0 (54.0), single-stream 34 rows 34.9 -> 32.7 (33.4).
 constexpr int kNarrowColumns = 64;
 int small_columns(int m, int n, int k, bool after_ln) {
     const int64_t row_tiles = (m + 15) / 16, wgs32 = row_tiles * ((n + 31) / 32), wgs64 = row_tiles * ((n + 63) / 64);
@@ -172,7 +175,7 @@ int small_columns(int m, int n, int k, bool after_ln) {
     if (n <= kNarrowColumns) return wgs32 <= 256 ? 32 : 64;
     if (k > 5120) return 0;
     if (wgs32 <= 256) return 32;
-    const int64_t most = k <= 256 || after_ln ? 512 : 256;
+    const int64_t most = k <= 256 && !after_ln ? 512 : 256;
     return k <= 3072 && wgs64 <= most ? 64 : 0;
 }
 // ... unless a comparison forces a plan of the tile kernels
