@@ -136,8 +136,9 @@ velocity_cache_kernel(int reuse, float factor, float dt, const T* __restrict__ v
     }
 }
 
-// LayerNorm over H with modulation, one wave per row (see layernorm_row).  Bound by the latency of its loads: 36 float32 rows of 256 values 5.3 us in the kernel of
-// scalar loads below, 3.6 here.  U: the output's storage type (bf16, or float32 in a float32 context).
+// LayerNorm over H with modulation, one wave per row (see layernorm_row).  Bound by the latency of its loads: 36 float32 rows of 256 values take 5.2 us in the kernel of
+// scalar loads below, 3.8 here with the registers and code of eight rounds of loads, 3.2 with those of the one round that such a row needs (in a kernel trace; among a
+// step's launches the call gains about 3 us of 65).  8704 rows: of 256 values 10.0 -> 4.8 (bf16), 10.7 -> 5.5 (float32); of 1024 13.4 -> 7.8, 17.5 -> 14.6.  U: the output's storage type (bf16, or float32 in a float32 context).
 template <typename T, typename U, int MAXV>
 __global__ void __launch_bounds__(kThreads)
 layernorm_mod_vec_kernel(const T* __restrict__ h, int n, int hidden, const float* __restrict__ shift,
@@ -456,7 +457,10 @@ static void launch_layernorm(regione_ctx* ctx, const T* h, int n, int hidden, co
     const dim3 grid((n + kThreads / 64 - 1) / (kThreads / 64));
     const bool vec = (hidden % 8 == 0) && hidden <= 64 * 8 * 8 && rg_aligned16(h) && rg_aligned16(u) &&
                      (!shift || rg_aligned16(shift)) && (!scale || rg_aligned16(scale));
-    if (vec) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 8>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
+    // as many registers and as much code as the row has rounds of 512 elements
+    if (vec && hidden <= 512) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 1>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
+    else if (vec && hidden <= 1024) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 2>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
+    else if (vec) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 8>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
     else hipLaunchKernelGGL((layernorm_mod_kernel<T, U>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
 }
 

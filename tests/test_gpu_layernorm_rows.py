@@ -1,4 +1,4 @@
-"""LayerNorm + modulation around the edges of the kernel that reads a row in 16-byte groups: one group, whole and partly filled rounds of 64 lanes, the longest
+"""LayerNorm + modulation around the edges of the kernel that reads a row in 16-byte groups: one group, whole and partly filled rounds of 64 lanes, one, two and more of them, the longest
 row, and rows that only the kernel for any width takes; bf16 and float32 in and out, tensors off the 16-byte grid.  The oracle is float64."""
 import pytest
 import torch
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("f32_ctx", [False, True])
 @pytest.mark.parametrize("f32_in", [False, True])
-@pytest.mark.parametrize("n,hidden,shifted", [(1, 8, 0), (3, 256, 0), (5, 520, 0), (2, 4096, 0), (4, 4104, 0), (3, 100, 0), (6, 512, 1)])
+@pytest.mark.parametrize("n,hidden,shifted", [(1, 8, 0), (3, 256, 0), (5, 520, 0), (3, 1024, 0), (5, 1032, 0), (2, 4096, 0), (4, 4104, 0), (3, 100, 0), (6, 512, 1)])
 def test_rows(f32_ctx, f32_in, n, hidden, shifted):
     g = torch.Generator(device="cuda")
     g.manual_seed(hidden + n)
