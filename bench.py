@@ -632,7 +632,7 @@ def main():
                            "measured_in": f"a second timed region of the same {args.steps} steps with HIP event pairs ({ms_profiled:.4f} ms per step there)"}
         out["attention"] = {"achieved": attn_flops / (a_ms * 1e-3) / 1e12, "unit": "TFLOP/s",
                             "frac": attn_flops / (a_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, "ms_per_step": a_ms}
-        out["roofline"]["others"] = [{"kernel": "attn_kvcache_kernel + attn_combine_kernel (regione_attn_kvcache inside the block)", "bound": "mfma",
+        out["roofline"]["others"] = [{"kernel": "attn_kvcache_kernel (regione_attn_kvcache inside the block; unsplit at the default sizes, else with attn_combine_kernel)", "bound": "mfma",
                                       "achieved": out["attention"]["achieved"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": out["attention"]["frac"],
                                       "avg_launch_ms": a_ms, "algorithmic_flops_per_launch": attn_flops, "traffic": traffic.get("attn_kvcache_kernel")}]
         out["gemm_plus_attention_tflops"] = (gemm_flops + attn_flops) / ((g_ms + a_ms) * 1e-3) / 1e12

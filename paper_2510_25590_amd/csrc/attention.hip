@@ -510,8 +510,8 @@ attn_narrow_kernel(AttnArgs a) {
 // Bound by latency: the kernel below spends 8 us outside its tile loop (groups that wait for each other, partial results of 128 queries through memory and
 // a second launch to join them).  Here every wave works on its own, without a barrier in its loop: its K and V blocks come into LDS of its own,
 // leave it for registers as fragments at once, and the next block is copied meanwhile; partial results meet in LDS.  us, key ranges and their merge
-// launch before -> now: 36 queries x 544 keys, 4 heads of 64, 8.4 -> 6.9; 544 x 544 9.4 -> 6.8; 1022 x 1022, 8 heads of 128, 22.7 -> 12.1; 95 x 759, 24
-// heads, 13.6 -> 11.5.
+// launch before -> now: 36 queries x 544 keys, 4 heads of 64, 8.5 -> 5.8; 544 x 544 9.4 -> 5.9; 1022 x 1022, 8 heads of 128, 23.1 -> 11.6; 95 x 759, 24
+// heads, 13.6 -> 9.8.
 template <int D> struct DealtTile {
     static constexpr int DB = D / 32, KK = D / 16, CPR = D / 8;
     static constexpr int COPIES = 32 * CPR / 64;            // copies per lane for the K (or V) rows of a block
@@ -758,14 +758,15 @@ attn_dealt_kernel(AttnArgs a) {
 // then the second product of this one: 32 MFMAs) the other forms its softmax and starts the copies of later tiles; a barrier ends each phase.  On this
 // chip a wave's vector instructions pass beside another wave's MFMAs at full rate on both sides (probe: 32.0 cycles per MFMA beside 7 FMAs of another
 // wave), but two waves of a SIMD that run freely meet in the same phase half of the time.  Per tile and wave: 1024 cycles of MFMAs, and some 110 vector
-// instructions (32 of them exponentials at 8 cycles).  The chip is then bound by its power: the clock falls to 1.65 GHz, and any work left out (copies, LDS
+// instructions (32 of them exponentials at 8 cycles).  The chip is then bound by its power: the clock falls to 1.64 GHz with
+// the matrix cores busy in 79 % of the SIMD-cycles (counters, 19456 x 19456; 72 % at 8704 x 8704), and any work left out (copies, LDS
 // reads, vector instructions) gives time in proportion to its energy, so tiles are shared by as many queries as the shape allows.
 //
 // How the groups share a workgroup's work.  SPLIT: 128 queries; the groups take the key tiles of one range in turns, or a range each, and their results
 // are joined at the end.  SHARE: 256 queries; both groups take every key tile, so that a tile is copied into LDS once for twice as many
-// queries (a tenth of the time went into copies).  24 heads, us, workgroups of four free waves before -> now: 8704 queries x 8704 keys 833 -> 763,
-// 2560 x 8704 258 -> 225, 1382 x 19456 379 -> 304, 1332 x 8704 by index list 212 -> 163 (SHARE); 820 x 8704 103.5 -> 100, 205 x 8704
-// 41 -> 36 (SPLIT).  16x16x32 MFMAs (less power, but twice the issue slots and eight more registers) were 3 % faster in unsplit calls and slower in all others.
+// queries (a tenth of the time went into copies).  24 heads, us, workgroups of four free waves before -> now: 8704 queries x 8704 keys 832 -> 766,
+// 2560 x 8704 259 -> 225, 1382 x 19456 374 -> 319, 1332 x 8704 by index list 220 -> 167 (SHARE); 820 x 8704 105 -> 96, 205 x 8704
+// 41 -> 35 (SPLIT).  16x16x32 MFMAs (less power, but twice the issue slots and eight more registers) were 3 % faster in unsplit calls and slower in all others.
 template <int D, bool SHARE> struct AttnTile {
     static constexpr int DB = D / 32;                       // 32-wide d blocks of the output
     static constexpr int KK = D / 16;                       // k-steps of the first product
