@@ -48,3 +48,29 @@ def test_create_during_a_relaxed_capture(on_default_stream):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.all(buf == i + 1.0)
+
+
+def test_a_small_context_holds_little_attention_scratch():
+    """400 rows of 8 heads of 128: the products' 128 MiB, 35 MB of partial rows of attentions and a few MB of rows, not the 69 MB that full chips need."""
+    torch.zeros(1, device="cuda")
+    rg.Context(1024, 8, 128, 1024, 400, 16).close()          # what the first context sets up for all
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    ctx = rg.Context(1024, 8, 128, 1024, 400, 16)
+    held = before - torch.cuda.mem_get_info()[0]
+    ctx.close()
+    rows = 400 * (4 * 1024 + 2 * 1024 + 1024) * 2 + 400 * 1024 * 4    # u q k v, a, m in bf16; h1 in float32
+    assert held <= (128 << 20) + 256 * 2 * 128 * 132 * 4 + rows + (12 << 20)    # and a dozen allocations' rounding to pages
+
+
+@pytest.mark.parametrize("heads,rows", [(8, 129), (8, 400), (8, 1024), (4, 2048)])
+def test_small_contexts_deal_attentions_as_large_ones_do(heads, rows):
+    torch.zeros(1, device="cuda")
+    small, large = (rg.Context(128 * heads, heads, 128, 256, n, 16) for n in (rows, 4096))
+    for n_q in (rows, rows - 1, 3 * rows // 4, rows // 2):
+        for n_keys in (65, 129, 400, 801, 1409, 2500, 4097, 6304, 8704, 12000, 19456):
+            for source in (rg.KEYS_CONTIGUOUS, rg.KEYS_TWO, rg.KEYS_INDEXED):
+                plans = [rg.regione_attention_workgroups(c, n_q, n_keys, heads, 128, source) for c in (small, large)]
+                assert plans[0] == plans[1], (n_q, n_keys, source)
+    small.close()
+    large.close()
