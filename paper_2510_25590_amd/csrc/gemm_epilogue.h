@@ -12,10 +12,16 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;   // a native 16-byte vector: copies are single loads/stores
 typedef __attribute__((ext_vector_type(8))) int i32x8;            // operand of the 8-bit MFMA: 32 E4M3 values per lane
 
+// 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3).  The divisor lies in [1, inf]: the reciprocal, one correction of the quotient and the
+// fix-up of the special values give what the general division gives, without its scaling and with fewer instructions: the epilogue of 820 x 12288
+// results is bound by them (one tile per CU, 96 values per thread); the whole product, K 3072, 68.0 -> 65.5 us in a kernel trace.
 __device__ __forceinline__ float gelu_tanh_f32(float x) {
-    // 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3)
-    const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-    return x / (1.0f + __expf(-2.0f * u));
+    constexpr float kLin = -2.0f * 0.7978845608028654f * 1.4426950408889634f, kCub = kLin * 0.044715f;   // -2u log2(e) = x (kLin + kCub x^2)
+    const float d = 1.0f + __builtin_amdgcn_exp2f(x * __builtin_fmaf(x * x, kCub, kLin));
+    const float r = __builtin_amdgcn_rcpf(d);
+    float q = x * r;
+    q = __builtin_fmaf(__builtin_fmaf(-d, q, x), r, q);
+    return __builtin_amdgcn_div_fixupf(q, d, x);
 }
 
 // Row of the key/value destination for output row `row` (its cache slot when a slot list is given).
@@ -95,66 +101,89 @@ __device__ __forceinline__ void store8(void* base, int64_t elem, int as_f32, con
     }
 }
 
+// Eight elements of a row as they lie in memory: float32 fills both halves, bf16 the first.  Kept raw between the load and the use, so that a conversion
+// does not wait for the load.
+struct Raw8 { u32x4 a, b; };
 template <bool ALIGNED>
-__device__ __forceinline__ void load8(const void* base, int64_t elem, int as_f32, float (&v)[8]) {
+__device__ __forceinline__ Raw8 load_raw8(const void* base, int64_t elem, int as_f32) {
+    Raw8 r;
     if (as_f32) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const f32x4 a = *reinterpret_cast<const typename Pieces<ALIGNED>::f32*>(static_cast<const float*>(base) + elem + 4 * h);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * h + e] = a[e];
-        }
+        typedef typename Pieces<ALIGNED>::f32 piece;
+        const float* p = static_cast<const float*>(base) + elem;
+        r.a = __builtin_bit_cast(u32x4, static_cast<f32x4>(*reinterpret_cast<const piece*>(p)));
+        r.b = __builtin_bit_cast(u32x4, static_cast<f32x4>(*reinterpret_cast<const piece*>(p + 4)));
     } else {
-        const bf16x8 a = *reinterpret_cast<const typename Pieces<ALIGNED>::b16*>(static_cast<const bf16_t*>(base) + elem);
+        r.a = __builtin_bit_cast(u32x4, static_cast<bf16x8>(*reinterpret_cast<const typename Pieces<ALIGNED>::b16*>(static_cast<const bf16_t*>(base) + elem)));
+        r.b = u32x4{0u, 0u, 0u, 0u};
+    }
+    return r;
+}
+__device__ __forceinline__ void raw_values(const Raw8& r, int as_f32, float (&v)[8]) {
+    if (as_f32) {
+        const f32x4 a = __builtin_bit_cast(f32x4, r.a), b = __builtin_bit_cast(f32x4, r.b);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
+    } else {
+        const bf16x8 a = __builtin_bit_cast(bf16x8, r.a);
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = static_cast<float>(a[e]);
     }
 }
 
-// The velocity step (see epilogue_store) on columns col0..col0+n-1 of a row, n <= 8.  WIDE: all eight, in whole pieces.  Otherwise one
-// at a time, but the row's place is looked up once and every element of x_e requested before the first store.
-template <bool WIDE, bool ALIGNED>
-__device__ __forceinline__ void epilogue_velocity(const GemmEpilogue& ep, int row, int col0, int n, float (&val)[8]) {
-    const int64_t o = static_cast<int64_t>(row) * ep.ldy + col0;
-    const int64_t full = ep.vel_index ? static_cast<int64_t>(ep.vel_index[row]) * ep.ldy + col0 : o;
-    float x[8];
-    if (WIDE) {
-        load8<ALIGNED>(ep.vel_xe, o, ep.y_f32, x);
-    } else {
+// What an epilogue reads besides the sums, in three parts that can be requested ahead of their use: of eight columns, of a row, and of eight elements.
+template <int KIND, bool SCALED> struct EpiColumns {
+    float bias[8], gate[KIND == EPI_RESID ? 8 : 1], scale[SCALED ? 8 : 1];
+    __device__ __forceinline__ void load(const GemmEpilogue& ep, int col0) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (e < n) x[e] = ep.y_f32 ? static_cast<const float*>(ep.vel_xe)[o + e] : bf16_to_f32(static_cast<const bf16_t*>(ep.vel_xe)[o + e]);
+        for (int e = 0; e < 8; ++e) {
+            bias[e] = ep.bias ? ep.bias[col0 + e] : 0.f;
+            if (KIND == EPI_RESID) gate[e] = ep.gate ? ep.gate[col0 + e] : 1.f;
+            if (SCALED) scale[e] = ep.col_scale[col0 + e];
+        }
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        if (!ep.y_f32) val[e] = static_cast<float>(static_cast<__bf16>(val[e]));
-        x[e] = __fsub_rn(x[e], __fmul_rn(ep.vel_dt, val[e]));
+};
+template <int KIND, bool SCALED> struct EpiRow {
+    int32_t place;      // cache slot (QKV) or row of the full latent (velocity step)
+    float scale;
+    __device__ __forceinline__ void load(const GemmEpilogue& ep, int row) {
+        place = row;
+        if (KIND == EPI_QKV && ep.slot) place = ep.slot[row] + ep.slot_offset;
+        if (KIND == EPI_VELOCITY && ep.vel_index) place = ep.vel_index[row];
+        scale = SCALED ? ep.row_scale[row] : 1.f;
     }
-    auto put = [&](void* base, int64_t at, const float (&v)[8]) __attribute__((always_inline)) {
-        if (WIDE) { store8<ALIGNED>(base, at, ep.y_f32, v); return; }
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (e < n) {
-                if (ep.y_f32) static_cast<float*>(base)[at + e] = v[e];
-                else static_cast<bf16_t*>(base)[at + e] = f32_to_bf16(v[e]);
-            }
-    };
-    if (ep.y) put(ep.y, o, val);
-    put(ep.vel_ca, o, val);
-    put(ep.vel_xe, o, x);
-    if (ep.vel_xfull) put(ep.vel_xfull, full, x);
+};
+template <int KIND> constexpr bool epi_reads() { return KIND == EPI_RESID || KIND == EPI_VELOCITY; }
+template <int KIND, bool ALIGNED>
+__device__ __forceinline__ Raw8 epi_load8(const GemmEpilogue& ep, int row, int col0) {
+    if (KIND == EPI_RESID) return load_raw8<ALIGNED>(ep.resid, static_cast<int64_t>(row) * ep.ldr + col0, ep.resid_f32);
+    return load_raw8<ALIGNED>(ep.vel_xe, static_cast<int64_t>(row) * ep.ldy + col0, ep.y_f32);
 }
 
-// Epilogue for the eight consecutive columns col0..col0+7 of one row (all inside N, col0 a multiple of 8; a group never
-// straddles two destinations): wide loads and stores only, of whole 16-byte pieces if ALIGNED.
-template <int KIND, bool ALIGNED>
-__device__ __forceinline__ void epilogue_store8(const GemmEpilogue& ep, int row, int col0, const float (&acc)[8],
-                                                const float (&bias)[8], const float (&gate)[8]) {
+// Eight consecutive columns col0..col0+7 of one row (all inside N, col0 a multiple of 8; a group never straddles two destinations): wide
+// stores only, of whole 16-byte pieces if ALIGNED.  SCALED (the 8-bit GEMM): the sums are first multiplied by their row's and column's scale.
+template <int KIND, bool SCALED, bool ALIGNED>
+__device__ __forceinline__ void epilogue_store8(const GemmEpilogue& ep, int row, int col0, const f32x4& acc0, const f32x4& acc1, const EpiColumns<KIND, SCALED>& c, const EpiRow<KIND, SCALED>& r,
+                                                const Raw8& raw) {
     float val[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) val[e] = acc[e] + bias[e];
+    for (int e = 0; e < 8; ++e) {
+        const float a = e < 4 ? acc0[e & 3] : acc1[e & 3];
+        val[e] = (SCALED ? a * (r.scale * c.scale[SCALED ? e : 0]) : a) + c.bias[e];
+    }
     if (KIND == EPI_VELOCITY) {
-        epilogue_velocity<true, ALIGNED>(ep, row, col0, 8, val);
+        // the velocity step, as in epilogue_store
+        const int64_t o = static_cast<int64_t>(row) * ep.ldy + col0;
+        float x[8];
+        raw_values(raw, ep.y_f32, x);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (!ep.y_f32) val[e] = static_cast<float>(static_cast<__bf16>(val[e]));
+            x[e] = __fsub_rn(x[e], __fmul_rn(ep.vel_dt, val[e]));
+        }
+        if (ep.y) store8<ALIGNED>(ep.y, o, ep.y_f32, val);
+        store8<ALIGNED>(ep.vel_ca, o, ep.y_f32, val);
+        store8<ALIGNED>(ep.vel_xe, o, ep.y_f32, x);
+        if (ep.vel_xfull) store8<ALIGNED>(ep.vel_xfull, static_cast<int64_t>(r.place) * ep.ldy + col0, ep.y_f32, x);
     } else if (KIND == EPI_PLAIN) {
         if (ep.act == REGIONE_ACT_GELU_TANH) {
 #pragma unroll
@@ -166,7 +195,7 @@ __device__ __forceinline__ void epilogue_store8(const GemmEpilogue& ep, int row,
         if (col0 < H) {
             store8<ALIGNED>(ep.q, static_cast<int64_t>(row) * ep.ldq + col0, 0, val);
         } else if (col0 < 3 * H) {
-            const int64_t kv_row = epilogue_kv_row<KIND>(ep, row);
+            const int64_t kv_row = r.place;
             if (col0 < 2 * H) store8<ALIGNED>(ep.k, kv_row * ep.ldkv + (col0 - H), 0, val);
             else store8<ALIGNED>(ep.v, kv_row * ep.ldkv + (col0 - 2 * H), 0, val);
         } else {
@@ -178,82 +207,119 @@ __device__ __forceinline__ void epilogue_store8(const GemmEpilogue& ep, int row,
         }
     } else {  // EPI_RESID
         float res[8];
-        load8<ALIGNED>(ep.resid, static_cast<int64_t>(row) * ep.ldr + col0, ep.resid_f32, res);
+        raw_values(raw, ep.resid_f32, res);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) val[e] = res[e] + gate[e] * val[e];
+        for (int e = 0; e < 8; ++e) val[e] = res[e] + c.gate[KIND == EPI_RESID ? e : 0] * val[e];
         store8<ALIGNED>(ep.y, static_cast<int64_t>(row) * ep.ldy + col0, ep.y_f32, val);
     }
 }
-// Writes a wave's accumulators, those of 16x16 matrix instructions whose FIRST operand were the weights: acc[i][j] of a lane
+
+// One element at a time, for column groups that run past N and for Q, K, V rows out of alignment.  The velocity step looks the row's place up once and
+// requests every element of x_e before its first store.
+template <int KIND, bool SCALED>
+__device__ __forceinline__ void epilogue_ragged(const GemmEpilogue& ep, int row, int col0, int N, const f32x4& acc0, const f32x4& acc1) {
+    if (KIND == EPI_VELOCITY) {
+        const int64_t o = static_cast<int64_t>(row) * ep.ldy + col0;
+        const int64_t full = ep.vel_index ? static_cast<int64_t>(ep.vel_index[row]) * ep.ldy + col0 : o;
+        const int n = N - col0;
+        float v[8], x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (e < n) x[e] = ep.y_f32 ? static_cast<const float*>(ep.vel_xe)[o + e] : bf16_to_f32(static_cast<const bf16_t*>(ep.vel_xe)[o + e]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[e] = (e < 4 ? acc0[e & 3] : acc1[e & 3]) + (ep.bias && e < n ? ep.bias[col0 + e] : 0.f);
+            if (!ep.y_f32) v[e] = static_cast<float>(static_cast<__bf16>(v[e]));
+            x[e] = __fsub_rn(x[e], __fmul_rn(ep.vel_dt, v[e]));
+        }
+        auto put = [&](void* base, int64_t at, const float (&w)[8]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (e < n) {
+                    if (ep.y_f32) static_cast<float*>(base)[at + e] = w[e];
+                    else static_cast<bf16_t*>(base)[at + e] = f32_to_bf16(w[e]);
+                }
+        };
+        if (ep.y) put(ep.y, o, v);
+        put(ep.vel_ca, o, v);
+        put(ep.vel_xe, o, x);
+        if (ep.vel_xfull) put(ep.vel_xfull, full, x);
+        return;
+    }
+    const float rs = SCALED ? ep.row_scale[row] : 1.f;
+    const int64_t kv_row = epilogue_kv_row<KIND>(ep, row);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int col = col0 + e;
+        if (col < N) {
+            const float a = (e < 4 ? acc0[e & 3] : acc1[e & 3]) * (SCALED ? rs * ep.col_scale[col] : 1.f);
+            epilogue_store<KIND>(ep, row, kv_row, col, a, ep.bias ? ep.bias[col] : 0.f, (KIND == EPI_RESID && ep.gate) ? ep.gate[col] : 1.f);
+        }
+    }
+}
+
+// Writes rows [I0, I1) of a wave's accumulators, those of 16x16 matrix instructions whose FIRST operand were the weights: acc[i][j] of a lane
 // holds row 16*i + lane%16 of the wave tile and the four columns 32*(j/2) + 8*(lane/16) + 4*(j%2) + 0..3 (the order in which
 // the caller presents the weight columns), i.e. eight consecutive columns per pair j = 2b, 2b+1.  A lane writes 16 bytes
 // (bf16) of its row per pair, the four lanes of a row 64 contiguous bytes: no transposition, no LDS, no barrier.
-// SCALED (the 8-bit GEMM): every sum is first multiplied by ep.row_scale[row] * ep.col_scale[column].
-template <int KIND, bool SCALED, int I0, int I1, int RF, int CF, int B, bool ALIGNED>
-__device__ __forceinline__ void gemm_epilogue16_wide(f32x4 (&acc)[RF][CF], int M, int m0, int col0, const GemmEpilogue& ep) {
-    const int l16 = threadIdx.x & 15;
-    float bias[8], gate[8], cscale[8];
+// The matrix cores are done by now and only two waves share a SIMD, so that every trip to memory that a store waits for is idle time: the slots and scales of all rows are
+// requested before the first store, the vectors of a pair of columns one pair and residual rows one chunk ahead of their use.  With the slot of each row looked up before its store the
+// QKV projection of 820 rows (K 3072) took 48.7 us, now 47.3 in a kernel trace; whole calls 1.3 % less (20 % edited 351 -> 346 us, E4M3 block 269 -> 263).
+template <int KIND, bool SCALED, int I0, int I1, int RF, int CF, bool ALIGNED>
+__device__ __forceinline__ void gemm_epilogue16_wide(const f32x4 (&acc)[RF][CF], int M, int N, int m0, int n0w, const GemmEpilogue& ep) {
+    constexpr int R = I1 - I0, P = CF / 2, Q = R * P, MOST = KIND == EPI_VELOCITY || (CF >= 6 && R >= 3) ? 1 : Q >= 12 ? 2 : 4, CH = Q < MOST ? Q : MOST, CHUNKS = (Q + CH - 1) / CH;
+    const int l16 = threadIdx.x & 15, c0 = n0w + 8 * ((threadIdx.x & 63) >> 4);
+    EpiColumns<KIND, SCALED> cols[2];
+    EpiRow<KIND, SCALED> rows[R];
+    Raw8 raw[2][CH];
+    auto fetch = [&](int c) __attribute__((always_inline)) {
+        if (!epi_reads<KIND>()) return;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        bias[e] = ep.bias ? ep.bias[col0 + e] : 0.f;
-        gate[e] = (KIND == EPI_RESID && ep.gate) ? ep.gate[col0 + e] : 1.f;
-        cscale[e] = SCALED ? ep.col_scale[col0 + e] : 1.f;
+        for (int k = 0; k < CH; ++k) {
+            const int q = c * CH + k, row = m0 + 16 * (I0 + q % R) + l16, col = c0 + 32 * (q / R);
+            if (q < Q && col + 8 <= N) raw[c & 1][k] = epi_load8<KIND, ALIGNED>(ep, row < M ? row : M - 1, col);
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int row = m0 + 16 * (I0 + r) + l16;
+        rows[r].load(ep, row < M ? row : M - 1);
     }
+    if (c0 + 8 <= N) cols[0].load(ep, c0);
+    fetch(0);
 #pragma unroll
-    for (int i = I0; i < I1; ++i) {
-        const int row = m0 + 16 * i + l16;
-        if (row < M) {
-            const float rs = SCALED ? ep.row_scale[row] : 1.f;
-            float v[8];
+    for (int c = 0; c < CHUNKS; ++c) {
+        if (c + 1 < CHUNKS) fetch(c + 1);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = SCALED ? acc[i][2 * B + (e >> 2)][e & 3] * (rs * cscale[e]) : acc[i][2 * B + (e >> 2)][e & 3];
-            epilogue_store8<KIND, ALIGNED>(ep, row, col0, v, bias, gate);
+        for (int k = 0; k < CH; ++k) {
+            const int q = c * CH + k, r = q % R, p = q / R;
+            const int row = m0 + 16 * (I0 + r) + l16, col = c0 + 32 * p;
+            if (r == 0 && p + 1 < P && col + 40 <= N) cols[(p + 1) & 1].load(ep, col + 32);
+            if (q < Q && row < M && col + 8 <= N)
+                epilogue_store8<KIND, SCALED, ALIGNED>(ep, row, col, acc[I0 + r][q < Q ? 2 * p : 0], acc[I0 + r][q < Q ? 2 * p + 1 : 0], cols[p & 1], rows[r], raw[c & 1][k]);
         }
     }
 }
-template <int KIND, bool SCALED, int I0, int I1, int RF, int CF, int B>
-__device__ __forceinline__ void gemm_epilogue16_pair(f32x4 (&acc)[RF][CF], int M, int N, int m0, int n0w, const GemmEpilogue& ep) {
-    const int lane = threadIdx.x & 63, l16 = lane & 15;
-    const int col0 = n0w + 32 * B + 8 * (lane >> 4);
-    if (ep.vec_ok) {
-        if (col0 < N) gemm_epilogue16_wide<KIND, SCALED, I0, I1, RF, CF, B, true>(acc, M, m0, col0, ep);    // N is a multiple of 8 on this path
-    } else if (KIND != EPI_QKV && col0 + 8 <= N) {
-        // odd widths or unaligned tensors: the same pieces without their alignment, which the memory path takes as it is.  One element at
-        // a time cost as much as the product (us): 11844 x 9156 x 832 358 -> 171, 543 x 9522 x 384 24 -> 13, 10605 x 201 x 5568 55 -> 45;
-        // velocity heads on 8704 rows of 65 channels 37 -> 27, of 100 45 -> 27
-        gemm_epilogue16_wide<KIND, SCALED, I0, I1, RF, CF, B, false>(acc, M, m0, col0, ep);
-    } else {
+template <int KIND, bool SCALED, int I0, int I1, int RF, int CF>
+__device__ __forceinline__ void gemm_epilogue16(const f32x4 (&acc)[RF][CF], int M, int N, int m0, int n0w, const GemmEpilogue& ep) {
+    if (ep.vec_ok) {                    // N is a multiple of 8
+        gemm_epilogue16_wide<KIND, SCALED, I0, I1, RF, CF, true>(acc, M, N, m0, n0w, ep);
+        return;
+    }
+    // odd widths or unaligned tensors: the same pieces without their alignment, which the memory path takes as it is.  One element at
+    // a time cost as much as the product (us): 11844 x 9156 x 832 358 -> 171, 543 x 9522 x 384 24 -> 13, 10605 x 201 x 5568 55 -> 45;
+    // velocity heads on 8704 rows of 65 channels 37 -> 27, of 100 45 -> 27
+    if (KIND != EPI_QKV) gemm_epilogue16_wide<KIND, SCALED, I0, I1, RF, CF, false>(acc, M, N, m0, n0w, ep);
+    const int l16 = threadIdx.x & 15, c0 = n0w + 8 * ((threadIdx.x & 63) >> 4);
 #pragma unroll
-        for (int i = I0; i < I1; ++i) {
-            const int row = m0 + 16 * i + l16;
-            if (row < M) {
-                if (KIND == EPI_VELOCITY) {
-                    float v[8];
+    for (int p = 0; p < CF / 2; ++p)
+        if (c0 + 32 * p < N && (KIND == EPI_QKV || c0 + 32 * p + 8 > N)) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] = acc[i][2 * B + (e >> 2)][e & 3] + (ep.bias && col0 + e < N ? ep.bias[col0 + e] : 0.f);
-                    epilogue_velocity<false, false>(ep, row, col0, N - col0, v);
-                    continue;
-                }
-                const float rs = SCALED ? ep.row_scale[row] : 1.f;
-                const int64_t kv_row = epilogue_kv_row<KIND>(ep, row);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int col = col0 + e;
-                    if (col < N) {
-                        const float a = acc[i][2 * B + (e >> 2)][e & 3] * (SCALED ? rs * ep.col_scale[col] : 1.f);
-                        epilogue_store<KIND>(ep, row, kv_row, col, a, ep.bias ? ep.bias[col] : 0.f, (KIND == EPI_RESID && ep.gate) ? ep.gate[col] : 1.f);
-                    }
-                }
+            for (int i = I0; i < I1; ++i) {
+                const int row = m0 + 16 * i + l16;
+                if (row < M) epilogue_ragged<KIND, SCALED>(ep, row, c0 + 32 * p, N, acc[i][2 * p], acc[i][2 * p + 1]);
             }
         }
-    }
-}
-// rows of fragments [I0, I1)
-template <int KIND, bool SCALED, int I0, int I1, int RF, int CF>
-__device__ __forceinline__ void gemm_epilogue16(f32x4 (&acc)[RF][CF], int M, int N, int m0, int n0w, const GemmEpilogue& ep) {
-    gemm_epilogue16_pair<KIND, SCALED, I0, I1, RF, CF, 0>(acc, M, N, m0, n0w, ep);
-    if constexpr (CF >= 4) gemm_epilogue16_pair<KIND, SCALED, I0, I1, RF, CF, 1>(acc, M, N, m0, n0w, ep);
-    if constexpr (CF >= 6) gemm_epilogue16_pair<KIND, SCALED, I0, I1, RF, CF, 2>(acc, M, N, m0, n0w, ep);
 }
 // one operand of the 8-bit instruction out of the two 16-byte pieces that the 16-bit form feeds to two instructions
 __device__ __forceinline__ i32x8 pp_pair(const bf16x8& lo, const bf16x8& hi) {

@@ -64,6 +64,9 @@ __device__ __forceinline__ unsigned pp_w_slot(unsigned lane, unsigned jl) {
     return (kc >> 1) * 1024u + ((kc & 1) * 32u + jl * 16u + g0 * 8u + (g1 ^ jl) * 4u + u) * 16u;
 }
 
+// the largest divisor of F up to 8: fragments that are requested together when partial sums are added
+constexpr int pp_group(int F) { int g = F < 8 ? F : 8; while (F % g) --g; return g; }
+
 // The end of a tile: fragments [I0, I1) x CF of a wave.  K splits: every workgroup of a tile leaves its sums in `partial`
 // (in register order: whole lines), and the one that arrives last adds all of them in split order (the same sums whoever
 // is last) and goes on to the epilogue.  Nobody waits.  wave_slot: the wave's place among the tile's WAVES fragment sets.
@@ -90,23 +93,32 @@ __device__ __forceinline__ void pp_finish(f32x4 (&acc)[RF][CF], unsigned char* l
         __syncthreads();
         if (*flag != splits - 1) return;
         if (threadIdx.x == 0) __hip_atomic_store(arrived + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
-        constexpr int F = (I1 - I0) * CF, G = F > 16 ? (F + 1) / 2 : F;   // fragments in flight per lane
-        for (int s = 0; s < splits; ++s) {
+        // Fragments in groups of G, split after split; the next request (the last one repeats itself) is on its way while the sums of one are added.
+        constexpr int F = (I1 - I0) * CF, G = pp_group(F);
+        u32x4 v[2][G];
+        auto request = [&](int b, int h, int s) __attribute__((always_inline)) {
+            const int off = s * static_cast<int>(part_bytes) + h * 1024;
 #pragma unroll
-            for (int h = 0; h < F; h += G) {
-                u32x4 v[G];
+            for (int f = 0; f < G; ++f) v[b][f] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, part_off + (I0 * CF + f) * 1024u, off, kDeviceScope);
+        };
+        auto add = [&](int b, int h, int s) __attribute__((always_inline)) {
 #pragma unroll
-                for (int f = 0; f < G; ++f)
-                    if (h + f < F) v[f] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, part_off + (I0 * CF + h + f) * 1024u, s * part_bytes, kDeviceScope);
-#pragma unroll
-                for (int f = 0; f < G; ++f)
-                    if (h + f < F) {
-                        f32x4& a = acc[I0 + (h + f) / CF][(h + f) % CF];
-                        const f32x4 x = __builtin_bit_cast(f32x4, v[f]);
-                        a = s == 0 ? x : a + x;
-                    }
+            for (int f = 0; f < G; ++f) {
+                f32x4& a = acc[I0 + (h + f) / CF][(h + f) % CF];
+                const f32x4 x = __builtin_bit_cast(f32x4, v[b][f]);
+                a = s == 0 ? x : a + x;
             }
-        }
+        };
+        request(0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < F; h += G)
+            for (int s = 0; s < splits; s += 2) {
+                request(1, h, s + 1 < splits ? s + 1 : s);
+                add(0, h, s);
+                const bool more = s + 2 < splits;
+                request(0, more || h + G >= F ? h : h + G, more ? s + 2 : 0);
+                if (s + 1 < splits) add(1, h, s + 1);
+            }
     }
     gemm_epilogue16<KIND, FP8, I0, I1, RF, CF>(acc, M, N, m0, n0w, ep);
 }

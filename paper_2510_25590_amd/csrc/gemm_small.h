@@ -56,9 +56,21 @@ gemm_small_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict_
     const bf16_t* ap = LN == LN_NONE ? static_cast<const bf16_t*>(A) + static_cast<int64_t>(row) * lda + 8 * quad : nullptr;
     const unsigned a_lds = static_cast<unsigned>(l16) * ln_row_bytes(K) + 16u * quad;
 
-    f32x4 acc[1][CF];
+    // The launch is a chain of trips to memory: what the epilogue reads is requested first, by the waves that finish the tile (wave b block b of 32 columns)
+    const int fin_col = n0 + 32 * wave + 8 * quad;
+    const bool finishes = wave < CF / 2, whole = (ep.vec_ok || KIND != EPI_QKV) && fin_col + 8 <= N;
+    EpiColumns<KIND, false> fin_cols;
+    EpiRow<KIND, false> fin_row;
+    Raw8 fin_raw;
+    if (finishes && whole) {
+        fin_row.load(ep, row);
+        fin_cols.load(ep, fin_col);
+        if (epi_reads<KIND>()) fin_raw = ep.vec_ok ? epi_load8<KIND, true>(ep, row, fin_col) : epi_load8<KIND, false>(ep, row, fin_col);
+    }
+
+    f32x4 acc[CF];
 #pragma unroll
-    for (int j = 0; j < CF; ++j) acc[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < CF; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     bf16x8 a[CHUNK], w[CHUNK][CF];
     auto load_w = [&](int base) __attribute__((always_inline)) {
 #pragma unroll
@@ -97,29 +109,26 @@ gemm_small_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict_
         for (int i = 0; i < CHUNK; ++i)
             if (base + i < s1) {
 #pragma unroll
-                for (int j = 0; j < CF; ++j) acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i][j], a[i], acc[0][j], 0, 0, 0);
+                for (int j = 0; j < CF; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i][j], a[i], acc[j], 0, 0, 0);
             }
     }
     if (LN != LN_NONE) __syncthreads();                         // the rows have been read
     f32x4* sums = reinterpret_cast<f32x4*>(lds) + lane;
 #pragma unroll
-    for (int j = 0; j < CF; ++j) sums[(wave * CF + j) * 64] = acc[0][j];
+    for (int j = 0; j < CF; ++j) sums[(wave * CF + j) * 64] = acc[j];
     __syncthreads();
-    if (wave >= CF / 2) return;
-    // wave b finishes block b of 32 columns
+    if (!finishes) return;
+    f32x4 sum[2];
 #pragma unroll
-    for (int b = 0; b < CF / 2; ++b)
-        if (wave == b) {
+    for (int jl = 0; jl < 2; ++jl) {
+        sum[jl] = sums[(2 * wave + jl) * 64];
 #pragma unroll
-            for (int jl = 0; jl < 2; ++jl) {
-                f32x4 s = sums[(2 * b + jl) * 64];
-#pragma unroll
-                for (int v = 1; v < kSmallWaves; ++v) s += sums[(v * CF + 2 * b + jl) * 64];
-                acc[0][2 * b + jl] = s;
-            }
-        }
-    if (wave == 0) gemm_epilogue16_pair<KIND, false, 0, 1, 1, CF, 0>(acc, M, N, m0, n0, ep);
-    if constexpr (CF >= 4) { if (wave == 1) gemm_epilogue16_pair<KIND, false, 0, 1, 1, CF, 1>(acc, M, N, m0, n0, ep); }
+        for (int v = 1; v < kSmallWaves; ++v) sum[jl] += sums[(v * CF + 2 * wave + jl) * 64];
+    }
+    if (m0 + l16 >= M || fin_col >= N) return;
+    if (!whole) epilogue_ragged<KIND, false>(ep, row, fin_col, N, sum[0], sum[1]);
+    else if (ep.vec_ok) epilogue_store8<KIND, false, true>(ep, row, fin_col, sum[0], sum[1], fin_cols, fin_row, fin_raw);
+    else epilogue_store8<KIND, false, false>(ep, row, fin_col, sum[0], sum[1], fin_cols, fin_row, fin_raw);
 }
 
 template <int CF, int KIND, int LN>
