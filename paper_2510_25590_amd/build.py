@@ -14,11 +14,11 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libregione.so")
-SOURCES = ["api.hip", "partition.hip", "rows.hip", "gemm.hip", "gemm_tiles_wide.hip", "gemm_tiles_128.hip", "gemm_tiles_96.hip", "gemm_tiles_fp8.hip",
+SOURCES = ["api.hip", "partition.hip", "rows.hip", "gemm.hip", "gemm_tiles_wide.hip", "gemm_tiles_128.hip", "gemm_tiles_96.hip", "gemm_tiles_kg.hip", "gemm_tiles_fp8.hip",
            "attention.hip", "block_extras.hip", "fp8.hip", "peaks.hip", "fp32.hip", "host_logic.cpp"]
 
 # sources whose machine code is checked, and by which function of isa_check.py
-CHECKED = {**dict.fromkeys(("gemm.hip", "gemm_tiles_wide.hip", "gemm_tiles_128.hip", "gemm_tiles_96.hip", "gemm_tiles_fp8.hip"), "check_asm"),
+CHECKED = {**dict.fromkeys(("gemm.hip", "gemm_tiles_wide.hip", "gemm_tiles_128.hip", "gemm_tiles_96.hip", "gemm_tiles_kg.hip", "gemm_tiles_fp8.hip"), "check_asm"),
            "attention.hip": "check_attention_asm"}
 
 

@@ -34,18 +34,20 @@ pack_weight_kernel(const bf16_t* __restrict__ w, int n, int k, bf16_t* __restric
 
 // ---- which tile and how many K splits
 //
-// A plan's time is estimated from what bounds its K-steps on this chip (cycles per step of 64 k and workgroup, measured):
-//   matrix cores : ROWS * COLS / 32 (both wave groups' MFMAs, 16 cycles each on four SIMDs) and about 60 of barriers;
-//   operand feed : 28 per KiB copied into LDS (the CU's address path; the L2 delivers what it asks for);
-//   latency      : 450-500, two steps of copies in flight;
-// at 2.2 GHz less what the matrix cores' power takes from the clock (0.45 GHz when all of them are busy), plus 7 us of launch,
-// first copies and epilogue per round of workgroups.  A K split adds its partial sums' way out and back (padded tiles).
-// Against the best of all plans, timed over 126 shapes (36-8704 rows, 256-21504 columns, k 256-15360), the choice loses 1.1 %
-// on average and 13 % at most.
-struct TileShape { int code, rows, cols, lds_kb, form; };   // form: kTilesFp8 only
-constexpr TileShape kTiles[] = {{222, 64, 64, 64},    {224, 64, 128, 96},   {242, 128, 64, 96},   {244, 128, 128, 128}, {274, 224, 128, 132}, {284, 256, 128, 144},
-                                {426, 128, 96, 112},  {436, 192, 96, 144},  {446, 256, 96, 132},  {44, 128, 256, 144},  {64, 192, 256, 136},  {74, 224, 256, 148},
-                                {84, 256, 256, 160}};
+// A plan's time is estimated from what bounds its K-steps on this chip (cycles per step of 64 k and workgroup):
+//   matrix cores : ROWS * COLS / 32 (both wave groups' MFMAs, 16 cycles each on four SIMDs) and what the barriers cost;
+//   operand feed : 29.6 per KiB copied into LDS (the CU's address path; the L2 delivers what it asks for);
+//   latency      : two steps of copies in flight;
+// at 2.2 GHz, times a factor of the tile that takes in its start, its epilogue and what the matrix cores' power takes from the clock; not below the time that the
+// weights take from HBM.  A K split adds its partial sums' way out and back (padded tiles).
+// All constants are fitted to every tile and K split of 267 shapes (32-9400 rows, 1024-21504 columns, k 1024-15360, weights of 3072-wide models uncached).  Against
+// the best of all plans the choice loses 0.6 % on average over these and over 143 others, 7 % at most on those; the constants before, fitted without the three widest tiles of gemm_kg_kernel,
+// lost 2.0 % with them.  us, then / now: 2048 x 9216 x 3072 103.3 / 95.8, 1640 x 12288 x 3072 103.5 / 98.9, 1382 x 3072 x 15360 116.7 / 109.9, 205 x 21504 x 3072 43.8 / 41.6.
+struct TileShape { int code, rows, cols, lds_kb, form; double factor; };   // form: kTilesFp8 only; factor: kTiles only
+constexpr TileShape kTiles[] = {{222, 64, 64, 64, 0, 1.089},   {224, 64, 128, 96, 0, 1.156},  {242, 128, 64, 96, 0, 1.056},  {244, 128, 128, 128, 0, 1.059},
+                                {274, 224, 128, 132, 0, 1.054}, {284, 256, 128, 144, 0, 1.381}, {426, 128, 96, 112, 0, 1.058}, {436, 192, 96, 144, 0, 1.114},
+                                {446, 256, 96, 132, 0, 0.985}, {44, 128, 256, 144, 0, 1.028}, {64, 192, 256, 136, 0, 1.143}, {74, 224, 256, 148, 0, 1.065},
+                                {84, 256, 256, 160, 0, 1.011}, {248, 128, 256, 144, 0, 1.402}, {266, 192, 192, 144, 0, 1.021}, {276, 224, 192, 156, 0, 1.012}};
 struct GemmPlan { int tile; int splits; };
 
 double plan_time_bf16(const TileShape& t, int m, int n, int steps, int splits) {
@@ -53,24 +55,24 @@ double plan_time_bf16(const TileShape& t, int m, int n, int steps, int splits) {
     const long units = static_cast<long>(m_tiles) * n_tiles * splits;
     const int per = (steps + splits - 1) / splits;
     const bool narrow = t.code >= 200;
-    const double mfma = t.rows * t.cols / 32.0, feed = 28.0 * (t.rows + t.cols) / 8.0;
-    double step = mfma + (narrow ? 120.0 : 60.0);
+    const double mfma = t.rows * t.cols / 32.0, feed = 29.55 * (t.rows + t.cols) / 8.0;
+    double step = mfma + (narrow ? 174.9 : 93.0);
     if (feed > step) step = feed;
-    if (step < (narrow ? 450.0 : 500.0)) step = narrow ? 450.0 : 500.0;
-    if (narrow) step += 53.0;
+    if (step < (narrow ? 546.2 : 310.6)) step = narrow ? 546.2 : 310.6;
+    if (narrow) step += 59.5;
     const double active = units < 256 ? units / 256.0 : 1.0, live = static_cast<double>(m) / (static_cast<double>(m_tiles) * t.rows);
-    const double mhz = 2200.0 - 455.0 * (mfma / step * active * live);
+    const double mhz = 2200.0 - 23.2 * (mfma / step * active * live);
     const long slots = t.lds_kb <= 80 ? 512 : 256;
     const long full = units / slots, rem = units % slots;
-    const double one = per * step / mhz;
-    auto round_time = [&](long u) { return one * (slots > 256 && u > 256 ? 2.35 : 1.0) + 6.9; };
+    const double one = per * step / mhz * t.factor;
+    auto round_time = [&](long u) { return one * (slots > 256 && u > 256 ? 4.13 : 1.0) + 0.14; };
     double us = full * round_time(slots) + (rem > 0 ? round_time(rem) : 0.0);
-    const double hbm = static_cast<double>(n) * steps * 128.0 / 5.5e6 + 6.9;      // the weights once from HBM
+    const double hbm = static_cast<double>(n) * steps * 128.0 / 7.18e6 + 0.14;     // the weights once from HBM
     if (us < hbm) us = hbm;
-    us += static_cast<double>(m) * n * 2.0 / 8.0e6;
+    us += static_cast<double>(m) * n * 2.0 / 128.0e6;
     if (splits > 1) {
         const double tile_kb = t.rows * t.cols * 4.0 / 1e3;
-        us += 1.8 + 0.19 * units * tile_kb / 1e3 + 0.0116 * splits * tile_kb;
+        us += 1.44 + 0.132 * units * tile_kb / 1e3 + 0.0267 * splits * tile_kb;
     }
     return us;
 }
@@ -196,6 +198,7 @@ bool wide_epilogue_ok(const GemmEpilogue& ep, int n) {
 }  // namespace
 
 static int gemm_tile(regione_ctx* ctx, const GemmPlan& p, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, const GemmEpilogue& ep) {
+    if (p.tile == 248 || p.tile == 266 || p.tile == 276) return rg_gemm_tile_kg(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
     if (p.tile >= 400) return rg_gemm_tile_96(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
     if (p.tile >= 200) return rg_gemm_tile_128(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
     return rg_gemm_tile_wide(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);

@@ -315,15 +315,26 @@ template <int I0, int I1, int RF, int CF> __device__ __forceinline__ void kg_add
         for (int j = 0; j < CF; ++j) acc[i][j] += ex[(i * CF + j) * 64];
 }
 // The end of a tile: rows [0, H) of the fragments are finished by group 0, the rest by group 1.  A macro: through a function that
-// holds both groups' branches the accumulators end up in scratch memory.
+// holds both groups' branches the accumulators end up in scratch memory.  Where the whole tile's sums do not fit into LDS (224 x 192) the groups
+// put their halves there one after the other.
 #define KG_FINISH(FP8)                                                                                      \
     {                                                                                                       \
         constexpr int H = (RF + 1) / 2;                                                                     \
-        f32x4* ex = reinterpret_cast<f32x4*>(lds_raw) + static_cast<unsigned>(w4) * (RF * CF * 64) + lane;  \
+        f32x4* ex = reinterpret_cast<f32x4*>(lds_raw) + static_cast<unsigned>(w4) * (T::EX_ROWS * CF * 64) + lane; \
         const int tile = n_tile * m_tiles + m_tile, m0 = m0_wg + wm * (RF * 16), n0w = n0 + wn * (16 * CF); \
-        if (kg == 1) kg_put<0, H>(acc, ex); else kg_put<H, RF>(acc, ex);                                    \
-        __syncthreads();                                                                                    \
-        if (kg == 0) kg_add<0, H>(acc, ex); else kg_add<H, RF>(acc, ex);                                    \
+        if constexpr (T::EX_ROWS == RF) {                                                                   \
+            if (kg == 1) kg_put<0, H>(acc, ex); else kg_put<H, RF>(acc, ex);                                \
+            __syncthreads();                                                                                \
+            if (kg == 0) kg_add<0, H>(acc, ex); else kg_add<H, RF>(acc, ex);                                \
+        } else {                                                                                            \
+            if (kg == 1) kg_put<0, H>(acc, ex);                                                             \
+            __syncthreads();                                                                                \
+            if (kg == 0) kg_add<0, H>(acc, ex);                                                             \
+            __syncthreads();                                                                                \
+            if (kg == 0) kg_put<H, RF>(acc, ex - H * CF * 64);                                              \
+            __syncthreads();                                                                                \
+            if (kg == 1) kg_add<H, RF>(acc, ex - H * CF * 64);                                              \
+        }                                                                                                   \
         if (splits > 1) __syncthreads();   /* the area is read before the arrival flag is written into it */ \
         if (kg == 0) pp_finish<0, H, RF, CF, KIND, FP8>(acc, lds_raw, w4, T::PART_FLOATS, tile, split, splits, partial, arrived, M, N, m0, n0w, ep); \
         else pp_finish<H, RF, RF, CF, KIND, FP8>(acc, lds_raw, w4, T::PART_FLOATS, tile, split, splits, partial, arrived, M, N, m0, n0w, ep); \
@@ -337,7 +348,8 @@ template <int RF, int CF, int WM> struct KgTile {
     static constexpr int A_COPIES = ROWS / 8, COPIES = A_COPIES + COLS / 8, CW = (COPIES + 7) / 8;   // 1 KiB copies per K-step, per wave
     static constexpr unsigned STEP = COPIES * 1024u, W_BASE = A_COPIES * 1024u;
     static constexpr int NS = STEP > 40960u ? 3 : 4;                // K-steps in LDS
-    static constexpr unsigned ACC_BYTES = ROWS * COLS * 4u;         // the exchange at the end
+    static constexpr int EX_ROWS = ROWS * COLS * 4u <= 163840u ? RF : (RF + 1) / 2;   // fragment rows of a wave in the exchange at the end
+    static constexpr unsigned ACC_BYTES = 4u * EX_ROWS * CF * 1024u;
     static constexpr unsigned LDS_BYTES = NS * STEP > ACC_BYTES ? NS * STEP : ACC_BYTES;
     static constexpr int64_t PART_FLOATS = static_cast<int64_t>(ROWS) * COLS;
     static_assert(COLS % 32 == 0 && ROWS % 32 == 0 && LDS_BYTES <= 163840u, "whole weight blocks, and what a CU has");
@@ -456,7 +468,8 @@ template <int RF, int CF, int WM> struct Kg8Tile {
     static constexpr unsigned STEP = (ROWS + COLS) * 128u, W_BASE = ROWS * 128u;
     static constexpr int LOOK = 5 * STEP <= 163840u ? 2 : 1;        // own steps that the copies run ahead
     static constexpr int NS = 2 * LOOK + 1;                         // steps in LDS
-    static constexpr unsigned ACC_BYTES = ROWS * COLS * 4u;         // the exchange at the end
+    static constexpr int EX_ROWS = ROWS * COLS * 4u <= 163840u ? RF : (RF + 1) / 2;   // fragment rows of a wave in the exchange at the end
+    static constexpr unsigned ACC_BYTES = 4u * EX_ROWS * CF * 1024u;
     static constexpr unsigned LDS_BYTES = NS * STEP > ACC_BYTES ? NS * STEP : ACC_BYTES;
     static constexpr int64_t PART_FLOATS = static_cast<int64_t>(ROWS) * COLS;
     static_assert(COLS % 32 == 0 && ROWS % 32 == 0 && LDS_BYTES <= 163840u, "whole weight blocks, and what a CU has");
