@@ -30,6 +30,7 @@ def test_activation_over_the_whole_range(tile):
     assert np.array_equal(got[0], got[1], equal_nan=True) and np.array_equal(got[0], got[2], equal_nan=True)
     assert np.array_equal(np.isnan(got[0]), np.isnan(v)) and np.array_equal(np.isposinf(got[0]), np.isposinf(v))
     ok = np.isfinite(v)
-    # the exponent 2u carries a few roundings of 2^-24 each, the exponential and the quotient one more each; results below the smallest normal number may be flushed
-    bound = np.abs(want[ok]) * (8 * np.minimum(np.abs(u[ok]), 50) + 4) * 2.0 ** -24 + 1.2e-38
+    # the exponent 2u carries a few roundings of 2^-24 each, the exponential and the quotient one more each; a divisor above 2^126 has no
+    # normal reciprocal, so that results below |x| 2^-126 may be flushed to zero
+    bound = np.abs(want[ok]) * (8 * np.minimum(np.abs(u[ok]), 50) + 4) * 2.0 ** -24 + np.abs(v[ok]) * 2.0 ** -126 * (np.abs(want[ok]) < 1e-30)
     assert np.all(np.abs(got[0][ok] - want[ok]) <= bound)
