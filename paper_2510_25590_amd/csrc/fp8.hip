@@ -2,12 +2,26 @@
 // Generation"); an extension, the paper itself computes in the model's precision.  This file: per-row quantisation
 // and the entry points; the matrix-core kernel is the 8-bit form of the LDS GEMM in gemm.hip.
 #include "common.h"
+#include "layernorm_row.h"
+#include <type_traits>
 
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 
 constexpr float kE4M3Max = 448.0f;
+
+__device__ __forceinline__ uint2 fp8_codes(const float (&x)[8], float mult) {
+    float y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = __builtin_fminf(__builtin_fmaxf(x[e] * mult, -kE4M3Max), kE4M3Max);
+    unsigned lo = 0, hi = 0;
+    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
+    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
+    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
+    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
+    return make_uint2(lo, hi);
+}
 
 // TPR threads per row (64: four rows per workgroup, 256: one); the row stays in registers between the maximum and the
 // conversion (up to 8 16-byte pieces per thread, so 4096 columns per wave and 16384 per workgroup).
@@ -52,33 +66,16 @@ quantize_rows_fp8_kernel(const bf16_t* __restrict__ x, int64_t rows, int cols, u
         if (p < pieces) {
             float y[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) y[e] = __builtin_fminf(__builtin_fmaxf(static_cast<float>(v[i][e]) * mult, -kE4M3Max), kE4M3Max);
-            unsigned lo = 0, hi = 0;
-            lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
-            lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
-            hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
-            hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
-            dst[p] = make_uint2(lo, hi);
+            for (int e = 0; e < 8; ++e) y[e] = static_cast<float>(v[i][e]);
+            dst[p] = fp8_codes(y, mult);
         }
     }
 }
 
 // LayerNorm + modulation (as layernorm_mod_vec_kernel in rows.hip: no affine, biased variance, eps 1e-6, two passes in
 // float32, u = y * (1 + scale) + shift) with the row quantisation above applied to its float32 result while the row is
-// still in registers: the bf16 rounding of u, its store and the quantiser's load of it fall away.  One wave per row.
-typedef __attribute__((ext_vector_type(4))) float q_f32x4;
-template <typename T> __device__ __forceinline__ void q_ld8(const T* p, float (&v)[8]);
-template <> __device__ __forceinline__ void q_ld8<bf16_t>(const bf16_t* p, float (&v)[8]) {
-    const bf16x8 x = *reinterpret_cast<const bf16x8*>(p);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = static_cast<float>(x[e]);
-}
-template <> __device__ __forceinline__ void q_ld8<float>(const float* p, float (&v)[8]) {
-    const q_f32x4 a = *reinterpret_cast<const q_f32x4*>(p), b = *reinterpret_cast<const q_f32x4*>(p + 4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
-}
-
+// still in registers: the bf16 rounding of u, its store and the quantiser's load of it fall away.  One wave per row of at most
+// 1024 values.
 template <typename T, int MAXV>
 __global__ void __launch_bounds__(256)
 layernorm_mod_fp8_kernel(const T* __restrict__ h, int n, int hidden, const float* __restrict__ shift, const float* __restrict__ scale,
@@ -94,7 +91,7 @@ layernorm_mod_fp8_kernel(const T* __restrict__ h, int n, int hidden, const float
     for (int i = 0; i < MAXV; ++i) {
         const int g = lane + 64 * i;
         if (g < groups) {
-            q_ld8<T>(hr + g * 8, x[i]);
+            ld8<T>(hr + g * 8, x[i]);
 #pragma unroll
             for (int e = 0; e < 8; ++e) sum += x[i][e];
         }
@@ -119,8 +116,8 @@ layernorm_mod_fp8_kernel(const T* __restrict__ h, int n, int hidden, const float
         const int g = lane + 64 * i;
         if (g < groups) {
             float sc[8], sh[8];
-            if (scale) q_ld8<float>(scale + g * 8, sc);
-            if (shift) q_ld8<float>(shift + g * 8, sh);
+            if (scale) ld8<float>(scale + g * 8, sc);
+            if (shift) ld8<float>(shift + g * 8, sh);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float y = (x[i][e] - mean) * rstd;
@@ -140,17 +137,35 @@ layernorm_mod_fp8_kernel(const T* __restrict__ h, int n, int hidden, const float
     for (int i = 0; i < MAXV; ++i) {
         const int g = lane + 64 * i;
         if (g < groups) {
-            float y[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) y[e] = __builtin_fminf(__builtin_fmaxf(x[i][e] * mult, -kE4M3Max), kE4M3Max);
-            unsigned lo = 0, hi = 0;
-            lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
-            lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
-            hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
-            hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
-            dst[g] = make_uint2(lo, hi);
+            dst[g] = fp8_codes(x[i], mult);
         }
     }
+}
+
+// The same for rows of more than 1024 values, a workgroup of W waves per row (layernorm_rows_wide); the waves' maxima meet in LDS like their sums.
+template <typename T, int W>
+__global__ void __launch_bounds__(64 * W)
+layernorm_mod_fp8_wide_kernel(const T* __restrict__ h, int n, int hidden, const float* __restrict__ shift, const float* __restrict__ scale,
+                              uint8_t* __restrict__ q, float* __restrict__ row_scale) {
+    __shared__ float2 part[2][W];
+    __shared__ float most[2][W];
+    int turn = 0;
+    layernorm_rows_wide<T, W>(h, n, hidden, shift, scale, part, [](int row) -> int64_t { return row; },
+                              [&](int row, int g, bool live, const LnRaw<T>&, const float (&o)[8]) {
+        float amax = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) amax = __builtin_fmaxf(amax, live ? __builtin_fabsf(o[e]) : 0.f);
+        amax = wave_max(amax);
+        if ((threadIdx.x & 63) == 0) most[turn][threadIdx.x >> 6] = amax;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < W; ++w) amax = __builtin_fmaxf(amax, most[turn][w]);
+        turn ^= 1;
+        const bool any = amax > 0.f;
+        const float mult = any ? kE4M3Max / amax : 1.0f;
+        if (threadIdx.x == 0) row_scale[row] = any ? amax / kE4M3Max : 1.0f;
+        if (live) reinterpret_cast<uint2*>(q + static_cast<int64_t>(row) * hidden)[g] = fp8_codes(o, mult);
+    });
 }
 
 }  // namespace
@@ -162,9 +177,14 @@ int rg_layernorm_mod_fp8(regione_ctx* ctx, const void* h, int h_f32, int n, int 
     if (!rg_aligned16(h) || !rg_aligned16(q) || (shift && !rg_aligned16(shift)) || (scale && !rg_aligned16(scale)))
         RG_FAIL(REGIONE_ERR_INVALID_ARG, "layernorm_fp8: tensors must be 16-byte aligned");
     ProfScope prof(ctx, REGIONE_PROF_LAYERNORM);
-    const dim3 grid((n + 3) / 4);
-    if (h_f32) hipLaunchKernelGGL((layernorm_mod_fp8_kernel<float, 8>), grid, dim3(256), 0, ctx->stream, static_cast<const float*>(h), n, hidden, shift, scale, q, row_scale);
-    else hipLaunchKernelGGL((layernorm_mod_fp8_kernel<bf16_t, 8>), grid, dim3(256), 0, ctx->stream, static_cast<const bf16_t*>(h), n, hidden, shift, scale, q, row_scale);
+    auto launch = [&](auto* rows) {
+        typedef std::remove_const_t<std::remove_pointer_t<decltype(rows)>> T;
+        if (hidden <= 1024) { hipLaunchKernelGGL((layernorm_mod_fp8_kernel<T, 2>), dim3((n + 3) / 4), dim3(256), 0, ctx->stream, rows, n, hidden, shift, scale, q, row_scale); return; }
+#define RG_LN_WIDE(W) case W: hipLaunchKernelGGL((layernorm_mod_fp8_wide_kernel<T, W>), dim3(n < ln_wide_grid(W) ? n : ln_wide_grid(W)), dim3(64 * W), 0, ctx->stream, rows, n, hidden, shift, scale, q, row_scale); break;
+        switch ((hidden / 8 + 63) / 64) { RG_LN_WIDE(3) RG_LN_WIDE(4) RG_LN_WIDE(5) RG_LN_WIDE(6) RG_LN_WIDE(7) RG_LN_WIDE(8) }
+#undef RG_LN_WIDE
+    };
+    if (h_f32) launch(static_cast<const float*>(h)); else launch(static_cast<const bf16_t*>(h));
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }

@@ -136,9 +136,9 @@ velocity_cache_kernel(int reuse, float factor, float dt, const T* __restrict__ v
     }
 }
 
-// LayerNorm over H with modulation, one wave per row (see layernorm_row).  Bound by the latency of its loads: 36 float32 rows of 256 values take 5.2 us in the kernel of
-// scalar loads below, 3.8 here with the registers and code of eight rounds of loads, 3.2 with those of the one round that such a row needs (in a kernel trace; among a
-// step's launches the call gains about 3 us of 65).  8704 rows: of 256 values 10.0 -> 4.8 (bf16), 10.7 -> 5.5 (float32); of 1024 13.4 -> 7.8, 17.5 -> 14.6.  U: the output's storage type (bf16, or float32 in a float32 context).
+// LayerNorm over H with modulation, one wave per row of at most 1024 values (see layernorm_row).  Bound by the latency of its loads: 36 float32 rows of 256 values take
+// 5.2 us in the kernel of scalar loads below, 3.2 here, with registers and code for as many rounds of 512 values as the row has (in a kernel trace).  8704 rows: of 256 values
+// 4.8 us (bf16), 5.5 (float32); of 1024 7.8, 14.6.  U: the output's storage type (bf16, or float32 in a float32 context).
 template <typename T, typename U, int MAXV>
 __global__ void __launch_bounds__(kThreads)
 layernorm_mod_vec_kernel(const T* __restrict__ h, int n, int hidden, const float* __restrict__ shift,
@@ -147,6 +147,16 @@ layernorm_mod_vec_kernel(const T* __restrict__ h, int n, int hidden, const float
     if (row >= n) return;
     U* ur = u + static_cast<int64_t>(row) * hidden;
     layernorm_row<T, MAXV>(h + static_cast<int64_t>(row) * hidden, hidden, shift, scale, [&](int g, const float (&o)[8]) { st8<U>(ur + g * 8, o); });
+}
+
+// Rows of more than 1024 values: a workgroup per row (layernorm_rows_wide).
+template <typename T, typename U, int W>
+__global__ void __launch_bounds__(64 * W)
+layernorm_mod_wide_kernel(const T* __restrict__ h, int n, int hidden, const float* __restrict__ shift,
+                          const float* __restrict__ scale, U* __restrict__ u) {
+    __shared__ float2 part[2][W];
+    layernorm_rows_wide<T, W>(h, n, hidden, shift, scale, part, [](int row) -> int64_t { return row; },
+                              [&](int row, int g, bool live, const LnRaw<T>&, const float (&o)[8]) { if (live) st8<U>(u + static_cast<int64_t>(row) * hidden + g * 8, o); });
 }
 
 // Any H: scalar loads, three passes over the row.
@@ -460,7 +470,11 @@ static void launch_layernorm(regione_ctx* ctx, const T* h, int n, int hidden, co
     // as many registers and as much code as the row has rounds of 512 elements
     if (vec && hidden <= 512) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 1>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
     else if (vec && hidden <= 1024) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 2>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
-    else if (vec) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 8>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
+    else if (vec) {
+#define RG_LN_WIDE(W) case W: hipLaunchKernelGGL((layernorm_mod_wide_kernel<T, U, W>), dim3(n < ln_wide_grid(W) ? n : ln_wide_grid(W)), dim3(64 * W), 0, ctx->stream, h, n, hidden, shift, scale, u); break;
+        switch ((hidden / 8 + 63) / 64) { RG_LN_WIDE(3) RG_LN_WIDE(4) RG_LN_WIDE(5) RG_LN_WIDE(6) RG_LN_WIDE(7) RG_LN_WIDE(8) }
+#undef RG_LN_WIDE
+    }
     else hipLaunchKernelGGL((layernorm_mod_kernel<T, U>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
 }
 
