@@ -521,6 +521,7 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
             ep.col_scale = g8->s_o; up.col_scale = g8->s_1; dn.col_scale = g8->s_2;
             if ((rc = regione_quantize_rows_fp8(ctx, a, g.n, H, ctx->q8, ctx->q8_scale)) != REGIONE_OK) return rc;
             if (taps && ((rc = tap(taps->a_codes, q8, g.r0, g.n, H)) != REGIONE_OK || (rc = tap(taps->a_scale, ctx->q8_scale, g.r0, g.n, 4)) != REGIONE_OK)) return rc;
+        ep.keep_sums = !ctx->f32 && (flags & REGIONE_FLAG_STORE);
             if ((rc = rg_gemm_fp8(ctx, q8, H, static_cast<const uint8_t*>(g8->w_o), g.n, H, H, ep)) != REGIONE_OK) return rc;
             if (taps && (rc = tap(taps->h1, h1, g.r0, g.n, static_cast<size_t>(H) * 4)) != REGIONE_OK) return rc;
             if ((rc = rg_layernorm_mod_fp8(ctx, h1, 1, g.n, H, g.w->shift2, g.w->scale2, ctx->q8, ctx->q8_scale)) != REGIONE_OK) return rc;

@@ -12,7 +12,7 @@ typedef uint16_t bf16_t;  // raw bfloat16 bits in memory
 constexpr int kMaxSplitTiles = 1024;   // tiles of one K-split GEMM launch
 
 constexpr int kGemmPlanSlots = 64;
-struct GemmPlanSlot { int m, n, k, fp8, tile, splits; size_t part_bytes; };   // a remembered choice of GEMM tile and K splits
+struct GemmPlanSlot { int m, n, k, kind, tile, splits; size_t part_bytes; };   // a remembered choice of GEMM tile and K splits
 
 struct regione_ctx {
     hipStream_t stream;
@@ -99,6 +99,7 @@ struct GemmEpilogue {
     const float* bias;   // [N] or null
     int act;             // REGIONE_ACT_* (applied to columns >= act_from)
     int act_from;
+    int keep_sums;       // host only: the sums of this product are those of the versions before (see rg_layernorm_mod)
     // EPI_PLAIN: y[row*ldy + col] (bf16 or f32)
     void* y; int ldy; int y_f32;
     // EPI_QKV: columns [0,H) -> q[row*ldq+col]; [H,2H) -> k[slot(row)*ldkv + col-H]; [2H,3H) -> v[...];
@@ -125,7 +126,10 @@ int rg_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m
 int rg_layernorm_mod_fp8(regione_ctx* ctx, const void* h, int h_f32, int n, int hidden, const float* shift, const float* scale,
                          uint8_t* q, float* row_scale);
 int rg_gemm_fp8(regione_ctx* ctx, const uint8_t* a, int lda, const uint8_t* w_packed, int m, int n, int k, const GemmEpilogue& ep);
-int rg_layernorm_mod(regione_ctx* ctx, const void* h, int h_f32, int n, int hidden, const float* shift, const float* scale, void* u);   // u: compute dtype
+// u: compute dtype.  keep_sums: a wave per row whatever its length, with the sums of the versions before, bit for bit.  Blocks want it where they store K and V: an E4M3 block that
+// reads those rows in later steps turns other last bits (0.04 % of the cache one bf16 rounding off) into 1.1 % of its output, more than the 1e-2 that such a block is
+// held to from one version to the next; the product behind takes its tile by the constants of then for the same reason.
+int rg_layernorm_mod(regione_ctx* ctx, const void* h, int h_f32, int n, int hidden, const float* shift, const float* scale, void* u, bool keep_sums = false);
 int rg_qk_norm_rope(regione_ctx* ctx, bf16_t* q, int ldq, bf16_t* k, int ldkv, const int32_t* kv_slot,
                     const int32_t* pos_slot, int pos0, int slot_offset, int slot_period, int slot_branch_rows, int n, int heads, int d,
                     const float* q_norm, const float* k_norm, const float* table, int table_rows);

@@ -50,29 +50,35 @@ constexpr TileShape kTiles[] = {{222, 64, 64, 64, 0, 1.089},   {224, 64, 128, 96
                                 {84, 256, 256, 160, 0, 1.011}, {248, 128, 256, 144, 0, 1.402}, {266, 192, 192, 144, 0, 1.021}, {276, 224, 192, 156, 0, 1.012}};
 struct GemmPlan { int tile; int splits; };
 
-double plan_time_bf16(const TileShape& t, int m, int n, int steps, int splits) {
+// cycles: per KiB copied, barriers and least time of a step by form (narrow, wide), once more for narrow ones; MHz; us per round; TB/s of weights and results; K splits
+struct PlanConstants { double feed, over_n, over_w, least_n, least_w, add_n, clock, round, hbm, out, split, split_unit, split_tile, two; bool wide_half_steps; };
+constexpr PlanConstants kPlan = {29.55, 174.9, 93.0, 546.2, 310.6, 59.5, 23.2, 0.14, 7.18e6, 128.0e6, 1.44, 0.132, 0.0267, 4.13, true};
+// those of before, without the factors and the three widest tiles of gemm_kg_kernel, where a product's sums are kept
+constexpr PlanConstants kPlanKept = {28.0, 120.0, 60.0, 450.0, 500.0, 53.0, 455.0, 6.9, 5.5e6, 8.0e6, 1.8, 0.19, 0.0116, 2.35, false};
+double plan_time_bf16(const PlanConstants& c, const TileShape& t, int m, int n, int steps, int splits) {
+    if (!c.wide_half_steps && (t.code == 248 || t.code == 266 || t.code == 276)) return 1e30;
     const int m_tiles = (m + t.rows - 1) / t.rows, n_tiles = (n + t.cols - 1) / t.cols;
     const long units = static_cast<long>(m_tiles) * n_tiles * splits;
     const int per = (steps + splits - 1) / splits;
     const bool narrow = t.code >= 200;
-    const double mfma = t.rows * t.cols / 32.0, feed = 29.55 * (t.rows + t.cols) / 8.0;
-    double step = mfma + (narrow ? 174.9 : 93.0);
+    const double mfma = t.rows * t.cols / 32.0, feed = c.feed * (t.rows + t.cols) / 8.0, least = narrow ? c.least_n : c.least_w;
+    double step = mfma + (narrow ? c.over_n : c.over_w);
     if (feed > step) step = feed;
-    if (step < (narrow ? 546.2 : 310.6)) step = narrow ? 546.2 : 310.6;
-    if (narrow) step += 59.5;
+    if (step < least) step = least;
+    if (narrow) step += c.add_n;
     const double active = units < 256 ? units / 256.0 : 1.0, live = static_cast<double>(m) / (static_cast<double>(m_tiles) * t.rows);
-    const double mhz = 2200.0 - 23.2 * (mfma / step * active * live);
+    const double mhz = 2200.0 - c.clock * (mfma / step * active * live);
     const long slots = t.lds_kb <= 80 ? 512 : 256;
     const long full = units / slots, rem = units % slots;
-    const double one = per * step / mhz * t.factor;
-    auto round_time = [&](long u) { return one * (slots > 256 && u > 256 ? 4.13 : 1.0) + 0.14; };
+    const double one = per * step / mhz * (c.wide_half_steps ? t.factor : 1.0);
+    auto round_time = [&](long u) { return one * (slots > 256 && u > 256 ? c.two : 1.0) + c.round; };
     double us = full * round_time(slots) + (rem > 0 ? round_time(rem) : 0.0);
-    const double hbm = static_cast<double>(n) * steps * 128.0 / 7.18e6 + 0.14;     // the weights once from HBM
+    const double hbm = static_cast<double>(n) * steps * 128.0 / c.hbm + c.round;     // the weights once from HBM
     if (us < hbm) us = hbm;
-    us += static_cast<double>(m) * n * 2.0 / 128.0e6;
+    us += static_cast<double>(m) * n * 2.0 / c.out;
     if (splits > 1) {
         const double tile_kb = t.rows * t.cols * 4.0 / 1e3;
-        us += 1.44 + 0.132 * units * tile_kb / 1e3 + 0.0267 * splits * tile_kb;
+        us += c.split + c.split_unit * units * tile_kb / 1e3 + c.split_tile * splits * tile_kb;
     }
     return us;
 }
@@ -138,24 +144,27 @@ GemmPlan plan_over(const TileShape (&tiles)[N], Time time, size_t part_bytes, in
     }
     return best;
 }
-GemmPlan choose_plan(int m, int n, int k, bool fp8, size_t part_bytes) {
-    return fp8 ? plan_over(kTilesFp8, plan_time_fp8, part_bytes, m, n, k / BK) : plan_over(kTiles, plan_time_bf16, part_bytes, m, n, k / BK);
+enum { PLAN_BF16 = 0, PLAN_FP8 = 1, PLAN_KEPT = 2 };
+GemmPlan choose_plan(int m, int n, int k, int kind, size_t part_bytes) {
+    if (kind == PLAN_FP8) return plan_over(kTilesFp8, plan_time_fp8, part_bytes, m, n, k / BK);
+    const PlanConstants& c = kind == PLAN_KEPT ? kPlanKept : kPlan;
+    return plan_over(kTiles, [&](const TileShape& t, int m_, int n_, int steps, int splits) { return plan_time_bf16(c, t, m_, n_, steps, splits); }, part_bytes, m, n, k / BK);
 }
 
 // The plan of a product, remembered per context (a direct-mapped table: a forward repeats a handful of shapes, and trying all
 // plans takes the host about as long as a small product takes the GPU).
-GemmPlan plan_gemm(regione_ctx* ctx, int m, int n, int k, bool fp8) {
+GemmPlan plan_gemm(regione_ctx* ctx, int m, int n, int k, int kind) {
     if (ctx->gemm_force_tn > 0) {
         const int by_size[7] = {0, 222, 244, 426, 44, 74, 84}, by_size_fp8[7] = {0, 42, 44, 62, 82, 42, 44};
-        const int tile = ctx->gemm_force_tn <= 6 ? (fp8 ? by_size_fp8 : by_size)[ctx->gemm_force_tn] : ctx->gemm_force_tn;
+        const int tile = ctx->gemm_force_tn <= 6 ? (kind == PLAN_FP8 ? by_size_fp8 : by_size)[ctx->gemm_force_tn] : ctx->gemm_force_tn;
         return {tile, ctx->gemm_force_splits > 0 ? ctx->gemm_force_splits : 1};
     }
-    if (ctx->gemm_force_splits > 0) return {choose_plan(m, n, k, fp8, ctx->gemm_part_bytes).tile, ctx->gemm_force_splits};
+    if (ctx->gemm_force_splits > 0) return {choose_plan(m, n, k, kind, ctx->gemm_part_bytes).tile, ctx->gemm_force_splits};
     const uint32_t h = (static_cast<uint32_t>(m) * 2654435761u) ^ (static_cast<uint32_t>(n) * 2246822519u) ^ (static_cast<uint32_t>(k) * 3266489917u);
     GemmPlanSlot& slot = ctx->gemm_plans[(h >> 16) % kGemmPlanSlots];
-    if (slot.m == m && slot.n == n && slot.k == k && slot.fp8 == fp8 && slot.part_bytes == ctx->gemm_part_bytes) return {slot.tile, slot.splits};
-    const GemmPlan p = choose_plan(m, n, k, fp8, ctx->gemm_part_bytes);
-    slot = {m, n, k, fp8, p.tile, p.splits, ctx->gemm_part_bytes};
+    if (slot.m == m && slot.n == n && slot.k == k && slot.kind == kind && slot.part_bytes == ctx->gemm_part_bytes) return {slot.tile, slot.splits};
+    const GemmPlan p = choose_plan(m, n, k, kind, ctx->gemm_part_bytes);
+    slot = {m, n, k, kind, p.tile, p.splits, ctx->gemm_part_bytes};
     return p;
 }
 
@@ -214,7 +223,7 @@ int rg_gemm_fp8(regione_ctx* ctx, const uint8_t* a, int lda, const uint8_t* wp, 
     GemmEpilogue ep = ep_in;
     ep.vec_ok = (n % 8 == 0) && rg_aligned16(ep.col_scale) && wide_epilogue_ok(ep, n);
     // the kernels count pairs of E4M3 values: the same bytes as half as many 16-bit elements
-    const GemmPlan p = plan_gemm(ctx, m, n, k / 2, true);
+    const GemmPlan p = plan_gemm(ctx, m, n, k / 2, PLAN_FP8);
     return rg_gemm_tile_fp8(ctx, p.tile, reinterpret_cast<const bf16_t*>(a), lda / 2, reinterpret_cast<const bf16_t*>(wp), m, n, k / 2, p.splits, ep);
 }
 
@@ -248,7 +257,7 @@ int rg_gemm(regione_ctx* ctx, const void* a_any, int lda, const void* wp_any, in
     GemmEpilogue ep = ep_in;
     ep.vec_ok = (n % 8 == 0) && wide_epilogue_ok(ep, n);
     if (const int columns = small_columns(ctx, m, n, k)) return gemm_small(ctx, a, lda, wp, m, n, k, columns, ep);
-    return gemm_tile(ctx, plan_gemm(ctx, m, n, k, false), a, lda, wp, m, n, k, ep);
+    return gemm_tile(ctx, plan_gemm(ctx, m, n, k, ep.keep_sums ? PLAN_KEPT : PLAN_BF16), a, lda, wp, m, n, k, ep);
 }
 
 int rg_layernorm_gemm(regione_ctx* ctx, const void* h, int h_f32, const float* shift, const float* scale, void* u, const void* wp, int m, int n, int k, const GemmEpilogue& ep_in) {
@@ -260,7 +269,7 @@ int rg_layernorm_gemm(regione_ctx* ctx, const void* h, int h_f32, const float* s
         ep.vec_ok = (n % 8 == 0) && wide_epilogue_ok(ep, n);
         return gemm_small_ln(ctx, h, h_f32, shift, scale, static_cast<const bf16_t*>(wp), m, n, k, columns, ep);
     }
-    if (int rc = rg_layernorm_mod(ctx, h, h_f32, m, k, shift, scale, u)) return rc;
+    if (int rc = rg_layernorm_mod(ctx, h, h_f32, m, k, shift, scale, u, ep_in.keep_sums != 0)) return rc;
     return rg_gemm(ctx, u, k, wp, m, n, k, ep_in);
 }
 
@@ -302,7 +311,7 @@ extern "C" int regione_gemm_plan_host(int32_t m, int32_t n, int32_t k, int32_t k
     const bool fp8 = kind == REGIONE_GEMM_E4M3;
     if (k % (fp8 ? 2 * BK : BK)) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "gemm_plan: k=%d must be a multiple of %d", k, fp8 ? 2 * BK : BK);
     GemmPlan p = {0, 1};
-    if (fp8 || !small_columns(m, n, k, false)) p = choose_plan(m, n, fp8 ? k / 2 : k, fp8, static_cast<size_t>(workspace_bytes));
+    if (fp8 || !small_columns(m, n, k, false)) p = choose_plan(m, n, fp8 ? k / 2 : k, fp8 ? PLAN_FP8 : PLAN_BF16, static_cast<size_t>(workspace_bytes));
     *tile = p.tile;
     *k_splits = p.splits;
     return REGIONE_OK;

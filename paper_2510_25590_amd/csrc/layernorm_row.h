@@ -20,6 +20,29 @@ template <> __device__ __forceinline__ void ld8<float>(const float* p, float (&v
     for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
 }
 
+template <int CTRL, int BANKS> __device__ __forceinline__ unsigned ln_dpp(unsigned old, unsigned x) { return __builtin_amdgcn_update_dpp(old, x, CTRL, 0xf, BANKS, false); }
+// op over the wave, the same bits in every lane: partners l ^ 32, 16, 8, 4, 2, 1 in this order, as a butterfly of shuffles takes them, but through the vector ALU instead of LDS
+// (gfx950's half and row swaps: two copies of x become the value of the one and of the other half everywhere, elements copied out before the casts; then DPP:
+// row_ror 8, lanes + 4 and - 4 by banks of four, and two permutations of quads).  The codes of an E4M3 block hang on every bit of these sums.
+template <typename Op> __device__ __forceinline__ float wave_reduce(float x, Op op) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const unsigned a0 = a[0], a1 = a[1];
+    x = op(__uint_as_float(a0), __uint_as_float(a1));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const unsigned b0 = b[0], b1 = b[1];
+    x = op(__uint_as_float(b0), __uint_as_float(b1));
+    unsigned u = __float_as_uint(x);
+    x = op(x, __uint_as_float(ln_dpp<0x128, 0xf>(u, u)));
+    u = __float_as_uint(x);
+    x = op(x, __uint_as_float(ln_dpp<0x114, 0xa>(ln_dpp<0x104, 0x5>(u, u), u)));
+    u = __float_as_uint(x);
+    x = op(x, __uint_as_float(ln_dpp<0x4e, 0xf>(u, u)));
+    u = __float_as_uint(x);
+    return op(x, __uint_as_float(ln_dpp<0xb1, 0xf>(u, u)));
+}
+__device__ __forceinline__ float wave_sum(float x) { return wave_reduce(x, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_max(float x) { return wave_reduce(x, [](float a, float b) { return __builtin_fmaxf(a, b); }); }
+
 // put(group, values): takes the eight results, as float32, of columns 8*group..8*group+7
 template <typename T, int MAXV, typename Put>
 __device__ __forceinline__ void layernorm_row(const T* hr, int hidden, const float* shift, const float* scale, Put put) {
@@ -46,8 +69,7 @@ __device__ __forceinline__ void layernorm_row(const T* hr, int hidden, const flo
             if (shift) ld8<float>(shift + g * 8, sh[i]);
         }
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
+    sum = wave_sum(sum);
     const float mean = sum / hidden;
     float sq = 0.f;
 #pragma unroll
@@ -57,8 +79,7 @@ __device__ __forceinline__ void layernorm_row(const T* hr, int hidden, const flo
             for (int e = 0; e < 8; ++e) { const float d = x[i][e] - mean; sq += d * d; }
         }
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) sq += __shfl_xor(sq, m, 64);
+    sq = wave_sum(sq);
     const float rstd = rsqrtf(sq / hidden + 1e-6f);
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
@@ -77,28 +98,12 @@ __device__ __forceinline__ void layernorm_row(const T* hr, int hidden, const flo
 }
 
 // ---- a row by several waves
-template <int CTRL> __device__ __forceinline__ float ln_dpp(float x) {
-    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
-}
-// Sum over the wave, the same bits in every lane, without a trip through LDS: xor 1, xor 2 and the two mirrors within rows of 16 lanes, then gfx950's row and half swaps (two
-// copies of x become the value of the one and of the other row everywhere; elements are copied out before the casts).
-template <typename Op> __device__ __forceinline__ float wave_reduce(float x, Op op) {
-    x = op(x, ln_dpp<0xB1>(x)); x = op(x, ln_dpp<0x4E>(x)); x = op(x, ln_dpp<0x141>(x)); x = op(x, ln_dpp<0x140>(x));
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    const unsigned a0 = a[0], a1 = a[1];
-    x = op(__uint_as_float(a0), __uint_as_float(a1));
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    const unsigned b0 = b[0], b1 = b[1];
-    return op(__uint_as_float(b0), __uint_as_float(b1));
-}
-__device__ __forceinline__ float wave_sum(float x) { return wave_reduce(x, [](float a, float b) { return a + b; }); }
-__device__ __forceinline__ float wave_max(float x) { return wave_reduce(x, [](float a, float b) { return __builtin_fmaxf(a, b); }); }
-
 // eight elements as loaded, converted when they are used
 template <typename T> struct LnRaw;
 template <> struct LnRaw<bf16_t> {
     ln_bf16x8 v;
     __device__ __forceinline__ void load(const bf16_t* p) { v = *reinterpret_cast<const ln_bf16x8*>(p); }
+    __device__ __forceinline__ void store(bf16_t* p) const { *reinterpret_cast<ln_bf16x8*>(p) = v; }
     __device__ __forceinline__ void values(float (&x)[8]) const {
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = static_cast<float>(v[e]);
@@ -107,6 +112,7 @@ template <> struct LnRaw<bf16_t> {
 template <> struct LnRaw<float> {
     ln_f32x4 a, b;
     __device__ __forceinline__ void load(const float* p) { a = *reinterpret_cast<const ln_f32x4*>(p); b = *reinterpret_cast<const ln_f32x4*>(p + 4); }
+    __device__ __forceinline__ void store(float* p) const { *reinterpret_cast<ln_f32x4*>(p) = a; *reinterpret_cast<ln_f32x4*>(p + 4) = b; }
     __device__ __forceinline__ void values(float (&x)[8]) const {
 #pragma unroll
         for (int e = 0; e < 4; ++e) { x[e] = a[e]; x[4 + e] = b[e]; }
@@ -119,7 +125,7 @@ template <> struct LnRaw<float> {
 // A wave for a whole row, as for shorter ones, is a long chain of its own (six rounds of loads, twelve shuffles through LDS) and reads the modulation vectors again for
 // every row, twice the bytes of the row itself.
 // us, a wave per row -> here, bf16 / float32 rows: 820 x 3072 7.0 / 6.7 -> 5.4 / 5.9, 8704 x 3072 42.5 / 42.4 -> 27.7 / 30.1 (3.9 and 5.3 TB/s; a copy reaches 5.9), 8704 x 1536 23.3 / 24.3 -> 13.8 / 17.4,
-// 2048 x 3072 the same; with E4M3 codes as the result 820 x 3072 9.4 / 10.7 -> 7.0 / 8.9 in a kernel trace.
+// 2048 x 3072 the same.
 // put(row, group, values): takes eight results of a live lane; each(row, lane's raw values) before them.
 template <typename T, int W, typename Each, typename Put>
 __device__ __forceinline__ void layernorm_rows_wide(const T* h, int n, int hidden, const float* shift, const float* scale, float2 (&part)[2][W], Each source, Put put) {

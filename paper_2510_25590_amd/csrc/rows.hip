@@ -136,7 +136,7 @@ velocity_cache_kernel(int reuse, float factor, float dt, const T* __restrict__ v
     }
 }
 
-// LayerNorm over H with modulation, one wave per row of at most 1024 values (see layernorm_row).  Bound by the latency of its loads: 36 float32 rows of 256 values take
+// LayerNorm over H with modulation, one wave per row (see layernorm_row): rows of at most 1024 values, and longer ones whose sums are kept.  Bound by the latency of its loads: 36 float32 rows of 256 values take
 // 5.2 us in the kernel of scalar loads below, 3.2 here, with registers and code for as many rounds of 512 values as the row has (in a kernel trace).  8704 rows: of 256 values
 // 4.8 us (bf16), 5.5 (float32); of 1024 7.8, 14.6.  U: the output's storage type (bf16, or float32 in a float32 context).
 template <typename T, typename U, int MAXV>
@@ -463,14 +463,18 @@ extern "C" int regione_cast(regione_ctx* ctx, const void* src, int32_t src_dtype
 }
 
 template <typename T, typename U>
-static void launch_layernorm(regione_ctx* ctx, const T* h, int n, int hidden, const float* shift, const float* scale, U* u) {
+static void launch_layernorm(regione_ctx* ctx, const T* h, int n, int hidden, const float* shift, const float* scale, U* u, bool keep_sums) {
     const dim3 grid((n + kThreads / 64 - 1) / (kThreads / 64));
     const bool vec = (hidden % 8 == 0) && hidden <= 64 * 8 * 8 && rg_aligned16(h) && rg_aligned16(u) &&
                      (!shift || rg_aligned16(shift)) && (!scale || rg_aligned16(scale));
     // as many registers and as much code as the row has rounds of 512 elements
     if (vec && hidden <= 512) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 1>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
     else if (vec && hidden <= 1024) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 2>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
-    else if (vec) {
+    else if (vec && keep_sums) {
+        if (hidden <= 2048) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 4>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
+        else if (hidden <= 3072) hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 6>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
+        else hipLaunchKernelGGL((layernorm_mod_vec_kernel<T, U, 8>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
+    } else if (vec) {
 #define RG_LN_WIDE(W) case W: hipLaunchKernelGGL((layernorm_mod_wide_kernel<T, U, W>), dim3(n < ln_wide_grid(W) ? n : ln_wide_grid(W)), dim3(64 * W), 0, ctx->stream, h, n, hidden, shift, scale, u); break;
         switch ((hidden / 8 + 63) / 64) { RG_LN_WIDE(3) RG_LN_WIDE(4) RG_LN_WIDE(5) RG_LN_WIDE(6) RG_LN_WIDE(7) RG_LN_WIDE(8) }
 #undef RG_LN_WIDE
@@ -478,13 +482,13 @@ static void launch_layernorm(regione_ctx* ctx, const T* h, int n, int hidden, co
     else hipLaunchKernelGGL((layernorm_mod_kernel<T, U>), grid, dim3(kThreads), 0, ctx->stream, h, n, hidden, shift, scale, u);
 }
 
-int rg_layernorm_mod(regione_ctx* ctx, const void* h, int h_f32, int n, int hidden, const float* shift, const float* scale, void* u) {
+int rg_layernorm_mod(regione_ctx* ctx, const void* h, int h_f32, int n, int hidden, const float* shift, const float* scale, void* u, bool keep_sums) {
     if (n <= 0) return REGIONE_OK;
     ProfScope prof(ctx, REGIONE_PROF_LAYERNORM);
-    if (ctx->f32 && h_f32) launch_layernorm(ctx, static_cast<const float*>(h), n, hidden, shift, scale, static_cast<float*>(u));
-    else if (ctx->f32) launch_layernorm(ctx, static_cast<const bf16_t*>(h), n, hidden, shift, scale, static_cast<float*>(u));
-    else if (h_f32) launch_layernorm(ctx, static_cast<const float*>(h), n, hidden, shift, scale, static_cast<bf16_t*>(u));
-    else launch_layernorm(ctx, static_cast<const bf16_t*>(h), n, hidden, shift, scale, static_cast<bf16_t*>(u));
+    if (ctx->f32 && h_f32) launch_layernorm(ctx, static_cast<const float*>(h), n, hidden, shift, scale, static_cast<float*>(u), keep_sums);
+    else if (ctx->f32) launch_layernorm(ctx, static_cast<const bf16_t*>(h), n, hidden, shift, scale, static_cast<float*>(u), keep_sums);
+    else if (h_f32) launch_layernorm(ctx, static_cast<const float*>(h), n, hidden, shift, scale, static_cast<bf16_t*>(u), keep_sums);
+    else launch_layernorm(ctx, static_cast<const bf16_t*>(h), n, hidden, shift, scale, static_cast<bf16_t*>(u), keep_sums);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }
