@@ -100,12 +100,13 @@ extern "C" int regione_create(regione_ctx** out, const regione_dims* dims, void*
     if (rc == REGIONE_OK) rc = dev_alloc(&c->h1, n * H);
     if (rc == REGIONE_OK) rc = dev_alloc(&c->m, n * M * es);
     if (rc == REGIONE_OK) rc = dev_alloc(&c->slot_all, n);
-    if (rc == REGIONE_OK) rc = dev_alloc(&c->mod_ws, static_cast<size_t>(12) * H);
+    if (rc == REGIONE_OK) rc = dev_alloc(&c->mod_ws, static_cast<size_t>(2 + kModSets) * 6 * H);
     if (rc == REGIONE_OK) rc = dev_alloc(reinterpret_cast<char**>(&c->attn_part), c->attn_part_bytes);
     c->gemm_part_bytes = n > 0 ? static_cast<size_t>(128) << 20 : 0;
     if (rc == REGIONE_OK) rc = dev_alloc(reinterpret_cast<char**>(&c->gemm_part), c->gemm_part_bytes);
-    if (rc == REGIONE_OK) rc = dev_alloc(&c->gemm_arrived, 2 * kMaxSplitTiles);
-    if (rc == REGIONE_OK) rc = clear_counters(c, 2 * kMaxSplitTiles);
+    if (rc == REGIONE_OK) rc = dev_alloc(&c->gemm_arrived, 2 * kMaxSplitTiles + 1);
+    if (rc == REGIONE_OK) rc = clear_counters(c, 2 * kMaxSplitTiles + 1);
+    if (rc == REGIONE_OK) c->part_arrived = c->gemm_arrived + 2 * kMaxSplitTiles;
     if (rc == REGIONE_OK) {   // pinned, device-visible host word for the edited-token count (saves the device-to-host copy)
         void* host = nullptr; void* dev = nullptr;
         if (hipHostMalloc(&host, 64, hipHostMallocMapped) != hipSuccess || hipHostGetDevicePointer(&dev, host, 0) != hipSuccess) {
@@ -172,10 +173,9 @@ extern "C" int regione_layernorm(regione_ctx* ctx, const void* h, int32_t h_dtyp
 
 // Velocity head of the step, fused with what follows it in a fresh region step: v = h W^T + b in the storage type, the
 // velocity cache takes v (Eq.9, fresh branch), x_e <- x_e - dt v (Eq.4), and the updated rows are written to their
-// positions in the full latent (the merge).  One launch in bf16 contexts.
-extern "C" int regione_velocity_head(regione_ctx* ctx, const void* h_rows, const void* w_head_packed, const float* b_head_opt,
-                                     int32_t n, int32_t c, int32_t hidden, float dt, void* v_out_opt, void* c_a, void* x_e,
-                                     void* x_full_opt, const int32_t* index_opt, int32_t dtype) {
+// positions in the full latent (the merge).  One launch in bf16 contexts.  merge (optional): hidden rows to merge in the same launch, where that is possible (*merged).
+static int velocity_head(regione_ctx* ctx, const void* h_rows, const void* w_head_packed, const float* b_head_opt, int32_t n, int32_t c, int32_t hidden, float dt, void* v_out_opt,
+                         void* c_a, void* x_e, void* x_full_opt, const int32_t* index_opt, int32_t dtype, const RowMerge* merge, bool* merged) {
     if (!ctx) RG_FAIL(REGIONE_ERR_INVALID_ARG, "velocity_head: null context");
     if (n < 0 || c <= 0 || hidden <= 0) RG_FAIL(REGIONE_ERR_INVALID_ARG, "velocity_head: n=%d c=%d hidden=%d", n, c, hidden);
     if (dtype != REGIONE_BF16 && dtype != REGIONE_FP32) RG_FAIL(REGIONE_ERR_INVALID_ARG, "velocity_head: bad dtype %d", dtype);
@@ -186,6 +186,11 @@ extern "C" int regione_velocity_head(regione_ctx* ctx, const void* h_rows, const
         // float32 contexts (and heads too short to split): the three calls the fused path stands for; v needs a place
         void* v = v_out_opt ? v_out_opt : c_a;      // the cache receives the fresh velocity anyway
         if (int rc = regione_linear(ctx, h_rows, w_head_packed, b_head_opt, n, c, hidden, REGIONE_ACT_NONE, dtype, v)) return rc;
+        if (merge && x_full_opt && c % 8 == 0 && rg_aligned16(v) && rg_aligned16(c_a) && rg_aligned16(x_e) && rg_aligned16(x_full_opt) &&
+            static_cast<int64_t>(n) * c <= INT32_MAX && static_cast<int64_t>(merge->rows) * merge->pieces <= INT32_MAX) {
+            *merged = true;
+            return rg_velocity_merge(ctx, v, c_a, x_e, x_full_opt, index_opt, dt, n, c, dtype, *merge);
+        }
         if (int rc = regione_velocity_cache(ctx, 0, 1.0f, dt, v, c_a, nullptr, x_e, nullptr, n, c, dtype)) return rc;
         if (x_full_opt) return regione_scatter(ctx, x_full_opt, c, dtype, index_opt, nullptr, n, x_e);
         return REGIONE_OK;
@@ -193,7 +198,62 @@ extern "C" int regione_velocity_head(regione_ctx* ctx, const void* h_rows, const
     GemmEpilogue ep = {};
     ep.bias = b_head_opt; ep.y = v_out_opt; ep.ldy = c; ep.y_f32 = dtype == REGIONE_FP32;
     ep.vel_ca = c_a; ep.vel_xe = x_e; ep.vel_xfull = x_full_opt; ep.vel_index = index_opt; ep.vel_dt = dt;
-    return rg_gemm_velocity(ctx, h_rows, hidden, w_head_packed, n, c, hidden, ep);
+    return rg_gemm_velocity(ctx, h_rows, hidden, w_head_packed, n, c, hidden, ep, merge, merged);
+}
+extern "C" int regione_velocity_head(regione_ctx* ctx, const void* h_rows, const void* w_head_packed, const float* b_head_opt,
+                                     int32_t n, int32_t c, int32_t hidden, float dt, void* v_out_opt, void* c_a, void* x_e,
+                                     void* x_full_opt, const int32_t* index_opt, int32_t dtype) {
+    return velocity_head(ctx, h_rows, w_head_packed, b_head_opt, n, c, hidden, dt, v_out_opt, c_a, x_e, x_full_opt, index_opt, dtype, nullptr, nullptr);
+}
+
+static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, int32_t block_type,
+                              const void* h_in, void* h_out, int32_t h_dtype, int32_t n_branches,
+                              int32_t n_fresh, int32_t n_txt_fresh, const int32_t* slot_index, int32_t slot_offset,
+                              void* k_cache, void* v_cache, int32_t n_all, int32_t flags,
+                              const regione_block_weights_fp8* w8 = nullptr, const regione_fp8_taps* taps = nullptr, bool image_rows_normalised = false);
+
+// The modulation vectors that a step's blocks [b0, ...) form from their conditioning vectors, as many blocks as there is room for, in one launch per kVecBatch of
+// them; they depend on nothing that the step computes.  sets[b - b0] tells where block b's are (-1: the block's own call sees to them); returns the
+// first block without.
+static int form_modulation(regione_ctx* ctx, const regione_region_step_args* a, int b0, int (&sets)[kModSets][2], int* next) {
+    const int H = ctx->dims.hidden;
+    VecBatch batch = {};
+    int used = 0, b = b0;
+    for (; b < a->n_blocks && b - b0 < kModSets; ++b) {
+        const regione_block_weights& w = a->blocks[b];
+        const bool dbl = a->block_types[b] == REGIONE_BLOCK_DOUBLE;
+        const regione_stream_weights* streams[2] = {&w.txt, &w.img};
+        if (used + 2 > kModSets) break;
+        for (int s = 0; s < 2; ++s) {
+            sets[b - b0][s] = -1;
+            if (!w.cond || !streams[s]->w_mod || (s == 0 && !(dbl && a->n_txt_fresh > 0))) continue;
+            if (ctx->f32 || H % 8 || H > 16384 || !rg_aligned16(streams[s]->w_mod)) continue;    // refused where the block's own call forms them
+            sets[b - b0][s] = used;
+            const int e = batch.count++;
+            batch.x[e] = w.cond; batch.w[e] = static_cast<const bf16_t*>(streams[s]->w_mod); batch.b[e] = streams[s]->b_mod;
+            batch.y[e] = ctx->mod_ws + static_cast<size_t>(2 + used++) * 6 * H; batch.n[e] = (dbl ? 6 : 3) * H;
+            if (batch.count == kVecBatch) {
+                if (int rc = rg_vec_linear_batch(ctx, batch, H)) return rc;
+                batch.count = 0;
+            }
+        }
+    }
+    *next = b;
+    return rg_vec_linear_batch(ctx, batch, H);
+}
+// block b's weights with the vectors formed above in place of its conditioning vector
+static regione_block_weights with_modulation(const regione_ctx* ctx, const regione_region_step_args* a, int b, const int (&set)[2]) {
+    regione_block_weights w = a->blocks[b];
+    regione_stream_weights* streams[2] = {&w.txt, &w.img};
+    for (int s = 0; s < 2; ++s) {
+        if (set[s] < 0) continue;
+        const size_t H = ctx->dims.hidden;
+        const float* mod = ctx->mod_ws + static_cast<size_t>(2 + set[s]) * 6 * H;
+        streams[s]->shift1 = mod; streams[s]->scale1 = mod + H; streams[s]->gate1 = mod + 2 * H;
+        if (a->block_types[b] == REGIONE_BLOCK_DOUBLE) { streams[s]->shift2 = mod + 3 * H; streams[s]->scale2 = mod + 4 * H; streams[s]->gate2 = mod + 5 * H; }
+        streams[s]->w_mod = nullptr;      // (a stream whose matrix is left is formed by the block's call)
+    }
+    return w;
 }
 
 extern "C" int regione_region_step(regione_ctx* ctx, const regione_region_step_args* a, int32_t* n_edited_host) {
@@ -206,14 +266,33 @@ extern "C" int regione_region_step(regione_ctx* ctx, const regione_region_step_a
     if (a->n_txt_fresh > 0 && !a->slots) RG_FAIL(REGIONE_ERR_INVALID_ARG, "region_step: fresh text rows need the slot list");
     const int H = ctx->dims.hidden;
     int32_t n = 0;
-    if (int rc = rg_partition_early_count(ctx, a->x_t, a->v, a->x_ref, a->n_tokens, a->c, a->dtype, a->sigma_t, a->eta, a->score_opt, a->mask,
-                                          a->e_index, a->u_index, a->n_edited_dev, &n)) return rc;
+    if (int rc = rg_partition_queue(ctx, a->x_t, a->v, a->x_ref, a->n_tokens, a->c, a->dtype, a->sigma_t, a->eta, a->score_opt, a->mask,
+                                    a->e_index, a->u_index, a->n_edited_dev)) return rc;
+    int sets[kModSets][2], set_first = 0, set_end = 0;
+    if (a->n_tokens > 0)
+        if (int rc = form_modulation(ctx, a, 0, sets, &set_end)) return rc;
+    if (int rc = rg_partition_count(ctx, &n)) return rc;
     *n_edited_host = n;
     if (n == 0) return REGIONE_OK;
     const size_t h_es = a->h_dtype == REGIONE_FP32 ? 4 : 2;
     const size_t txt_bytes = static_cast<size_t>(a->n_txt_fresh) * H * h_es;
     char* rows_in = static_cast<char*>(a->h_rows) + txt_bytes;          // the gathered rows follow the text rows
-    if (int rc = regione_gather_pair(ctx, a->h_full, H, a->h_dtype, rows_in, a->x_t, a->c, a->dtype, a->x_e, a->e_index, a->n_edited_dev, n)) return rc;
+    // The first block's LayerNorm reads the rows that the gather writes: one launch does both where the image rows are a group of their own.  Calls that the block would
+    // refuse go the general way, and are refused there.
+    bool normalised = false;
+    if (a->n_blocks > 0 && (a->block_types[0] == REGIONE_BLOCK_DOUBLE || (a->block_types[0] == REGIONE_BLOCK_SINGLE && a->n_txt_fresh == 0)) &&
+        a->n_txt_fresh + n <= ctx->dims.max_fresh && (!ctx->f32 || a->h_dtype == REGIONE_FP32)) {
+        const regione_block_weights w = with_modulation(ctx, a, 0, sets[0]);
+        char* u = ctx->u + static_cast<size_t>(a->n_txt_fresh) * H * (ctx->f32 ? 4 : 2);
+        const int64_t x_row = static_cast<int64_t>(a->c) * (a->dtype == REGIONE_FP32 ? 4 : 2);
+        const bool formed = !(w.cond && w.img.w_mod);
+        if (formed && rg_gather_layernorm_ok(a->h_full, rows_in, u, w.img.shift1, w.img.scale1, a->x_t, a->x_e, H, x_row)) {
+            if (int rc = rg_gather_layernorm(ctx, a->h_full, a->h_dtype == REGIONE_FP32, a->e_index, n, H, w.img.shift1, w.img.scale1, rows_in, u, a->x_t, a->x_e, static_cast<int>(x_row / 16))) return rc;
+            normalised = true;
+        }
+    }
+    if (!normalised)
+        if (int rc = regione_gather_pair(ctx, a->h_full, H, a->h_dtype, rows_in, a->x_t, a->c, a->dtype, a->x_e, a->e_index, a->n_edited_dev, n)) return rc;
     const int32_t* slot_index = a->e_index;
     int32_t slot_offset = a->slot_offset;
     if (a->n_txt_fresh > 0) {
@@ -222,14 +301,23 @@ extern "C" int regione_region_step(regione_ctx* ctx, const regione_region_step_a
     }
     const void* in = a->h_rows;
     for (int b = 0; b < a->n_blocks; ++b) {
-        if (int rc = regione_block_forward(ctx, &a->blocks[b], a->block_types[b], in, a->h_rows_out, a->h_dtype, a->n_txt_fresh + n, a->n_txt_fresh,
-                                           slot_index, slot_offset, a->k_caches[b], a->v_caches[b], a->n_all, REGIONE_FLAG_RETRIEVE)) return rc;
+        if (b == set_end) {
+            set_first = b;
+            if (int rc = form_modulation(ctx, a, b, sets, &set_end)) return rc;
+        }
+        const regione_block_weights w = with_modulation(ctx, a, b, sets[b - set_first]);
+        if (int rc = block_forward_impl(ctx, &w, a->block_types[b], in, a->h_rows_out, a->h_dtype, 1, a->n_txt_fresh + n, a->n_txt_fresh,
+                                        slot_index, slot_offset, a->k_caches[b], a->v_caches[b], a->n_all, REGIONE_FLAG_RETRIEVE, nullptr, nullptr, b == 0 && normalised)) return rc;
         in = a->h_rows_out;
     }
     const char* rows_out = static_cast<const char*>(in) + txt_bytes;
-    if (int rc = regione_velocity_head(ctx, rows_out, a->w_head_packed, a->b_head_opt, n, a->c, H, a->dt, a->v_out_opt, a->c_a, a->x_e,
-                                       a->x_next_full, a->e_index, a->dtype)) return rc;
-    if (a->h_next_full_opt) return regione_scatter(ctx, a->h_next_full_opt, H, a->h_dtype, a->e_index, a->n_edited_dev, n, rows_out);
+    const int64_t h_row = static_cast<int64_t>(H) * h_es;
+    const RowMerge merge = {rows_out, a->h_next_full_opt, a->e_index, n, static_cast<int>(h_row / 16)};
+    const bool can_merge = a->h_next_full_opt && h_row % 16 == 0 && rg_aligned16(rows_out) && rg_aligned16(a->h_next_full_opt);
+    bool merged = false;
+    if (int rc = velocity_head(ctx, rows_out, a->w_head_packed, a->b_head_opt, n, a->c, H, a->dt, a->v_out_opt, a->c_a, a->x_e,
+                               a->x_next_full, a->e_index, a->dtype, can_merge ? &merge : nullptr, &merged)) return rc;
+    if (a->h_next_full_opt && !merged) return regione_scatter(ctx, a->h_next_full_opt, H, a->h_dtype, a->e_index, a->n_edited_dev, n, rows_out);
     return REGIONE_OK;
 }
 
@@ -325,12 +413,12 @@ int check_stream_weights(const regione_stream_weights& w, int block_type, const 
 // and positions are shared.  When no text row is fresh (or the block is single-stream) all branches' rows form ONE
 // row group, so every projection is one GEMM over n_branches*n_fresh rows; attention runs per branch.
 // w8 != null: the 8-bit form of the block's projections (regione_block_forward_fp8); `taps`
-// then names the places that receive copies of the intermediates.
+// then names the places that receive copies of the intermediates.  image_rows_normalised: the first LayerNorm of the image rows is in the workspace already.
 static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, int32_t block_type,
                               const void* h_in, void* h_out, int32_t h_dtype, int32_t n_branches,
                               int32_t n_fresh, int32_t n_txt_fresh, const int32_t* slot_index, int32_t slot_offset,
                               void* k_cache, void* v_cache, int32_t n_all, int32_t flags,
-                              const regione_block_weights_fp8* w8 = nullptr, const regione_fp8_taps* taps = nullptr) {
+                              const regione_block_weights_fp8* w8, const regione_fp8_taps* taps, bool image_rows_normalised) {
     if (!ctx || !w) RG_FAIL(REGIONE_ERR_INVALID_ARG, "block_forward: null context or weights");
     if (n_branches < 1) RG_FAIL(REGIONE_ERR_INVALID_ARG, "block_forward: %d branches", n_branches);
     if (block_type != REGIONE_BLOCK_DOUBLE && block_type != REGIONE_BLOCK_SINGLE) RG_FAIL(REGIONE_ERR_INVALID_ARG, "block_forward: bad block type %d", block_type);
@@ -427,11 +515,13 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
         LaneHalf half(ctx, two_lanes && &g == &groups[1]);
         const char* hin = static_cast<const char*>(h_in) + static_cast<size_t>(g.r0) * H * h_elem;
         char* u = ctx->u + static_cast<size_t>(g.r0) * H * es;
+        const bool u_ready = image_rows_normalised && &g == &groups[1];
         const regione_stream_weights_fp8* g8 = w8 ? (&g == &groups[0] ? &w8->txt : &w8->img) : nullptr;
         if (g8 && (rc = rg_layernorm_mod_fp8(ctx, hin, h_f32, g.n, H, g.w->shift1, g.w->scale1, ctx->q8, ctx->q8_scale)) != REGIONE_OK) return rc;
         if (g8 && taps && ((rc = tap(taps->u1_codes, ctx->q8, g.r0, g.n, H)) != REGIONE_OK || (rc = tap(taps->u1_scale, ctx->q8_scale, g.r0, g.n, 4)) != REGIONE_OK)) return rc;
         GemmEpilogue ep = {};
         ep.kind = EPI_QKV; ep.hidden = H;
+        ep.keep_sums = !ctx->f32 && (flags & REGIONE_FLAG_STORE);
         ep.q = reinterpret_cast<bf16_t*>(ctx->q + static_cast<size_t>(g.r0) * H * es); ep.ldq = H;
         if (flags) { ep.k = reinterpret_cast<bf16_t*>(kc); ep.v = reinterpret_cast<bf16_t*>(vc); ep.slot = gemm_slots + g.r0; ep.slot_offset = slot_offset; }
         else { ep.k = reinterpret_cast<bf16_t*>(ctx->kf + static_cast<size_t>(g.r0) * H * es); ep.v = reinterpret_cast<bf16_t*>(ctx->vf + static_cast<size_t>(g.r0) * H * es); ep.slot = nullptr; }
@@ -445,11 +535,11 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
             rc = rg_gemm_fp8(ctx, ctx->q8, H, static_cast<const uint8_t*>(g8->w_1), g.n, 3 * H + M, H, ep);
         } else if (dbl) {
             ep.bias = g.w->b_qkv;
-            rc = rg_layernorm_gemm(ctx, hin, h_f32, g.w->shift1, g.w->scale1, u, g.w->w_qkv, g.n, 3 * H, H, ep);
+            rc = u_ready ? rg_gemm(ctx, u, H, g.w->w_qkv, g.n, 3 * H, H, ep) : rg_layernorm_gemm(ctx, hin, h_f32, g.w->shift1, g.w->scale1, u, g.w->w_qkv, g.n, 3 * H, H, ep);
         } else {
             ep.bias = g.w->b_1; ep.act = REGIONE_ACT_GELU_TANH;
             ep.y = ctx->a + static_cast<size_t>(g.r0) * lda_attn * es; ep.ldy = lda_attn; ep.y_col0 = H; ep.y_f32 = ctx->f32;
-            rc = rg_layernorm_gemm(ctx, hin, h_f32, g.w->shift1, g.w->scale1, u, g.w->w_1, g.n, 3 * H + M, H, ep);
+            rc = u_ready ? rg_gemm(ctx, u, H, g.w->w_1, g.n, 3 * H + M, H, ep) : rg_layernorm_gemm(ctx, hin, h_f32, g.w->shift1, g.w->scale1, u, g.w->w_1, g.n, 3 * H + M, H, ep);
         }
         if (rc != REGIONE_OK) return rc;
         // extras: normalised and rotated queries and keys, in place where the projection wrote them (bf16 contexts only)
@@ -521,7 +611,6 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
             ep.col_scale = g8->s_o; up.col_scale = g8->s_1; dn.col_scale = g8->s_2;
             if ((rc = regione_quantize_rows_fp8(ctx, a, g.n, H, ctx->q8, ctx->q8_scale)) != REGIONE_OK) return rc;
             if (taps && ((rc = tap(taps->a_codes, q8, g.r0, g.n, H)) != REGIONE_OK || (rc = tap(taps->a_scale, ctx->q8_scale, g.r0, g.n, 4)) != REGIONE_OK)) return rc;
-        ep.keep_sums = !ctx->f32 && (flags & REGIONE_FLAG_STORE);
             if ((rc = rg_gemm_fp8(ctx, q8, H, static_cast<const uint8_t*>(g8->w_o), g.n, H, H, ep)) != REGIONE_OK) return rc;
             if (taps && (rc = tap(taps->h1, h1, g.r0, g.n, static_cast<size_t>(H) * 4)) != REGIONE_OK) return rc;
             if ((rc = rg_layernorm_mod_fp8(ctx, h1, 1, g.n, H, g.w->shift2, g.w->scale2, ctx->q8, ctx->q8_scale)) != REGIONE_OK) return rc;

@@ -220,11 +220,9 @@ constexpr int kVecRowsPerWave = 4;
 // kVecRowsPerWave consecutive rows and streams them 16 bytes per lane and row, so four independent loads are in
 // flight per lane and iteration.
 template <int ACT>
-__global__ void __launch_bounds__(kThreads)
-vec_linear_kernel(const float* __restrict__ x, const bf16_t* __restrict__ w, const float* __restrict__ b, int n, int k, float* __restrict__ y) {
-    extern __shared__ __attribute__((aligned(16))) float xs[];
+__device__ __forceinline__ void vec_linear_rows(float* xs, int wg, const float* __restrict__ x, const bf16_t* __restrict__ w, const float* __restrict__ b, int n, int k, float* __restrict__ y) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row0 = (blockIdx.x * (kThreads / 64) + wave) * kVecRowsPerWave;
+    const int row0 = (wg * (kThreads / 64) + wave) * kVecRowsPerWave;
     const bf16_t* wrow[kVecRowsPerWave];
 #pragma unroll
     for (int r = 0; r < kVecRowsPerWave; ++r) {
@@ -272,6 +270,22 @@ vec_linear_kernel(const float* __restrict__ x, const bf16_t* __restrict__ w, con
     }
 }
 
+template <int ACT>
+__global__ void __launch_bounds__(kThreads)
+vec_linear_kernel(const float* __restrict__ x, const bf16_t* __restrict__ w, const float* __restrict__ b, int n, int k, float* __restrict__ y) {
+    extern __shared__ __attribute__((aligned(16))) float xs[];
+    vec_linear_rows<ACT>(xs, blockIdx.x, x, w, b, n, k, y);
+}
+// Several matrices one after the other in the grid: a launch's first requests and its last workgroups cost a 57 MB matrix as much as half its bytes (a block's vectors, width 3072,
+// 16.6 us by itself, two of them 26.7 in one launch).
+__global__ void __launch_bounds__(kThreads)
+vec_linear_batch_kernel(VecBatch a, int k) {
+    extern __shared__ __attribute__((aligned(16))) float xs[];
+    int e = 0;
+    while (e + 1 < a.count && static_cast<int>(blockIdx.x) >= a.first_wg[e + 1]) ++e;
+    vec_linear_rows<REGIONE_ACT_SILU>(xs, static_cast<int>(blockIdx.x) - a.first_wg[e], a.x[e], a.w[e], a.b[e], a.n[e], k, a.y[e]);
+}
+
 // out[j] = cos(t f_j), out[dim/2 + j] = sin(t f_j), f_j = max_period^(-j / (dim/2)); formed in float64.
 __global__ void __launch_bounds__(kThreads)
 timestep_embedding_kernel(double t, int half, double max_period, float* __restrict__ out) {
@@ -300,6 +314,17 @@ extern "C" int regione_vec_linear(regione_ctx* ctx, const float* x, int32_t pre_
     const bf16_t* wb = static_cast<const bf16_t*>(w);
     if (pre_act == REGIONE_ACT_SILU) hipLaunchKernelGGL(vec_linear_kernel<REGIONE_ACT_SILU>, grid, dim3(kThreads), lds, ctx->stream, x, wb, b_opt, n, k, y);
     else hipLaunchKernelGGL(vec_linear_kernel<REGIONE_ACT_NONE>, grid, dim3(kThreads), lds, ctx->stream, x, wb, b_opt, n, k, y);
+    RG_LAUNCH_CHECK();
+    return REGIONE_OK;
+}
+
+int rg_vec_linear_batch(regione_ctx* ctx, VecBatch& batch, int k) {
+    if (batch.count == 0) return REGIONE_OK;
+    const int rows_per_wg = (kThreads / 64) * kVecRowsPerWave;
+    batch.first_wg[0] = 0;
+    for (int e = 0; e < batch.count; ++e) batch.first_wg[e + 1] = batch.first_wg[e] + (batch.n[e] + rows_per_wg - 1) / rows_per_wg;
+    ProfScope prof(ctx, REGIONE_PROF_GEMM);
+    hipLaunchKernelGGL(vec_linear_batch_kernel, dim3(static_cast<unsigned>(batch.first_wg[batch.count])), dim3(kThreads), static_cast<size_t>(k) * sizeof(float), ctx->stream, batch, k);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }

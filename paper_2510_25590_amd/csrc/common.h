@@ -11,6 +11,8 @@ typedef uint16_t bf16_t;  // raw bfloat16 bits in memory
 
 constexpr int kMaxSplitTiles = 1024;   // tiles of one K-split GEMM launch
 
+constexpr int kModSets = 32;           // sets of modulation vectors that a step forms at a time
+
 constexpr int kGemmPlanSlots = 64;
 struct GemmPlanSlot { int m, n, k, kind, tile, splits; size_t part_bytes; };   // a remembered choice of GEMM tile and K splits
 
@@ -22,6 +24,7 @@ struct regione_ctx {
     // workspace (device)
     int32_t* part_counts;  // scratch of the partition: per-block edited counts, then one decision bit per token
     int64_t part_counts_cap;   // its size in int32 entries
+    int* part_arrived;             // arrival counter of the partition's workgroups (behind those of the GEMMs); zero between launches
     int32_t* n_edited_pinned;      // pinned host copy of the last edited-token count (host address)
     int32_t* n_edited_pinned_dev;  // the same memory as the device sees it
     int32_t count_ticket;          // last ticket handed to a partition whose count the host polls for (word 1 of the pinned memory)
@@ -37,7 +40,7 @@ struct regione_ctx {
     size_t attn_part_bytes;
     size_t attn_range_bytes;   // how much of it plan_ranges counts on
     int32_t* slot_all; // [max_fresh] slot list of all branches of a batched block call
-    float* mod_ws;     // [2][6H] modulation vectors of the two streams when a block call forms them itself
+    float* mod_ws;     // [2 + kModSets][6H] modulation vectors: of the two streams when a block call forms them itself, then those of a step's blocks
     // workspace of the 8-bit block (allocated by its first call): codes of one projection's input rows and their scales
     uint8_t* q8; size_t q8_bytes; float* q8_scale;
     float* gemm_part;  // split-K partial sums
@@ -96,10 +99,10 @@ enum { EPI_PLAIN = 0, EPI_QKV = 1, EPI_RESID = 2, EPI_VELOCITY = 3 };
 struct GemmEpilogue {
     int kind;            // EPI_*
     int vec_ok;          // set by rg_gemm: the wide (8 columns per lane) epilogue may be used
+    int keep_sums;       // host only: the sums of this product are those of the versions before (see rg_layernorm_mod)
     const float* bias;   // [N] or null
     int act;             // REGIONE_ACT_* (applied to columns >= act_from)
     int act_from;
-    int keep_sums;       // host only: the sums of this product are those of the versions before (see rg_layernorm_mod)
     // EPI_PLAIN: y[row*ldy + col] (bf16 or f32)
     void* y; int ldy; int y_f32;
     // EPI_QKV: columns [0,H) -> q[row*ldq+col]; [H,2H) -> k[slot(row)*ldkv + col-H]; [2H,3H) -> v[...];
@@ -116,8 +119,21 @@ struct GemmEpilogue {
 
 // a, w_packed (and the epilogue's q, k, v, y, resid where they are activations) are bf16, or float32 in a float32 context
 int rg_gemm(regione_ctx* ctx, const void* a, int lda, const void* w_packed, int m, int n, int k, const GemmEpilogue& ep);
-// y = x W^T + b with the velocity step (EPI_VELOCITY) as its epilogue (bf16 contexts)
-int rg_gemm_velocity(regione_ctx* ctx, const void* a, int lda, const void* w_packed, int m, int n, int k, const GemmEpilogue& ep);
+// y = x W^T + b with the velocity step (EPI_VELOCITY) as its epilogue (bf16 contexts); merge (optional): rows to write to their places in the same launch,
+// *merged tells whether they were
+struct RowMerge { const void* src; void* dst; const int32_t* index; int rows, pieces; };   // dst[index[i]] = src[i], rows of `pieces` 16-byte pieces
+int rg_gemm_velocity(regione_ctx* ctx, const void* a, int lda, const void* w_packed, int m, int n, int k, const GemmEpilogue& ep, const RowMerge* merge, bool* merged);
+// the velocity step and the merges of latent and hidden rows behind a head's product (float32 contexts); v: the product, c_a may be the same tensor
+int rg_velocity_merge(regione_ctx* ctx, const void* v, void* c_a, void* x_e, void* x_full, const int32_t* index, float dt, int n, int c, int dtype, const RowMerge& merge);
+// rows h_full[index[i]] to h_rows[i], their LayerNorm + modulation to u[i], and latent rows x_t[index[i]] (x_pieces 16-byte pieces) to x_e[i]: one launch where
+// gather_layernorm_ok (rows of more than 1024 values, everything 16-byte aligned)
+bool rg_gather_layernorm_ok(const void* h_full, const void* h_rows, const void* u, const float* shift, const float* scale, const void* x_t, const void* x_e, int hidden, int64_t x_row_bytes);
+int rg_gather_layernorm(regione_ctx* ctx, const void* h_full, int h_f32, const int32_t* index, int n, int hidden, const float* shift, const float* scale, void* h_rows, void* u,
+                        const void* x_t, void* x_e, int x_pieces);
+// modulation vectors of several blocks in one launch: y = silu(x) W^T + b for each entry, W [n, k] row-major bf16
+constexpr int kVecBatch = 16;
+struct VecBatch { const float* x[kVecBatch]; const bf16_t* w[kVecBatch]; const float* b[kVecBatch]; float* y[kVecBatch]; int n[kVecBatch]; int first_wg[kVecBatch + 1]; int count; };
+int rg_vec_linear_batch(regione_ctx* ctx, VecBatch& batch, int k);
 // the product of layernorm_mod(h) (h: rows of k values, bf16 or float32); u: workspace [m, k] of the compute dtype
 int rg_layernorm_gemm(regione_ctx* ctx, const void* h, int h_f32, const float* shift, const float* scale, void* u, const void* w_packed, int m, int n, int k, const GemmEpilogue& ep);
 int rg_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m, int n, int k, const GemmEpilogue& ep);
@@ -144,10 +160,11 @@ int rg_attention_f32(regione_ctx* ctx, const float* q, int ldq, int n_q,
                      int heads, int d, float scale, float* out, int ldo);
 int rg_pack_weight_f32(regione_ctx* ctx, const float* w, int n, int k, float* w_packed);
 // regione_partition whose host count arrives through a ticketed pinned word instead of a stream synchronisation
-int rg_partition_early_count(regione_ctx* ctx, const void* x_t, const void* v, const void* x_ref,
-                             int64_t n_tokens, int32_t c, int32_t dtype, float sigma_t, float eta,
-                             float* score_opt, uint8_t* mask, int32_t* e_index, int32_t* u_index,
-                             int32_t* n_edited_dev, int32_t* n_edited_host);
+// (rg_partition_queue), which rg_partition_count waits for
+int rg_partition_queue(regione_ctx* ctx, const void* x_t, const void* v, const void* x_ref,
+                       int64_t n_tokens, int32_t c, int32_t dtype, float sigma_t, float eta,
+                       float* score_opt, uint8_t* mask, int32_t* e_index, int32_t* u_index, int32_t* n_edited_dev);
+int rg_partition_count(regione_ctx* ctx, int32_t* n_edited_host);
 // the static-scratch lookup of regione_partition_static, done ahead of time by regione_create
 int rg_partition_static_warm(void);
 // int32 entries of scratch memory the partition needs for max_tokens tokens

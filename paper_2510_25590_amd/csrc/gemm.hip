@@ -227,7 +227,8 @@ int rg_gemm_fp8(regione_ctx* ctx, const uint8_t* a, int lda, const uint8_t* wp, 
     return rg_gemm_tile_fp8(ctx, p.tile, reinterpret_cast<const bf16_t*>(a), lda / 2, reinterpret_cast<const bf16_t*>(wp), m, n, k / 2, p.splits, ep);
 }
 
-int rg_gemm_velocity(regione_ctx* ctx, const void* a_any, int lda, const void* wp_any, int m, int n, int k, const GemmEpilogue& ep_in) {
+int rg_gemm_velocity(regione_ctx* ctx, const void* a_any, int lda, const void* wp_any, int m, int n, int k, const GemmEpilogue& ep_in, const RowMerge* merge, bool* merged) {
+    if (merged) *merged = false;
     if (m <= 0 || n <= 0) return REGIONE_OK;
     if (ctx->f32) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "gemm: the fused velocity step is a bf16-context path");
     if (k <= 0 || (k % BK) || (lda & 7)) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "gemm: k=%d must be a positive multiple of 64 and lda=%d of 8", k, lda);
@@ -238,11 +239,16 @@ int rg_gemm_velocity(regione_ctx* ctx, const void* a_any, int lda, const void* w
     ep.vec_ok = (n % 8 == 0) && wide_epilogue_ok(ep, n);
     const bf16_t* a = static_cast<const bf16_t*>(a_any);
     const bf16_t* wp = static_cast<const bf16_t*>(wp_any);
-    if (const int columns = small_columns(ctx, m, n, k)) return gemm_small(ctx, a, lda, wp, m, n, k, columns, ep);
+    if (const int columns = small_columns(ctx, m, n, k)) {
+        const int row_tiles = (m + kSmallRows - 1) / kSmallRows;
+        if (!merge || row_tiles + 2048 > 65535 || static_cast<int64_t>(merge->rows) * merge->pieces > INT32_MAX) return gemm_small(ctx, a, lda, wp, m, n, k, columns, ep);
+        *merged = true;
+        return columns == 32 ? launch_small_merge<2>(ctx, a, lda, wp, m, n, k, ep, *merge) : launch_small_merge<4>(ctx, a, lda, wp, m, n, k, ep, *merge);
+    }
     // The plan of the product alone: the sums are then those of rg_gemm bit for bit.  Tile 222 with one K split for all such heads took
     // (us, kernel before the two-group ones / 222 / now; hidden 3072): 820 x 128 14.1 / 19.3 / 10.6, 36 x 256 11.4 / 16.7 / 9.0, 8704 x 1024 122 / 139 / 60.
     // Odd widths (see the epilogue): 8704 x 65 22 / 28 / 27, 8704 x 100 23.5 / - / 27, 4096 x 65 16.5 / - / 17.3, 2048 x 66 15.4 / - / 12.4.
-    return gemm_tile(ctx, plan_gemm(ctx, m, n, k, false), a, lda, wp, m, n, k, ep);
+    return gemm_tile(ctx, plan_gemm(ctx, m, n, k, PLAN_BF16), a, lda, wp, m, n, k, ep);
 }
 
 int rg_gemm(regione_ctx* ctx, const void* a_any, int lda, const void* wp_any, int m, int n, int k, const GemmEpilogue& ep_in) {

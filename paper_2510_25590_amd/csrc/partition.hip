@@ -78,19 +78,79 @@ template <int LPT> __device__ __forceinline__ double group_sum(double x) {
     return x;
 }
 
+// The count's second destination.  With a ticket (a host waits for THIS call's count on a pinned host word without
+// waiting for the stream) the ticket follows the count into the next word, behind a system-scope fence, so that a host
+// that sees the ticket reads the count that belongs to it.
+__device__ __forceinline__ void publish_count(int32_t* __restrict__ dst, int32_t total, int32_t ticket) {
+    *dst = total;
+    if (ticket) {
+        __threadfence_system();
+        *reinterpret_cast<volatile int32_t*>(dst + 1) = ticket;
+    }
+}
+
+// The byte mask and the list entries of the 64 tokens of a word, by one wave: e_before edited tokens come before them.
+__device__ __forceinline__ void write_word(unsigned long long word, int64_t first_token, int64_t e_before, int64_t n_tokens, uint8_t* __restrict__ mask,
+                                           int32_t* __restrict__ e_index, int32_t* __restrict__ u_index) {
+    const int lane = threadIdx.x & 63;
+    const int64_t tok = first_token + lane;
+    if (tok >= n_tokens) return;
+    const bool ed = (word >> lane) & 1ull;
+    const int rank = __popcll(word & ((1ull << lane) - 1ull));
+    if (mask) mask[tok] = ed ? 1 : 0;
+    if (ed) e_index[e_before + rank] = static_cast<int32_t>(tok);
+    else u_index[first_token - e_before + (lane - rank)] = static_cast<int32_t>(tok);
+}
+
+// What the workgroup that finishes last writes (LISTS below).
+struct PartLists {
+    uint8_t* mask; int32_t* e_index; int32_t* u_index; int32_t* n_edited; int32_t* n_edited_pinned; int32_t ticket;
+    int* arrived;       // workgroups that are done; zero between launches
+};
+// Up to this many tokens.  Every workgroup of a launch adds some 35 ns to the meeting (stores and additions past the L2 go one after the other), so that a second
+// launch is cheaper for more: us per partition in two launches / one, 64 tokens 7.7 / 5.1, 1024 7.9 / 5.5, 2304 8.0 / 6.2, 4096 7.9 / 7.5, 9216 7.9 / 11.6.
+// A counter for every 16 workgroups and one for these was no faster (4096 7.6), nor lists put together in LDS.
+constexpr int kListTokens = 2560, kListWords = kListTokens / 64;
+__device__ __forceinline__ void write_lists(const PartLists& l, const uint64_t* __restrict__ bits, int64_t n_tokens) {
+    static_assert(kListWords <= 64, "the first wave holds all words");
+    __shared__ unsigned long long s_words[kListWords];
+    __shared__ int s_before[kListWords];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n_words = static_cast<int>((n_tokens + 63) / 64);
+    if (wave == 0) {
+        unsigned long long word = 0;        // the other workgroups' words, from the level that all XCDs share
+        if (lane < n_words) word = __hip_atomic_load(bits + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int cnt = __popcll(word);
+        int incl = cnt;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int up = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += up;
+        }
+        if (lane == 63) {
+            *l.n_edited = incl;
+            publish_count(l.n_edited_pinned, incl, l.ticket);
+        }
+        if (lane < n_words) { s_words[lane] = word; s_before[lane] = incl - cnt; }
+    }
+    __syncthreads();
+    for (int w = wave; w < n_words; w += kWaves) write_word(s_words[w], 64 * static_cast<int64_t>(w), s_before[w], n_tokens, l.mask, l.e_index, l.u_index);
+}
+
 // One block handles tokens [blockIdx.x * tok_per_block, +tok_per_block); tok_per_block is a multiple of 64 and at most
 // kMaxBlockTokens.  PIPE: every lane owns exactly one chunk of its token (c == VEC * LPT) and the chunks of the next
 // STAGE tokens are requested before the current ones are reduced.  Otherwise a lane loops over its chunks.
 // bits: one 64-bit word per 64 tokens, bit = edited; words of tokens past n_tokens are written with those bits clear.
-template <typename T, int VEC, int LPT, bool PIPE>
+// LISTS (up to kListTokens, in blocks of 64): the workgroup that arrives last writes the mask and the index lists too.
+template <typename T, int VEC, int LPT, bool PIPE, bool LISTS>
 __global__ void __launch_bounds__(kThreads)
 score_bits_kernel(const T* __restrict__ x_t, const T* __restrict__ v, const T* __restrict__ x_ref,
                   int64_t n_tokens, int c, int tok_per_block, float sigma, float eta,
-                  float* __restrict__ score, uint64_t* __restrict__ bits, int32_t* __restrict__ counts) {
+                  float* __restrict__ score, uint64_t* __restrict__ bits, int32_t* __restrict__ counts, PartLists lists) {
     constexpr int TPW = 64 / LPT;                       // tokens per wave and pass
     constexpr int STAGE = 2;                            // passes whose loads travel together
     constexpr int STAGE_TOK = kWaves * TPW * STAGE;     // tokens per workgroup and stage
-    __shared__ double s_sum[3][kMaxBlockTokens];
+    __shared__ double s_sum[3][LISTS ? 64 : kMaxBlockTokens];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int sub = lane % LPT, tiw = lane / LPT;
     const int64_t block_first = static_cast<int64_t>(blockIdx.x) * tok_per_block;
@@ -180,7 +240,23 @@ score_bits_kernel(const T* __restrict__ x_t, const T* __restrict__ v, const T* _
         }
         const unsigned long long word = __ballot(edited);
         edited_count += __popcll(word);
-        if (lane == 0 && t0 + wave * 64 < block_tokens) bits[(block_first + t0) / 64 + wave] = word;
+        if (lane == 0 && t0 + wave * 64 < block_tokens) {
+            uint64_t* at = bits + (block_first + t0) / 64 + wave;
+            if (LISTS) __hip_atomic_store(at, static_cast<uint64_t>(word), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // past this XCD's own L2
+            else *at = word;
+        }
+    }
+    if constexpr (LISTS) {
+        __shared__ int s_last;
+        if (threadIdx.x == 0) {         // thread 0 wrote the block's only word
+            __builtin_amdgcn_s_waitcnt(0);
+            asm volatile("" ::: "memory");
+            s_last = __hip_atomic_fetch_add(lists.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == static_cast<int>(gridDim.x) - 1;
+            if (s_last) __hip_atomic_store(lists.arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+        }
+        __syncthreads();
+        if (s_last) write_lists(lists, bits, n_tokens);
+        return;
     }
     __shared__ int wave_counts[kWaves];
     if (lane == 0) wave_counts[wave] = edited_count;
@@ -190,17 +266,6 @@ score_bits_kernel(const T* __restrict__ x_t, const T* __restrict__ v, const T* _
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) s += wave_counts[w];
         counts[blockIdx.x] = s;
-    }
-}
-
-// The count's second destination.  With a ticket (a host waits for THIS call's count on a pinned host word without
-// waiting for the stream) the ticket follows the count into the next word, behind a system-scope fence, so that a host
-// that sees the ticket reads the count that belongs to it.
-__device__ __forceinline__ void publish_count(int32_t* __restrict__ dst, int32_t total, int32_t ticket) {
-    *dst = total;
-    if (ticket) {
-        __threadfence_system();
-        *reinterpret_cast<volatile int32_t*>(dst + 1) = ticket;
     }
 }
 
@@ -297,18 +362,8 @@ write_index_kernel(const uint64_t* __restrict__ bits, uint8_t* __restrict__ mask
     }
     __syncthreads();
     for (int w = wave; w < n_words; w += kWaves) {
-        const unsigned long long word = s_words[w];
-        const int64_t tok = block_first + 64 * w + lane;
-        const bool live = tok < n_tokens;
-        const bool ed = (word >> lane) & 1ull;
-        const int rank = __popcll(word & ((1ull << lane) - 1ull));
-        const int64_t e_at = static_cast<int64_t>(base_e) + s_before[w];          // edited tokens before this word
-        const int64_t u_at = block_first + 64 * w - e_at;                          // unedited tokens before it
-        if (live) {
-            if (BITS) mask[tok] = ed ? 1 : 0;
-            if (ed) e_index[e_at + rank] = static_cast<int32_t>(tok);
-            else u_index[u_at + (lane - rank)] = static_cast<int32_t>(tok);
-        }
+        const int64_t first = block_first + 64 * w;
+        write_word(s_words[w], first, static_cast<int64_t>(base_e) + s_before[w], n_tokens, BITS ? mask : nullptr, e_index, u_index);
     }
 }
 
@@ -331,15 +386,18 @@ __host__ inline PartScratch part_scratch_in(int32_t* base, int64_t max_tokens) {
 
 template <typename T, int VEC>
 int launch_score(hipStream_t stream, const PartScratch& ps, int lpt, bool pipe, dim3 grid, const void* x_t, const void* v, const void* x_ref, int64_t n, int c,
-                 int tpb, float sigma, float eta, float* score) {
+                 int tpb, float sigma, float eta, float* score, const PartLists* lists) {
+    const PartLists l = lists ? *lists : PartLists{};
     const T* a = static_cast<const T*>(x_t); const T* b = static_cast<const T*>(v); const T* r = static_cast<const T*>(x_ref);
+#define RG_SCORE(L, P, S) hipLaunchKernelGGL((score_bits_kernel<T, VEC, L, P, S>), grid, dim3(kThreads), 0, stream, a, b, r, n, c, tpb, sigma, eta, score, ps.bits, ps.counts, l)
 #define RG_CASE(L) case L: \
-        if (VEC > 1 && pipe) hipLaunchKernelGGL((score_bits_kernel<T, VEC, L, (VEC > 1)>), grid, dim3(kThreads), 0, stream, a, b, r, n, c, tpb, sigma, eta, score, ps.bits, ps.counts); \
-        else hipLaunchKernelGGL((score_bits_kernel<T, VEC, L, false>), grid, dim3(kThreads), 0, stream, a, b, r, n, c, tpb, sigma, eta, score, ps.bits, ps.counts); \
+        if (VEC > 1 && pipe) { if (lists) RG_SCORE(L, (VEC > 1), true); else RG_SCORE(L, (VEC > 1), false); } \
+        else { if (lists) RG_SCORE(L, false, true); else RG_SCORE(L, false, false); } \
         break;
     switch (lpt) { RG_CASE(1) RG_CASE(2) RG_CASE(4) RG_CASE(8) RG_CASE(16) RG_CASE(32) RG_CASE(64)
         default: RG_FAIL(REGIONE_ERR_INVALID_ARG, "partition: bad lane group %d", lpt); }
 #undef RG_CASE
+#undef RG_SCORE
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }
@@ -424,10 +482,11 @@ int launch_index_lists(hipStream_t stream, int32_t* counts, const uint64_t* bits
     return REGIONE_OK;
 }
 
-// The launches of the partition on `stream` with its scratch memory in `ps`.
+// The launches of the partition on `stream` with its scratch memory in `ps`.  arrived: a counter of its own, null where calls may overlap (a counter would
+// stay wrong after a race).
 int partition_launches(hipStream_t stream, const PartScratch& ps, const void* x_t, const void* v, const void* x_ref,
                        int64_t n_tokens, int32_t c, int32_t dtype, float sigma_t, float eta, float* score_opt, uint8_t* mask,
-                       int32_t* e_index, int32_t* u_index, int32_t* n_edited_dev, int32_t* n_edited_copy, int32_t ticket = 0) {
+                       int32_t* e_index, int32_t* u_index, int32_t* n_edited_dev, int32_t* n_edited_copy, int* arrived, int32_t ticket = 0) {
     if (n_tokens == 0) {
         hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(1), 0, stream, n_edited_dev, n_edited_copy, 0, ticket);
         RG_LAUNCH_CHECK();
@@ -446,15 +505,17 @@ int partition_launches(hipStream_t stream, const PartScratch& ps, const void* x_
     if (nblocks > ps.counts_cap || (n_tokens + 63) / 64 > ps.words_cap)
         RG_FAIL(REGIONE_ERR_WORKSPACE, "partition: %lld tokens in %lld blocks exceed the workspace", (long long)n_tokens, (long long)nblocks);
     dim3 grid(static_cast<unsigned>(nblocks));
+    const bool one_launch = arrived && tpb == 64 && n_tokens <= kListTokens;
+    const PartLists lists = {mask, e_index, u_index, n_edited_dev, n_edited_copy, ticket, arrived};
     int rc;
     if (dtype == REGIONE_BF16) {
-        rc = vec == 8 ? launch_score<bf16_t, 8>(stream, ps, lpt, pipe, grid, x_t, v, x_ref, n_tokens, c, tpb, sigma_t, eta, score_opt)
-                      : launch_score<bf16_t, 1>(stream, ps, lpt, pipe, grid, x_t, v, x_ref, n_tokens, c, tpb, sigma_t, eta, score_opt);
+        rc = vec == 8 ? launch_score<bf16_t, 8>(stream, ps, lpt, pipe, grid, x_t, v, x_ref, n_tokens, c, tpb, sigma_t, eta, score_opt, one_launch ? &lists : nullptr)
+                      : launch_score<bf16_t, 1>(stream, ps, lpt, pipe, grid, x_t, v, x_ref, n_tokens, c, tpb, sigma_t, eta, score_opt, one_launch ? &lists : nullptr);
     } else {
-        rc = vec == 4 ? launch_score<float, 4>(stream, ps, lpt, pipe, grid, x_t, v, x_ref, n_tokens, c, tpb, sigma_t, eta, score_opt)
-                      : launch_score<float, 1>(stream, ps, lpt, pipe, grid, x_t, v, x_ref, n_tokens, c, tpb, sigma_t, eta, score_opt);
+        rc = vec == 4 ? launch_score<float, 4>(stream, ps, lpt, pipe, grid, x_t, v, x_ref, n_tokens, c, tpb, sigma_t, eta, score_opt, one_launch ? &lists : nullptr)
+                      : launch_score<float, 1>(stream, ps, lpt, pipe, grid, x_t, v, x_ref, n_tokens, c, tpb, sigma_t, eta, score_opt, one_launch ? &lists : nullptr);
     }
-    if (rc != REGIONE_OK) return rc;
+    if (rc != REGIONE_OK || one_launch) return rc;
     return launch_index_lists(stream, ps.counts, ps.bits, grid, mask, n_tokens, tpb, e_index, u_index, n_edited_dev, n_edited_copy, ticket);
 }
 
@@ -482,7 +543,7 @@ extern "C" int regione_partition(regione_ctx* ctx, const void* x_t, const void* 
     {
     ProfScope prof(ctx, REGIONE_PROF_PARTITION);
     if (int rc = partition_launches(ctx->stream, part_scratch_in(ctx->part_counts, ctx->dims.max_tokens), x_t, v, x_ref, n_tokens, c, dtype, sigma_t, eta,
-                                    score_opt, mask, e_index, u_index, n_edited_dev, ctx->n_edited_pinned_dev)) return rc;
+                                    score_opt, mask, e_index, u_index, n_edited_dev, ctx->n_edited_pinned_dev, ctx->part_arrived)) return rc;
     }
     if (n_edited_host_opt) {   // the kernels wrote the count to pinned host memory too: no copy to wait for, only the stream
         RG_HIP(hipStreamSynchronize(ctx->stream));
@@ -494,20 +555,19 @@ extern "C" int regione_partition(regione_ctx* ctx, const void* x_t, const void* 
 // regione_partition for a caller inside the library that goes on launching on the same stream: the host gets the count
 // as soon as the kernels have published it (a ticketed pinned host word, polled), not when the stream has drained, so
 // the launches that need the count are queued while the index kernel still writes its lists.
-int rg_partition_early_count(regione_ctx* ctx, const void* x_t, const void* v, const void* x_ref,
-                             int64_t n_tokens, int32_t c, int32_t dtype, float sigma_t, float eta,
-                             float* score_opt, uint8_t* mask, int32_t* e_index, int32_t* u_index,
-                             int32_t* n_edited_dev, int32_t* n_edited_host) {
-    if (!ctx || !n_edited_host) RG_FAIL(REGIONE_ERR_INVALID_ARG, "partition: null context or count");
+int rg_partition_queue(regione_ctx* ctx, const void* x_t, const void* v, const void* x_ref,
+                       int64_t n_tokens, int32_t c, int32_t dtype, float sigma_t, float eta,
+                       float* score_opt, uint8_t* mask, int32_t* e_index, int32_t* u_index, int32_t* n_edited_dev) {
+    if (!ctx) RG_FAIL(REGIONE_ERR_INVALID_ARG, "partition: null context");
     if (int rc = check_partition_args("partition", x_t, v, x_ref, n_tokens, c, dtype, mask, e_index, u_index, n_edited_dev)) return rc;
     if (n_tokens > ctx->dims.max_tokens) RG_FAIL(REGIONE_ERR_WORKSPACE, "partition: %lld tokens, context made for %d", (long long)n_tokens, ctx->dims.max_tokens);
     ctx->count_ticket = ctx->count_ticket == INT32_MAX ? 1 : ctx->count_ticket + 1;
-    const int32_t ticket = ctx->count_ticket;
-    {
     ProfScope prof(ctx, REGIONE_PROF_PARTITION);
-    if (int rc = partition_launches(ctx->stream, part_scratch_in(ctx->part_counts, ctx->dims.max_tokens), x_t, v, x_ref, n_tokens, c, dtype, sigma_t, eta,
-                                    score_opt, mask, e_index, u_index, n_edited_dev, ctx->n_edited_pinned_dev, ticket)) return rc;
-    }
+    return partition_launches(ctx->stream, part_scratch_in(ctx->part_counts, ctx->dims.max_tokens), x_t, v, x_ref, n_tokens, c, dtype, sigma_t, eta,
+                              score_opt, mask, e_index, u_index, n_edited_dev, ctx->n_edited_pinned_dev, ctx->part_arrived, ctx->count_ticket);
+}
+int rg_partition_count(regione_ctx* ctx, int32_t* n_edited_host) {
+    const int32_t ticket = ctx->count_ticket;
     volatile int32_t* word = ctx->n_edited_pinned;
     const auto t0 = std::chrono::steady_clock::now();
     for (;;) {
@@ -616,5 +676,5 @@ extern "C" int regione_partition_static(void* hip_stream, const void* x_t, const
     const PartScratch ps = part_scratch_in(counts, kStaticMaxTokens);
     if (ps.counts_cap + 2 * ps.words_cap > RG_STATIC_INTS) RG_FAIL(REGIONE_ERR_WORKSPACE, "partition_static: the static array is smaller than its layout");
     return partition_launches(static_cast<hipStream_t>(hip_stream), ps, x_t, v, x_ref, n_tokens, c, dtype, sigma_t, eta,
-                              score_opt, mask, e_index, u_index, n_edited_dev, n_edited_dev);
+                              score_opt, mask, e_index, u_index, n_edited_dev, n_edited_dev, nullptr);
 }

@@ -159,6 +159,23 @@ layernorm_mod_wide_kernel(const T* __restrict__ h, int n, int hidden, const floa
                               [&](int row, int g, bool live, const LnRaw<T>&, const float (&o)[8]) { if (live) st8<U>(u + static_cast<int64_t>(row) * hidden + g * 8, o); });
 }
 
+// The same on rows picked by an index list, which go to h_rows on the way, and the latent rows of the same tokens beside them.
+template <typename T, typename U, int W>
+__global__ void __launch_bounds__(64 * W)
+gather_layernorm_kernel(const T* __restrict__ h_full, const int32_t* __restrict__ index, int n, int hidden, const float* __restrict__ shift, const float* __restrict__ scale,
+                        T* __restrict__ h_rows, U* __restrict__ u, const rows_u32x4* __restrict__ x_t, rows_u32x4* __restrict__ x_e, int x_pieces) {
+    __shared__ float2 part[2][W];
+    for (int row = blockIdx.x; row < n; row += gridDim.x)
+        for (int p = threadIdx.x; p < x_pieces; p += 64 * W) x_e[static_cast<int64_t>(row) * x_pieces + p] = x_t[static_cast<int64_t>(index[row]) * x_pieces + p];
+    layernorm_rows_wide<T, W>(h_full, n, hidden, shift, scale, part, [&](int row) -> int64_t { return index[row]; },
+                              [&](int row, int g, bool live, const LnRaw<T>& raw, const float (&o)[8]) {
+        if (!live) return;
+        const int64_t at = static_cast<int64_t>(row) * hidden + g * 8;
+        raw.store(h_rows + at);
+        st8<U>(u + at, o);
+    });
+}
+
 // Any H: scalar loads, three passes over the row.
 template <typename T, typename U>
 __global__ void __launch_bounds__(kThreads)
@@ -489,6 +506,75 @@ int rg_layernorm_mod(regione_ctx* ctx, const void* h, int h_f32, int n, int hidd
     else if (ctx->f32) launch_layernorm(ctx, static_cast<const bf16_t*>(h), n, hidden, shift, scale, static_cast<float*>(u), keep_sums);
     else if (h_f32) launch_layernorm(ctx, static_cast<const float*>(h), n, hidden, shift, scale, static_cast<bf16_t*>(u), keep_sums);
     else launch_layernorm(ctx, static_cast<const bf16_t*>(h), n, hidden, shift, scale, static_cast<bf16_t*>(u), keep_sums);
+    RG_LAUNCH_CHECK();
+    return REGIONE_OK;
+}
+
+bool rg_gather_layernorm_ok(const void* h_full, const void* h_rows, const void* u, const float* shift, const float* scale, const void* x_t, const void* x_e, int hidden, int64_t x_row_bytes) {
+    return hidden > 1024 && hidden <= 4096 && hidden % 8 == 0 && x_row_bytes > 0 && x_row_bytes % 16 == 0 && rg_aligned16(h_full) && rg_aligned16(h_rows) && rg_aligned16(u) &&
+           rg_aligned16(shift) && rg_aligned16(scale) && rg_aligned16(x_t) && rg_aligned16(x_e);
+}
+template <typename T, typename U>
+static void launch_gather_layernorm(regione_ctx* ctx, const void* h_full, const int32_t* index, int n, int hidden, const float* shift, const float* scale, void* h_rows, void* u,
+                                    const void* x_t, void* x_e, int x_pieces) {
+#define RG_LN_WIDE(W) case W: hipLaunchKernelGGL((gather_layernorm_kernel<T, U, W>), dim3(n < ln_wide_grid(W) ? n : ln_wide_grid(W)), dim3(64 * W), 0, ctx->stream, \
+        static_cast<const T*>(h_full), index, n, hidden, shift, scale, static_cast<T*>(h_rows), static_cast<U*>(u), static_cast<const rows_u32x4*>(x_t), static_cast<rows_u32x4*>(x_e), x_pieces); break;
+    switch ((hidden / 8 + 63) / 64) { RG_LN_WIDE(3) RG_LN_WIDE(4) RG_LN_WIDE(5) RG_LN_WIDE(6) RG_LN_WIDE(7) RG_LN_WIDE(8) }
+#undef RG_LN_WIDE
+}
+int rg_gather_layernorm(regione_ctx* ctx, const void* h_full, int h_f32, const int32_t* index, int n, int hidden, const float* shift, const float* scale, void* h_rows, void* u,
+                        const void* x_t, void* x_e, int x_pieces) {
+    if (n <= 0) return REGIONE_OK;
+    ProfScope prof(ctx, REGIONE_PROF_LAYERNORM);
+    if (ctx->f32) launch_gather_layernorm<float, float>(ctx, h_full, index, n, hidden, shift, scale, h_rows, u, x_t, x_e, x_pieces);
+    else if (h_f32) launch_gather_layernorm<float, bf16_t>(ctx, h_full, index, n, hidden, shift, scale, h_rows, u, x_t, x_e, x_pieces);
+    else launch_gather_layernorm<bf16_t, bf16_t>(ctx, h_full, index, n, hidden, shift, scale, h_rows, u, x_t, x_e, x_pieces);
+    RG_LAUNCH_CHECK();
+    return REGIONE_OK;
+}
+
+namespace {
+// The velocity step of a fresh head (Eq.9, Eq.4: the arithmetic of velocity_cache_vec_kernel) with the merge of the updated latent rows, and in workgroups of their own
+// the merge of the hidden rows: three launches of a few microseconds in one.
+template <typename T>
+__global__ void __launch_bounds__(kThreads)
+velocity_merge_kernel(const T* v, T* c_a, T* __restrict__ x_e, T* __restrict__ x_full, const int32_t* __restrict__ index, float dt, int groups, int c, int step_wgs, RowMerge merge) {
+    if (static_cast<int>(blockIdx.x) < step_wgs) {
+        const int g = blockIdx.x * kThreads + threadIdx.x;
+        if (g >= groups) return;
+        const int per_row = c / 8, row = g / per_row;
+        const int64_t i = static_cast<int64_t>(g) * 8;
+        const int64_t to = static_cast<int64_t>(index[row]) * c + (g - row * per_row) * 8;
+        float vu[8], x[8];
+        ld8<T>(v + i, vu);
+        ld8<T>(x_e + i, x);
+        if (c_a != v) st8<T>(c_a + i, vu);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = __fsub_rn(x[e], __fmul_rn(dt, vu[e]));
+        st8<T>(x_e + i, x);
+        st8<T>(x_full + to, x);
+        return;
+    }
+    const unsigned total = static_cast<unsigned>(merge.rows) * static_cast<unsigned>(merge.pieces), stride = (gridDim.x - step_wgs) * kThreads;
+    for (unsigned u = (blockIdx.x - step_wgs) * kThreads + threadIdx.x; u < total; u += stride) {
+        const unsigned row = u / static_cast<unsigned>(merge.pieces);
+        static_cast<rows_u32x4*>(merge.dst)[static_cast<int64_t>(merge.index[row]) * merge.pieces + (u - row * merge.pieces)] = static_cast<const rows_u32x4*>(merge.src)[u];
+    }
+}
+}  // namespace
+
+int rg_velocity_merge(regione_ctx* ctx, const void* v, void* c_a, void* x_e, void* x_full, const int32_t* index, float dt, int n, int c, int dtype, const RowMerge& merge) {
+    ProfScope prof(ctx, REGIONE_PROF_VELOCITY);
+    const int groups = n * c / 8, step_wgs = (groups + kThreads - 1) / kThreads;
+    int64_t wgs = (static_cast<int64_t>(merge.rows) * merge.pieces + kThreads - 1) / kThreads;
+    if (wgs > 256 * 32) wgs = 256 * 32;
+    const dim3 grid(static_cast<unsigned>(step_wgs + wgs));
+    if (dtype == REGIONE_BF16)
+        hipLaunchKernelGGL(velocity_merge_kernel<bf16_t>, grid, dim3(kThreads), 0, ctx->stream, static_cast<const bf16_t*>(v), static_cast<bf16_t*>(c_a), static_cast<bf16_t*>(x_e),
+                           static_cast<bf16_t*>(x_full), index, dt, groups, c, step_wgs, merge);
+    else
+        hipLaunchKernelGGL(velocity_merge_kernel<float>, grid, dim3(kThreads), 0, ctx->stream, static_cast<const float*>(v), static_cast<float*>(c_a), static_cast<float*>(x_e),
+                           static_cast<float*>(x_full), index, dt, groups, c, step_wgs, merge);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }
