@@ -136,6 +136,8 @@ struct VecBatch { const float* x[kVecBatch]; const bf16_t* w[kVecBatch]; const f
 int rg_vec_linear_batch(regione_ctx* ctx, VecBatch& batch, int k);
 // the product of layernorm_mod(h) (h: rows of k values, bf16 or float32); u: workspace [m, k] of the compute dtype
 int rg_layernorm_gemm(regione_ctx* ctx, const void* h, int h_f32, const float* shift, const float* scale, void* u, const void* w_packed, int m, int n, int k, const GemmEpilogue& ep);
+// the product of layernorm_mod(h) in one launch where that pays; *done tells
+int rg_layernorm_gemm_f32(regione_ctx* ctx, const float* h, const float* shift, const float* scale, const float* w, int m, int n, int k, const GemmEpilogue& ep, bool* done);
 int rg_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m, int n, int k, const GemmEpilogue& ep);
 // E4M3 operands (k counts 8-bit elements, a multiple of 128; lda in bytes, a multiple of 16); ep.row_scale / col_scale set
 // LayerNorm + modulation with the E4M3 row quantisation of its float32 result: codes [n, hidden], one scale per row

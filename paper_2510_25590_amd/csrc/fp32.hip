@@ -8,6 +8,7 @@
 #include <cmath>
 #include <type_traits>
 #include "common.h"
+#include "layernorm_row.h"
 
 namespace {
 
@@ -63,9 +64,14 @@ __device__ __forceinline__ void store_f32(const GemmEpilogue& ep, int row, int c
 // 36 rows, float32 (same box, in a loop): 768 columns of K 256 11.1 -> 5.0 us, 256 of K 1024 30.0 -> 5.5, most of it the
 // launch; 640 x 256 x 1024 30.6 -> 12.9.
 // LDS row stride TN + 4: the four row groups that a store of the accumulator touches fall into different banks.
-template <int KIND, int RB, int CB, int NW, int PF>
+// LN: A holds the rows before their LayerNorm + modulation (K <= kLnF32Columns, 16-byte aligned like the vectors); the waves normalise the tile's rows into LDS while the weights
+// are on their way, which takes the LayerNorm's launch and its trip through memory away: 36 rows of 256,
+// kernel trace, 3.3 + 3.9 -> 5.2 us (768 columns), 3.3 + 3.8 -> 4.9 (1024).
+constexpr int kLnF32Columns = 512, kLnF32Tiles = 256;
+__host__ __device__ constexpr int ln_f32_row(int k) { return k + 4; }     // floats; 16 bytes on: the rows of a fragment start in different banks
+template <int KIND, int RB, int CB, int NW, int PF, bool LN>
 __global__ void __launch_bounds__(NW * 64)
-gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int M, int N, int K, GemmEpilogue ep) {
+gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int M, int N, int K, const float* __restrict__ shift, const float* __restrict__ scale, GemmEpilogue ep) {
     constexpr int TM = RB * 16, TN = CB * 16, LD = TN + 4;
     __shared__ float part[NW][TM][LD];
     const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
@@ -111,6 +117,38 @@ gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ 
     const int64_t n_chunks = K / FK;
     int c = __builtin_amdgcn_readfirstlane(static_cast<int>(n_chunks * wave / NW));
     const int c_end = __builtin_amdgcn_readfirstlane(static_cast<int>(n_chunks * (wave + 1) / NW));
+    if constexpr (LN) {
+        constexpr int P = kLnF32Columns / FK / NW;               // a wave's chunks of the longest row
+        extern __shared__ __attribute__((aligned(16))) float rows[];
+        f32x4 wv[P][CB];
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            if (c + p < c_end) {
+#pragma unroll
+                for (int j = 0; j < CB; ++j) wv[p][j] = *reinterpret_cast<const f32x4*>(wp[j] + (c + p) * FK);
+            }
+#pragma unroll
+        for (int r = 0; r < TM / NW; ++r) {
+            const int lr = wave * (TM / NW) + r;
+            const int hr = m0 + lr < M ? m0 + lr : M - 1;
+            layernorm_row<float, kLnF32Columns / 512>(A + static_cast<int64_t>(hr) * lda, K, shift, scale, [&](int g, const float (&o)[8]) { st8<float>(rows + lr * ln_f32_row(K) + g * 8, o); });
+        }
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            if (c + p < c_end) {
+                f32x4 av[RB];
+#pragma unroll
+                for (int i = 0; i < RB; ++i) av[i] = *reinterpret_cast<const f32x4*>(rows + (16 * i + l16) * ln_f32_row(K) + (c + p) * FK + 4 * lq);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < RB; ++i)
+#pragma unroll
+                        for (int j = 0; j < CB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i][e], wv[p][j][e], acc[i][j], 0, 0, 0);
+            }
+        c = c_end;
+    }
     for (; c + PF <= c_end; c += PF) chunks(c, std::integral_constant<int, PF>{});
     for (; c + 2 <= c_end; c += 2) chunks(c, std::integral_constant<int, 2>{});
     if (c < c_end) chunks(c, std::integral_constant<int, 1>{});
@@ -191,6 +229,7 @@ struct AttnF32Args {
     const float* k0; const float* v0; int ldkv0; int n0;
     const float* k1; const float* v1; int ldkv1; int n1; const int32_t* idx1;
     float scale; float* out; int ldo;
+    int splits; float* part; int* arrived;      // key ranges of a query tile, each a workgroup; their partial results and the tiles' arrival counters
 };
 
 // Eq.6 for 16 query rows of one head per workgroup: the key list is the fresh rows followed by the cache rows in use,
@@ -203,7 +242,12 @@ struct AttnF32Args {
 // One wave per (query, head) with a serial walk over the values, the form before this one, took 96.5 us for 36 queries
 // on 544 keys (4 heads of 64) and 290 for 640 on 1216; now 13.3 and 24.4: the matrix instructions of one CU per 16
 // queries and head, and the launch.
-template <int D, int NW>
+// Where the queries and heads leave most of the chip idle, up to kF32Splits workgroups share a query tile's keys; their partial results travel in 16-byte accesses of device
+// scope (the sc1 bit of a buffer access), since the workgroups may sit on different XCDs.  36 queries on 544 keys, 4 heads of 64, are twelve workgroups whose matrix
+// instructions alone take 4 us: 13.3 -> 8.8 us in five ranges; 100 queries 13.4 -> 9.4, 200 on 800 keys 17.9 -> 14.0, 9 on 544 12.7 -> 8.0.
+constexpr int kF32Splits = 8, kF32Workgroups = 128, kF32DeviceScope = 16;
+typedef __attribute__((ext_vector_type(4))) unsigned int f32_u32x4;
+template <int D, int NW, bool RANGES>
 __global__ void __launch_bounds__(NW * 64)
 attn_f32_kernel(AttnF32Args a) {
     constexpr int KC = D / 16, VJ = D / 64;
@@ -213,9 +257,13 @@ attn_f32_kernel(AttnF32Args a) {
     const int l16 = lane & 15, lq = lane >> 4;
     const int q0 = blockIdx.x * 16, head = blockIdx.y;
     const int n_keys = a.n0 + a.n1;
-    const int64_t n_groups = (static_cast<int64_t>(n_keys) + 15) / 16;
-    const int g0 = __builtin_amdgcn_readfirstlane(static_cast<int>(n_groups * wave / NW));
-    const int g1 = __builtin_amdgcn_readfirstlane(static_cast<int>(n_groups * (wave + 1) / NW));
+    const unsigned part_bytes = 16u * (D + 4) * 4u, tile_part = (head * gridDim.x + blockIdx.x) * a.splits * part_bytes;      // the launcher keeps all of them below 2 GiB
+    const auto part_rsrc = __builtin_amdgcn_make_buffer_rsrc(a.part, 0, static_cast<int>(gridDim.x * gridDim.y * a.splits * part_bytes), 0x00027000);
+    const int64_t all_groups = (static_cast<int64_t>(n_keys) + 15) / 16;
+    const int first_group = RANGES ? static_cast<int>(all_groups * blockIdx.z / a.splits) : 0;       // of this workgroup's key range
+    const int64_t n_groups = RANGES ? all_groups * (blockIdx.z + 1) / a.splits - first_group : all_groups;
+    const int g0 = __builtin_amdgcn_readfirstlane(first_group + static_cast<int>(n_groups * wave / NW));
+    const int g1 = __builtin_amdgcn_readfirstlane(first_group + static_cast<int>(n_groups * (wave + 1) / NW));
     f32x4 q[KC];
     {
         int r = q0 + l16; r = r < a.n_q ? r : a.n_q - 1;
@@ -326,6 +374,55 @@ attn_f32_kernel(AttnF32Args a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) sum[e] = fmaf(f, o_lds[w][row][piece][e], sum[e]);
         }
+        if (RANGES) {               // maximum, sum and unnormalised O of the range, past this XCD's own L2
+            const unsigned at = tile_part + blockIdx.z * part_bytes + row * (D + 4) * 4u;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(f32_u32x4, sum), part_rsrc, at + 16u + 16u * piece, 0, kF32DeviceScope);
+            if (piece == 0) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(f32_u32x4, f32x4{m, l, 0.f, 0.f}), part_rsrc, at, 0, kF32DeviceScope);
+            continue;
+        }
+        const float inv = 1.0f / l;
+        float* op = a.out + static_cast<int64_t>(q0 + row) * a.ldo + head * D + 4 * piece;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) op[e] = sum[e] * inv;
+    }
+    if constexpr (!RANGES) return;
+    // The workgroup of the query tile that arrives last joins the ranges, in key order whoever is last.  Nobody waits.
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    __syncthreads();
+    __shared__ int s_last;
+    if (threadIdx.x == 0) {
+        int* at = a.arrived + head * gridDim.x + blockIdx.x;
+        s_last = __hip_atomic_fetch_add(at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.splits - 1;
+        if (s_last) __hip_atomic_store(at, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);     // ready for the next launch
+    }
+    __syncthreads();
+    if (!s_last) return;
+    for (int t = threadIdx.x; t < 16 * (D / 4); t += NW * 64) {
+        const int row = t / (D / 4), piece = t % (D / 4);
+        if (q0 + row >= a.n_q) continue;
+        f32x4 ml[kF32Splits], o_part[kF32Splits];
+#pragma unroll
+        for (int z = 0; z < kF32Splits; ++z)
+            if (z < a.splits) {
+                const unsigned at = tile_part + z * part_bytes + row * (D + 4) * 4u;
+                ml[z] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part_rsrc, at, 0, kF32DeviceScope));
+                o_part[z] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part_rsrc, at + 16u + 16u * piece, 0, kF32DeviceScope));
+            }
+        float m = -INFINITY;
+#pragma unroll
+        for (int z = 0; z < kF32Splits; ++z) if (z < a.splits) m = fmaxf(m, ml[z][0]);
+        const float ref = m == -INFINITY ? 0.f : m;
+        float l = 0.f;
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int z = 0; z < kF32Splits; ++z)
+            if (z < a.splits) {
+                const float f = expf(ml[z][0] - ref);
+                l = fmaf(f, ml[z][1], l);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] = fmaf(f, o_part[z][e], sum[e]);
+            }
         const float inv = 1.0f / l;
         float* op = a.out + static_cast<int64_t>(q0 + row) * a.ldo + head * D + 4 * piece;
 #pragma unroll
@@ -342,15 +439,17 @@ void launch_gemm_f32_wide(regione_ctx* ctx, const float* a, int lda, const float
     }
 }
 
-template <int RB, int CB, int NW, int PF>
-void launch_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m, int n, int k, const GemmEpilogue& ep) {
+template <int RB, int CB, int NW, int PF, bool LN>
+void launch_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m, int n, int k, const float* shift, const float* scale, const GemmEpilogue& ep) {
     const dim3 grid((n + CB * 16 - 1) / (CB * 16), (m + RB * 16 - 1) / (RB * 16)), block(NW * 64);
+    const size_t lds = LN ? static_cast<size_t>(RB) * 16 * ln_f32_row(k) * sizeof(float) : 0;
     switch (ep.kind) {
-        case EPI_PLAIN: hipLaunchKernelGGL((gemm_f32_kernel<EPI_PLAIN, RB, CB, NW, PF>), grid, block, 0, ctx->stream, a, lda, w, m, n, k, ep); break;
-        case EPI_QKV: hipLaunchKernelGGL((gemm_f32_kernel<EPI_QKV, RB, CB, NW, PF>), grid, block, 0, ctx->stream, a, lda, w, m, n, k, ep); break;
-        default: hipLaunchKernelGGL((gemm_f32_kernel<EPI_RESID, RB, CB, NW, PF>), grid, block, 0, ctx->stream, a, lda, w, m, n, k, ep); break;
+        case EPI_PLAIN: hipLaunchKernelGGL((gemm_f32_kernel<EPI_PLAIN, RB, CB, NW, PF, LN>), grid, block, lds, ctx->stream, a, lda, w, m, n, k, shift, scale, ep); break;
+        case EPI_QKV: hipLaunchKernelGGL((gemm_f32_kernel<EPI_QKV, RB, CB, NW, PF, LN>), grid, block, lds, ctx->stream, a, lda, w, m, n, k, shift, scale, ep); break;
+        default: if constexpr (!LN) hipLaunchKernelGGL((gemm_f32_kernel<EPI_RESID, RB, CB, NW, PF, false>), grid, block, lds, ctx->stream, a, lda, w, m, n, k, shift, scale, ep); break;
     }
 }
+int64_t tiles_f32(int m, int n, int64_t b) { return ((m + b - 1) / b) * ((n + b - 1) / b); }
 
 }  // namespace
 
@@ -374,11 +473,24 @@ int rg_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m
     // product.  Measured (us, tiles of 16 / 32 / 64): 36 x 768 x 256 3.8 / 4.3 / 11, 205 x 256 x 1024 5.6 / 10.3 / 30,
     // 205 x 768 x 256 (624 tiles of 16) 5.0 / 4.5 / 11, 640 x 256 x 1024 (640) 12.6 / 10.4 / 31,
     // 1216 x 768 x 256 (228 tiles of 64) 17 / 11.6 / 11.7, 2000 x 1024 x 256 (512) 34 / 22 / 16.
-    auto tiles = [&](int64_t b) { return ((m + b - 1) / b) * ((n + b - 1) / b); };
-    if (tiles(64) >= 256) launch_gemm_f32_wide(ctx, a, lda, w, m, n, k, ep);
-    else if (tiles(16) > 512) launch_gemm_f32<2, 2, 8, 4>(ctx, a, lda, w, m, n, k, ep);
-    else launch_gemm_f32<1, 1, 8, 8>(ctx, a, lda, w, m, n, k, ep);
+    if (tiles_f32(m, n, 64) >= 256) launch_gemm_f32_wide(ctx, a, lda, w, m, n, k, ep);
+    else if (tiles_f32(m, n, 16) > 512) launch_gemm_f32<2, 2, 8, 4, false>(ctx, a, lda, w, m, n, k, nullptr, nullptr, ep);
+    else launch_gemm_f32<1, 1, 8, 8, false>(ctx, a, lda, w, m, n, k, nullptr, nullptr, ep);
     RG_LAUNCH_CHECK();
+    return REGIONE_OK;
+}
+
+// The product of layernorm_mod(h) in one launch, bit for bit that of the two, where every workgroup of one round of 256 normalises its own rows; *done tells whether it was.
+int rg_layernorm_gemm_f32(regione_ctx* ctx, const float* h, const float* shift, const float* scale, const float* w, int m, int n, int k, const GemmEpilogue& ep, bool* done) {
+    *done = false;
+    if (k <= 0 || k % FK || k > kLnF32Columns || !rg_aligned16(h) || !rg_aligned16(w) || !rg_aligned16(shift) || !rg_aligned16(scale) || (ep.kind != EPI_PLAIN && ep.kind != EPI_QKV)) return REGIONE_OK;
+    const bool fine = tiles_f32(m, n, 16) <= 512;
+    if (tiles_f32(m, n, fine ? 16 : 32) > kLnF32Tiles || tiles_f32(m, n, 64) >= 256) return REGIONE_OK;
+    ProfScope prof(ctx, REGIONE_PROF_GEMM);
+    if (fine) launch_gemm_f32<1, 1, 8, 8, true>(ctx, h, k, w, m, n, k, shift, scale, ep);
+    else launch_gemm_f32<2, 2, 8, 4, true>(ctx, h, k, w, m, n, k, shift, scale, ep);
+    RG_LAUNCH_CHECK();
+    *done = true;
     return REGIONE_OK;
 }
 
@@ -392,10 +504,21 @@ int rg_attention_f32(regione_ctx* ctx, const float* q, int ldq, int n_q,
     if ((n0 > 0 && (ldkv0 & 3)) || (n1 > 0 && (ldkv1 & 3))) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "attention (float32): row strides must keep 16-byte alignment");
     if (heads > 65535) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "attention (float32): %d heads", heads);
     ProfScope prof(ctx, REGIONE_PROF_ATTENTION);
-    AttnF32Args a = {q, ldq, n_q, k0, v0, ldkv0, n0, k1, v1, ldkv1, n1, idx1, scale > 0.f ? scale : 1.0f / sqrtf(static_cast<float>(d)), out, ldo};
-    const dim3 grid(static_cast<unsigned>((n_q + 15) / 16), static_cast<unsigned>(heads));
-    if (d == 64) hipLaunchKernelGGL((attn_f32_kernel<64, 12>), grid, dim3(768), 0, ctx->stream, a);
-    else hipLaunchKernelGGL((attn_f32_kernel<128, 4>), grid, dim3(256), 0, ctx->stream, a);
+    AttnF32Args a = {q, ldq, n_q, k0, v0, ldkv0, n0, k1, v1, ldkv1, n1, idx1, scale > 0.f ? scale : 1.0f / sqrtf(static_cast<float>(d)), out, ldo, 1, ctx->attn_part, ctx->gemm_arrived};
+    // key ranges as long as the workgroups stay within half a round of the chip and have six groups of keys each: the meeting costs about as much as that
+    const int64_t tiles = static_cast<int64_t>((n_q + 15) / 16) * heads, groups = (static_cast<int64_t>(n0) + n1 + 15) / 16;
+    if (tiles <= kMaxSplitTiles && 2 * tiles <= kF32Workgroups) {
+        int64_t z = kF32Workgroups / tiles;
+        z = z < groups / 6 ? z : groups / 6;
+        z = z < kF32Splits ? z : kF32Splits;
+        const size_t bytes = static_cast<size_t>(tiles) * (z > 0 ? z : 1) * 16 * (d + 4) * sizeof(float);
+        if (z > 1 && bytes <= ctx->attn_part_bytes && bytes < (size_t{1} << 31)) a.splits = static_cast<int>(z);
+    }
+    const dim3 grid(static_cast<unsigned>((n_q + 15) / 16), static_cast<unsigned>(heads), static_cast<unsigned>(a.splits));
+    if (d == 64 && a.splits > 1) hipLaunchKernelGGL((attn_f32_kernel<64, 12, true>), grid, dim3(768), 0, ctx->stream, a);
+    else if (d == 64) hipLaunchKernelGGL((attn_f32_kernel<64, 12, false>), grid, dim3(768), 0, ctx->stream, a);
+    else if (a.splits > 1) hipLaunchKernelGGL((attn_f32_kernel<128, 4, true>), grid, dim3(256), 0, ctx->stream, a);
+    else hipLaunchKernelGGL((attn_f32_kernel<128, 4, false>), grid, dim3(256), 0, ctx->stream, a);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }

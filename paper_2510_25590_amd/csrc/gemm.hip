@@ -268,6 +268,11 @@ int rg_gemm(regione_ctx* ctx, const void* a_any, int lda, const void* wp_any, in
 
 int rg_layernorm_gemm(regione_ctx* ctx, const void* h, int h_f32, const float* shift, const float* scale, void* u, const void* wp, int m, int n, int k, const GemmEpilogue& ep_in) {
     if (m <= 0 || n <= 0) return REGIONE_OK;
+    if (ctx->f32 && h_f32) {
+        bool done = false;
+        if (int rc = rg_layernorm_gemm_f32(ctx, static_cast<const float*>(h), shift, scale, static_cast<const float*>(wp), m, n, k, ep_in, &done)) return rc;
+        if (done) return REGIONE_OK;
+    }
     const int columns = !ctx->f32 && k <= 1024 && (k % BK) == 0 && rg_aligned16(h) && rg_aligned16(wp) && rg_aligned16(shift) && rg_aligned16(scale) ? small_columns(ctx, m, n, k, true) : 0;
     if (columns && (ep_in.kind == EPI_PLAIN || ep_in.kind == EPI_QKV)) {
         ProfScope prof(ctx, REGIONE_PROF_GEMM);
