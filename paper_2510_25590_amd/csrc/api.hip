@@ -18,7 +18,7 @@ int dev_alloc(T** p, size_t count) {
     return REGIONE_OK;
 }
 void free_all(regione_ctx* c) {
-    void* ptrs[] = {c->part_counts, c->u, c->q, c->kf, c->vf, c->a, c->h1, c->m, c->slot_all, c->mod_ws, c->attn_part, c->gemm_part, c->gemm_arrived, c->q8, c->q8_scale};
+    void* ptrs[] = {c->part_counts, c->u, c->q, c->kf, c->vf, c->a, c->h1, c->m, c->mod_ws, c->attn_part, c->gemm_part, c->gemm_arrived, c->q8, c->q8_scale};
     for (void* p : ptrs) if (p) (void)hipFree(p);
     if (c->n_edited_pinned) (void)hipHostFree(c->n_edited_pinned);
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
@@ -99,7 +99,6 @@ extern "C" int regione_create(regione_ctx** out, const regione_dims* dims, void*
     if (rc == REGIONE_OK) rc = dev_alloc(&c->a, n * (H + M) * es);
     if (rc == REGIONE_OK) rc = dev_alloc(&c->h1, n * H);
     if (rc == REGIONE_OK) rc = dev_alloc(&c->m, n * M * es);
-    if (rc == REGIONE_OK) rc = dev_alloc(&c->slot_all, n);
     if (rc == REGIONE_OK) rc = dev_alloc(&c->mod_ws, static_cast<size_t>(2 + kModSets) * 6 * H);
     if (rc == REGIONE_OK) rc = dev_alloc(reinterpret_cast<char**>(&c->attn_part), c->attn_part_bytes);
     c->gemm_part_bytes = n > 0 ? static_cast<size_t>(128) << 20 : 0;
@@ -287,18 +286,17 @@ extern "C" int regione_region_step(regione_ctx* ctx, const regione_region_step_a
         const int64_t x_row = static_cast<int64_t>(a->c) * (a->dtype == REGIONE_FP32 ? 4 : 2);
         const bool formed = !(w.cond && w.img.w_mod);
         if (formed && rg_gather_layernorm_ok(a->h_full, rows_in, u, w.img.shift1, w.img.scale1, a->x_t, a->x_e, H, x_row)) {
-            if (int rc = rg_gather_layernorm(ctx, a->h_full, a->h_dtype == REGIONE_FP32, a->e_index, n, H, w.img.shift1, w.img.scale1, rows_in, u, a->x_t, a->x_e, static_cast<int>(x_row / 16))) return rc;
+            if (int rc = rg_gather_layernorm(ctx, a->h_full, a->h_dtype == REGIONE_FP32, a->e_index, n, H, w.img.shift1, w.img.scale1, rows_in, u, a->x_t, a->x_e, static_cast<int>(x_row / 16),
+                                             a->n_txt_fresh > 0 ? a->slots : nullptr, a->n_txt_fresh)) return rc;
             normalised = true;
         }
     }
     if (!normalised)
-        if (int rc = regione_gather_pair(ctx, a->h_full, H, a->h_dtype, rows_in, a->x_t, a->c, a->dtype, a->x_e, a->e_index, a->n_edited_dev, n)) return rc;
+        if (int rc = rg_gather_pair_slots(ctx, a->h_full, H, a->h_dtype, rows_in, a->x_t, a->c, a->dtype, a->x_e, a->e_index, a->n_edited_dev, n,
+                                          a->n_txt_fresh > 0 ? a->slots : nullptr, a->n_txt_fresh)) return rc;
     const int32_t* slot_index = a->e_index;
     int32_t slot_offset = a->slot_offset;
-    if (a->n_txt_fresh > 0) {
-        if (int rc = regione_fresh_slots(ctx, a->e_index, a->n_edited_dev, n, a->n_txt_fresh, a->slots)) return rc;
-        slot_index = a->slots; slot_offset = 0;
-    }
+    if (a->n_txt_fresh > 0) { slot_index = a->slots; slot_offset = 0; }
     const void* in = a->h_rows;
     for (int b = 0; b < a->n_blocks; ++b) {
         if (b == set_end) {
@@ -486,12 +484,9 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
     struct Rows { int r0, n; const regione_stream_weights* w; };
     const Rows groups[2] = {{0, n_txt, &sw[0]}, {n_txt, n_rows - n_txt, &sw[1]}};
 
-    // several branches: the projection's epilogue takes one slot per row, branch b's shifted by b * n_all cache rows
-    const int32_t* gemm_slots = slot_index;
-    if (flags && n_branches > 1) {
-        if ((rc = rg_expand_slots(ctx, slot_index, n_fresh, n_branches, n_all, ctx->slot_all)) != REGIONE_OK) return rc;
-        gemm_slots = ctx->slot_all;
-    }
+    // several branches: the projection's epilogue takes the slot list once per branch, branch b's shifted by b * n_all cache rows
+    if (flags && n_branches > 1 && static_cast<int64_t>(n_branches) * n_all > INT32_MAX)
+        RG_FAIL(REGIONE_ERR_BAD_SHAPE, "block_forward: %d branches of %d cache rows exceed 32-bit row numbers", n_branches, n_all);
 
     // Text and image rows of a double-stream block go through different weights: until the attention joins them, and
     // again after it, the two groups are independent, so the text group may run on the context's second lane and the
@@ -523,7 +518,7 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
         ep.kind = EPI_QKV; ep.hidden = H;
         ep.keep_sums = !ctx->f32 && (flags & REGIONE_FLAG_STORE);
         ep.q = reinterpret_cast<bf16_t*>(ctx->q + static_cast<size_t>(g.r0) * H * es); ep.ldq = H;
-        if (flags) { ep.k = reinterpret_cast<bf16_t*>(kc); ep.v = reinterpret_cast<bf16_t*>(vc); ep.slot = gemm_slots + g.r0; ep.slot_offset = slot_offset; }
+        if (flags) { ep.k = reinterpret_cast<bf16_t*>(kc); ep.v = reinterpret_cast<bf16_t*>(vc); ep.slot = slot_index + g.r0; ep.slot_offset = slot_offset; ep.slot_period = period; ep.slot_branch_rows = n_all; }
         else { ep.k = reinterpret_cast<bf16_t*>(ctx->kf + static_cast<size_t>(g.r0) * H * es); ep.v = reinterpret_cast<bf16_t*>(ctx->vf + static_cast<size_t>(g.r0) * H * es); ep.slot = nullptr; }
         ep.ldkv = H;
         if (g8 && dbl) {

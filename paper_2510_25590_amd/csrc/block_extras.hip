@@ -127,25 +127,6 @@ int rg_qk_norm_rope(regione_ctx* ctx, bf16_t* q, int ldq, bf16_t* k, int ldkv, c
 }
 
 namespace {
-// out[b*n + i] = slot[i] + b * branch_rows: the slot list of every branch of a batched block call
-__global__ void __launch_bounds__(kThreads)
-expand_slots_kernel(const int32_t* __restrict__ slot, int n, int n_branches, int branch_rows, int32_t* __restrict__ out) {
-    const int gid = blockIdx.x * kThreads + threadIdx.x;
-    if (gid >= n * n_branches) return;
-    const int b = gid / n;
-    out[gid] = slot[gid - b * n] + b * branch_rows;
-}
-}  // namespace
-
-int rg_expand_slots(regione_ctx* ctx, const int32_t* slot, int n, int n_branches, int branch_rows, int32_t* out) {
-    if (n <= 0 || n_branches <= 0) return REGIONE_OK;
-    if (static_cast<int64_t>(n_branches) * branch_rows > INT32_MAX) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "block_forward: %d branches of %d cache rows exceed 32-bit row numbers", n_branches, branch_rows);
-    hipLaunchKernelGGL(expand_slots_kernel, dim3((n * n_branches + kThreads - 1) / kThreads), dim3(kThreads), 0, ctx->stream, slot, n, n_branches, branch_rows, out);
-    RG_LAUNCH_CHECK();
-    return REGIONE_OK;
-}
-
-namespace {
 // slots of the fresh rows of a region step whose text rows are recomputed: [0, n_txt) for the text rows, then
 // index[i] + n_txt for the edited rows (image rows sit behind the text rows in the cached sequence)
 __global__ void __launch_bounds__(kThreads)

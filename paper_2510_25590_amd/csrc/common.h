@@ -39,7 +39,6 @@ struct regione_ctx {
     float* attn_part;  // split-KV partial results
     size_t attn_part_bytes;
     size_t attn_range_bytes;   // how much of it plan_ranges counts on
-    int32_t* slot_all; // [max_fresh] slot list of all branches of a batched block call
     float* mod_ws;     // [2 + kModSets][6H] modulation vectors: of the two streams when a block call forms them itself, then those of a step's blocks
     // workspace of the 8-bit block (allocated by its first call): codes of one projection's input rows and their scales
     uint8_t* q8; size_t q8_bytes; float* q8_scale;
@@ -108,6 +107,7 @@ struct GemmEpilogue {
     // EPI_QKV: columns [0,H) -> q[row*ldq+col]; [H,2H) -> k[slot(row)*ldkv + col-H]; [2H,3H) -> v[...];
     //          columns >= 3H -> y[row*ldy + y_col0 + col-3H] (single-stream MLP part)
     bf16_t* q; int ldq; bf16_t* k; bf16_t* v; int ldkv; const int32_t* slot; int slot_offset; int hidden; int y_col0;
+    int slot_period, slot_branch_rows;   // slot_period > 0: rows [b * slot_period, + slot_period) are branch b; the slot list repeats, each branch's rows sit slot_branch_rows further
     // EPI_RESID: y[row*ldy+col] = resid[row*ldr+col] + gate[col]*(acc+bias)
     const void* resid; int ldr; int resid_f32; const float* gate;
     // 8-bit GEMM only: the float32 sums are multiplied by row_scale[row] * col_scale[col] before anything else
@@ -116,6 +116,14 @@ struct GemmEpilogue {
     //   v = storage-rounded(acc + bias); y (if non-null) = v; vel_ca = v; vel_xe -= vel_dt * v; vel_xfull[vel_index[row]] = vel_xe
     void* vel_ca; void* vel_xe; void* vel_xfull; const int32_t* vel_index; float vel_dt;
 };
+
+// Row of the key/value destination of output row `row`: its cache slot when a slot list is given.
+__device__ __forceinline__ int32_t epilogue_slot(const GemmEpilogue& ep, int row) {
+    if (!ep.slot) return row;
+    if (ep.slot_period == 0) return ep.slot[row] + ep.slot_offset;
+    const int branch = row / ep.slot_period;
+    return ep.slot[row - branch * ep.slot_period] + ep.slot_offset + branch * ep.slot_branch_rows;
+}
 
 // a, w_packed (and the epilogue's q, k, v, y, resid where they are activations) are bf16, or float32 in a float32 context
 int rg_gemm(regione_ctx* ctx, const void* a, int lda, const void* w_packed, int m, int n, int k, const GemmEpilogue& ep);
@@ -128,8 +136,11 @@ int rg_velocity_merge(regione_ctx* ctx, const void* v, void* c_a, void* x_e, voi
 // rows h_full[index[i]] to h_rows[i], their LayerNorm + modulation to u[i], and latent rows x_t[index[i]] (x_pieces 16-byte pieces) to x_e[i]: one launch where
 // gather_layernorm_ok (rows of more than 1024 values, everything 16-byte aligned)
 bool rg_gather_layernorm_ok(const void* h_full, const void* h_rows, const void* u, const float* shift, const float* scale, const void* x_t, const void* x_e, int hidden, int64_t x_row_bytes);
+// slots (optional): the slot list of regione_fresh_slots, [0, n_txt) and index[i] + n_txt, in the same launch
 int rg_gather_layernorm(regione_ctx* ctx, const void* h_full, int h_f32, const int32_t* index, int n, int hidden, const float* shift, const float* scale, void* h_rows, void* u,
-                        const void* x_t, void* x_e, int x_pieces);
+                        const void* x_t, void* x_e, int x_pieces, int32_t* slots, int n_txt);
+int rg_gather_pair_slots(regione_ctx* ctx, const void* src_a, int32_t row_elems_a, int32_t dtype_a, void* dst_a, const void* src_b, int32_t row_elems_b, int32_t dtype_b, void* dst_b,
+                         const int32_t* index, const int32_t* n_dev, int64_t n_max, int32_t* slots, int n_txt);
 // modulation vectors of several blocks in one launch: y = silu(x) W^T + b for each entry, W [n, k] row-major bf16
 constexpr int kVecBatch = 16;
 struct VecBatch { const float* x[kVecBatch]; const bf16_t* w[kVecBatch]; const float* b[kVecBatch]; float* y[kVecBatch]; int n[kVecBatch]; int first_wg[kVecBatch + 1]; int count; };
@@ -151,7 +162,6 @@ int rg_layernorm_mod(regione_ctx* ctx, const void* h, int h_f32, int n, int hidd
 int rg_qk_norm_rope(regione_ctx* ctx, bf16_t* q, int ldq, bf16_t* k, int ldkv, const int32_t* kv_slot,
                     const int32_t* pos_slot, int pos0, int slot_offset, int slot_period, int slot_branch_rows, int n, int heads, int d,
                     const float* q_norm, const float* k_norm, const float* table, int table_rows);
-int rg_expand_slots(regione_ctx* ctx, const int32_t* slot, int n, int n_branches, int branch_rows, int32_t* out);
 int rg_attention(regione_ctx* ctx, const void* q, int ldq, int n_q,
                  const void* k0, const void* v0, int ldkv0, int n0,
                  const void* k1, const void* v1, int ldkv1, int n1, const int32_t* idx1, int rows1,   // rows1: rows of the array that idx1 picks from

@@ -40,7 +40,7 @@ __device__ __forceinline__ void store_f32(const GemmEpilogue& ep, int row, int c
         if (col < H) {
             reinterpret_cast<float*>(ep.q)[static_cast<int64_t>(row) * ep.ldq + col] = val;
         } else if (col < 3 * H) {
-            const int64_t kv_row = ep.slot ? static_cast<int64_t>(ep.slot[row]) + ep.slot_offset : row;
+            const int64_t kv_row = epilogue_slot(ep, row);
             if (col < 2 * H) reinterpret_cast<float*>(ep.k)[kv_row * ep.ldkv + (col - H)] = val;
             else reinterpret_cast<float*>(ep.v)[kv_row * ep.ldkv + (col - 2 * H)] = val;
         } else {

@@ -27,8 +27,7 @@ __device__ __forceinline__ float gelu_tanh_f32(float x) {
 // Row of the key/value destination for output row `row` (its cache slot when a slot list is given).
 template <int KIND>
 __device__ __forceinline__ int64_t epilogue_kv_row(const GemmEpilogue& ep, int row) {
-    if (KIND != EPI_QKV) return row;
-    return ep.slot ? static_cast<int64_t>(ep.slot[row]) + ep.slot_offset : row;
+    return KIND == EPI_QKV ? epilogue_slot(ep, row) : row;
 }
 
 template <int KIND>
@@ -147,7 +146,7 @@ template <int KIND, bool SCALED> struct EpiRow {
     float scale;
     __device__ __forceinline__ void load(const GemmEpilogue& ep, int row) {
         place = row;
-        if (KIND == EPI_QKV && ep.slot) place = ep.slot[row] + ep.slot_offset;
+        if (KIND == EPI_QKV) place = epilogue_slot(ep, row);
         if (KIND == EPI_VELOCITY && ep.vel_index) place = ep.vel_index[row];
         scale = SCALED ? ep.row_scale[row] : 1.f;
     }

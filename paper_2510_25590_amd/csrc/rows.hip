@@ -59,15 +59,23 @@ int rows_by_index(regione_ctx* ctx, const void* src, void* dst, int32_t row_elem
     return REGIONE_OK;
 }
 
+// The slot list of a step's fresh rows (regione_fresh_slots) beside the launch that gathers them: the text rows' own by the launch's threads, a gathered row's by whoever moves
+// its first piece.
+struct FreshSlots { int32_t* slots; int n_txt; };
+__device__ __forceinline__ void text_slots(const FreshSlots& f, int64_t thread, int64_t threads) {
+    if (f.slots) for (int64_t i = thread; i < f.n_txt; i += threads) f.slots[i] = static_cast<int32_t>(i);
+}
+
 // Two tensors by one index list in one launch (the hidden rows and the latent rows of the edited tokens): a row of the
 // pair is pa + pb 16-byte pieces, the first pa of tensor A.
 template <bool GATHER>
 __global__ void __launch_bounds__(kThreads)
 rows_pair_by_index_kernel(const rows_u32x4* __restrict__ src_a, rows_u32x4* __restrict__ dst_a, int pa,
                           const rows_u32x4* __restrict__ src_b, rows_u32x4* __restrict__ dst_b, int pb,
-                          const int32_t* __restrict__ index, const int32_t* __restrict__ n_dev, int64_t n_max) {
+                          const int32_t* __restrict__ index, const int32_t* __restrict__ n_dev, int64_t n_max, FreshSlots fresh) {
     int64_t n = n_max;
     if (n_dev) { const int64_t nd = *n_dev; n = nd < n_max ? (nd < 0 ? 0 : nd) : n_max; }
+    text_slots(fresh, static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x, static_cast<int64_t>(gridDim.x) * kThreads);
     const int ppr = pa + pb;
     const int64_t total = n * ppr;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
@@ -75,6 +83,7 @@ rows_pair_by_index_kernel(const rows_u32x4* __restrict__ src_a, rows_u32x4* __re
         const int64_t row = u / ppr;
         int piece = static_cast<int>(u - row * ppr);
         const int64_t other = index[row];
+        if (fresh.slots && piece == 0) fresh.slots[fresh.n_txt + row] = static_cast<int32_t>(other) + fresh.n_txt;
         const bool first = piece < pa;
         const rows_u32x4* src = first ? src_a : src_b;
         rows_u32x4* dst = first ? dst_a : dst_b;
@@ -87,7 +96,7 @@ rows_pair_by_index_kernel(const rows_u32x4* __restrict__ src_a, rows_u32x4* __re
 
 template <bool GATHER>
 int rows_pair(regione_ctx* ctx, const void* src_a, void* dst_a, int32_t elems_a, int32_t dtype_a, const void* src_b, void* dst_b, int32_t elems_b, int32_t dtype_b,
-              const int32_t* index, const int32_t* n_dev, int64_t n_max, const char* who) {
+              const int32_t* index, const int32_t* n_dev, int64_t n_max, const char* who, FreshSlots fresh = {nullptr, 0}) {
     if (!ctx) RG_FAIL(REGIONE_ERR_INVALID_ARG, "%s: null context", who);
     const int64_t bytes_a = static_cast<int64_t>(elems_a) * (dtype_a == REGIONE_BF16 ? 2 : 4), bytes_b = static_cast<int64_t>(elems_b) * (dtype_b == REGIONE_BF16 ? 2 : 4);
     const bool wide = elems_a > 0 && elems_b > 0 && n_max > 0 && src_a && dst_a && src_b && dst_b && index && (bytes_a % 16 == 0) && (bytes_b % 16 == 0) &&
@@ -95,6 +104,8 @@ int rows_pair(regione_ctx* ctx, const void* src_a, void* dst_a, int32_t elems_a,
                       (dtype_a == REGIONE_BF16 || dtype_a == REGIONE_FP32) && (dtype_b == REGIONE_BF16 || dtype_b == REGIONE_FP32);
     if (!wide) {   // anything unusual (odd row widths, empty lists, bad arguments): the single-tensor path, with its checks
         if (int rc = rows_by_index<GATHER>(ctx, src_a, dst_a, elems_a, dtype_a, index, n_dev, n_max, who)) return rc;
+        if (fresh.slots)
+            if (int rc = regione_fresh_slots(ctx, index, n_dev, n_max, fresh.n_txt, fresh.slots)) return rc;
         return rows_by_index<GATHER>(ctx, src_b, dst_b, elems_b, dtype_b, index, n_dev, n_max, who);
     }
     const int pa = static_cast<int>(bytes_a / 16), pb = static_cast<int>(bytes_b / 16);
@@ -103,7 +114,7 @@ int rows_pair(regione_ctx* ctx, const void* src_a, void* dst_a, int32_t elems_a,
     ProfScope prof(ctx, REGIONE_PROF_ROWS);
     hipLaunchKernelGGL((rows_pair_by_index_kernel<GATHER>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, ctx->stream,
                        static_cast<const rows_u32x4*>(src_a), static_cast<rows_u32x4*>(dst_a), pa, static_cast<const rows_u32x4*>(src_b), static_cast<rows_u32x4*>(dst_b), pb,
-                       index, n_dev, n_max);
+                       index, n_dev, n_max, fresh);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }
@@ -163,8 +174,11 @@ layernorm_mod_wide_kernel(const T* __restrict__ h, int n, int hidden, const floa
 template <typename T, typename U, int W>
 __global__ void __launch_bounds__(64 * W)
 gather_layernorm_kernel(const T* __restrict__ h_full, const int32_t* __restrict__ index, int n, int hidden, const float* __restrict__ shift, const float* __restrict__ scale,
-                        T* __restrict__ h_rows, U* __restrict__ u, const rows_u32x4* __restrict__ x_t, rows_u32x4* __restrict__ x_e, int x_pieces) {
+                        T* __restrict__ h_rows, U* __restrict__ u, const rows_u32x4* __restrict__ x_t, rows_u32x4* __restrict__ x_e, int x_pieces, FreshSlots fresh) {
     __shared__ float2 part[2][W];
+    text_slots(fresh, static_cast<int64_t>(blockIdx.x) * (64 * W) + threadIdx.x, static_cast<int64_t>(gridDim.x) * (64 * W));
+    if (fresh.slots && threadIdx.x == 0)
+        for (int row = blockIdx.x; row < n; row += gridDim.x) fresh.slots[fresh.n_txt + row] = index[row] + fresh.n_txt;
     for (int row = blockIdx.x; row < n; row += gridDim.x)
         for (int p = threadIdx.x; p < x_pieces; p += 64 * W) x_e[static_cast<int64_t>(row) * x_pieces + p] = x_t[static_cast<int64_t>(index[row]) * x_pieces + p];
     layernorm_rows_wide<T, W>(h_full, n, hidden, shift, scale, part, [&](int row) -> int64_t { return index[row]; },
@@ -320,6 +334,11 @@ extern "C" int regione_gather(regione_ctx* ctx, const void* src, int32_t row_ele
 extern "C" int regione_scatter(regione_ctx* ctx, void* dst_full, int32_t row_elems, int32_t dtype,
                                const int32_t* index, const int32_t* n_dev, int64_t n_max, const void* src) {
     return rows_by_index<false>(ctx, src, dst_full, row_elems, dtype, index, n_dev, n_max, "scatter");
+}
+
+int rg_gather_pair_slots(regione_ctx* ctx, const void* src_a, int32_t row_elems_a, int32_t dtype_a, void* dst_a, const void* src_b, int32_t row_elems_b, int32_t dtype_b, void* dst_b,
+                         const int32_t* index, const int32_t* n_dev, int64_t n_max, int32_t* slots, int n_txt) {
+    return rows_pair<true>(ctx, src_a, dst_a, row_elems_a, dtype_a, src_b, dst_b, row_elems_b, dtype_b, index, n_dev, n_max, "gather_pair", FreshSlots{slots, n_txt});
 }
 
 extern "C" int regione_gather_pair(regione_ctx* ctx, const void* src_a, int32_t row_elems_a, int32_t dtype_a, void* dst_a,
@@ -516,19 +535,20 @@ bool rg_gather_layernorm_ok(const void* h_full, const void* h_rows, const void* 
 }
 template <typename T, typename U>
 static void launch_gather_layernorm(regione_ctx* ctx, const void* h_full, const int32_t* index, int n, int hidden, const float* shift, const float* scale, void* h_rows, void* u,
-                                    const void* x_t, void* x_e, int x_pieces) {
+                                    const void* x_t, void* x_e, int x_pieces, FreshSlots fresh) {
 #define RG_LN_WIDE(W) case W: hipLaunchKernelGGL((gather_layernorm_kernel<T, U, W>), dim3(n < ln_wide_grid(W) ? n : ln_wide_grid(W)), dim3(64 * W), 0, ctx->stream, \
-        static_cast<const T*>(h_full), index, n, hidden, shift, scale, static_cast<T*>(h_rows), static_cast<U*>(u), static_cast<const rows_u32x4*>(x_t), static_cast<rows_u32x4*>(x_e), x_pieces); break;
+        static_cast<const T*>(h_full), index, n, hidden, shift, scale, static_cast<T*>(h_rows), static_cast<U*>(u), static_cast<const rows_u32x4*>(x_t), static_cast<rows_u32x4*>(x_e), x_pieces, fresh); break;
     switch ((hidden / 8 + 63) / 64) { RG_LN_WIDE(3) RG_LN_WIDE(4) RG_LN_WIDE(5) RG_LN_WIDE(6) RG_LN_WIDE(7) RG_LN_WIDE(8) }
 #undef RG_LN_WIDE
 }
 int rg_gather_layernorm(regione_ctx* ctx, const void* h_full, int h_f32, const int32_t* index, int n, int hidden, const float* shift, const float* scale, void* h_rows, void* u,
-                        const void* x_t, void* x_e, int x_pieces) {
+                        const void* x_t, void* x_e, int x_pieces, int32_t* slots, int n_txt) {
     if (n <= 0) return REGIONE_OK;
+    const FreshSlots fresh = {slots, n_txt};
     ProfScope prof(ctx, REGIONE_PROF_LAYERNORM);
-    if (ctx->f32) launch_gather_layernorm<float, float>(ctx, h_full, index, n, hidden, shift, scale, h_rows, u, x_t, x_e, x_pieces);
-    else if (h_f32) launch_gather_layernorm<float, bf16_t>(ctx, h_full, index, n, hidden, shift, scale, h_rows, u, x_t, x_e, x_pieces);
-    else launch_gather_layernorm<bf16_t, bf16_t>(ctx, h_full, index, n, hidden, shift, scale, h_rows, u, x_t, x_e, x_pieces);
+    if (ctx->f32) launch_gather_layernorm<float, float>(ctx, h_full, index, n, hidden, shift, scale, h_rows, u, x_t, x_e, x_pieces, fresh);
+    else if (h_f32) launch_gather_layernorm<float, bf16_t>(ctx, h_full, index, n, hidden, shift, scale, h_rows, u, x_t, x_e, x_pieces, fresh);
+    else launch_gather_layernorm<bf16_t, bf16_t>(ctx, h_full, index, n, hidden, shift, scale, h_rows, u, x_t, x_e, x_pieces, fresh);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }
