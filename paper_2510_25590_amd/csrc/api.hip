@@ -502,7 +502,31 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
     };
     if (two_lanes && (rc = ensure_side_lane(ctx)) != REGIONE_OK) return rc;
 
+    // both groups in one lane: products that are small for both go out in one launch
+    const bool pairs = n_txt > 0 && groups[1].n > 0 && !two_lanes && !w8;
+
     // ---- first half: LayerNorm + modulation, QKV (and MLP-in for single-stream) projection
+    GemmCall qkv[2] = {};
+    bool paired = false;
+    auto qkv_epilogue = [&](const Rows& g) {
+        GemmEpilogue ep = {};
+        ep.kind = EPI_QKV; ep.hidden = H;
+        ep.keep_sums = !ctx->f32 && (flags & REGIONE_FLAG_STORE);
+        ep.q = reinterpret_cast<bf16_t*>(ctx->q + static_cast<size_t>(g.r0) * H * es); ep.ldq = H;
+        if (flags) { ep.k = reinterpret_cast<bf16_t*>(kc); ep.v = reinterpret_cast<bf16_t*>(vc); ep.slot = slot_index + g.r0; ep.slot_offset = slot_offset; ep.slot_period = period; ep.slot_branch_rows = n_all; }
+        else { ep.k = reinterpret_cast<bf16_t*>(ctx->kf + static_cast<size_t>(g.r0) * H * es); ep.v = reinterpret_cast<bf16_t*>(ctx->vf + static_cast<size_t>(g.r0) * H * es); ep.slot = nullptr; }
+        ep.ldkv = H;
+        return ep;
+    };
+    if (pairs && !image_rows_normalised) {
+        for (int i = 0; i < 2; ++i) {
+            const Rows& g = groups[i];
+            qkv[i] = {static_cast<const char*>(h_in) + static_cast<size_t>(g.r0) * H * h_elem, H, 1, h_f32, g.w->shift1, g.w->scale1, g.w->w_qkv, g.n, 3 * H, H, qkv_epilogue(g)};
+            qkv[i].ep.bias = g.w->b_qkv;
+        }
+        paired = rg_gemm_pairs(ctx, qkv[0], qkv[1]);
+        if (paired && (rc = rg_gemm_pair(ctx, qkv[0], qkv[1])) != REGIONE_OK) return rc;
+    }
     if (two_lanes && (rc = lane_fork(ctx)) != REGIONE_OK) return rc;
     for (const Rows& g : groups) {
         if (g.n <= 0) continue;
@@ -514,13 +538,7 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
         const regione_stream_weights_fp8* g8 = w8 ? (&g == &groups[0] ? &w8->txt : &w8->img) : nullptr;
         if (g8 && (rc = rg_layernorm_mod_fp8(ctx, hin, h_f32, g.n, H, g.w->shift1, g.w->scale1, ctx->q8, ctx->q8_scale)) != REGIONE_OK) return rc;
         if (g8 && taps && ((rc = tap(taps->u1_codes, ctx->q8, g.r0, g.n, H)) != REGIONE_OK || (rc = tap(taps->u1_scale, ctx->q8_scale, g.r0, g.n, 4)) != REGIONE_OK)) return rc;
-        GemmEpilogue ep = {};
-        ep.kind = EPI_QKV; ep.hidden = H;
-        ep.keep_sums = !ctx->f32 && (flags & REGIONE_FLAG_STORE);
-        ep.q = reinterpret_cast<bf16_t*>(ctx->q + static_cast<size_t>(g.r0) * H * es); ep.ldq = H;
-        if (flags) { ep.k = reinterpret_cast<bf16_t*>(kc); ep.v = reinterpret_cast<bf16_t*>(vc); ep.slot = slot_index + g.r0; ep.slot_offset = slot_offset; ep.slot_period = period; ep.slot_branch_rows = n_all; }
-        else { ep.k = reinterpret_cast<bf16_t*>(ctx->kf + static_cast<size_t>(g.r0) * H * es); ep.v = reinterpret_cast<bf16_t*>(ctx->vf + static_cast<size_t>(g.r0) * H * es); ep.slot = nullptr; }
-        ep.ldkv = H;
+        GemmEpilogue ep = qkv_epilogue(g);
         if (g8 && dbl) {
             ep.bias = g.w->b_qkv; ep.row_scale = ctx->q8_scale; ep.col_scale = g8->s_qkv;
             rc = rg_gemm_fp8(ctx, ctx->q8, H, static_cast<const uint8_t*>(g8->w_qkv), g.n, 3 * H, H, ep);
@@ -528,6 +546,8 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
             ep.bias = g.w->b_1; ep.act = REGIONE_ACT_GELU_TANH; ep.row_scale = ctx->q8_scale; ep.col_scale = g8->s_1;
             ep.y = ctx->a + static_cast<size_t>(g.r0) * lda_attn * es; ep.ldy = lda_attn; ep.y_col0 = H; ep.y_f32 = 0;
             rc = rg_gemm_fp8(ctx, ctx->q8, H, static_cast<const uint8_t*>(g8->w_1), g.n, 3 * H + M, H, ep);
+        } else if (paired) {
+            rc = REGIONE_OK;
         } else if (dbl) {
             ep.bias = g.w->b_qkv;
             rc = u_ready ? rg_gemm(ctx, u, H, g.w->w_qkv, g.n, 3 * H, H, ep) : rg_layernorm_gemm(ctx, hin, h_f32, g.w->shift1, g.w->scale1, u, g.w->w_qkv, g.n, 3 * H, H, ep);
@@ -559,6 +579,41 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
     if (w8 && taps && (rc = tap(taps->attn, ctx->a, 0, n_fresh, static_cast<size_t>(lda_attn) * 2)) != REGIONE_OK) return rc;
 
     // ---- second half
+    if (pairs) {
+        // the same three products as below, each for both groups before the next
+        GemmCall out[2] = {}, up[2] = {}, down[2] = {};
+        for (int i = 0; i < 2; ++i) {
+            const Rows& g = groups[i];
+            float* h1 = ctx->h1 + static_cast<size_t>(g.r0) * H;
+            char* m = ctx->m + static_cast<size_t>(g.r0) * M * es;
+            out[i] = {ctx->a + static_cast<size_t>(g.r0) * lda_attn * es, H, 0, 0, nullptr, nullptr, g.w->w_o, g.n, H, H, {}};
+            out[i].ep.kind = EPI_RESID; out[i].ep.bias = g.w->b_o; out[i].ep.gate = g.w->gate1;
+            out[i].ep.resid = static_cast<const char*>(h_in) + static_cast<size_t>(g.r0) * H * h_elem; out[i].ep.ldr = H; out[i].ep.resid_f32 = h_f32;
+            out[i].ep.y = h1; out[i].ep.ldy = H; out[i].ep.y_f32 = 1;
+            up[i] = {h1, H, 1, 1, g.w->shift2, g.w->scale2, g.w->w_1, g.n, M, H, {}};
+            up[i].ep.kind = EPI_PLAIN; up[i].ep.bias = g.w->b_1; up[i].ep.act = REGIONE_ACT_GELU_TANH;
+            up[i].ep.y = m; up[i].ep.ldy = M; up[i].ep.y_f32 = ctx->f32;
+            down[i] = {m, M, 0, 0, nullptr, nullptr, g.w->w_2, g.n, H, M, {}};
+            down[i].ep.kind = EPI_RESID; down[i].ep.bias = g.w->b_2; down[i].ep.gate = g.w->gate2;
+            down[i].ep.resid = h1; down[i].ep.ldr = H; down[i].ep.resid_f32 = 1;
+            down[i].ep.y = static_cast<char*>(h_out) + static_cast<size_t>(g.r0) * H * h_elem; down[i].ep.ldy = H; down[i].ep.y_f32 = h_f32;
+        }
+        const GemmCall (*const calls[3])[2] = {&out, &up, &down};
+        bool pair[3];
+        for (int j = 0; j < 3; ++j) pair[j] = rg_gemm_pairs(ctx, (*calls[j])[0], (*calls[j])[1]);
+        for (int j = 0; j < 3 && (pair[0] || pair[1] || pair[2]); ++j) {
+            const GemmCall& txt = (*calls[j])[0];
+            const GemmCall& img = (*calls[j])[1];
+            if (pair[j] && (rc = rg_gemm_pair(ctx, txt, img)) != REGIONE_OK) return rc;
+            for (int i = 0; i < 2 && !pair[j]; ++i) {
+                const GemmCall& p = i == 0 ? txt : img;
+                char* u = ctx->u + static_cast<size_t>(groups[i].r0) * H * es;
+                rc = p.norm ? rg_layernorm_gemm(ctx, p.a, p.a_f32, p.shift, p.scale, u, p.w, p.m, p.n, p.k, p.ep) : rg_gemm(ctx, p.a, p.lda, p.w, p.m, p.n, p.k, p.ep);
+                if (rc != REGIONE_OK) return rc;
+            }
+            if (j == 2) return REGIONE_OK;
+        }
+    }
     if (two_lanes && (rc = lane_fork(ctx)) != REGIONE_OK) return rc;
     for (const Rows& g : groups) {
         if (g.n <= 0) continue;

@@ -145,6 +145,14 @@ int rg_gather_pair_slots(regione_ctx* ctx, const void* src_a, int32_t row_elems_
 constexpr int kVecBatch = 16;
 struct VecBatch { const float* x[kVecBatch]; const bf16_t* w[kVecBatch]; const float* b[kVecBatch]; float* y[kVecBatch]; int n[kVecBatch]; int first_wg[kVecBatch + 1]; int count; };
 int rg_vec_linear_batch(regione_ctx* ctx, VecBatch& batch, int k);
+// One product: norm: of layernorm_mod(a), rows a of k values (a_f32: float32).
+struct GemmCall { const void* a; int lda, norm, a_f32; const float* shift; const float* scale; const void* w; int m, n, k; GemmEpilogue ep; };
+// Two products of the same shape but for their rows (the text and the image rows of a block, each with weights of their own) in one launch, with the results of two calls bit for
+// bit; rg_gemm_pairs tells where that pays (nothing else may be passed to rg_gemm_pair).
+bool rg_gemm_pairs(const regione_ctx* ctx, const GemmCall& a, const GemmCall& b);
+bool rg_gemm_pairs_f32(const GemmCall& a, const GemmCall& b);
+int rg_gemm_pair(regione_ctx* ctx, const GemmCall& a, const GemmCall& b);
+int rg_gemm_pair_f32(regione_ctx* ctx, const GemmCall& a, const GemmCall& b);
 // the product of layernorm_mod(h) (h: rows of k values, bf16 or float32); u: workspace [m, k] of the compute dtype
 int rg_layernorm_gemm(regione_ctx* ctx, const void* h, int h_f32, const float* shift, const float* scale, void* u, const void* w_packed, int m, int n, int k, const GemmEpilogue& ep);
 // the product of layernorm_mod(h) in one launch where that pays; *done tells

@@ -284,6 +284,32 @@ int rg_layernorm_gemm(regione_ctx* ctx, const void* h, int h_f32, const float* s
     return rg_gemm(ctx, u, k, wp, m, n, k, ep_in);
 }
 
+// the columns of a workgroup for the row tiles of both products; 0: not a pair of small ones
+static int pair_columns(const regione_ctx* ctx, const GemmCall& a, const GemmCall& b) {
+    return small_columns(ctx, 16 * ((a.m + 15) / 16 + (b.m + 15) / 16), a.n, a.k, a.norm != 0);
+}
+
+bool rg_gemm_pairs(const regione_ctx* ctx, const GemmCall& a, const GemmCall& b) {
+    if (a.m <= 0 || b.m <= 0 || a.n != b.n || a.k != b.k || a.norm != b.norm || a.a_f32 != b.a_f32 || a.ep.kind != b.ep.kind || a.n <= kNarrowColumns) return false;
+    if (a.ep.kind != EPI_PLAIN && a.ep.kind != EPI_QKV && (a.ep.kind != EPI_RESID || a.norm)) return false;
+    // what either product would be refused for is left to its own call
+    const int unit = ctx->f32 ? 3 : 7;
+    for (const GemmCall* c : {&a, &b})
+        if ((c->lda & unit) || !rg_aligned16(c->a) || !rg_aligned16(c->w) || !rg_aligned16(c->shift) || !rg_aligned16(c->scale)) return false;
+    if (ctx->f32) return rg_gemm_pairs_f32(a, b);
+    // The rule of one product (small_columns) for the row tiles of both: each alone is then one of the small ones, too, and its sums are taken in the same order.
+    return a.k > 0 && a.k % BK == 0 && (!a.norm || a.k <= kLnColumns) && pair_columns(ctx, a, b) != 0;
+}
+
+int rg_gemm_pair(regione_ctx* ctx, const GemmCall& a, const GemmCall& b) {
+    ProfScope prof(ctx, REGIONE_PROF_GEMM);
+    if (ctx->f32) return rg_gemm_pair_f32(ctx, a, b);
+    GemmEpilogue ep_a = a.ep, ep_b = b.ep;
+    ep_a.vec_ok = (a.n % 8 == 0) && wide_epilogue_ok(ep_a, a.n);
+    ep_b.vec_ok = (b.n % 8 == 0) && wide_epilogue_ok(ep_b, b.n);
+    return pair_columns(ctx, a, b) == 32 ? launch_small_pair_kind<2>(ctx, a, b, ep_a, ep_b) : launch_small_pair_kind<4>(ctx, a, b, ep_a, ep_b);
+}
+
 extern "C" int64_t regione_packed_weight_elems(int32_t n, int32_t k) {
     if (n <= 0 || k <= 0) return 0;
     return static_cast<int64_t>((n + 31) / 32) * 32 * k;

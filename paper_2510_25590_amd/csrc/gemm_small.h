@@ -31,13 +31,13 @@ template <int CF> constexpr unsigned small_lds_bytes(bool ln, int k) {
 static_assert(small_lds_bytes<4>(true, kLnColumns) <= 65536u, "what a launch may ask for without hipFuncSetAttribute");
 
 template <int CF, int KIND, int LN>
-__device__ __forceinline__ void gemm_small_tile(unsigned char* lds, const void* __restrict__ A, int lda, const bf16_t* __restrict__ Wp, int M, int N, int K,
+__device__ __forceinline__ void gemm_small_tile(unsigned char* lds, int tile_y, const void* __restrict__ A, int lda, const bf16_t* __restrict__ Wp, int M, int N, int K,
                                                 const float* __restrict__ shift, const float* __restrict__ scale, const GemmEpilogue& ep) {
     constexpr int CHUNK = SmallTile<CF>::CHUNK;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, quad = lane >> 4;
-    const int n0 = blockIdx.x * (16 * CF), m0 = blockIdx.y * kSmallRows;
+    const int n0 = blockIdx.x * (16 * CF), m0 = tile_y * kSmallRows;
     const int steps = K >> 5, per = (steps + kSmallWaves - 1) / kSmallWaves;
     const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
 
@@ -135,8 +135,20 @@ __global__ void __launch_bounds__(kSmallWaves * 64) __attribute__((amdgpu_waves_
 gemm_small_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict__ Wp, int M, int N, int K,
                   const float* __restrict__ shift, const float* __restrict__ scale, GemmEpilogue ep) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    gemm_small_tile<CF, KIND, LN>(lds, A, lda, Wp, M, N, K, shift, scale, ep);
+    gemm_small_tile<CF, KIND, LN>(lds, blockIdx.y, A, lda, Wp, M, N, K, shift, scale, ep);
 }
+// Two products of one shape but for their rows.  Either is a few us of weights' latency that fills part of the chip, behind a gap between two launches that is as long; tiles_p: the
+// first product's row tiles.  A block (attention included), us, two launches -> one: hidden 256, 16 + 36 rows 36.8 -> 21.9, 64 + 256 39.3 -> 28.9, 512 + 512 54 -> 47; hidden
+// 1024, 16 + 64 rows 59 -> 42; hidden 3072 (the two residual products at most), 16 + 36 rows 153 -> 147.
+struct SmallProduct { const void* a; int lda; const bf16_t* w; int m; const float* shift; const float* scale; GemmEpilogue ep; };
+template <int CF, int KIND, int LN>
+__global__ void __launch_bounds__(kSmallWaves * 64) __attribute__((amdgpu_waves_per_eu(2)))
+gemm_small_pair_kernel(SmallProduct p, SmallProduct q, int tiles_p, int N, int K) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    if (static_cast<int>(blockIdx.y) < tiles_p) gemm_small_tile<CF, KIND, LN>(lds, blockIdx.y, p.a, p.lda, p.w, p.m, N, K, p.shift, p.scale, p.ep);
+    else gemm_small_tile<CF, KIND, LN>(lds, blockIdx.y - tiles_p, q.a, q.lda, q.w, q.m, N, K, q.shift, q.scale, q.ep);
+}
+
 // The velocity head and, in workgroups of their own behind its tiles, the merge of the hidden rows (dst[index[i]] = src[i] in 16-byte pieces): neither reads what the
 // other writes, and both are shorter than what lies between two launches.  820 rows of 3072 values, kernel trace: 8.8 + 5.0 -> 10.5 us.
 template <int CF>
@@ -144,7 +156,7 @@ __global__ void __launch_bounds__(kSmallWaves * 64) __attribute__((amdgpu_waves_
 gemm_small_merge_kernel(const void* __restrict__ A, int lda, const bf16_t* __restrict__ Wp, int M, int N, int K, GemmEpilogue ep, int head_tiles_y, RowMerge merge) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     if (static_cast<int>(blockIdx.y) < head_tiles_y) {
-        gemm_small_tile<CF, EPI_VELOCITY, LN_NONE>(lds, A, lda, Wp, M, N, K, nullptr, nullptr, ep);
+        gemm_small_tile<CF, EPI_VELOCITY, LN_NONE>(lds, blockIdx.y, A, lda, Wp, M, N, K, nullptr, nullptr, ep);
         return;
     }
     const unsigned wg = (blockIdx.y - head_tiles_y) * gridDim.x + blockIdx.x, stride = (gridDim.y - head_tiles_y) * gridDim.x * (kSmallWaves * 64);
@@ -194,6 +206,26 @@ int launch_small_kind(regione_ctx* ctx, const void* a, int lda, const bf16_t* wp
         return launch_small<CF, EPI_RESID, LN>(ctx, a, lda, wp, m, n, k, shift, scale, ep);
     }
     RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm_small: epilogue kind %d", ep.kind);
+}
+
+inline SmallProduct small_product(const GemmCall& c, const GemmEpilogue& ep) { return {c.a, c.lda, static_cast<const bf16_t*>(c.w), c.m, c.shift, c.scale, ep}; }
+template <int CF, int KIND, int LN>
+int launch_small_pair(regione_ctx* ctx, const GemmCall& a, const GemmCall& b, const GemmEpilogue& ep_a, const GemmEpilogue& ep_b) {
+    const int ya = (a.m + kSmallRows - 1) / kSmallRows, yb = (b.m + kSmallRows - 1) / kSmallRows;
+    hipLaunchKernelGGL((gemm_small_pair_kernel<CF, KIND, LN>), dim3(static_cast<unsigned>((a.n + 16 * CF - 1) / (16 * CF)), static_cast<unsigned>(ya + yb)), dim3(kSmallWaves * 64),
+                       small_lds_bytes<CF>(LN != LN_NONE, a.k), ctx->stream, small_product(a, ep_a), small_product(b, ep_b), ya, a.n, a.k);
+    RG_LAUNCH_CHECK();
+    return REGIONE_OK;
+}
+template <int CF>
+int launch_small_pair_kind(regione_ctx* ctx, const GemmCall& a, const GemmCall& b, const GemmEpilogue& ep_a, const GemmEpilogue& ep_b) {
+    const int ln = a.norm ? (a.a_f32 ? LN_F32 : LN_BF16) : LN_NONE;
+    if (a.ep.kind == EPI_RESID) return launch_small_pair<CF, EPI_RESID, LN_NONE>(ctx, a, b, ep_a, ep_b);
+#define RG_PAIR(LN) return a.ep.kind == EPI_QKV ? launch_small_pair<CF, EPI_QKV, LN>(ctx, a, b, ep_a, ep_b) : launch_small_pair<CF, EPI_PLAIN, LN>(ctx, a, b, ep_a, ep_b)
+    if (ln == LN_BF16) RG_PAIR(LN_BF16);
+    if (ln == LN_F32) RG_PAIR(LN_F32);
+    RG_PAIR(LN_NONE);
+#undef RG_PAIR
 }
 
 // tiles of 16 rows x `columns` (32 or 64); every epilogue kind
