@@ -41,22 +41,22 @@ pack_weight_kernel(const bf16_t* __restrict__ w, int n, int k, bf16_t* __restric
 // at 2.2 GHz, times a factor of the tile that takes in its start, its epilogue and what the matrix cores' power takes from the clock; not below the time that the
 // weights take from HBM.  A K split adds its partial sums' way out and back (padded tiles).
 // All constants are fitted to every tile and K split of 267 shapes (32-9400 rows, 1024-21504 columns, k 1024-15360, weights of 3072-wide models uncached).  Against
-// the best of all plans the choice loses 0.6 % on average over these and over 143 others, 7 % at most on those; the constants before, fitted without the three widest tiles of gemm_kg_kernel,
+// the best of all plans the choice loses 0.6 % on average over these and over 143 others, 7 % at most on those; the constants before, fitted without the two widest tiles of gemm_kg_kernel,
 // lost 2.0 % with them.  us, then / now: 2048 x 9216 x 3072 103.3 / 95.8, 1640 x 12288 x 3072 103.5 / 98.9, 1382 x 3072 x 15360 116.7 / 109.9, 205 x 21504 x 3072 43.8 / 41.6.
 struct TileShape { int code, rows, cols, lds_kb, form; double factor; };   // form: kTilesFp8 only; factor: kTiles only
 constexpr TileShape kTiles[] = {{222, 64, 64, 64, 0, 1.089},   {224, 64, 128, 96, 0, 1.156},  {242, 128, 64, 96, 0, 1.056},  {244, 128, 128, 128, 0, 1.059},
                                 {274, 224, 128, 132, 0, 1.054}, {284, 256, 128, 144, 0, 1.381}, {426, 128, 96, 112, 0, 1.058}, {436, 192, 96, 144, 0, 1.114},
                                 {446, 256, 96, 132, 0, 0.985}, {44, 128, 256, 144, 0, 1.028}, {64, 192, 256, 136, 0, 1.143}, {74, 224, 256, 148, 0, 1.065},
-                                {84, 256, 256, 160, 0, 1.011}, {248, 128, 256, 144, 0, 1.402}, {266, 192, 192, 144, 0, 1.021}, {276, 224, 192, 156, 0, 1.012}};
+                                {84, 256, 256, 160, 0, 1.011}, {266, 192, 192, 144, 0, 1.021}, {276, 224, 192, 156, 0, 1.012}};
 struct GemmPlan { int tile; int splits; };
 
 // cycles: per KiB copied, barriers and least time of a step by form (narrow, wide), once more for narrow ones; MHz; us per round; TB/s of weights and results; K splits
 struct PlanConstants { double feed, over_n, over_w, least_n, least_w, add_n, clock, round, hbm, out, split, split_unit, split_tile, two; bool wide_half_steps; };
 constexpr PlanConstants kPlan = {29.55, 174.9, 93.0, 546.2, 310.6, 59.5, 23.2, 0.14, 7.18e6, 128.0e6, 1.44, 0.132, 0.0267, 4.13, true};
-// those of before, without the factors and the three widest tiles of gemm_kg_kernel, where a product's sums are kept
+// those of before, without the factors and the two widest tiles of gemm_kg_kernel, where a product's sums are kept
 constexpr PlanConstants kPlanKept = {28.0, 120.0, 60.0, 450.0, 500.0, 53.0, 455.0, 6.9, 5.5e6, 8.0e6, 1.8, 0.19, 0.0116, 2.35, false};
 double plan_time_bf16(const PlanConstants& c, const TileShape& t, int m, int n, int steps, int splits) {
-    if (!c.wide_half_steps && (t.code == 248 || t.code == 266 || t.code == 276)) return 1e30;
+    if (!c.wide_half_steps && (t.code == 266 || t.code == 276)) return 1e30;
     const int m_tiles = (m + t.rows - 1) / t.rows, n_tiles = (n + t.cols - 1) / t.cols;
     const long units = static_cast<long>(m_tiles) * n_tiles * splits;
     const int per = (steps + splits - 1) / splits;
@@ -207,7 +207,7 @@ bool wide_epilogue_ok(const GemmEpilogue& ep, int n) {
 }  // namespace
 
 static int gemm_tile(regione_ctx* ctx, const GemmPlan& p, const bf16_t* a, int lda, const bf16_t* wp, int m, int n, int k, const GemmEpilogue& ep) {
-    if (p.tile == 248 || p.tile == 266 || p.tile == 276) return rg_gemm_tile_kg(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
+    if (p.tile == 266 || p.tile == 276) return rg_gemm_tile_kg(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
     if (p.tile >= 400) return rg_gemm_tile_96(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
     if (p.tile >= 200) return rg_gemm_tile_128(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
     return rg_gemm_tile_wide(ctx, p.tile, a, lda, wp, m, n, k, p.splits, ep);
