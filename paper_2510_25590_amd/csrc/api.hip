@@ -569,10 +569,13 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
     // ---- attention (Eq.6).  With a flag set the fresh K,V already sit in their cache slots, so the
     // key list is the whole cached sequence; without a flag it is the fresh rows only.
     const bool keep_ranges = w8 && dbl && H > 1024;
+    // one group of rows in the 8-bit form: the merge of key ranges quantises the rows as the output projection wants them
+    RowCodes row_codes = {ctx->q8, ctx->q8_scale, taps && taps->attn, false};
+    RowCodes* const codes = w8 && dbl && n_branches == 1 && (n_txt == 0 || n_txt == n_rows) ? &row_codes : nullptr;
     for (int b = 0; b < n_branches; ++b) {
         const size_t r0 = static_cast<size_t>(b) * n_fresh * es, c0 = static_cast<size_t>(b) * n_all * H * es;
-        if (flags) rc = rg_attention(ctx, ctx->q + r0 * H, H, n_fresh, nullptr, nullptr, H, 0, kc + c0, vc + c0, H, n_all, nullptr, 0, heads, D, 0.f, ctx->a + r0 * lda_attn, lda_attn, keep_ranges);
-        else rc = rg_attention(ctx, ctx->q + r0 * H, H, n_fresh, ctx->kf + r0 * H, ctx->vf + r0 * H, H, n_fresh, nullptr, nullptr, H, 0, nullptr, 0, heads, D, 0.f, ctx->a + r0 * lda_attn, lda_attn, keep_ranges);
+        if (flags) rc = rg_attention(ctx, ctx->q + r0 * H, H, n_fresh, nullptr, nullptr, H, 0, kc + c0, vc + c0, H, n_all, nullptr, 0, heads, D, 0.f, ctx->a + r0 * lda_attn, lda_attn, keep_ranges, codes);
+        else rc = rg_attention(ctx, ctx->q + r0 * H, H, n_fresh, ctx->kf + r0 * H, ctx->vf + r0 * H, H, n_fresh, nullptr, nullptr, H, 0, nullptr, 0, heads, D, 0.f, ctx->a + r0 * lda_attn, lda_attn, keep_ranges, codes);
         if (rc != REGIONE_OK) return rc;
     }
 
@@ -659,7 +662,7 @@ static int block_forward_impl(regione_ctx* ctx, const regione_block_weights* w, 
             const uint8_t* q8 = ctx->q8;
             ep.row_scale = up.row_scale = dn.row_scale = ctx->q8_scale;
             ep.col_scale = g8->s_o; up.col_scale = g8->s_1; dn.col_scale = g8->s_2;
-            if ((rc = regione_quantize_rows_fp8(ctx, a, g.n, H, ctx->q8, ctx->q8_scale)) != REGIONE_OK) return rc;
+            if (!row_codes.done && (rc = regione_quantize_rows_fp8(ctx, a, g.n, H, ctx->q8, ctx->q8_scale)) != REGIONE_OK) return rc;
             if (taps && ((rc = tap(taps->a_codes, q8, g.r0, g.n, H)) != REGIONE_OK || (rc = tap(taps->a_scale, ctx->q8_scale, g.r0, g.n, 4)) != REGIONE_OK)) return rc;
             if ((rc = rg_gemm_fp8(ctx, q8, H, static_cast<const uint8_t*>(g8->w_o), g.n, H, H, ep)) != REGIONE_OK) return rc;
             if (taps && (rc = tap(taps->h1, h1, g.r0, g.n, static_cast<size_t>(H) * 4)) != REGIONE_OK) return rc;

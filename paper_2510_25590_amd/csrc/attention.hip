@@ -17,6 +17,8 @@
 #include <cfloat>
 #include <cmath>
 #include "common.h"
+#include "e4m3.h"
+#include "layernorm_row.h"
 
 namespace {
 
@@ -1294,27 +1296,18 @@ attn_kvcache_kernel(AttnArgs a) {
 }
 
 // Merges the split-KV partial results: out = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s.  RANGED: of the even ranges
-// that met in a query tile (QW rows, tiles from q_full on; n_q counts the rows from there), in key order; query tiles
-// that one range covered are finished already.
+// that met in a query tile (QW rows, tiles from q_full on; qrow counts from there), in key order; false for query tiles
+// that one range covered, which are finished already.  Four values of a head's row, the g-th of them.
+struct Partials { const float* part; int splits, heads, n_q_pad, q_full, q_rest, n_tiles, range; };
 template <int D, int QW, bool RANGED, int MAXS>
-__global__ void __launch_bounds__(kThreads)
-attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n_q, int n_q_pad, bf16_t* __restrict__ out, int ldo,
-                    int q_full, int q_rest, int n_tiles, int range) {
-    // one thread per (query, head, 4 d's)
-    constexpr int G = D / 4;
-    const int64_t gid = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    const int64_t total = static_cast<int64_t>(n_q) * heads * G;
-    if (gid >= total) return;
-    const int g = static_cast<int>(gid % G);
-    const int head = static_cast<int>((gid / G) % heads);
-    const int qrow = static_cast<int>(gid / (static_cast<int64_t>(G) * heads));
-    int w0 = 0, w0_slot = 0;
+__device__ __forceinline__ bool merge_partials(const Partials& p, int qrow, int head, int g, bf16x4& pk) {
+    int splits = p.splits, w0 = 0, w0_slot = 0;
     if (RANGED) {
-        const int first = (head * q_rest + qrow / QW) * n_tiles;      // this query tile's place in the list of key tiles
-        w0 = first / range;
-        splits = (first + n_tiles - 1) / range - w0 + 1;
-        if (splits == 1) return;
-        w0_slot = 2 * w0 + (w0 * range / n_tiles == first / n_tiles ? 0 : 1);   // later ranges start inside this query tile: slot 0
+        const int first = (head * p.q_rest + qrow / QW) * p.n_tiles;      // this query tile's place in the list of key tiles
+        w0 = first / p.range;
+        splits = (first + p.n_tiles - 1) / p.range - w0 + 1;
+        if (splits == 1) return false;
+        w0_slot = 2 * w0 + (w0 * p.range / p.n_tiles == first / p.n_tiles ? 0 : 1);   // later ranges start inside this query tile: slot 0
     }
     // every split's row is requested before the first value is used; a wave's loads of one split are contiguous
     float ms[MAXS], ls[MAXS];
@@ -1322,8 +1315,8 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
 #pragma unroll
     for (int s = 0; s < MAXS; ++s)
         if (s < splits) {
-            const int64_t prow = RANGED ? static_cast<int64_t>(s == 0 ? w0_slot : 2 * (w0 + s)) * QW + qrow % QW : (static_cast<int64_t>(s) * heads + head) * n_q_pad + qrow;
-            const float* pp = part + prow * (D + 4);
+            const int64_t prow = RANGED ? static_cast<int64_t>(s == 0 ? w0_slot : 2 * (w0 + s)) * QW + qrow % QW : (static_cast<int64_t>(s) * p.heads + head) * p.n_q_pad + qrow;
+            const float* pp = p.part + prow * (D + 4);
             const float2 ml = *reinterpret_cast<const float2*>(pp + D);
             ms[s] = ml.x; ls[s] = ml.y;
             val[s] = *reinterpret_cast<const f32x4*>(pp + 4 * g);
@@ -1344,10 +1337,70 @@ attn_combine_kernel(const float* __restrict__ part, int splits, int heads, int n
             acc[0] += w * val[s][0]; acc[1] += w * val[s][1]; acc[2] += w * val[s][2]; acc[3] += w * val[s][3];
         }
     const float inv = 1.0f / l;
-    bf16x4 pk;
 #pragma unroll
     for (int e = 0; e < 4; ++e) pk[e] = static_cast<__bf16>(acc[e] * inv);
-    *reinterpret_cast<bf16x4*>(out + static_cast<int64_t>(qrow + (RANGED ? q_full * QW : 0)) * ldo + head * D + 4 * g) = pk;
+    return true;
+}
+template <int D, int QW, bool RANGED, int MAXS>
+__global__ void __launch_bounds__(kThreads)
+attn_combine_kernel(Partials p, int n_q, bf16_t* __restrict__ out, int ldo) {
+    // one thread per (query, head, 4 d's)
+    constexpr int G = D / 4;
+    const int64_t gid = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+    const int64_t total = static_cast<int64_t>(n_q) * p.heads * G;
+    if (gid >= total) return;
+    const int g = static_cast<int>(gid % G);
+    const int head = static_cast<int>((gid / G) % p.heads);
+    const int qrow = static_cast<int>(gid / (static_cast<int64_t>(G) * p.heads));
+    bf16x4 pk;
+    if (merge_partials<D, QW, RANGED, MAXS>(p, qrow, head, g, pk))
+        *reinterpret_cast<bf16x4*>(out + static_cast<int64_t>(qrow + (RANGED ? p.q_full * QW : 0)) * ldo + head * D + 4 * g) = pk;
+}
+
+// The merge and the row's E4M3 codes (quantize_rows_fp8_kernel, bit for bit) in one pass, a workgroup per row: the merged rows' way out and back and one launch fall away.
+// A block's us, separate -> here (24 heads, 4608 keys): 100 rows 103 -> 99-105, 205 rows 121.6 -> 115-119, 820 rows 253.8 -> 249.5, 3000 rows 740 -> 740; 8 heads: 100 rows 55.4 -> 51.4,
+// 820 rows 91.0 -> 88.6, 24 rows 50.4 -> 50.8.
+constexpr int kCodesColumns = 4096, kCodesRanges = 8;
+template <int D, int QW, bool RANGED>
+__global__ void __launch_bounds__(kThreads)
+attn_combine_codes_kernel(Partials p, bf16_t* __restrict__ out, int ldo, uint8_t* __restrict__ codes, float* __restrict__ scale, int keep_out) {
+    constexpr int G = D / 4, PIECES = kCodesColumns / 4 / kThreads;
+    __shared__ float most[kThreads / 64];
+    const int row = blockIdx.x, pieces = p.heads * G;
+    float x[PIECES][4];
+    float amax = 0.f;
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+        const int piece = i * kThreads + threadIdx.x;
+        if (piece < pieces) {
+            const int head = piece / G, g = piece % G;
+            bf16_t* to = out + static_cast<int64_t>(row) * ldo + 4 * piece;
+            bf16x4 pk;
+            if ((!RANGED || row >= p.q_full * QW) && merge_partials<D, QW, RANGED, kCodesRanges>(p, row - (RANGED ? p.q_full * QW : 0), head, g, pk)) {
+                if (keep_out) *reinterpret_cast<bf16x4*>(to) = pk;
+            } else {
+                pk = *reinterpret_cast<const bf16x4*>(to);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[i][e] = static_cast<float>(pk[e]);
+                amax = __builtin_fmaxf(amax, __builtin_fabsf(x[i][e]));
+            }
+        }
+    }
+    amax = wave_max(amax);
+    if ((threadIdx.x & 63) == 0) most[threadIdx.x >> 6] = amax;
+    __syncthreads();
+    amax = __builtin_fmaxf(__builtin_fmaxf(most[0], most[1]), __builtin_fmaxf(most[2], most[3]));
+    const bool live = amax > 0.f;
+    const float mult = live ? kE4M3Max / amax : 1.0f;
+    if (threadIdx.x == 0) scale[row] = live ? amax / kE4M3Max : 1.0f;
+    unsigned* to = reinterpret_cast<unsigned*>(codes + static_cast<int64_t>(row) * 4 * pieces);
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+        const int piece = i * kThreads + threadIdx.x;
+        if (piece < pieces) to[piece] = fp8_codes4(x[i], mult);
+    }
 }
 
 // ---------------------------------------------------------------- how a call is dealt to workgroups
@@ -1573,7 +1626,7 @@ AttnPlan plan_attention(const regione_ctx* ctx, int source, int n_q, int n_keys,
 }
 
 template <int D>
-int launch_attention(regione_ctx* ctx, AttnArgs a, bool keep_ranges) {
+int launch_attention(regione_ctx* ctx, AttnArgs a, bool keep_ranges, RowCodes* row_codes) {
     const int n_tiles = (a.n0 + a.n1 + KT - 1) / KT;
     const int source = a.idx1 ? SRC_INDEXED : a.n0 == 0 || a.n1 == 0 ? SRC_CONTIG : SRC_TWO;
     a.ld = a.n0 > 0 ? a.ldkv0 : a.ldkv1;
@@ -1633,16 +1686,24 @@ int launch_attention(regione_ctx* ctx, AttnArgs a, bool keep_ranges) {
         const int64_t total = static_cast<int64_t>(rows) * a.heads * (D / 4);
         const dim3 merge_grid(static_cast<unsigned>((total + kThreads - 1) / kThreads));
         const bool many = (ranged ? (n_tiles - 1) / a.range + 2 : a.splits) > 8;
+        const Partials p = {a.part, a.splits, a.heads, a.n_q_pad, a.q_full, a.q_tiles - a.q_full, n_tiles, a.range};
         if constexpr (D == 128) {
+            if (row_codes && !many && a.heads * D <= kCodesColumns) {
+                const auto merge = !ranged ? attn_combine_codes_kernel<D, 128, false> : qw == 256 ? attn_combine_codes_kernel<D, 256, true> : attn_combine_codes_kernel<D, 128, true>;
+                hipLaunchKernelGGL(merge, dim3(static_cast<unsigned>(a.n_q)), dim3(kThreads), 0, ctx->stream, p, a.out, a.ldo, row_codes->codes, row_codes->scale, row_codes->keep_out);
+                RG_LAUNCH_CHECK();
+                row_codes->done = true;
+                return REGIONE_OK;
+            }
             if (ranged) {
                 const auto merge = qw == 256 ? (many ? attn_combine_kernel<D, 256, true, kMaxSplits> : attn_combine_kernel<D, 256, true, 8>)
                                              : (many ? attn_combine_kernel<D, 128, true, kMaxSplits> : attn_combine_kernel<D, 128, true, 8>);
-                hipLaunchKernelGGL(merge, merge_grid, dim3(kThreads), 0, ctx->stream, a.part, 0, a.heads, rows, 0, a.out, a.ldo, a.q_full, a.q_tiles - a.q_full, n_tiles, a.range);
+                hipLaunchKernelGGL(merge, merge_grid, dim3(kThreads), 0, ctx->stream, p, rows, a.out, a.ldo);
             }
         }
         if (!ranged)
             hipLaunchKernelGGL((many ? attn_combine_kernel<D, 128, false, kMaxSplits> : attn_combine_kernel<D, 128, false, 8>), merge_grid, dim3(kThreads), 0, ctx->stream,
-                               a.part, a.splits, a.heads, a.n_q, a.n_q_pad, a.out, a.ldo, 0, 0, 0, 0);
+                               p, rows, a.out, a.ldo);
         RG_LAUNCH_CHECK();
     }
     return REGIONE_OK;
@@ -1697,7 +1758,7 @@ extern "C" int regione_attention_plan(regione_ctx* ctx, int32_t n_q, int32_t n_k
 int rg_attention(regione_ctx* ctx, const void* q_any, int ldq, int n_q,
                  const void* k0_any, const void* v0_any, int ldkv0, int n0,
                  const void* k1_any, const void* v1_any, int ldkv1, int n1, const int32_t* idx1, int rows1,
-                 int heads, int d, float scale, void* out_any, int ldo, bool keep_ranges) {
+                 int heads, int d, float scale, void* out_any, int ldo, bool keep_ranges, RowCodes* row_codes) {
     if (n_q <= 0) return REGIONE_OK;
     if (ctx->f32)
         return rg_attention_f32(ctx, static_cast<const float*>(q_any), ldq, n_q, static_cast<const float*>(k0_any), static_cast<const float*>(v0_any), ldkv0, n0,
@@ -1718,8 +1779,8 @@ int rg_attention(regione_ctx* ctx, const void* q_any, int ldq, int n_q,
     a.heads = heads;
     a.scale_log2e = (scale > 0.f ? scale : 1.0f / sqrtf(static_cast<float>(d))) * 1.4426950408889634f;
     a.out = out; a.ldo = ldo;
-    if (d == 64) return launch_attention<64>(ctx, a, keep_ranges);
-    return launch_attention<128>(ctx, a, keep_ranges);
+    if (d == 64) return launch_attention<64>(ctx, a, keep_ranges, row_codes);
+    return launch_attention<128>(ctx, a, keep_ranges, row_codes);
 }
 
 extern "C" int regione_attn_kvcache(regione_ctx* ctx, const void* q, int32_t n_q,

@@ -170,10 +170,13 @@ int rg_layernorm_mod(regione_ctx* ctx, const void* h, int h_f32, int n, int hidd
 int rg_qk_norm_rope(regione_ctx* ctx, bf16_t* q, int ldq, bf16_t* k, int ldkv, const int32_t* kv_slot,
                     const int32_t* pos_slot, int pos0, int slot_offset, int slot_period, int slot_branch_rows, int n, int heads, int d,
                     const float* q_norm, const float* k_norm, const float* table, int table_rows);
+// E4M3 codes of the attention's result rows (heads * d columns) and their scales, formed by the launch that merges key ranges where there is one; keep_out: the rows are wanted, too.
+// done tells whether they were formed.
+struct RowCodes { uint8_t* codes; float* scale; bool keep_out, done; };
 int rg_attention(regione_ctx* ctx, const void* q, int ldq, int n_q,
                  const void* k0, const void* v0, int ldkv0, int n0,
                  const void* k1, const void* v1, int ldkv1, int n1, const int32_t* idx1, int rows1,   // rows1: rows of the array that idx1 picks from
-                 int heads, int d, float scale, void* out, int ldo, bool keep_ranges);       // keep_ranges: for wide E4M3 blocks, see plan_ranges
+                 int heads, int d, float scale, void* out, int ldo, bool keep_ranges, RowCodes* row_codes = nullptr);       // keep_ranges: for wide E4M3 blocks, see plan_ranges
 int rg_attention_f32(regione_ctx* ctx, const float* q, int ldq, int n_q,
                      const float* k0, const float* v0, int ldkv0, int n0,
                      const float* k1, const float* v1, int ldkv1, int n1, const int32_t* idx1,

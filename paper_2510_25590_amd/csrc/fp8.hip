@@ -2,26 +2,13 @@
 // Generation"); an extension, the paper itself computes in the model's precision.  This file: per-row quantisation
 // and the entry points; the matrix-core kernel is the 8-bit form of the LDS GEMM in gemm.hip.
 #include "common.h"
+#include "e4m3.h"
 #include "layernorm_row.h"
 #include <type_traits>
 
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-
-constexpr float kE4M3Max = 448.0f;
-
-__device__ __forceinline__ uint2 fp8_codes(const float (&x)[8], float mult) {
-    float y[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = __builtin_fminf(__builtin_fmaxf(x[e] * mult, -kE4M3Max), kE4M3Max);
-    unsigned lo = 0, hi = 0;
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
-    return make_uint2(lo, hi);
-}
 
 // TPR threads per row (64: four rows per workgroup, 256: one); the row stays in registers between the maximum and the
 // conversion (up to 8 16-byte pieces per thread, so 4096 columns per wave and 16384 per workgroup).
