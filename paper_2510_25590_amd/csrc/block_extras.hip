@@ -260,8 +260,9 @@ vec_linear_kernel(const float* __restrict__ x, const bf16_t* __restrict__ w, con
 // Several matrices one after the other in the grid: a launch's first requests and its last workgroups cost a 57 MB matrix as much as half its bytes (a block's vectors, width 3072,
 // 16.6 us by itself, two of them 26.7 in one launch).
 __global__ void __launch_bounds__(kThreads)
-vec_linear_batch_kernel(VecBatch a, int k) {
+vec_linear_batch_kernel(VecBatch a, int k, const int32_t* __restrict__ go) {
     extern __shared__ __attribute__((aligned(16))) float xs[];
+    if (go && *go == 0) return;
     int e = 0;
     while (e + 1 < a.count && static_cast<int>(blockIdx.x) >= a.first_wg[e + 1]) ++e;
     vec_linear_rows<REGIONE_ACT_SILU>(xs, static_cast<int>(blockIdx.x) - a.first_wg[e], a.x[e], a.w[e], a.b[e], a.n[e], k, a.y[e]);
@@ -299,13 +300,13 @@ extern "C" int regione_vec_linear(regione_ctx* ctx, const float* x, int32_t pre_
     return REGIONE_OK;
 }
 
-int rg_vec_linear_batch(regione_ctx* ctx, VecBatch& batch, int k) {
+int rg_vec_linear_batch(regione_ctx* ctx, VecBatch& batch, int k, const int32_t* go) {
     if (batch.count == 0) return REGIONE_OK;
     const int rows_per_wg = (kThreads / 64) * kVecRowsPerWave;
     batch.first_wg[0] = 0;
     for (int e = 0; e < batch.count; ++e) batch.first_wg[e + 1] = batch.first_wg[e] + (batch.n[e] + rows_per_wg - 1) / rows_per_wg;
     ProfScope prof(ctx, REGIONE_PROF_GEMM);
-    hipLaunchKernelGGL(vec_linear_batch_kernel, dim3(static_cast<unsigned>(batch.first_wg[batch.count])), dim3(kThreads), static_cast<size_t>(k) * sizeof(float), ctx->stream, batch, k);
+    hipLaunchKernelGGL(vec_linear_batch_kernel, dim3(static_cast<unsigned>(batch.first_wg[batch.count])), dim3(kThreads), static_cast<size_t>(k) * sizeof(float), ctx->stream, batch, k, go);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }

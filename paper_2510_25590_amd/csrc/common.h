@@ -11,7 +11,7 @@ typedef uint16_t bf16_t;  // raw bfloat16 bits in memory
 
 constexpr int kMaxSplitTiles = 1024;   // tiles of one K-split GEMM launch
 
-constexpr int kModSets = 32;           // sets of modulation vectors that a step forms at a time
+constexpr int kModSets = 16;           // sets of modulation vectors that a step forms at a time, in one launch
 
 constexpr int kGemmPlanSlots = 64;
 struct GemmPlanSlot { int m, n, k, kind, tile, splits; size_t part_bytes; };   // a remembered choice of GEMM tile and K splits
@@ -141,10 +141,9 @@ int rg_gather_layernorm(regione_ctx* ctx, const void* h_full, int h_f32, const i
                         const void* x_t, void* x_e, int x_pieces, int32_t* slots, int n_txt);
 int rg_gather_pair_slots(regione_ctx* ctx, const void* src_a, int32_t row_elems_a, int32_t dtype_a, void* dst_a, const void* src_b, int32_t row_elems_b, int32_t dtype_b, void* dst_b,
                          const int32_t* index, const int32_t* n_dev, int64_t n_max, int32_t* slots, int n_txt);
-// modulation vectors of several blocks in one launch: y = silu(x) W^T + b for each entry, W [n, k] row-major bf16
-constexpr int kVecBatch = 16;
-struct VecBatch { const float* x[kVecBatch]; const bf16_t* w[kVecBatch]; const float* b[kVecBatch]; float* y[kVecBatch]; int n[kVecBatch]; int first_wg[kVecBatch + 1]; int count; };
-int rg_vec_linear_batch(regione_ctx* ctx, VecBatch& batch, int k);
+// modulation vectors of several blocks in one launch: y = silu(x) W^T + b for each entry, W [n, k] row-major bf16; go (optional): nothing is done where *go is zero on the GPU
+struct VecBatch { const float* x[kModSets]; const bf16_t* w[kModSets]; const float* b[kModSets]; float* y[kModSets]; int n[kModSets]; int first_wg[kModSets + 1]; int count; };
+int rg_vec_linear_batch(regione_ctx* ctx, VecBatch& batch, int k, const int32_t* go);
 // One product: norm: of layernorm_mod(a), rows a of k values (a_f32: float32).
 struct GemmCall { const void* a; int lda, norm, a_f32; const float* shift; const float* scale; const void* w; int m, n, k; GemmEpilogue ep; };
 // Two products of the same shape but for their rows (the text and the image rows of a block, each with weights of their own) in one launch, with the results of two calls bit for
