@@ -1,6 +1,7 @@
 // Shared declarations of the library's translation units (not part of the public ABI).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <atomic>
 #include <stdint.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -82,6 +83,15 @@ void regione_set_error(const char* fmt, ...);
 #define RG_HIP(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) { \
     regione_set_error("%s failed: %s", #call, hipGetErrorString(e_)); return REGIONE_ERR_HIP; } } while (0)
 #define RG_LAUNCH_CHECK() RG_HIP(hipGetLastError())
+
+// More than 64 KiB of LDS, a kernel's own and what its launch asks for together, has to be granted: once per kernel (`granted` is the kernel's) and device.
+static inline int rg_grant_lds(const regione_ctx* ctx, const void* kernel, std::atomic<uint64_t>& granted, size_t launch_bytes) {
+    const uint64_t bit = uint64_t{1} << (ctx->device & 63);
+    if (granted.load(std::memory_order_relaxed) & bit) return REGIONE_OK;
+    RG_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(launch_bytes)));
+    granted.fetch_or(bit, std::memory_order_relaxed);
+    return REGIONE_OK;
+}
 
 static inline bool rg_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 

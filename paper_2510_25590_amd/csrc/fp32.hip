@@ -454,15 +454,28 @@ void launch_gemm_f32_wide(regione_ctx* ctx, const float* a, int lda, const float
     }
 }
 
+// Rows that are normalised in LDS beside the partial sums: 10 + 33 KiB at most with tiles of 16 x 16, 36 + 65 with 32 x 32.
+template <auto KERNEL, int RB, int CB, int NW> int grant_rows(const regione_ctx* ctx) {
+    constexpr size_t sums = sizeof(float) * NW * RB * 16 * (CB * 16 + 4), rows = sizeof(float) * RB * 16 * ln_f32_row(kLnF32Columns);
+    if constexpr (sums + rows <= 65536) return REGIONE_OK;
+    static std::atomic<uint64_t> granted{0};
+    return rg_grant_lds(ctx, reinterpret_cast<const void*>(KERNEL), granted, rows);
+}
 template <int RB, int CB, int NW, int PF, bool LN>
-void launch_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m, int n, int k, const float* shift, const float* scale, const GemmEpilogue& ep) {
+int launch_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m, int n, int k, const float* shift, const float* scale, const GemmEpilogue& ep) {
     const dim3 grid((n + CB * 16 - 1) / (CB * 16), (m + RB * 16 - 1) / (RB * 16)), block(NW * 64);
     const size_t lds = LN ? static_cast<size_t>(RB) * 16 * ln_f32_row(k) * sizeof(float) : 0;
+#define RG_LAUNCH(KIND) { \
+        if constexpr (LN) { if (int rc = grant_rows<&gemm_f32_kernel<KIND, RB, CB, NW, PF, LN>, RB, CB, NW>(ctx)) return rc; } \
+        hipLaunchKernelGGL((gemm_f32_kernel<KIND, RB, CB, NW, PF, LN>), grid, block, lds, ctx->stream, a, lda, w, m, n, k, shift, scale, ep); break; }
     switch (ep.kind) {
-        case EPI_PLAIN: hipLaunchKernelGGL((gemm_f32_kernel<EPI_PLAIN, RB, CB, NW, PF, LN>), grid, block, lds, ctx->stream, a, lda, w, m, n, k, shift, scale, ep); break;
-        case EPI_QKV: hipLaunchKernelGGL((gemm_f32_kernel<EPI_QKV, RB, CB, NW, PF, LN>), grid, block, lds, ctx->stream, a, lda, w, m, n, k, shift, scale, ep); break;
-        default: if constexpr (!LN) hipLaunchKernelGGL((gemm_f32_kernel<EPI_RESID, RB, CB, NW, PF, false>), grid, block, lds, ctx->stream, a, lda, w, m, n, k, shift, scale, ep); break;
+        case EPI_PLAIN: RG_LAUNCH(EPI_PLAIN)
+        case EPI_QKV: RG_LAUNCH(EPI_QKV)
+        default: if constexpr (!LN) RG_LAUNCH(EPI_RESID)
     }
+#undef RG_LAUNCH
+    RG_LAUNCH_CHECK();
+    return REGIONE_OK;
 }
 int64_t tiles_f32(int m, int n, int64_t b) { return ((m + b - 1) / b) * ((n + b - 1) / b); }
 
@@ -488,24 +501,29 @@ int rg_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m
     // product.  Measured (us, tiles of 16 / 32 / 64): 36 x 768 x 256 3.8 / 4.3 / 11, 205 x 256 x 1024 5.6 / 10.3 / 30,
     // 205 x 768 x 256 (624 tiles of 16) 5.0 / 4.5 / 11, 640 x 256 x 1024 (640) 12.6 / 10.4 / 31,
     // 1216 x 768 x 256 (228 tiles of 64) 17 / 11.6 / 11.7, 2000 x 1024 x 256 (512) 34 / 22 / 16.
-    if (tiles_f32(m, n, 64) >= 256) launch_gemm_f32_wide(ctx, a, lda, w, m, n, k, ep);
-    else if (tiles_f32(m, n, 16) > 512) launch_gemm_f32<2, 2, 8, 4, false>(ctx, a, lda, w, m, n, k, nullptr, nullptr, ep);
-    else launch_gemm_f32<1, 1, 8, 8, false>(ctx, a, lda, w, m, n, k, nullptr, nullptr, ep);
+    if (tiles_f32(m, n, 64) < 256)
+        return tiles_f32(m, n, 16) > 512 ? launch_gemm_f32<2, 2, 8, 4, false>(ctx, a, lda, w, m, n, k, nullptr, nullptr, ep)
+                                         : launch_gemm_f32<1, 1, 8, 8, false>(ctx, a, lda, w, m, n, k, nullptr, nullptr, ep);
+    launch_gemm_f32_wide(ctx, a, lda, w, m, n, k, ep);
     RG_LAUNCH_CHECK();
     return REGIONE_OK;
 }
 
 template <int RB, int CB, int NW, int PF>
-static void launch_gemm_f32_pair(regione_ctx* ctx, const GemmCall& a, const GemmCall& b) {
+static int launch_gemm_f32_pair(regione_ctx* ctx, const GemmCall& a, const GemmCall& b) {
     const int ya = (a.m + RB * 16 - 1) / (RB * 16), yb = (b.m + RB * 16 - 1) / (RB * 16);
     const dim3 grid((a.n + CB * 16 - 1) / (CB * 16), ya + yb), block(NW * 64);
     const size_t lds = a.norm ? static_cast<size_t>(RB) * 16 * ln_f32_row(a.k) * sizeof(float) : 0;
     auto product = [](const GemmCall& c) { return F32Product{static_cast<const float*>(c.a), c.lda, static_cast<const float*>(c.w), c.m, c.shift, c.scale, c.ep}; };
-#define RG_PAIR(KIND, LN) hipLaunchKernelGGL((gemm_f32_pair_kernel<KIND, RB, CB, NW, PF, LN>), grid, block, lds, ctx->stream, product(a), product(b), ya, a.n, a.k)
-    if (a.ep.kind == EPI_RESID) RG_PAIR(EPI_RESID, false);
-    else if (a.ep.kind == EPI_QKV) { if (a.norm) RG_PAIR(EPI_QKV, true); else RG_PAIR(EPI_QKV, false); }
-    else { if (a.norm) RG_PAIR(EPI_PLAIN, true); else RG_PAIR(EPI_PLAIN, false); }
+#define RG_PAIR(KIND, LN) { \
+        if constexpr (LN) { if (int rc = grant_rows<&gemm_f32_pair_kernel<KIND, RB, CB, NW, PF, LN>, RB, CB, NW>(ctx)) return rc; } \
+        hipLaunchKernelGGL((gemm_f32_pair_kernel<KIND, RB, CB, NW, PF, LN>), grid, block, lds, ctx->stream, product(a), product(b), ya, a.n, a.k); }
+    if (a.ep.kind == EPI_RESID) RG_PAIR(EPI_RESID, false)
+    else if (a.ep.kind == EPI_QKV) { if (a.norm) RG_PAIR(EPI_QKV, true) else RG_PAIR(EPI_QKV, false) }
+    else { if (a.norm) RG_PAIR(EPI_PLAIN, true) else RG_PAIR(EPI_PLAIN, false) }
 #undef RG_PAIR
+    RG_LAUNCH_CHECK();
+    return REGIONE_OK;
 }
 static bool pair_fine(const GemmCall& a, const GemmCall& b) { return tiles_f32(a.m, a.n, 16) + tiles_f32(b.m, b.n, 16) <= 512; }
 // The rules of one product for the tiles of both.  Tiles of 32 x 32 only while the pair takes no round of the 256 compute units more than its larger product alone: a product that
@@ -519,9 +537,7 @@ bool rg_gemm_pairs_f32(const GemmCall& a, const GemmCall& b) {
     return fine || (ta + tb + 255) / 256 == ((ta > tb ? ta : tb) + 255) / 256;
 }
 int rg_gemm_pair_f32(regione_ctx* ctx, const GemmCall& a, const GemmCall& b) {
-    if (pair_fine(a, b)) launch_gemm_f32_pair<1, 1, 8, 8>(ctx, a, b); else launch_gemm_f32_pair<2, 2, 8, 4>(ctx, a, b);
-    RG_LAUNCH_CHECK();
-    return REGIONE_OK;
+    return pair_fine(a, b) ? launch_gemm_f32_pair<1, 1, 8, 8>(ctx, a, b) : launch_gemm_f32_pair<2, 2, 8, 4>(ctx, a, b);
 }
 
 // The product of layernorm_mod(h) in one launch, bit for bit that of the two, where every workgroup of one round of 256 normalises its own rows; *done tells whether it was.
@@ -531,11 +547,8 @@ int rg_layernorm_gemm_f32(regione_ctx* ctx, const float* h, const float* shift, 
     const bool fine = tiles_f32(m, n, 16) <= 512;
     if (tiles_f32(m, n, fine ? 16 : 32) > kLnF32Tiles || tiles_f32(m, n, 64) >= 256) return REGIONE_OK;
     ProfScope prof(ctx, REGIONE_PROF_GEMM);
-    if (fine) launch_gemm_f32<1, 1, 8, 8, true>(ctx, h, k, w, m, n, k, shift, scale, ep);
-    else launch_gemm_f32<2, 2, 8, 4, true>(ctx, h, k, w, m, n, k, shift, scale, ep);
-    RG_LAUNCH_CHECK();
     *done = true;
-    return REGIONE_OK;
+    return fine ? launch_gemm_f32<1, 1, 8, 8, true>(ctx, h, k, w, m, n, k, shift, scale, ep) : launch_gemm_f32<2, 2, 8, 4, true>(ctx, h, k, w, m, n, k, shift, scale, ep);
 }
 
 int rg_attention_f32(regione_ctx* ctx, const float* q, int ldq, int n_q,

@@ -2,7 +2,6 @@
 #pragma once
 #include "gemm_pp.h"
 #include "gemm_tiles.h"
-#include <atomic>
 
 namespace {
 
@@ -17,11 +16,7 @@ int launch_tile(regione_ctx* ctx, Kernel kernel, std::atomic<uint64_t>& granted,
     // many row tiles: groups of four (the workgroups that run at a time on an XCD then share weight and activation lines in
     // its L2: 2-7 % on the 8704-row GEMMs against all row tiles of a column tile in a row); few row tiles: one group
     const int group_rows = m_tiles > 8 ? 4 : m_tiles;
-    const uint64_t bit = uint64_t{1} << (ctx->device & 63);   // more than 64 KiB of LDS has to be granted explicitly, once per device
-    if (!(granted.load(std::memory_order_relaxed) & bit)) {
-        RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(T::LDS_BYTES)));
-        granted.fetch_or(bit, std::memory_order_relaxed);
-    }
+    if (int rc = rg_grant_lds(ctx, reinterpret_cast<const void*>(kernel), granted, T::LDS_BYTES)) return rc;
     const int units_per_xcd = (tiles * used_splits + 7) / 8;
     hipLaunchKernelGGL(kernel, dim3(units_per_xcd * 8), dim3(T::THREADS), T::LDS_BYTES, ctx->stream,
                        a, lda, wp, m, n, k, m_tiles, n_tiles, units_per_xcd, group_rows, used_splits, per, ctx->gemm_part, ctx->gemm_arrived, ep);
