@@ -41,20 +41,25 @@ pack_weight_kernel(const bf16_t* __restrict__ w, int n, int k, bf16_t* __restric
 // at 2.2 GHz, times a factor of the tile that takes in its start, its epilogue and what the matrix cores' power takes from the clock; not below the time that the
 // weights take from HBM.  A K split adds its partial sums' way out and back (padded tiles).
 // All constants are fitted to every tile and K split of 267 shapes (32-9400 rows, 1024-21504 columns, k 1024-15360, weights of 3072-wide models uncached).  Against
-// the best of all plans the choice loses 0.6 % on average over these and over 143 others, 7 % at most on those; the constants before, fitted without the two widest tiles of gemm_kg_kernel,
+// the best of all plans the choice loses 0.6 % on average over these and over 143 others, 7 % at most on those (fitted together, so that no constant is a rate by itself: what a round or
+// its results cost beside the steps went into the tiles' factors); the constants before, fitted without the two widest tiles of gemm_kg_kernel,
 // lost 2.0 % with them.  us, then / now: 2048 x 9216 x 3072 103.3 / 95.8, 1640 x 12288 x 3072 103.5 / 98.9, 1382 x 3072 x 15360 116.7 / 109.9, 205 x 21504 x 3072 43.8 / 41.6.
-struct TileShape { int code, rows, cols, lds_kb, form; double factor; };   // form: kTilesFp8 only; factor: kTiles only
-constexpr TileShape kTiles[] = {{222, 64, 64, 64, 0, 1.089},   {224, 64, 128, 96, 0, 1.156},  {242, 128, 64, 96, 0, 1.056},  {244, 128, 128, 128, 0, 1.059},
-                                {274, 224, 128, 132, 0, 1.054}, {284, 256, 128, 144, 0, 1.381}, {426, 128, 96, 112, 0, 1.058}, {436, 192, 96, 144, 0, 1.114},
-                                {446, 256, 96, 132, 0, 0.985}, {44, 128, 256, 144, 0, 1.028}, {64, 192, 256, 136, 0, 1.143}, {74, 224, 256, 148, 0, 1.065},
-                                {84, 256, 256, 160, 0, 1.011}, {266, 192, 192, 144, 0, 1.021}, {276, 224, 192, 156, 0, 1.012}};
+struct TileShape { int code, rows, cols, lds_kb, form; double factor[2]; };   // form: kTilesFp8 only; factor: kTiles only, of kPlan and of kPlanSmall
+constexpr TileShape kTiles[] = {{222, 64, 64, 64, 0, {1.089, 0.865}}, {224, 64, 128, 96, 0, {1.156, 0.725}}, {242, 128, 64, 96, 0, {1.056, 1.022}}, {244, 128, 128, 128, 0, {1.059, 0.932}},
+                                {274, 224, 128, 132, 0, {1.054, 1.141}}, {284, 256, 128, 144, 0, {1.381, 1.103}}, {426, 128, 96, 112, 0, {1.058, 0.939}}, {436, 192, 96, 144, 0, {1.114, 1.093}},
+                                {446, 256, 96, 132, 0, {0.985, 1.053}}, {44, 128, 256, 144, 0, {1.028, 0.989}}, {64, 192, 256, 136, 0, {1.143, 1.057}}, {74, 224, 256, 148, 0, {1.065, 1.013}},
+                                {84, 256, 256, 160, 0, {1.011, 0.971}}, {266, 192, 192, 144, 0, {1.021, 1.015}}, {276, 224, 192, 156, 0, {1.012, 1.269}}};
 struct GemmPlan { int tile; int splits; };
 
 // cycles: per KiB copied, barriers and least time of a step by form (narrow, wide), once more for narrow ones; MHz; us per round; TB/s of weights and results; K splits
-struct PlanConstants { double feed, over_n, over_w, least_n, least_w, add_n, clock, round, hbm, out, split, split_unit, split_tile, two; bool wide_half_steps; };
-constexpr PlanConstants kPlan = {29.55, 174.9, 93.0, 546.2, 310.6, 59.5, 23.2, 0.14, 7.18e6, 128.0e6, 1.44, 0.132, 0.0267, 4.13, true};
+struct PlanConstants { double feed, over_n, over_w, least_n, least_w, add_n, clock, round, hbm, out, split, split_unit, split_tile, two; int factors; bool wide_half_steps; };   // factors: which of a tile's, -1: none
+constexpr PlanConstants kPlan = {29.55, 174.9, 93.0, 546.2, 310.6, 59.5, 23.2, 0.14, 7.18e6, 128.0e6, 1.44, 0.132, 0.0267, 4.13, 0, true};
+// Fewer than 1024 columns or less K: the fit above saw none of these.  Fitted to every tile and K split of 750 such products (100-20000 rows, 65-16000 columns, k 64-12800, weights cached),
+// 1.0 % behind the best plan on average there and 1.3 % over 180 others, where kPlan is 3.2 % behind (47 % at most) and kPlanKept 3.6 %.
+// us, kPlanKept / kPlan / now: 1458 x 512 x 2560 13.2 / 15.5 / 13.2, 10085 x 1792 x 256 20.8 / 24.2 / 20.8, 9358 x 1024 x 256 12.3 / 13.8 / 12.3; the other way 4832 x 960 x 3840 42.7 / 38.9 / 42.7.
+constexpr PlanConstants kPlanSmall = {27.49, 310.0, 1.0, 159.5, 267.7, 41.3, 448.9, 0.0, 1e12, 1e12, 0.552, 0.4445, 0.0059, 3.208, 1, true};
 // those of before, without the factors and the two widest tiles of gemm_kg_kernel, where a product's sums are kept
-constexpr PlanConstants kPlanKept = {28.0, 120.0, 60.0, 450.0, 500.0, 53.0, 455.0, 6.9, 5.5e6, 8.0e6, 1.8, 0.19, 0.0116, 2.35, false};
+constexpr PlanConstants kPlanKept = {28.0, 120.0, 60.0, 450.0, 500.0, 53.0, 455.0, 6.9, 5.5e6, 8.0e6, 1.8, 0.19, 0.0116, 2.35, -1, false};
 double plan_time_bf16(const PlanConstants& c, const TileShape& t, int m, int n, int steps, int splits) {
     if (!c.wide_half_steps && (t.code == 266 || t.code == 276)) return 1e30;
     const int m_tiles = (m + t.rows - 1) / t.rows, n_tiles = (n + t.cols - 1) / t.cols;
@@ -70,7 +75,7 @@ double plan_time_bf16(const PlanConstants& c, const TileShape& t, int m, int n, 
     const double mhz = 2200.0 - c.clock * (mfma / step * active * live);
     const long slots = t.lds_kb <= 80 ? 512 : 256;
     const long full = units / slots, rem = units % slots;
-    const double one = per * step / mhz * (c.wide_half_steps ? t.factor : 1.0);
+    const double one = per * step / mhz * (c.factors < 0 ? 1.0 : t.factor[c.factors]);
     auto round_time = [&](long u) { return one * (slots > 256 && u > 256 ? c.two : 1.0) + c.round; };
     double us = full * round_time(slots) + (rem > 0 ? round_time(rem) : 0.0);
     const double hbm = static_cast<double>(n) * steps * 128.0 / c.hbm + c.round;     // the weights once from HBM
@@ -147,7 +152,7 @@ GemmPlan plan_over(const TileShape (&tiles)[N], Time time, size_t part_bytes, in
 enum { PLAN_BF16 = 0, PLAN_FP8 = 1, PLAN_KEPT = 2 };
 GemmPlan choose_plan(int m, int n, int k, int kind, size_t part_bytes) {
     if (kind == PLAN_FP8) return plan_over(kTilesFp8, plan_time_fp8, part_bytes, m, n, k / BK);
-    const PlanConstants& c = kind == PLAN_KEPT ? kPlanKept : kPlan;
+    const PlanConstants& c = kind == PLAN_KEPT ? kPlanKept : n < 1024 || k < 1024 ? kPlanSmall : kPlan;
     return plan_over(kTiles, [&](const TileShape& t, int m_, int n_, int steps, int splits) { return plan_time_bf16(c, t, m_, n_, steps, splits); }, part_bytes, m, n, k / BK);
 }
 
