@@ -20,8 +20,10 @@ int regione_tune_gemm(regione_ctx* ctx, int32_t wave_tile_blocks, int32_t k_spli
 
 /* The tile and the number of K splits that a product of m rows, n columns and k elements gets by itself, with a K-split workspace
  * of that many bytes (a context has 128 MiB, half of it while text and image rows run side by side).  A pure host function.  *tile
- * is a tile code of csrc/gemm_tiles.h, or 0 for the kernel of few bf16 rows and of narrow bf16 results (at most 64 columns). */
-enum { REGIONE_GEMM_BF16 = 0, REGIONE_GEMM_E4M3 = 1 };
+ * is a tile code of csrc/gemm_tiles.h, or 0 for the kernel of few bf16 rows and of narrow bf16 results (at most 64 columns).
+ * REGIONE_GEMM_BF16_STORED: the bf16 projection that writes K and V in a storing forward (REGIONE_FLAG_STORE), whose tiles are chosen apart so
+ * that the same rows give the same stored bits from one version of the library to the next. */
+enum { REGIONE_GEMM_BF16 = 0, REGIONE_GEMM_E4M3 = 1, REGIONE_GEMM_BF16_STORED = 2 };
 int regione_gemm_plan_host(int32_t m, int32_t n, int32_t k, int32_t kind, int64_t workspace_bytes, int32_t* tile, int32_t* k_splits);
 
 /* How many lanes (streams) the projections of a double-stream block run on with that many fresh text and image rows: 2 where the two groups run

@@ -505,7 +505,7 @@ def regione_tune_gemm(ctx, wave_tile_blocks: int, k_splits: int):
     _check(lib().regione_tune_gemm(ctx.handle, wave_tile_blocks, k_splits))
 
 
-GEMM_BF16, GEMM_E4M3 = 0, 1
+GEMM_BF16, GEMM_E4M3, GEMM_BF16_STORED = 0, 1, 2
 
 
 def regione_gemm_plan_host(m: int, n: int, k: int, kind: int, workspace_bytes: int = 128 << 20):

@@ -108,7 +108,7 @@ enum { EPI_PLAIN = 0, EPI_QKV = 1, EPI_RESID = 2, EPI_VELOCITY = 3 };
 struct GemmEpilogue {
     int kind;            // EPI_*
     int vec_ok;          // set by rg_gemm: the wide (8 columns per lane) epilogue may be used
-    int keep_sums;       // host only: the sums of this product are those of the versions before (see rg_layernorm_mod)
+    int keep_sums;       // host only: this product stores K and V (see rg_layernorm_mod)
     const float* bias;   // [N] or null
     int act;             // REGIONE_ACT_* (applied to columns >= act_from)
     int act_from;
@@ -172,9 +172,11 @@ int rg_gemm_f32(regione_ctx* ctx, const float* a, int lda, const float* w, int m
 int rg_layernorm_mod_fp8(regione_ctx* ctx, const void* h, int h_f32, int n, int hidden, const float* shift, const float* scale,
                          uint8_t* q, float* row_scale);
 int rg_gemm_fp8(regione_ctx* ctx, const uint8_t* a, int lda, const uint8_t* w_packed, int m, int n, int k, const GemmEpilogue& ep);
-// u: compute dtype.  keep_sums: a wave per row whatever its length, with the sums of the versions before, bit for bit.  Blocks want it where they store K and V: an E4M3 block that
-// reads those rows in later steps turns other last bits (0.04 % of the cache one bf16 rounding off) into 1.1 % of its output, more than the 1e-2 that such a block is
-// held to from one version to the next; the product behind takes its tile by the constants of then for the same reason.
+// u: compute dtype.  keep_sums: a wave per row whatever its length.  Blocks ask for it ahead of the projection whose K and V they store, and that projection takes its tile by kPlanKept:
+// so the same input rows give the same stored bits as before there were LayerNorms of several waves.  An E4M3 block that reads such rows turns other last bits (0.04 % of the cache one bf16
+// rounding off) into 1.1 % of its output, more than the 1e-2 that two versions' outputs may differ by.  That holds block by block, not for what a stack of blocks hands on: the block's other
+// products and its second LayerNorm are as fast as anywhere, and the rows that the next block gets differ in last bits.  Which cache an E4M3 block will read is not known here, so
+// every storing bf16 forward pays: 8704 rows of 3072 42 us for 28, of 2.4 ms.
 int rg_layernorm_mod(regione_ctx* ctx, const void* h, int h_f32, int n, int hidden, const float* shift, const float* scale, void* u, bool keep_sums = false);
 int rg_qk_norm_rope(regione_ctx* ctx, bf16_t* q, int ldq, bf16_t* k, int ldkv, const int32_t* kv_slot,
                     const int32_t* pos_slot, int pos0, int slot_offset, int slot_period, int slot_branch_rows, int n, int heads, int d,

@@ -58,7 +58,8 @@ constexpr PlanConstants kPlan = {29.55, 174.9, 93.0, 546.2, 310.6, 59.5, 23.2, 0
 // 1.0 % behind the best plan on average there and 1.3 % over 180 others, where kPlan is 3.2 % behind (47 % at most) and kPlanKept 3.6 %.
 // us, kPlanKept / kPlan / now: 1458 x 512 x 2560 13.2 / 15.5 / 13.2, 10085 x 1792 x 256 20.8 / 24.2 / 20.8, 9358 x 1024 x 256 12.3 / 13.8 / 12.3; the other way 4832 x 960 x 3840 42.7 / 38.9 / 42.7.
 constexpr PlanConstants kPlanSmall = {27.49, 310.0, 1.0, 159.5, 267.7, 41.3, 448.9, 0.0, 1e12, 1e12, 0.552, 0.4445, 0.0059, 3.208, 1, true};
-// those of before, without the factors and the two widest tiles of gemm_kg_kernel, where a product's sums are kept
+// The constants before those, without the factors and the two widest tiles of gemm_kg_kernel, for the projection of a storing forward (see rg_layernorm_mod); the one choice that still takes
+// 256 x 128 tiles at 1024 columns and K and more.  us, kPlanKept / kPlan: 2048 x 9216 x 3072 103.3 / 95.8, of 4608 and 8704 rows the same tiles.
 constexpr PlanConstants kPlanKept = {28.0, 120.0, 60.0, 450.0, 500.0, 53.0, 455.0, 6.9, 5.5e6, 8.0e6, 1.8, 0.19, 0.0116, 2.35, -1, false};
 double plan_time_bf16(const PlanConstants& c, const TileShape& t, int m, int n, int steps, int splits) {
     if (!c.wide_half_steps && (t.code == 266 || t.code == 276)) return 1e30;
@@ -349,11 +350,12 @@ extern "C" int regione_tune_gemm(regione_ctx* ctx, int32_t wave_tile_blocks, int
 extern "C" int regione_gemm_plan_host(int32_t m, int32_t n, int32_t k, int32_t kind, int64_t workspace_bytes, int32_t* tile, int32_t* k_splits) {
     if (!tile || !k_splits) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm_plan: null argument");
     if (m <= 0 || n <= 0 || k <= 0 || workspace_bytes < 0) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm_plan: m=%d n=%d k=%d", m, n, k);
-    if (kind != REGIONE_GEMM_BF16 && kind != REGIONE_GEMM_E4M3) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm_plan: kind %d", kind);
+    if (kind != REGIONE_GEMM_BF16 && kind != REGIONE_GEMM_E4M3 && kind != REGIONE_GEMM_BF16_STORED) RG_FAIL(REGIONE_ERR_INVALID_ARG, "gemm_plan: kind %d", kind);
     const bool fp8 = kind == REGIONE_GEMM_E4M3;
     if (k % (fp8 ? 2 * BK : BK)) RG_FAIL(REGIONE_ERR_BAD_SHAPE, "gemm_plan: k=%d must be a multiple of %d", k, fp8 ? 2 * BK : BK);
     GemmPlan p = {0, 1};
-    if (fp8 || !small_columns(m, n, k, false)) p = choose_plan(m, n, fp8 ? k / 2 : k, fp8 ? PLAN_FP8 : PLAN_BF16, static_cast<size_t>(workspace_bytes));
+    const int plan = fp8 ? PLAN_FP8 : kind == REGIONE_GEMM_BF16_STORED ? PLAN_KEPT : PLAN_BF16;
+    if (fp8 || !small_columns(m, n, k, false)) p = choose_plan(m, n, fp8 ? k / 2 : k, plan, static_cast<size_t>(workspace_bytes));
     *tile = p.tile;
     *k_splits = p.splits;
     return REGIONE_OK;
