@@ -226,7 +226,7 @@ static int form_modulation(regione_ctx* ctx, const regione_region_step_args* a, 
         for (int s = 0; s < 2; ++s) {
             sets[b - b0][s] = -1;
             if (!w.cond || !streams[s]->w_mod || (s == 0 && !(dbl && a->n_txt_fresh > 0))) continue;
-            if (ctx->f32 || H % 8 || H > 16384 || !rg_aligned16(streams[s]->w_mod)) continue;    // refused where the block's own call forms them
+            if (ctx->f32 || !rg_vec_columns_ok(H) || !rg_aligned16(streams[s]->w_mod)) continue;    // refused where the block's own call forms them
             sets[b - b0][s] = used;
             const int e = batch.count++;
             batch.x[e] = w.cond; batch.w[e] = static_cast<const bf16_t*>(streams[s]->w_mod); batch.b[e] = streams[s]->b_mod;

@@ -285,7 +285,7 @@ extern "C" int regione_vec_linear(regione_ctx* ctx, const float* x, int32_t pre_
     if (!ctx) RG_FAIL(REGIONE_ERR_INVALID_ARG, "vec_linear: null context");
     if (n < 0 || k <= 0) RG_FAIL(REGIONE_ERR_INVALID_ARG, "vec_linear: n=%d k=%d", n, k);
     if (pre_act != REGIONE_ACT_NONE && pre_act != REGIONE_ACT_SILU) RG_FAIL(REGIONE_ERR_INVALID_ARG, "vec_linear: activation %d (none or SiLU on the input)", pre_act);
-    if (k % 8 || k > 16384) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "vec_linear: k=%d must be a multiple of 8, at most 16384", k);
+    if (!rg_vec_columns_ok(k)) RG_FAIL(REGIONE_ERR_UNSUPPORTED, "vec_linear: k=%d must be a multiple of 8, at most 16384", k);
     if (n == 0) return REGIONE_OK;
     if (!x || !w || !y) RG_FAIL(REGIONE_ERR_INVALID_ARG, "vec_linear: null operand");
     if (!rg_aligned16(w)) RG_FAIL(REGIONE_ERR_INVALID_ARG, "vec_linear: the matrix must be 16-byte aligned");

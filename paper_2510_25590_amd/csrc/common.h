@@ -153,6 +153,7 @@ int rg_gather_pair_slots(regione_ctx* ctx, const void* src_a, int32_t row_elems_
                          const int32_t* index, const int32_t* n_dev, int64_t n_max, int32_t* slots, int n_txt);
 // modulation vectors of several blocks in one launch: y = silu(x) W^T + b for each entry, W [n, k] row-major bf16; go (optional): nothing is done where *go is zero on the GPU
 struct VecBatch { const float* x[kModSets]; const bf16_t* w[kModSets]; const float* b[kModSets]; float* y[kModSets]; int n[kModSets]; int first_wg[kModSets + 1]; int count; };
+static inline bool rg_vec_columns_ok(int k) { return k % 8 == 0 && k <= 16384; }      // whole 16-byte pieces, and the vector as float32 within 64 KiB of LDS
 int rg_vec_linear_batch(regione_ctx* ctx, VecBatch& batch, int k, const int32_t* go);
 // One product: norm: of layernorm_mod(a), rows a of k values (a_f32: float32).
 struct GemmCall { const void* a; int lda, norm, a_f32; const float* shift; const float* scale; const void* w; int m, n, k; GemmEpilogue ep; };
