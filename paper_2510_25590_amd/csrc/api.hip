@@ -220,13 +220,13 @@ static int form_modulation(regione_ctx* ctx, const regione_region_step_args* a, 
     int used = 0, b = b0;
     for (; b < a->n_blocks && b - b0 < kModSets; ++b) {
         const regione_block_weights& w = a->blocks[b];
-        const bool dbl = a->block_types[b] == REGIONE_BLOCK_DOUBLE;
+        const bool dbl = a->block_types[b] == REGIONE_BLOCK_DOUBLE, known = dbl || a->block_types[b] == REGIONE_BLOCK_SINGLE;
         const regione_stream_weights* streams[2] = {&w.txt, &w.img};
         if (used + 2 > kModSets) break;
         for (int s = 0; s < 2; ++s) {
             sets[b - b0][s] = -1;
             if (!w.cond || !streams[s]->w_mod || (s == 0 && !(dbl && a->n_txt_fresh > 0))) continue;
-            if (ctx->f32 || !rg_vec_columns_ok(H) || !rg_aligned16(streams[s]->w_mod)) continue;    // refused where the block's own call forms them
+            if (!known || ctx->f32 || !rg_vec_columns_ok(H) || !rg_aligned16(streams[s]->w_mod)) continue;    // refused where the block's own call forms them
             sets[b - b0][s] = used;
             const int e = batch.count++;
             batch.x[e] = w.cond; batch.w[e] = static_cast<const bf16_t*>(streams[s]->w_mod); batch.b[e] = streams[s]->b_mod;

@@ -2,6 +2,7 @@
 // every grant of LDS.  Device memory is addresses only; nothing runs.  Commands from stdin, one a line:
 //   context <hidden> <heads> <head_dim> <mlp> <max_fresh> <max_tokens> <dtype>
 //   block <type> <text rows> <image rows> <dtype of h> <flags> <n_all> <fp8>
+//   step <edited> <tokens> <channels> <fresh text rows> <dtype> <block type>...   (up to the end of the line; every block with a conditioning vector; `edited` is the count that the call gets)
 // Output: "grant <bytes> <kernel>" and "launch <x> <y> <z> <dynamic LDS> <kernel>", "rc <code> <message>" behind a command's calls.
 #include <hip/hip_runtime_api.h>
 #include <cxxabi.h>
@@ -11,6 +12,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <vector>
 #include "regione.h"
 
 namespace {
@@ -18,6 +20,8 @@ std::map<const void*, std::string>& kernels() { static std::map<const void*, std
 struct Config { dim3 grid, block; size_t lds; hipStream_t stream; };
 Config pushed;
 uintptr_t next_address = uintptr_t{1} << 40;
+int32_t* pinned;             // the context's words that the count of a step's partition and the number of the step arrive in
+int32_t steps;
 const char* name(const void* f) { return kernels().count(f) ? kernels()[f].c_str() : "unknown"; }
 }  // namespace
 
@@ -40,7 +44,7 @@ hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute attr, int value) 
 }
 hipError_t hipMalloc(void** p, size_t n) { *p = reinterpret_cast<void*>(next_address); next_address += (n + 255) / 256 * 256; return hipSuccess; }
 hipError_t hipFree(void*) { return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = calloc(1, n); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = pinned = static_cast<int32_t*>(calloc(1, n)); steps = 0; return hipSuccess; }
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void*) { return hipMalloc(p, 1 << 20); }
@@ -67,6 +71,7 @@ int main(int, char** argv) {
     const auto destroy = reinterpret_cast<decltype(&regione_destroy)>(dlsym(lib, "regione_destroy"));
     const auto block = reinterpret_cast<decltype(&regione_block_forward)>(dlsym(lib, "regione_block_forward"));
     const auto block_fp8 = reinterpret_cast<decltype(&regione_block_forward_fp8)>(dlsym(lib, "regione_block_forward_fp8"));
+    const auto step = reinterpret_cast<decltype(&regione_region_step)>(dlsym(lib, "regione_region_step"));
     const auto error = reinterpret_cast<decltype(&regione_last_error)>(dlsym(lib, "regione_last_error"));
     auto device = [] { void* p = nullptr; (void)hipMalloc(&p, size_t{1} << 30); return p; };
     regione_ctx* ctx = nullptr;
@@ -93,6 +98,34 @@ int main(int, char** argv) {
             const int32_t* slots = static_cast<const int32_t*>(device());
             rc = fp8 ? block_fp8(ctx, &w, &w8, type, h, out, dtype, n_txt + n_img, n_txt, slots, 0, k, v, n_all, flags, nullptr)
                      : block(ctx, &w, type, h, out, dtype, n_txt + n_img, n_txt, slots, 0, k, v, n_all, flags);
+        } else if (!strcmp(cmd, "step")) {
+            int edited, tokens, channels, n_txt, dtype, used = 0;
+            char line[4096];
+            if (scanf("%d %d %d %d %d", &edited, &tokens, &channels, &n_txt, &dtype) != 5 || !fgets(line, sizeof line, stdin)) return 2;
+            std::vector<int32_t> types;
+            int type;
+            for (const char* p = line; sscanf(p, "%d%n", &type, &used) == 1; p += used) types.push_back(type);
+            std::vector<regione_block_weights> blocks(types.size());
+            std::vector<void*> caches(types.size());
+            for (size_t i = 0; i < types.size(); ++i) {
+                blocks[i] = {};
+                for (regione_stream_weights* s : {&blocks[i].txt, &blocks[i].img})
+                    for (const void** p : {&s->w_qkv, &s->w_o, &s->w_1, &s->w_2, &s->w_mod}) *p = device();
+                blocks[i].cond = static_cast<const float*>(device());
+                caches[i] = device();
+            }
+            regione_region_step_args a = {};
+            a.x_t = device(); a.v = device(); a.x_ref = device(); a.n_tokens = tokens; a.c = channels; a.dtype = dtype; a.sigma_t = 0.5f; a.eta = 0.9f;
+            a.mask = static_cast<uint8_t*>(device());
+            for (int32_t** p : {&a.e_index, &a.u_index, &a.n_edited_dev, &a.slots}) *p = static_cast<int32_t*>(device());
+            a.h_full = device(); a.h_dtype = dtype; a.n_txt_fresh = n_txt; a.h_rows = device(); a.h_rows_out = device();
+            a.n_blocks = static_cast<int32_t>(types.size()); a.n_all = tokens + n_txt; a.slot_offset = n_txt;
+            a.blocks = blocks.data(); a.block_types = types.data(); a.k_caches = caches.data(); a.v_caches = caches.data();
+            a.w_head_packed = device(); a.dt = 0.04f; a.c_a = device(); a.x_e = device(); a.x_next_full = device(); a.h_next_full_opt = device();
+            pinned[0] = edited; pinned[1] = ++steps;
+            int32_t got = -1;
+            rc = step(ctx, &a, &got);
+            if (!rc && got != edited) return 3;
         } else {
             return 2;
         }
