@@ -12,10 +12,11 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;   // a native 16-byte vector: copies are single loads/stores
 typedef __attribute__((ext_vector_type(8))) int i32x8;            // operand of the 8-bit MFMA: 32 E4M3 values per lane
 
-// 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3).  Both sides of the quotient are taken by four, so that the divisor, in [1/4, inf], has a normal
+// 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3).  Both sides of the quotient are divided by four, so that the divisor, in [1/4, inf], has a normal
 // reciprocal up to where the exponential overflows; then the reciprocal, one correction of the quotient and the fix-up of the special values give what the general division gives (but for
 // the last bit of |x| < 2^-124), without its scaling and with fewer instructions: the epilogue of 820 x 12288 results is bound by them (one tile per CU, 96 values per thread); the whole
-// product, K 3072, 68.0 -> 65.5 us in a kernel trace.  Without the factor results between 4e-38 and 1.6e-37 (x = -13) came out as zero.
+// product, K 3072, 68.0 -> 65.5 us in a kernel trace.  Without the factor, which costs a call 0.1 to 0.6 % (20 % edited 342.1 -> 343.0 us), results between 4e-38 and
+// 1.6e-37 (x = -13) came out as zero.
 __device__ __forceinline__ float gelu_tanh_f32(float x) {
     constexpr float kLin = -2.0f * 0.7978845608028654f * 1.4426950408889634f, kCub = kLin * 0.044715f;   // -2u log2(e) = x (kLin + kCub x^2)
     const float e = __builtin_amdgcn_exp2f(x * __builtin_fmaf(x * x, kCub, kLin));
